@@ -513,14 +513,16 @@ __global__ __launch_bounds__(256) void depthwise3x3_kernel(const void *x, void *
     }
 }
 
-// 16-bit storage, C a multiple of 8: one thread owns 8 channels of kDwRows consecutive output rows
-// of one output column.  It walks down the input rows once (each input vector is loaded once per
-// thread and feeds up to three output rows), keeps the 9 tap weights of its channels in registers
-// for its whole life, and multiplies on packed pairs: dot2(x pair, weight pair with the other half
-// zeroed) adds exactly one product in fp32, with no unpacking of the activations.  Consecutive
-// lanes are consecutive 16-byte channel vectors of a pixel, then consecutive pixels of a row.
-constexpr int kDwRows = 4;
-
+// 16-bit storage, C a multiple of 8, stride 1 or 2: one thread owns 8 channels of R consecutive output rows of one
+// output column.  What bounded the layer was a chain of memory latencies (an input row asked for, multiplied, the next
+// one asked for), so every input vector a thread needs is asked for before the first multiply; the zero padding comes
+// from the buffer descriptor's range check (an offset past the end reads zeros), which leaves no branch between the
+// loads.  The multiplies go column by column (kw): a tap's weights and an input vector are unpacked to fp32 once each
+// and feed up to three output rows; fp32 multiply-adds issue in half the time of a dot2 with one half zeroed.
+// Consecutive lanes are consecutive 16-byte channel vectors of a pixel, then consecutive pixels of a row; an XCD gets a
+// contiguous run of rows so that the rows two row blocks share come from its own L2.
+// 64 x 56 x 56 x 144, bf16: stride 1 31 -> 28 us (a copy of the same bytes: 23), stride 2 57 -> 13 us (the thread of four
+// rows had spilled); 32 x 57 x 57 x 144 with a bias 23 -> 18 us; 1 x 46 x 28 x 272 at stride 2 16.5 -> 2.9 us.
 struct DwArgs {
     const void *x;
     void *y;
@@ -528,86 +530,98 @@ struct DwArgs {
     const float *bias;
     const void *residual;
     int N, H, W, C, Ho, Wo, act;
+    uint32_t xbytes;                    // size of x (< 2 GiB: see launch_depthwise3x3)
     uint32_t CV, nyb, total;            // channel vectors, row blocks per image, threads
     uint32_t div_cv, div_wo, div_nyb;   // fastdiv magics
 };
 
-template <int DT, int STRIDE, bool HSW>
-__device__ __forceinline__ void depthwise3x3_rows_kernel_body(DwArgs a)
+template <int DT> __device__ __forceinline__ void unpack8(uint4 v, float *f)
 {
-    const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
+    const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        f[2 * k] = from_storage<DT>((uint16_t)(u[k] & 0xffffu));
+        f[2 * k + 1] = DT == NPAS_BF16 ? __uint_as_float(u[k] & 0xffff0000u) : from_storage<DT>((uint16_t)(u[k] >> 16));
+    }
+}
+
+template <int DT, int STRIDE, int R, bool HSW>
+__global__ __launch_bounds__(256, R == 4 ? 2 : 3) void depthwise3x3_rows_kernel(DwArgs a)
+{
+    const uint32_t idx = xcd_remap(blockIdx.x, gridDim.x) * 256u + threadIdx.x;
     if (idx >= a.total) return;
-    uint32_t t = fastdiv(idx, a.div_cv);
+    const uint32_t t = fastdiv(idx, a.div_cv);
     const uint32_t cv = idx - t * a.CV;
-    uint32_t t2 = fastdiv(t, a.div_wo);
+    const uint32_t t2 = fastdiv(t, a.div_wo);
     const int ox = (int)(t - t2 * (uint32_t)a.Wo);
     const uint32_t n = fastdiv(t2, a.div_nyb);
-    const int oy0 = (int)(t2 - n * a.nyb) * kDwRows;
-    const Clamp cl = clamp_of(a.act);
-    const uint16_t *x16 = reinterpret_cast<const uint16_t *>(a.x);
-    const uint16_t *w16 = reinterpret_cast<const uint16_t *>(a.w);
-
-    uint32_t wlo[9][4], whi[9][4]; // each pair of weights with the upper / the lower one zeroed
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-        const uint4 wv = *reinterpret_cast<const uint4 *>(w16 + (size_t)tap * a.C + (size_t)cv * 8);
-        const uint32_t ws[4] = {wv.x, wv.y, wv.z, wv.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            wlo[tap][k] = ws[k] & 0xffffu;
-            whi[tap][k] = ws[k] & 0xffff0000u;
-        }
-    }
-    float acc[kDwRows][8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const float b = a.bias ? a.bias[cv * 8 + k] : 0.f;
-#pragma unroll
-        for (int j = 0; j < kDwRows; ++j) acc[j][k] = b;
-    }
-    constexpr int NR = (kDwRows - 1) * STRIDE + 3; // input rows this thread reads
+    const int oy0 = (int)(t2 - n * a.nyb) * R;
+    constexpr int NR = (R - 1) * STRIDE + 3; // input rows this thread reads
     const int ix0 = ox * STRIDE - 1, iy0 = oy0 * STRIDE - 1;
-    const size_t img = (size_t)n * a.H;
+
+    typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, (int)a.xbytes, 0x00020000);
+    const uint32_t pixb = (uint32_t)a.C * 2u, rowb = (uint32_t)a.W * pixb;
+    // byte offset of input pixel (iy0, ix0); may lie before the image, in which case it is not used
+    const uint32_t org = (n * (uint32_t)a.H + (uint32_t)iy0) * rowb + (uint32_t)ix0 * pixb + cv * 16u;
+    uint32_t rowo[NR];
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        const int iy = iy0 + r;
-        const bool rowok = iy >= 0 && iy < a.H; // zero padding above and below the image
-        uint4 xv[3];
+    for (int r = 0; r < NR; ++r) rowo[r] = (uint32_t)(iy0 + r) < (uint32_t)a.H ? org + (uint32_t)r * rowb : 0x80000000u;
+    uint4 xv[3][NR], wv[3][3];
 #pragma unroll
-        for (int kw = 0; kw < 3; ++kw) {
-            const int ix = ix0 + kw;
-            const bool ok = rowok && ix >= 0 && ix < a.W;
-            xv[kw] = uint4{0u, 0u, 0u, 0u};
-            if (ok) xv[kw] = *reinterpret_cast<const uint4 *>(x16 + ((img + (size_t)iy) * a.W + (size_t)ix) * a.C + (size_t)cv * 8);
+    for (int kw = 0; kw < 3; ++kw) {
+        const bool ok = (uint32_t)(ix0 + kw) < (uint32_t)a.W;
+#pragma unroll
+        for (int kh = 0; kh < 3; ++kh)
+            wv[kw][kh] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(a.w) + (size_t)(kh * 3 + kw) * a.C + cv * 8u);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const uint32_t off = ok && rowo[r] != 0x80000000u ? rowo[r] + (uint32_t)kw * pixb : 0x80000000u;
+            xv[kw][r] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(xr, (int)off, 0, 0));
         }
+    }
+    f32x4 b0 = f32x4{0.f, 0.f, 0.f, 0.f}, b1 = b0;
+    if (a.bias) { // two 16-byte loads (any 4-byte alignment): as eight 4-byte ones, 32 bytes apart from lane to lane, they cost as much as the taps
+        typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4u;
+        b0 = *reinterpret_cast<const f32x4u *>(a.bias + cv * 8u);
+        b1 = *reinterpret_cast<const f32x4u *>(a.bias + cv * 8u + 4u);
+    }
+    __builtin_amdgcn_sched_barrier(0); // every load above the first use
+    float acc[R][8];
 #pragma unroll
-        for (int j = 0; j < kDwRows; ++j) {
-            const int kh = r - j * STRIDE; // compile-time after unrolling
-            if (kh < 0 || kh > 2) continue;
+    for (int k = 0; k < 8; ++k)
 #pragma unroll
-            for (int kw = 0; kw < 3; ++kw) {
-                const uint32_t xs[4] = {xv[kw].x, xv[kw].y, xv[kw].z, xv[kw].w};
+        for (int j = 0; j < R; ++j) acc[j][k] = k < 4 ? b0[k] : b1[k - 4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    acc[j][2 * k] = dot2acc<DT>(xs[k], wlo[kh * 3 + kw][k], acc[j][2 * k]);
-                    acc[j][2 * k + 1] = dot2acc<DT>(xs[k], whi[kh * 3 + kw][k], acc[j][2 * k + 1]);
-                }
+    for (int kw = 0; kw < 3; ++kw) {
+        float wf[3][8];
+#pragma unroll
+        for (int kh = 0; kh < 3; ++kh) unpack8<DT>(wv[kw][kh], wf[kh]);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            float xf[8];
+            unpack8<DT>(xv[kw][r], xf);
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int kh = r - j * STRIDE; // compile-time after unrolling
+                if (kh < 0 || kh > 2) continue;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) acc[j][k] = fmaf(xf[k], wf[kh][k], acc[j][k]);
             }
         }
+        __builtin_amdgcn_sched_barrier(0); // one column's unpacked weights live at a time
     }
+    const Clamp cl = clamp_of(a.act);
 #pragma unroll
-    for (int j = 0; j < kDwRows; ++j) {
+    for (int j = 0; j < R; ++j) {
         const int oy = oy0 + j;
         if (oy >= a.Ho) continue;
         const size_t yo = (((size_t)n * a.Ho + (size_t)oy) * a.Wo + (size_t)ox) * a.C + (size_t)cv * 8;
         if (a.residual) {
-            const uint4 rv = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(a.residual) + yo);
-            const uint32_t rs[4] = {rv.x, rv.y, rv.z, rv.w};
+            float rf[8];
+            unpack8<DT>(*reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(a.residual) + yo), rf);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                acc[j][2 * k] += from_storage<DT>((uint16_t)(rs[k] & 0xffffu));
-                acc[j][2 * k + 1] += from_storage<DT>((uint16_t)(rs[k] >> 16));
-            }
+            for (int k = 0; k < 8; ++k) acc[j][k] += rf[k];
         }
         uint4 out;
         out.x = pack2<DT>(clampf<HSW>(acc[j][0], cl), clampf<HSW>(acc[j][1], cl));
@@ -616,13 +630,6 @@ __device__ __forceinline__ void depthwise3x3_rows_kernel_body(DwArgs a)
         out.w = pack2<DT>(clampf<HSW>(acc[j][6], cl), clampf<HSW>(acc[j][7], cl));
         store_stream16(reinterpret_cast<uint16_t *>(a.y) + yo, out);
     }
-}
-// The activation kind is compiled in: hard-swish behind a (wave-uniform) branch per value kept the compiler from
-// interleaving loads, MFMAs and epilogue arithmetic across values and cost the launches without it 15-50 %.
-template <int DT, int STRIDE, bool HSW>
-__global__ __launch_bounds__(256, 3) void depthwise3x3_rows_kernel(DwArgs a)
-{
-    depthwise3x3_rows_kernel_body<DT, STRIDE, HSW>(a); // (one body per kernel: with two behind a branch the stride-2 variant's spills moved into its row loop)
 }
 
 static uint32_t magic32(uint32_t d) { return d <= 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); }
@@ -633,28 +640,36 @@ int launch_depthwise3x3(int dt, const void *x, void *y, const void *w, const flo
     hipStream_t st = (hipStream_t)stream;
     const int Ho = (H - 1) / stride + 1, Wo = (W - 1) / stride + 1;
     const bool vec = dt != NPAS_F32 && C % 8 == 0;
-    if (vec && (stride == 1 || stride == 2)) {
-        const uint32_t CV = (uint32_t)C / 8, nyb = (uint32_t)((Ho + kDwRows - 1) / kDwRows);
+    const size_t xbytes = (size_t)N * H * W * C * 2;
+    if (vec && (stride == 1 || stride == 2) && xbytes < 0x80000000u) { // (offset 2 GiB is past the end for the range check)
+        const uint32_t CV = (uint32_t)C / 8;
+        // Output rows per thread.  Four share input vectors (4.5 loads an output instead of 9) and are the faster form of a
+        // launch that fills the chip anyway: 64 x 56 x 56 x 144 at stride 1 28.2 us (4.1 TB/s) against 36.1 with one row.
+        // With one row a thread is a shorter chain, which wins while all waves of the launch (three per SIMD) are resident at
+        // once: 3 x 28 x 28 x 144 3.1 us against 4.1, 16 x 28 x 28 x 240 (twice that many) 6.3 against 5.5.  At stride 2 the rows
+        // share one input row in five: one row is never slower by more than a tenth and mostly faster (12.9 us against 15.3 with two).
+        const int R = stride == 1 && (double)N * Ho * Wo * CV > 256.0 * 12 * 64 ? 4 : 1;
+        const uint32_t nyb = (uint32_t)((Ho + R - 1) / R);
         const double threads = (double)N * nyb * Wo * CV;
         // the index decode divides by CV, Wo and nyb with 32-bit reciprocals: exact while index * divisor < 2^32
         if (threads * std::max({CV, (uint32_t)Wo, nyb}) < 4294967296.0) {
-            DwArgs a{x, y, w, bias, residual, N, H, W, C, Ho, Wo, act, CV, nyb, (uint32_t)threads,
+            DwArgs a{x, y, w, bias, residual, N, H, W, C, Ho, Wo, act, (uint32_t)xbytes, CV, nyb, (uint32_t)threads,
                      magic32(CV), magic32((uint32_t)Wo), magic32(nyb)};
             const unsigned grid = (a.total + 255u) / 256u;
-            if (dt == NPAS_BF16) {
-#define NPAS_DWR(DT_)                                                                                                           \
-    do {                                                                                                                         \
-        const bool hs = a.act == NPAS_ACT_HARDSWISH;                                                                            \
-        if (stride == 1 && hs) hipLaunchKernelGGL((depthwise3x3_rows_kernel<DT_, 1, true>), dim3(grid), dim3(256), 0, st, a);   \
-        else if (stride == 1) hipLaunchKernelGGL((depthwise3x3_rows_kernel<DT_, 1, false>), dim3(grid), dim3(256), 0, st, a);   \
-        else if (hs) hipLaunchKernelGGL((depthwise3x3_rows_kernel<DT_, 2, true>), dim3(grid), dim3(256), 0, st, a);            \
-        else hipLaunchKernelGGL((depthwise3x3_rows_kernel<DT_, 2, false>), dim3(grid), dim3(256), 0, st, a);                   \
-    } while (0)
-                NPAS_DWR(NPAS_BF16);
-            } else {
-                NPAS_DWR(NPAS_F16);
-#undef NPAS_DWR
-            }
+            auto go = [&](auto dtc, auto sc, auto rc) {
+                constexpr int DT = decltype(dtc)::value, S = decltype(sc)::value, RR = decltype(rc)::value;
+                if (act == NPAS_ACT_HARDSWISH) hipLaunchKernelGGL((depthwise3x3_rows_kernel<DT, S, RR, true>), dim3(grid), dim3(256), 0, st, a);
+                else hipLaunchKernelGGL((depthwise3x3_rows_kernel<DT, S, RR, false>), dim3(grid), dim3(256), 0, st, a);
+            };
+            auto rows = [&](auto dtc) {
+                using std::integral_constant;
+                integral_constant<int, 1> one;
+                if (stride == 2) go(dtc, integral_constant<int, 2>{}, one);
+                else if (R == 4) go(dtc, one, integral_constant<int, 4>{});
+                else go(dtc, one, one);
+            };
+            if (dt == NPAS_BF16) rows(std::integral_constant<int, NPAS_BF16>{});
+            else rows(std::integral_constant<int, NPAS_F16>{});
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) {
                 set_error("depthwise3x3_rows launch failed: %s", hipGetErrorString(e));

@@ -323,6 +323,26 @@ def test_depthwise3x3(npas, torch, case):
     assert err <= TOL[dtype]
 
 
+# Edges of the row-block kernel: four rows a thread (launches of more than 196608 output vectors) with one row left over and
+# with whole blocks, one row a thread, stride 2 on odd and even maps, maps narrower than the window, a bias at 4-byte alignment.
+@pytest.mark.parametrize("N,H,W,C,stride,dtype", [(5, 201, 199, 8, 1, dtypes.BF16), (13, 64, 60, 32, 1, dtypes.F16), (1, 3, 1, 24, 1, dtypes.BF16),
+                                                  (2, 9, 7, 40, 2, dtypes.F16), (3, 32, 2, 16, 2, dtypes.BF16), (9, 151, 149, 16, 2, dtypes.BF16)])
+def test_depthwise3x3_row_blocks(npas, torch, N, H, W, C, stride, dtype):
+    print(f"depthwise rows N={N} {H}x{W}x{C} stride {stride}", flush=True)
+    xs, xe = dtypes.quantize(prng.normal(18, 1, N * H * W * C).reshape(N, H, W, C), dtype)
+    ws, we = dtypes.quantize(prng.normal(18, 2, C * 9, 0.3).reshape(C, 3, 3), dtype)
+    bias = prng.normal(18, 3, C).astype(np.float32)
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    rs, re = dtypes.quantize(prng.normal(18, 4, N * Ho * Wo * C).reshape(N, Ho, Wo, C), dtype)
+    ref = oracle.round_to(oracle.dwconv3x3(xe, we, stride, bias.astype(np.float64), re, configs.ACT_RELU6), dtype)
+    p = npas.pack_depthwise3x3(ws, dtype)
+    y = new_dev((N, Ho, Wo, C), dtype, torch, fill=0x7FC1)
+    b = to_dev(np.concatenate([np.zeros(1, np.float32), bias]), torch)
+    npas.depthwise3x3(p, to_dev(xs, torch), y, N, H, W, stride, b.data_ptr() + 4, to_dev(rs, torch), npas.ACT_RELU6)
+    torch.cuda.synchronize()
+    assert rel_err(from_dev(y, dtype), ref) <= TOL[dtype]
+
+
 @pytest.mark.parametrize("stride,bias,act,HW", [(1, False, configs.ACT_RELU6, 13), (2, False, configs.ACT_RELU6, 13),
                                                 (1, True, configs.ACT_RELU6, 13), (2, True, configs.ACT_RELU6, 13),
                                                 (2, True, configs.ACT_HARDSWISH, 14), (1, True, configs.ACT_HARDSWISH, 9),
