@@ -661,7 +661,8 @@ struct npas_stack {
         const void *ir_w1 = nullptr, *ir_w3 = nullptr;
         const int *ir_perm = nullptr;
         const uint32_t *ir_wdw = nullptr;
-        int ir_nslots = 0, ir_TH = 0, ir_TW = 0, ir_residual = 0;
+        int ir_nslots = 0, ir_residual = 0;
+        int ir_TH[3] = {0, 0, 0}, ir_TW[3] = {0, 0, 0}; // tiles of at most 32, 64 and any number of output pixels
     };
     std::vector<Node> nodes;
     std::vector<void *> blobs; // device allocations owned by the stack (fused-pair weight images)
@@ -810,10 +811,11 @@ static FppPlan build_fpp(const npas_packed *p1, const npas_packed *p2)
 }
 
 // Plan and weight images of a fused inverted-residual block (layouts: see fused_inverted_residual_kernel).
+constexpr int kIrTileCap[3] = {32, 64, 256};
 struct IrPlan {
     int nslots = 0;                 // live intermediate channels, padded to a multiple of 32
     std::vector<uint16_t> w1, w3;   // A-operand images
-    std::vector<uint32_t> wdw;      // [9][nslots]: the weight's storage bits in the low (even slot) or high (odd slot) half
+    std::vector<uint32_t> wdw;      // [nslots / 16][5 steps][64 lanes]: the lane's one nonzero weight of a diagonal row operand
     std::vector<int> perm;          // [nslots]: intermediate channel of each slot, -1 = padding
 };
 
@@ -835,7 +837,8 @@ static IrPlan build_ir(const npas_packed *p1, const npas_packed *pdw, const npas
     for (int t = 0; t < nt1; ++t)
         for (int lane = 0; lane < 64; ++lane)
             for (int i = 0; i < 8; ++i) {
-                const int r = lane & 15, q = lane >> 4, f = perm[16 * t + r], c = 8 * q + i;
+                // row r of tile t = slot 32 (t / 2) + 8 (r / 4) + 4 (t & 1) + r % 4: a lane's results of two tiles are eight consecutive slots
+                const int r = lane & 15, q = lane >> 4, f = perm[32 * (t >> 1) + 8 * (r >> 2) + 4 * (t & 1) + (r & 3)], c = 8 * q + i;
                 if (f >= 0 && c < p1->C) plan.w1[((size_t)t * 64 + lane) * 8 + i] = d1[(size_t)f * p1->C + c];
             }
     plan.w3.assign((size_t)nt3 * nk * 512, 0);
@@ -843,30 +846,38 @@ static IrPlan build_ir(const npas_packed *p1, const npas_packed *pdw, const npas
         for (int k = 0; k < nk; ++k)
             for (int lane = 0; lane < 64; ++lane)
                 for (int i = 0; i < 8; ++i) {
-                    const int r = lane & 15, q = lane >> 4, f = 16 * u + r, c = perm[32 * k + 8 * q + i];
+                    // K position 8 q + i: the slots a lane holds of the two depthwise result tiles of this step
+                    const int r = lane & 15, q = lane >> 4, f = 16 * u + r, c = perm[32 * k + 16 * (i >> 2) + 4 * q + (i & 3)];
                     if (f < p3->F && c >= 0) plan.w3[((size_t)(u * nk + k) * 64 + lane) * 8 + i] = d3[(size_t)f * p3->C + c];
                 }
-    plan.wdw.assign((size_t)9 * plan.nslots, 0u);
+    // Depthwise step m of tile t: K position 8 q + i = (tap 2 m + q / 2, slot 16 t + 8 (q & 1) + i), row r = slot 16 t + r.
+    // The diagonal leaves lane (q, r) the one position i = r & 7, when r / 8 == (q & 1): its weight's bits, in the low
+    // (even r) or high (odd r) half of the operand word that holds the position.
+    plan.wdw.assign((size_t)nt1 * 5 * 64, 0u);
     const uint16_t *wd = reinterpret_cast<const uint16_t *>(pdw->w_compact.data());
-    for (int s = 0; s < plan.nslots; ++s)
-        if (perm[s] >= 0)
-            for (int t = 0; t < 9; ++t) plan.wdw[(size_t)t * plan.nslots + s] = (uint32_t)wd[(size_t)perm[s] * 9 + t] << (s & 1 ? 16 : 0);
+    for (int t = 0; t < nt1; ++t)
+        for (int m = 0; m < 5; ++m)
+            for (int lane = 0; lane < 64; ++lane) {
+                const int r = lane & 15, q = lane >> 4, tap = 2 * m + (q >> 1), c = perm[16 * t + r];
+                if (c >= 0 && tap < 9 && (r >> 3) == (q & 1))
+                    plan.wdw[((size_t)t * 5 + m) * 64 + lane] = (uint32_t)wd[(size_t)c * 9 + tap] << (r & 1 ? 16 : 0);
+            }
     plan.perm = perm;
     return plan;
 }
 
-// Output tile of the fused block for an H x W map: the shape that costs least, counting the
-// halo pixels expanded (cheap) and the 16-pixel blocks of depthwise work (about four times dearer),
-// among those whose LDS footprint leaves room for several workgroups per CU.
-static void plan_ir_tile(int Ho, int Wo, int nslots, int stride, int *TH, int *TW)
+// Output tile of at most `cap` pixels of the fused block for an Ho x Wo map: the shape that costs least, counting the
+// halo pixels expanded and the 16-pixel blocks of depthwise work (about four times dearer), among those whose LDS
+// footprint leaves room for as many workgroups per CU as their registers do.
+static void plan_ir_tile(int Ho, int Wo, int nslots, int stride, int cap, int *TH, int *TW)
 {
     double best = 1e300;
     *TH = 1; *TW = 1;
     for (int th = 1; th <= 32; ++th)
         for (int tw = 1; tw <= 64; ++tw) {
             const int ph = (th - 1) * stride + 3, pw = (tw - 1) * stride + 3; // input pixels under the tile, with halo
-            if (ph * pw > 256) continue; // four 16-pixel halo blocks per wave at most
-            if (fused_ir_lds_bytes(th, tw, nslots, stride) > 64 * 1024) continue;
+            if (th * tw > cap || ph * pw > 256) continue; // four 16-pixel halo blocks per wave at most
+            if (fused_ir_lds_bytes(th, tw, nslots, stride) > (size_t)160 * 1024 / fused_ir_wgs_per_cu(nslots)) continue;
             const double tiles = (double)((Ho + th - 1) / th) * ((Wo + tw - 1) / tw);
             const double cost = tiles * (1.0 * ((ph * pw + 15) / 16) + 4.0 * ((th * tw + 15) / 16) + 2.0);
             if (cost < best) {
@@ -1133,10 +1144,6 @@ int npas_stack_create(const npas_layer_desc *layers, int n_layers, int H, int W,
             if (p1->C > 32 || p1->C % 8 || p3->F % 4 || p3->F > 32 || (c.d.res >= 0 && p3->F != p1->C)) continue;
             IrPlan ip = build_ir(p1, b.d.packed, p3);
             if (ip.nslots > 192) continue;
-            int th, tw;
-            const int st2 = b.d.stride;
-            plan_ir_tile((a.H - 1) / st2 + 1, (a.W - 1) / st2 + 1, ip.nslots, st2, &th, &tw);
-            if (fused_ir_lds_bytes(th, tw, ip.nslots, st2) > 64 * 1024) continue;
             const size_t b1 = ip.w1.size() * 2, b3 = ip.w3.size() * 2, bd = ip.wdw.size() * 4, bp = ip.perm.size() * 4;
             const size_t o3 = (b1 + 255) / 256 * 256, od = o3 + (b3 + 255) / 256 * 256, op = od + (bd + 255) / 256 * 256;
             std::vector<uint8_t> blob(op + bp);
@@ -1153,7 +1160,9 @@ int npas_stack_create(const npas_layer_desc *layers, int n_layers, int H, int W,
                 a.ir_wdw = (const uint32_t *)((const uint8_t *)dptr + od);
                 a.ir_perm = (const int *)((const uint8_t *)dptr + op);
             }
-            a.ir_nslots = ip.nslots; a.ir_TH = th; a.ir_TW = tw; a.ir_residual = c.d.res >= 0;
+            a.ir_nslots = ip.nslots; a.ir_residual = c.d.res >= 0;
+            for (int t = 0; t < 3; ++t)
+                plan_ir_tile((a.H - 1) / b.d.stride + 1, (a.W - 1) / b.d.stride + 1, ip.nslots, b.d.stride, kIrTileCap[t], &a.ir_TH[t], &a.ir_TW[t]);
             b.fused_away = true;
             c.fused_away = true;
         }
@@ -1310,7 +1319,13 @@ int run_stack_impl(const npas_stack *s, const void *x_dev, void *y_dev, int N, v
                 IrLaunch l;
                 l.x = x; l.y = tensor(i + 3); l.w1 = n.ir_w1; l.w3 = n.ir_w3; l.wdw = n.ir_wdw; l.perm = n.ir_perm;
                 l.b1 = (const float *)n.d.bias_dev; l.b2 = (const float *)d2.bias_dev; l.b3 = (const float *)d3.bias_dev;
-                l.N = N; l.H = n.H; l.W = n.W; l.C1 = p1->C; l.F3 = p3->F; l.nslots = n.ir_nslots; l.TH = n.ir_TH; l.TW = n.ir_TW;
+                // Half a 16-pixel block per wave or one, while such tiles still find a place on the chip together: a launch of few
+                // tiles lasts as long as one (1 x 56 x 56 x 24 -> 144 -> 24: 4.8 us with 4 x 8 pixels, 6.6 with 14 x 8;
+                // 90 x 14 x 14 x 32 -> 192 -> 32: 9.2 us with 4 x 8, 7.9 with 8 x 7 and 8.0 with the cheapest shape)
+                const int Ho = (n.H - 1) / d2.stride + 1, Wo = (n.W - 1) / d2.stride + 1;
+                auto tiles = [&](int t) { return (double)N * ((Ho + n.ir_TH[t] - 1) / n.ir_TH[t]) * ((Wo + n.ir_TW[t] - 1) / n.ir_TW[t]); };
+                const int t = tiles(0) <= 512 ? 0 : tiles(1) <= 1024 ? 1 : 2;
+                l.N = N; l.H = n.H; l.W = n.W; l.C1 = p1->C; l.F3 = p3->F; l.nslots = n.ir_nslots; l.TH = n.ir_TH[t]; l.TW = n.ir_TW[t];
                 l.stride = d2.stride; l.act1 = n.d.act; l.act2 = d2.act; l.act3 = d3.act; l.residual = n.ir_residual;
                 rc = launch_fused_inverted_residual(p1->dtype, l, hip_stream);
             }

@@ -1,5 +1,5 @@
-// gfx950 kernels of libnpas that run more than one layer, or the depthwise layer between two of them: the fused 1x1 pair,
-// the fused 1x1 -> depthwise 3x3 -> 1x1 block, and the depthwise 3x3 layer on its own.
+// gfx950 kernels of libnpas: the fused 1x1 pair and the depthwise 3x3 layer on its own (the fused block of the two is in
+// inverted_residual_kernel.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -180,266 +180,6 @@ int launch_fused_pointwise_pair(int dtype, const void *x, void *y, const void *w
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         set_error("fused_pointwise_pair launch failed: %s", hipGetErrorString(e));
-        return NPAS_E_HIP;
-    }
-    return NPAS_OK;
-}
-
-// ------------------------------------------------------------------------------
-// fused_inverted_residual: y = act3(W3 . act2(DW3x3(act1(W1 . x + b1)) + b2) + b3 [+ x]) for the cascade
-// 1x1 -> 3x3 depthwise (stride 1 or 2) -> 1x1 of the search space (section 5.1.1) when the two wide
-// tensors between the layers have no other reader.  They never leave the CU: HBM sees x once and y once.
-// The block input is added at stride 1 only (at stride 2 the shapes differ); the biases are optional.
-//
-// A workgroup (4 waves) owns an output tile of TH x TW pixels.
-//   1. Expansion: for the input pixels under the tile plus a one-pixel halo ((TH-1) stride + 3 rows),
-//      16 pixels at a time, layer 1's MFMAs
-//      (K = C1 <= 32 in one step) produce 16 x 16 output tiles that get their bias, are clamped, rounded and
-//      written to LDS as [halo pixel][slot] in the storage type.  Halo pixels outside the image are written
-//      as zero, as the padding of the depthwise
-//      layer must be.  A slot is an intermediate channel some filter of layer 3 keeps; channels
-//      nobody keeps are dead and are never computed (the pruning of layer 3 pays in layers 1 and 2).
-//   2. Depthwise + projection, 16 output pixels at a time: lane (q, n) forms the depthwise output
-//      of pixel n for 8 slots (nine 16-byte LDS reads of activations, weights from an LDS table,
-//      one dot2 instruction per multiply-add on the packed pairs, fp32 accumulate, clamp, round):
-//      exactly the B operand of layer 3's MFMA step for
-//      those 32 slots.  After all steps: residual (x again, 8 bytes per lane), clamp, round, store.
-// Bound: vector ALUs (the depthwise arithmetic and the unpacking of 16-bit pairs), not HBM.
-// c + x.lo * w.lo + x.hi * w.hi on two packed 16-bit pairs (v_dot2c_f32_bf16 / v_dot2_f32_f16).  With one half of
-// w zero this is a multiply-add on the other half without unpacking it (the zero half adds an exact zero as long
-// as the activation beside it is finite).
-template <int DT> __device__ __forceinline__ float dot2acc(uint32_t x, uint32_t w, float c)
-{
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
-    if (DT == NPAS_BF16) return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, x), __builtin_bit_cast(bf16x2, w), c, false);
-    return __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, x), __builtin_bit_cast(f16x2, w), c, false);
-}
-
-// Padding of a halo pixel's row in LDS: 32 bytes measured best among 16 .. 144 for 96 slots (a 256-byte row
-// pitch, i.e. 64, is the worst case: every pixel on the same banks).
-constexpr uint32_t kIrPad = 32;
-
-struct IrArgs {
-    const void *x;
-    void *y;
-    const void *w1;      // [nt1][64 lanes][8] layer-1 A-operand images, rows in slot order
-    const void *w3;      // [nt3][nk][64 lanes][8] layer-3 A-operand images, K in slot order
-    const uint32_t *wdw; // [9][nslots] depthwise weights in slot order, each alone in its half of a 16-bit pair
-                         // (even slots low, odd slots high, the other half zero)
-    const int *perm;     // [nslots] intermediate channel of each slot, -1: padding slot
-    const float *b1, *b2, *b3; // biases of the three layers in channel order, or null
-    int N, H, W, C1, F3;
-    int stride, Ho, Wo;  // of the depthwise layer; output map
-    int nt1, nk, nt3;    // slots / 16, slots / 32, ceil(F3 / 16)
-    int TH, TW, tilesY, tilesX;
-    int act1, act2, act3;
-    int residual;        // 1: add the block input (needs F3 == C1 and stride 1)
-    uint32_t div_tw, div_pw;
-};
-
-// BIAS: some layer of the block has one (bias tables in LDS, halo pixels outside the image zeroed explicitly: the
-// padding of the depthwise layer is zero, not act1(b1)).  Without, x = 0 there already gives zero, and the kernel
-// keeps the registers that let three workgroups share a CU.
-template <int DT, bool BIAS, bool HSW>
-__device__ __forceinline__ void fused_inverted_residual_kernel_body(IrArgs a)
-{
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n16 = lane & 15, q = lane >> 4;
-    const int PH = (a.TH - 1) * a.stride + 3, PW = (a.TW - 1) * a.stride + 3, nslots = a.nt1 * 16;
-    const int nhb = (PH * PW + 15) >> 4, nob = (a.TH * a.TW + 15) >> 4; // 16-pixel blocks of the halo tile / the tile
-    const uint32_t pitch = (uint32_t)nslots * 2u + kIrPad;               // bytes per halo pixel
-    uint8_t *y1 = lds;
-    uint32_t *dww = reinterpret_cast<uint32_t *>(lds + (size_t)nhb * 16 * pitch);
-    float *lb1 = reinterpret_cast<float *>(dww + 9 * nslots), *lb2 = lb1 + nslots; // biases of layers 1 and 2 in slot order
-
-    uint32_t tile = blockIdx.x;
-    const int txi = (int)(tile % (uint32_t)a.tilesX);
-    tile /= (uint32_t)a.tilesX;
-    const int tyi = (int)(tile % (uint32_t)a.tilesY), n = (int)(tile / (uint32_t)a.tilesY);
-    const int ty0 = tyi * a.TH, tx0 = txi * a.TW;             // in the output map
-    const int iy0 = ty0 * a.stride - 1, ix0 = tx0 * a.stride - 1; // input pixel of halo pixel (0, 0)
-
-    for (int i = tid; i < 9 * nslots; i += 256) dww[i] = a.wdw[i];
-
-    // ---- 1. expansion into LDS ------------------------------------------------------------
-    const Clamp cl1 = clamp_of(a.act1);
-    const uint16_t *x16 = reinterpret_cast<const uint16_t *>(a.x);
-    const uint4 *w1 = reinterpret_cast<const uint4 *>(a.w1) + lane;
-    // every load of this phase is issued before the first MFMA: the wave's activation vectors (up to four
-    // 16-pixel blocks) and layer 1's images, so that one memory latency is paid instead of one per block and image
-    uint4 xv[4], w1r[12];
-    bool inside[4]; // the lane's halo pixel of round r lies in the image
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int hb = wave + 4 * r;
-        const uint32_t hp = (uint32_t)(hb * 16 + n16);
-        const uint32_t py = fastdiv(hp, a.div_pw), px = hp - py * (uint32_t)PW;
-        const int iy = iy0 + (int)py, ix = ix0 + (int)px;
-        inside[r] = hb < nhb && (int)py < PH && (uint32_t)iy < (uint32_t)a.H && (uint32_t)ix < (uint32_t)a.W;
-        xv[r] = uint4{0u, 0u, 0u, 0u};
-        if (inside[r] && 8 * q < a.C1) xv[r] = *reinterpret_cast<const uint4 *>(x16 + ((size_t)(n * a.H + iy) * a.W + ix) * a.C1 + 8 * q);
-    }
-#pragma unroll
-    for (int t = 0; t < 12; ++t) w1r[t] = t < a.nt1 ? w1[t * 64] : uint4{0u, 0u, 0u, 0u};
-    if (BIAS) {
-        for (int i = tid; i < nslots; i += 256) { // bias tables, asked for behind the loads above
-            const int c = a.b1 || a.b2 ? a.perm[i] : -1;
-            lb1[i] = a.b1 && c >= 0 ? a.b1[c] : 0.f;
-            lb2[i] = a.b2 && c >= 0 ? a.b2[c] : 0.f;
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int hb = wave + 4 * r;
-        uint8_t *dst = y1 + (size_t)(hb * 16 + n16) * pitch + (uint32_t)(4 * q) * 2u;
-#pragma unroll
-        for (int t = 0; t < 12; ++t) {
-            if (hb < nhb && t < a.nt1) {
-                const f32x4 d = mfma16<DT>(w1r[t], xv[r], f32x4{0.f, 0.f, 0.f, 0.f});
-                float4 bb = float4{0.f, 0.f, 0.f, 0.f};
-                if (BIAS) bb = *reinterpret_cast<const float4 *>(lb1 + 16 * t + 4 * q); // result register i: slot 16 t + 4 q + i
-                uint2 o;
-                o.x = pack2<DT>(clampf<HSW>(d[0] + bb.x, cl1), clampf<HSW>(d[1] + bb.y, cl1));
-                o.y = pack2<DT>(clampf<HSW>(d[2] + bb.z, cl1), clampf<HSW>(d[3] + bb.w, cl1));
-                if (BIAS && !inside[r]) o = uint2{0u, 0u}; // padding of the depthwise layer, whatever the bias
-                *reinterpret_cast<uint2 *>(dst + t * 32) = o;
-            }
-        }
-    }
-    __syncthreads();
-
-    // ---- 2. depthwise + projection ---------------------------------------------------------
-    const Clamp cl2 = clamp_of(a.act2), cl3 = clamp_of(a.act3);
-    const uint4 *w3 = reinterpret_cast<const uint4 *>(a.w3) + lane;
-    uint16_t *y16 = reinterpret_cast<uint16_t *>(a.y);
-    for (int ob = wave; ob < nob; ob += 4) {
-        const uint32_t m = (uint32_t)(ob * 16 + n16);
-        const uint32_t ty = fastdiv(m, a.div_tw), tx = m - ty * (uint32_t)a.TW;
-        const int oy = ty0 + (int)ty, ox = tx0 + (int)tx;
-        const bool valid = (int)ty < a.TH && oy < a.Ho && ox < a.Wo;
-        const uint8_t *base = y1 + (valid ? (size_t)((ty * (uint32_t)PW + tx) * (uint32_t)a.stride) * pitch : 0) + (uint32_t)(8 * q) * 2u;
-        f32x4 acc0 = f32x4{0.f, 0.f, 0.f, 0.f}, acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < a.nk; ++k) {
-            const uint4 w3a = w3[k * 64], w3b = a.nt3 == 2 ? w3[(a.nk + k) * 64] : uint4{0u, 0u, 0u, 0u}; // asked for before the taps
-            float4 ba = float4{0.f, 0.f, 0.f, 0.f}, bb = ba;
-            if (BIAS) {
-                ba = *reinterpret_cast<const float4 *>(lb2 + 32 * k + 8 * q);
-                bb = *reinterpret_cast<const float4 *>(lb2 + 32 * k + 8 * q + 4);
-            }
-            float s[8] = {ba.x, ba.y, ba.z, ba.w, bb.x, bb.y, bb.z, bb.w};
-            uint4 vt[9]; // all nine taps asked for before the first is used
-#pragma unroll
-            for (int tap = 0; tap < 9; ++tap)
-                vt[tap] = *reinterpret_cast<const uint4 *>(base + (size_t)((tap / 3) * PW + tap % 3) * pitch + k * 64);
-#pragma unroll
-            for (int tap = 0; tap < 9; ++tap) {
-                const uint4 v = vt[tap];
-                const uint4 wa = *reinterpret_cast<const uint4 *>(dww + tap * nslots + 32 * k + 8 * q);
-                const uint4 wb = *reinterpret_cast<const uint4 *>(dww + tap * nslots + 32 * k + 8 * q + 4);
-                s[0] = dot2acc<DT>(v.x, wa.x, s[0]);
-                s[1] = dot2acc<DT>(v.x, wa.y, s[1]);
-                s[2] = dot2acc<DT>(v.y, wa.z, s[2]);
-                s[3] = dot2acc<DT>(v.y, wa.w, s[3]);
-                s[4] = dot2acc<DT>(v.z, wb.x, s[4]);
-                s[5] = dot2acc<DT>(v.z, wb.y, s[5]);
-                s[6] = dot2acc<DT>(v.w, wb.z, s[6]);
-                s[7] = dot2acc<DT>(v.w, wb.w, s[7]);
-            }
-            uint4 b;
-            b.x = pack2<DT>(clampf<HSW>(s[0], cl2), clampf<HSW>(s[1], cl2));
-            b.y = pack2<DT>(clampf<HSW>(s[2], cl2), clampf<HSW>(s[3], cl2));
-            b.z = pack2<DT>(clampf<HSW>(s[4], cl2), clampf<HSW>(s[5], cl2));
-            b.w = pack2<DT>(clampf<HSW>(s[6], cl2), clampf<HSW>(s[7], cl2));
-            acc0 = mfma16<DT>(w3a, b, acc0);
-            if (a.nt3 == 2) acc1 = mfma16<DT>(w3b, b, acc1);
-        }
-        if (!valid) continue;
-        const size_t pix = (size_t)(n * a.Ho + oy) * a.Wo + ox;
-        for (int u = 0; u < a.nt3; ++u) {
-            const int f = 16 * u + 4 * q;
-            if (f >= a.F3) continue;
-            const f32x4 d = u == 0 ? acc0 : acc1;
-            float v[4] = {d[0], d[1], d[2], d[3]};
-            if (BIAS && a.b3) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] += a.b3[f + i];
-            }
-            if (a.residual) {
-                const uint2 r = *reinterpret_cast<const uint2 *>(x16 + pix * a.C1 + f);
-                v[0] += from_storage<DT>((uint16_t)(r.x & 0xffffu));
-                v[1] += from_storage<DT>((uint16_t)(r.x >> 16));
-                v[2] += from_storage<DT>((uint16_t)(r.y & 0xffffu));
-                v[3] += from_storage<DT>((uint16_t)(r.y >> 16));
-            }
-            uint2 o;
-            o.x = pack2<DT>(clampf<HSW>(v[0], cl3), clampf<HSW>(v[1], cl3));
-            o.y = pack2<DT>(clampf<HSW>(v[2], cl3), clampf<HSW>(v[3], cl3));
-            store_stream8(y16 + pix * a.F3 + f, o);
-        }
-    }
-}
-// The activation kind is compiled in: hard-swish behind a (wave-uniform) branch per value kept the compiler from
-// interleaving loads, MFMAs and epilogue arithmetic across values and cost the launches without it 15-50 %.
-template <int DT, bool BIAS, bool HSW>
-__global__ __launch_bounds__(256, 3) void fused_inverted_residual_kernel(IrArgs a) // three workgroups per CU: at most 168 registers
-{
-    fused_inverted_residual_kernel_body<DT, BIAS, HSW>(a); // (a kernel per activation class, chosen at the launch: registers are tight here)
-}
-
-size_t fused_ir_lds_bytes(int TH, int TW, int nslots, int stride)
-{
-    const int nhb = (((TH - 1) * stride + 3) * ((TW - 1) * stride + 3) + 15) / 16;
-    return (size_t)nhb * 16 * ((size_t)nslots * 2 + kIrPad) + (size_t)9 * nslots * 4 + (size_t)2 * nslots * 4;
-}
-
-int launch_fused_inverted_residual(int dtype, const IrLaunch &l, void *stream)
-{
-    hipStream_t st = (hipStream_t)stream;
-    const int N = l.N, H = l.H, W = l.W, C1 = l.C1, F3 = l.F3, nslots = l.nslots, TH = l.TH, TW = l.TW, stride = l.stride;
-    IrArgs a;
-    a.x = l.x; a.y = l.y; a.w1 = l.w1; a.w3 = l.w3; a.wdw = l.wdw; a.perm = l.perm;
-    a.b1 = l.b1; a.b2 = l.b2; a.b3 = l.b3;
-    a.N = N; a.H = H; a.W = W; a.C1 = C1; a.F3 = F3;
-    a.stride = stride; a.Ho = (H - 1) / stride + 1; a.Wo = (W - 1) / stride + 1; // 3 x 3, padding 1
-    a.nt1 = nslots / 16; a.nk = nslots / 32; a.nt3 = (F3 + 15) / 16;
-    a.TH = TH; a.TW = TW; a.tilesY = (a.Ho + TH - 1) / TH; a.tilesX = (a.Wo + TW - 1) / TW;
-    a.act1 = l.act1; a.act2 = l.act2; a.act3 = l.act3; a.residual = l.residual;
-    const int PH = (TH - 1) * stride + 3, PW = (TW - 1) * stride + 3;
-    a.div_tw = TW <= 1 ? 0u : (uint32_t)(((1ull << 32) + TW - 1) / TW);
-    a.div_pw = (uint32_t)(((1ull << 32) + PW - 1) / PW);
-    const size_t lds_bytes = fused_ir_lds_bytes(TH, TW, nslots, stride);
-    if (nslots <= 0 || nslots % 32 || nslots > 192 || TH < 1 || TW < 1 || PH * PW > 256 || a.nt3 < 1 || a.nt3 > 2 || C1 > 32 || C1 % 8 || F3 % 4 ||
-        lds_bytes > 160 * 1024 || (stride != 1 && stride != 2) || (l.residual && (F3 != C1 || stride != 1)) || !l.perm) {
-        set_error("fused inverted residual: unsupported shape (slots %d, C1 %d, F3 %d, stride %d, LDS %zu)", nslots, C1, F3, stride, lds_bytes);
-        return NPAS_E_SHAPE;
-    }
-    const long grid = (long)N * a.tilesY * a.tilesX;
-    const bool bias = l.b1 || l.b2 || l.b3;
-    const bool hsw = l.act1 == NPAS_ACT_HARDSWISH || l.act2 == NPAS_ACT_HARDSWISH || l.act3 == NPAS_ACT_HARDSWISH;
-    static std::once_flag once[8];
-    auto go = [&](auto kern, std::once_flag &flag) {
-        allow_lds_once(flag, kern, 160 * 1024);
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds_bytes, st, a);
-    };
-    if (dtype == NPAS_BF16) {
-        if (bias && hsw) go(fused_inverted_residual_kernel<NPAS_BF16, true, true>, once[0]);
-        else if (bias) go(fused_inverted_residual_kernel<NPAS_BF16, true, false>, once[1]);
-        else if (hsw) go(fused_inverted_residual_kernel<NPAS_BF16, false, true>, once[2]);
-        else go(fused_inverted_residual_kernel<NPAS_BF16, false, false>, once[3]);
-    } else if (dtype == NPAS_F16) {
-        if (bias && hsw) go(fused_inverted_residual_kernel<NPAS_F16, true, true>, once[4]);
-        else if (bias) go(fused_inverted_residual_kernel<NPAS_F16, true, false>, once[5]);
-        else if (hsw) go(fused_inverted_residual_kernel<NPAS_F16, false, true>, once[6]);
-        else go(fused_inverted_residual_kernel<NPAS_F16, false, false>, once[7]);
-    } else {
-        set_error("fused inverted residual needs a 16-bit storage type");
-        return NPAS_E_DTYPE;
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) {
-        set_error("fused_inverted_residual launch failed: %s", hipGetErrorString(e));
         return NPAS_E_HIP;
     }
     return NPAS_OK;

@@ -356,12 +356,13 @@ bool fpp_supported(int nt1, int nt2);
 int launch_fused_pointwise_pair(int dtype, const void *x, void *y, const void *wblob, int M, int C1, int nt1, int F2,
                                 int act1, int act2, uint32_t use0, uint32_t use1, void *stream);
 size_t fused_ir_lds_bytes(int TH, int TW, int nslots, int stride);
+constexpr int fused_ir_wgs_per_cu(int nslots) { return nslots <= 96 ? 3 : 2; } // what the kernel's launch bounds allow
 // One launch of the fused 1x1 -> depthwise 3x3 -> 1x1 block (all pointers device memory).
 struct IrLaunch {
     const void *x;
     void *y;
     const void *w1, *w3;       // operand images of the two 1x1 layers in slot order
-    const uint32_t *wdw;       // depthwise weights in slot order
+    const uint32_t *wdw;       // depthwise weights, one word per lane and step
     const int *perm;           // intermediate channel of each slot (-1: padding)
     const float *b1, *b2, *b3; // biases in channel order, or null
     int N, H, W, C1, F3, nslots, TH, TW, stride;

@@ -367,6 +367,25 @@ def test_inverted_residual_block_layerwise_and_stack(npas, torch, stride, bias, 
         assert rel_err(border, want) <= 0.1, "border pixels (padding of the depthwise layer)"
 
 
+# Every slot count the fused block is compiled for, partial tiles of 32, 64 and more pixels (the tile follows the number of
+# tiles in the batch), filter counts that leave a 16-filter tile partial, dense and pruned projections.
+@pytest.mark.parametrize("N,HW,C,t,stride,rate,dtype,bias,act",
+                         [(1, 5, 8, 4, 1, 1, dtypes.BF16, True, configs.ACT_RELU6), (2, 9, 16, 4, 2, 1, dtypes.F16, True, configs.ACT_HARDSWISH),
+                          (3, 17, 24, 3, 1, 1, dtypes.BF16, False, configs.ACT_RELU), (24, 33, 24, 6, 1, 4, dtypes.BF16, True, configs.ACT_RELU6),
+                          (40, 41, 16, 8, 1, 1, dtypes.F16, True, configs.ACT_RELU6), (2, 31, 32, 5, 2, 1, dtypes.BF16, True, configs.ACT_RELU6),
+                          (33, 45, 32, 6, 1, 1, dtypes.BF16, True, configs.ACT_HARDSWISH), (70, 31, 24, 8, 2, 1, dtypes.BF16, False, configs.ACT_RELU6),
+                          (1, 1, 32, 6, 1, 2, dtypes.F16, True, configs.ACT_RELU6)])
+def test_fused_block_slots_and_tiles(npas, torch, N, HW, C, t, stride, rate, dtype, bias, act):
+    from workloads import sweeps
+    print(f"fused block N={N} {HW}x{HW} {C}->{C * t} stride {stride} rate {rate}", flush=True)
+    w = sweeps.inverted_residual_block(batch=N, HW=HW, C=C, t=t, stride=stride, rate=rate, dtype=dtype, bias=bias, act=act)
+    ref = oracle.run_stack(w.x_exact, w.layers, w.dtype)[0][-1]
+    got, st = _run_stack_gpu(npas, torch, w, npas.STACK_FUSE_INVERTED_RESIDUAL)
+    assert st.num_launches() == 1
+    norm, worst = helpers.check_stack_output(got.reshape(ref.shape), ref, STACK_NORM_TOL)
+    print(f"  norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
+
+
 def test_run_stack_in_a_hip_graph_replays_like_the_eager_call(npas, torch):
     """npas_run_stack allocates nothing and clears nothing during a run, so a caller may capture it.
     Several replays, with eager work and synchronisations in between, each against the eager result."""
