@@ -152,7 +152,8 @@ int npas_conv2d_sparse(const npas_packed *p, const void *x_dev, void *y_dev, int
 
 /* Name of the kernel npas_conv2d_sparse / npas_fc_sparse launch for this layer and geometry
  * ("conv_valu_f32", "conv_wave_f32", "conv_gather_mfma", "conv_slab_mfma", "pointwise_ring",
- * "spatial_ring", "spatial_resident", "conv_smallc_mfma", "conv_smallm_mfma", "fc_gather_mfma");
+ * "spatial_ring", "spatial_resident", "conv_smallc_mfma", "conv_smallm_mfma", "fc_gather_mfma";
+ * "conv_slab_mfma" names both forms of the slab route: the tiled kernel, and the flat one of 1x1 layers);
  * a static string, NULL for a NULL handle.  For reports and tests:
  * the choice depends on the packed format and on how well the problem fills the chip. */
 const char *npas_conv2d_kernel_name(const npas_packed *p, int N, int H, int W, int stride, int pad);

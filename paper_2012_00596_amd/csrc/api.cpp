@@ -329,7 +329,7 @@ bool plan_resident(const npas_packed *p, int N, int H, int W, int pad, SpatialRi
 }
 
 // Which kernel a run call launches for this layer and geometry.
-enum Route { R_VALU, R_WAVE_F32, R_FC_GATHER, R_POINTWISE_RING, R_SPATIAL_RING, R_SPATIAL_RESIDENT, R_SMALLC, R_SMALLM, R_SLAB, R_GATHER };
+enum Route { R_VALU, R_WAVE_F32, R_FC_GATHER, R_POINTWISE_RING, R_SPATIAL_RING, R_SPATIAL_RESIDENT, R_SMALLC, R_SMALLM, R_STREAM, R_SLAB, R_GATHER };
 
 // Tile and patch of a small-channel launch: TH x TW = 256 output pixels with the fewest computed-but-
 // unused ones, the patch within 48 KB of LDS.  False when no tile shape fits.
@@ -443,6 +443,7 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
         return R_POINTWISE_RING;
     }
     const int fv = switches().force;
+    if (p->stream.present && pad == 0) return R_STREAM;
     if (ring_ok && stride == 1 && (p->KH > 1 || p->KW > 1) && p->F <= 64 && fv != FV_NORESIDENT && plan_resident(p, N, H, W, pad, sp))
         return R_SPATIAL_RESIDENT;
     {
@@ -474,6 +475,7 @@ const char *route_name(const npas_packed *p, int N, int H, int W, int stride, in
     case R_SPATIAL_RESIDENT: return "spatial_resident";
     case R_SMALLC: return "conv_smallc_mfma";
     case R_SMALLM: return "conv_smallm_mfma";
+    case R_STREAM: // the slab route's flat form
     case R_SLAB: return "conv_slab_mfma";
     default: return "conv_gather_mfma";
     }
@@ -528,6 +530,15 @@ int run_conv(const npas_packed *p, const ConvPlan *plan, const void *x, void *y,
                 break;
             }
         return launch_fc_gather(p->dtype, a, stream);
+    }
+    if (route == R_STREAM) {
+        PwStreamArgs a;
+        a.x = x; a.y = y; a.residual = residual; a.bias = (const float *)bias; a.wimg = p->dev.swimg;
+        a.C = p->C; a.F = p->F; a.act = act;
+        a.H = H; a.W = W; a.stride = stride; a.flat = stride == 1;
+        a.Ho = (H - 1) / stride + 1; a.Wo = (W - 1) / stride + 1;
+        a.M = N * a.Ho * a.Wo;
+        return launch_pointwise_stream(p->dtype, a, stream);
     }
     if (route == R_WAVE_F32) {
         WaveF32Args a;

@@ -120,6 +120,13 @@ struct FcFormat {
     std::vector<uint16_t> wimg;
 };
 
+// ---- stream format: 16-bit 1x1 layers with C <= 320, no multiple of 64 (pointwise_stream): row-operand images of all
+// positions, image t*NS + s (NS = ceil(C / 32)), lane 16*q + r, value i = W[16 t + r][32 s + 8 q + i] (zero where pruned, past C or F).
+struct StreamFormat {
+    bool present = false;
+    std::vector<uint16_t> wimg;
+};
+
 // ---- lane-split format of fp32 layers (conv_wave_f32): the canonical group lists, each padded to a multiple of
 // 8 entries (entry coding as vkent, weight rows [entry][VB] as vw; padding entries carry zero weights and repeat the
 // group's first position, or position 0 of an empty group).  wg_ptr[v] .. wg_ptr[v+1] in entries.
@@ -147,6 +154,7 @@ struct DeviceCopy {
     const int32_t *fc_tptr = nullptr; // exact-list format
     const uint16_t *fc_koff = nullptr;
     const void *fc_wimg = nullptr;
+    const void *swimg = nullptr;      // stream format
     const int32_t *wv_ptr = nullptr;  // lane-split fp32 format
     const uint32_t *wv_kent = nullptr;
     const float *wv_w = nullptr;
@@ -171,6 +179,7 @@ struct npas_packed {
     npas::SmallCFormat smallc;
     npas::FcFormat fc;
     npas::WaveF32Format wavef;
+    npas::StreamFormat stream;
     npas::DeviceCopy dev;
     // launch plans already computed for this layer, by geometry (filled by the run calls)
     mutable std::mutex plan_mu;
@@ -311,6 +320,19 @@ struct FcGatherArgs {
     uint32_t div_howo, div_wo;
 };
 
+// 16-bit 1x1 layer through the stream format: see pointwise_stream_kernel (nt, tpg, groups are filled at the launch)
+struct PwStreamArgs {
+    const void *x;
+    void *y;
+    const void *residual;
+    const float *bias;
+    const void *wimg;
+    int M, C, F;                  // output pixels
+    int H, W, Ho, Wo, stride, flat; // flat: stride 1, input pixel index == output pixel index
+    int act;
+    int nt, tpg, groups;          // 16-filter tiles; tiles per filter group; groups
+};
+
 // fp32 layer with the reduction of every output split over 8 lanes: see conv_wave_f32_kernel
 struct WaveF32Args {
     const float *x;
@@ -351,6 +373,8 @@ size_t spatial_resident_lds_bytes(int npb, int nst); // LDS of a launch with npb
 int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream);
 int launch_conv_smallm(int dtype, const SmallMArgs &a, void *stream);
 int launch_fc_gather(int dtype, const FcGatherArgs &a, void *stream);
+bool pw_stream_supported(int C, int F);
+int launch_pointwise_stream(int dtype, PwStreamArgs a, void *stream);
 int launch_conv_wave_f32(const WaveF32Args &a, void *stream);
 bool fpp_supported(int nt1, int nt2);
 int launch_fused_pointwise_pair(int dtype, const void *x, void *y, const void *wblob, int M, int C1, int nt1, int F2,

@@ -379,6 +379,20 @@ static void build_fc(npas_packed *p, const uint8_t *m, const uint8_t *w)
     fc.tptr[fc.ntiles] = (int32_t)(fc.koff.size() / 32);
 }
 
+// Stream format (see npas_internal.h).
+static void build_stream(npas_packed *p, const uint8_t *m, const uint8_t *w)
+{
+    const int F = p->F, C = p->C, ns = (C + 31) / 32, nt = (F + 15) / 16;
+    p->stream.present = true;
+    p->stream.wimg.assign((size_t)nt * ns * 512, 0);
+    const uint16_t *w16 = reinterpret_cast<const uint16_t *>(w);
+    for (int f = 0; f < F; ++f)
+        for (int c = 0; c < C; ++c) {
+            const size_t wi = (size_t)f * C + c;
+            if (m[wi]) p->stream.wimg[(((size_t)(f >> 4) * ns + (c >> 5)) * 64 + ((c >> 3) & 3) * 16 + (f & 15)) * 8 + (c & 7)] = w16[wi];
+        }
+}
+
 // Lane-split fp32 format (see npas_internal.h): the sub-group lists of build_valu_f32, padded to multiples of 8.
 static void build_wave_f32(npas_packed *p)
 {
@@ -466,6 +480,9 @@ int build_device_format(npas_packed *p, const std::vector<uint8_t> &mask_full, c
         // sparse 1x1 / FC layers also get the exact per-tile lists (a staged activation row must fit in LDS sixteen times)
         if (p->KH == 1 && p->KW == 1 && p->F % 4 == 0 && p->C % 8 == 0 && p->C <= 4096 && p->fmt.density <= 0.5 && force != FV_NOFCGATHER)
             build_fc(p, mask_full.data(), (const uint8_t *)w_host);
+        // 1x1 layers without whole 64-channel chunks: every position present, streamed without any list
+        if (p->KH == 1 && p->KW == 1 && p->C % 64 != 0 && pw_stream_supported(p->C, p->F) && force != FV_GATHER && force != FV_SLAB)
+            build_stream(p, mask_full.data(), (const uint8_t *)w_host);
         if (p->C < 8 && p->F <= 64 && p->F % 4 == 0 && p->C * p->KH * p->KW <= 160 && p->KH * p->KW > 1 &&
             force != FV_NOSMALLC)
             build_smallc(p, mask_full.data(), (const uint8_t *)w_host);
@@ -500,6 +517,7 @@ int upload(npas_packed *p, void *hip_stream)
     size_t o_rp = place(blob, p->ring.rg_ptr), o_rc = place(blob, p->ring.rg_chunk), o_ri = place(blob, p->ring.wimg);
     size_t o_sc = place(blob, p->smallc.wimg);
     size_t o_ft = place(blob, p->fc.tptr), o_fk = place(blob, p->fc.koff), o_fw = place(blob, p->fc.wimg);
+    size_t o_sw = place(blob, p->stream.wimg);
     size_t o_wp = place(blob, p->wavef.wg_ptr), o_wk = place(blob, p->wavef.kent), o_ww = place(blob, p->wavef.w);
     blob.resize((blob.size() + 255) / 256 * 256 + 256);
     void *ptr = nullptr;
@@ -534,6 +552,7 @@ int upload(npas_packed *p, void *hip_stream)
     p->dev.fc_tptr = (const int32_t *)(b + o_ft);
     p->dev.fc_koff = (const uint16_t *)(b + o_fk);
     p->dev.fc_wimg = b + o_fw;
+    p->dev.swimg = b + o_sw;
     p->dev.wv_ptr = (const int32_t *)(b + o_wp);
     p->dev.wv_kent = (const uint32_t *)(b + o_wk);
     p->dev.wv_w = (const float *)(b + o_ww);

@@ -367,6 +367,23 @@ def test_inverted_residual_block_layerwise_and_stack(npas, torch, stride, bias, 
         assert rel_err(border, want) <= 0.1, "border pixels (padding of the depthwise layer)"
 
 
+# The flat 1x1 kernel: a last block of 1..15 pixels, a last 16-filter tile of 4, 8 and 12 filters, channel counts that end inside a
+# 32-deep step and 8 channels only, one and several filter groups (with and without 16-byte output segments), stride 2.
+STREAM_EDGES = [
+    ("flat_c8_f4_one_pixel", 1, 1, 1, 8, 4, 1, 1, 1, 0, 4, 4, 2, dtypes.BF16, 0, False, True),
+    ("flat_c24_f144_tail1", 3, 7, 83, 24, 144, 1, 1, 1, 0, 8, 8, 2, dtypes.BF16, 2, False, False),
+    ("flat_c144_f40_tail15_res", 5, 11, 37, 144, 40, 1, 1, 1, 0, 8, 8, 2, dtypes.F16, 3, True, True),
+    ("flat_c320m8_f300_groups", 2, 17, 61, 312, 300, 1, 1, 1, 0, 8, 4, 2, dtypes.BF16, 1, True, True),
+    ("flat_c280_f200_groups_s2", 5, 41, 39, 280, 200, 1, 1, 2, 0, 8, 8, 2, dtypes.F16, 0, True, False),
+    ("flat_c96_f12_many", 9, 61, 59, 96, 12, 1, 1, 1, 0, 4, 8, 2, dtypes.BF16, 2, True, True),
+]
+
+
+@pytest.mark.parametrize("case", STREAM_EDGES, ids=[c[0] for c in STREAM_EDGES])
+def test_flat_pointwise(npas, torch, case):
+    _run_edge_case(npas, torch, case)
+
+
 # Every slot count the fused block is compiled for, partial tiles of 32, 64 and more pixels (the tile follows the number of
 # tiles in the batch), filter counts that leave a 16-filter tile partial, dense and pruned projections.
 @pytest.mark.parametrize("N,HW,C,t,stride,rate,dtype,bias,act",
