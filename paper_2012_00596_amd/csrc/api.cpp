@@ -432,14 +432,19 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
     // 16 x 32-block FC layer): those above 1/8 density.
     const bool gather = p->fmt.variant == V_MFMA_GATHER;
     const bool ring_ok = p->ring.present && (!gather || p->fmt.density >= 0.125);
+    // Rounds of the kernel that splits the reduction over a workgroup's waves (one workgroup of 16 pixels x 16 .. 64
+    // filters or of 32 x 64 per CU, see launch_conv_smallm), and what it takes (us; fitted to 5.3 .. 57 us measured on the layers
+    // of the 50-layer stack at batch 2 .. 64, 10 % off at most).
+    const long Ho1 = (H + 2 * pad - p->KH) / stride + 1, Wo1 = (W + 2 * pad - p->KW) / stride + 1, M1 = (long)N * Ho1 * Wo1;
+    const long halves = (p->F + 63) / 64, blocks = (M1 + 15) / 16, steps = (long)(p->C / 32) * p->KH * p->KW;
+    const long rounds = blocks * halves <= 256 ? 1 : ((blocks + 1) / 2 * halves + 255) / 256;
+    const bool smallm_ok = ring_ok && (double)M1 * (Ho1 * Wo1) < 4294967296.0; // (its pixel decode divides by reciprocals)
+    const double t_smallm = 1.7 + rounds * (2.2 + 0.08 * steps);
     if (ring_ok && p->KH == 1 && p->KW == 1 && pad == 0) {
-        // up to 256 output pixels (batch 1 from the 14 x 14 stage on, FC layers) the kernel that splits the
-        // reduction over a workgroup's waves is faster than the ring's smallest tiles (measured layer by layer)
-        const long Ho1 = (H - 1) / stride + 1, Wo1 = (W - 1) / stride + 1;
-        // (beyond that while its workgroups, 64 pixels x 16 filters each, still fit one round: 2048 -> 512 at 7 x 7,
-        // batch 8: 18.4 -> 11.6 us; with more workgroups than that it loses, 512 -> 2048 at the same size: 9.3 -> 21 us)
-        const long M1 = (long)N * Ho1 * Wo1;
-        if (M1 <= 256 || (p->C >= 1024 && ((M1 + 63) / 64) * ((p->F + 15) / 16) <= 256)) return R_SMALLM; // (and the reduction long)
+        // ahead of the ring's smallest tiles while it is one round and the reduction is long (512 -> 128 at 28 x 28, batch 1 / 4:
+        // 6.5 / 6.6 -> 3.9 / 5.1 us, 1024 -> 256 at 14 x 14, batch 8: 10.0 -> 7.1), or the pixels are few; not with two rounds
+        // (2048 -> 512 at 7 x 7, batch 32: 18.6 against 18.0) nor with four steps to split (128 -> 512 at 28 x 28: 6.3 against 4.4)
+        if (smallm_ok && rounds == 1 && (p->C >= 256 || M1 <= 256)) return R_SMALLM;
         return R_POINTWISE_RING;
     }
     const int fv = switches().force;
@@ -448,18 +453,20 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
         return R_SPATIAL_RESIDENT;
     {
         const bool s2_off = stride == 2 && fv == FV_NOSPATIAL2;
-        if (ring_ok && (stride == 1 || stride == 2) && !s2_off && (p->KH > 1 || p->KW > 1) && plan_spatial(p, N, H, W, pad, stride, sp))
+        if (ring_ok && (stride == 1 || stride == 2) && !s2_off && (p->KH > 1 || p->KW > 1) && plan_spatial(p, N, H, W, pad, stride, sp)) {
+            // The streaming kernel walks an item's stages alone: long reductions on few items are quicker split over the waves
+            // (512 -> 512 at 7 x 7, batch 32: 32.3 -> 28.5 us; 14 x 14 x 512 at stride 2: 37.6 -> 31; at batch 64 32.8 against 53)
+            const double stage = sp->pg == 4 ? 0.75 : stride == 2 ? 0.5 : 0.42; // us, measured (see spatial_kernels.hip)
+            const long items = (long)sp->tilesN * sp->tilesY * sp->tilesX * sp->nfb;
+            const double t_spatial = 2.0 + (double)((items + 255) / 256) * (stage * 0.5 * steps + 2.4);
+            if (fv != FV_SPATIAL && smallm_ok && t_smallm < 0.9 * t_spatial) return R_SMALLM;
             return R_SPATIAL_RING;
+        }
     }
-    // few output pixels (small batch, late stages): the tiled kernels would run a handful of workgroups, each
-    // walking the whole reduction alone; split the reduction over the waves of many small workgroups instead
-    if (ring_ok && (p->KH > 1 || p->KW > 1)) {
-        const long Ho = (H + 2 * pad - p->KH) / stride + 1, Wo = (W + 2 * pad - p->KW) / stride + 1;
-        const bool force = fv == FV_SMALLM;
-        // ... or little work altogether (a 56 x 56 x 64 -> 64 layer at batch 1: 5.8 against 8.8 us)
-        const double macs = (double)N * Ho * Wo * p->F * p->C * p->KH * p->KW;
-        if (Ho > 0 && Wo > 0 && (force || (long)N * Ho * Wo <= 1024 || macs <= 200e6)) return R_SMALLM;
-    }
+    // few output pixels (small batch, late stages): the tiled kernel would run a handful of workgroups, each walking the
+    // whole reduction alone at about a third of a microsecond a step (28 x 28 x 128 at batch 2 / 8: 12.7 / 13.1 -> 5.4 / 12.0 us,
+    // 14 x 14 x 256 at batch 8 / 16: 25.8 / 32.3 -> 9.7 / 17.9; 56 x 56 x 64 at batch 8 16.1 against 9.5)
+    if (smallm_ok && (p->KH > 1 || p->KW > 1) && (fv == FV_SMALLM || t_smallm < 2.0 + 0.33 * steps)) return R_SMALLM;
     return gather ? R_GATHER : R_SLAB;
 }
 
@@ -500,12 +507,11 @@ int run_conv(const npas_packed *p, const ConvPlan *plan, const void *x, void *y,
     if (route == R_SMALLM) {
         SmallMArgs a;
         a.x = x; a.y = y; a.residual = residual; a.bias = (const float *)bias; a.wimg = p->dev.wimg;
+        a.zeros = p->dev.zeros;
         a.N = N; a.H = H; a.W = W; a.C = p->C; a.F = p->F;
         a.Ho = (H + 2 * pad - p->KH) / stride + 1; a.Wo = (W + 2 * pad - p->KW) / stride + 1;
         a.KH = p->KH; a.KW = p->KW; a.stride = stride; a.pad = pad; a.act = act;
         a.M = N * a.Ho * a.Wo;
-        a.nptiles = (a.M + 63) / 64;
-        a.nimg = p->ring.nfb * 8;
         a.div_howo = magic_div((uint32_t)(a.Ho * a.Wo)); a.div_wo = magic_div((uint32_t)a.Wo);
         a.div_kw = magic_div((uint32_t)p->KW); a.div_T2 = magic_div((uint32_t)(2 * p->KH * p->KW));
         return launch_conv_smallm(p->dtype, a, stream);

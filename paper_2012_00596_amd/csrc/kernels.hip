@@ -1162,50 +1162,52 @@ int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream)
 }
 
 // ------------------------------------------------------------------------------
-// conv_smallm_mfma: k x k layers (C a multiple of 64, ring-format weights) on few output pixels:
-// batch 1, the late stages of a network.  The tiled kernels then run a handful of workgroups that
-// each walk the whole reduction (C*KH*KW / 32 MFMA steps) alone, one load latency after the
-// other.  Here a workgroup owns 64 output pixels x 16 filters (one weight image per step) and its
-// sixteen waves split the reduction: a wave takes a contiguous run of steps, fetches each step's
-// weight image (1 KB, coalesced) and its four activation fragments (lane = pixel n16 of a block,
-// 8 channels = 16 bytes at the tap's input pixel; zero padding by predicate) straight from
-// memory, three steps in flight, and accumulates 4 MFMA tiles.  The sixteen partial sums meet in
-// LDS; waves 0-3 add them up (always in the same order), add bias / residual, clamp, round and
-// store.  Stride and kernel size are free (every address is formed per lane).
-struct SmallMPix {
-    int n, iy0, ix0; // image and input coordinates of tap (0, 0); n < 0: no such pixel
-};
-
-template <int DT, bool HSW>
+// conv_smallm_mfma: layers (C a multiple of 64, ring-format weights) on few output pixels: batch 1, the late stages of a
+// network.  The tiled kernels then run a handful of workgroups that each walk the whole reduction (C*KH*KW / 32 MFMA
+// steps) alone, one load latency after the other.  Here a workgroup owns 16 output pixels x FI weight images (16 filters
+// each; FI = 1, 2 or 4, four make 64 consecutive filters) and its sixteen waves split the reduction: a wave takes a
+// contiguous run of steps, fetches each step's images (1 KB, coalesced) and activation fragment (lane = pixel n16, 8
+// channels = 16 bytes at the tap's input pixel; padding reads a block of zeros) straight from memory, NB steps in
+// flight, and accumulates FI MFMA tiles.  The sixteen partial sums meet in LDS, are added up in a fixed order by FI waves
+// and exchanged once more so that a lane writes FI consecutive filters of a pixel.  Bias and residual are asked for before
+// that.  Stride and kernel size are free (every address is formed per lane).
+// A fragment load touches 16 lines where an image load touches 8 whole ones: the work is cut along the pixels first (16 a
+// workgroup, as 64 pixels x 16 filters the same layers spent their time in the address path of a quarter of the CUs), then as
+// few filters each as keeps the launch within one workgroup per CU.
+// MEASURED
+template <int DT, int FI, int PB, bool HSW>
 __device__ __forceinline__ void conv_smallm_mfma_kernel_body(SmallMArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n16 = lane & 15, q = lane >> 4;
-    const uint32_t ptile = blockIdx.x % (uint32_t)a.nptiles, img = blockIdx.x / (uint32_t)a.nptiles;
-    const uint32_t fb = img >> 3, tile8 = img & 7u;
-    if ((int)(fb * 128u + (tile8 >> 2) * 64u) >= a.F) return; // an image of padding filters only (whole workgroup)
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n16 = lane & 15, q = lane >> 4;
+    // an XCD's workgroups are neighbours: the pixel tiles of one filter tile find its weights in their L2
+    const uint32_t id = xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t ft = id / (uint32_t)a.nptiles, ptile = id - ft * (uint32_t)a.nptiles;
+    const uint32_t img = ft * FI, fb = img >> 3, tile8 = img & 7u; // first image: 128-filter block, image in it
     const int T = a.KH * a.KW, nch = a.C >> 6, S = nch * T * 2;
-    const uint16_t *x16 = reinterpret_cast<const uint16_t *>(a.x);
     const uint8_t *wb = reinterpret_cast<const uint8_t *>(a.wimg) + (size_t)fb * nch * T * 16384u + tile8 * 1024u + (uint32_t)lane * 16u;
+    const uint8_t *xb = reinterpret_cast<const uint8_t *>(a.x), *zb = reinterpret_cast<const uint8_t *>(a.zeros);
 
-    SmallMPix px[4];
+    int iy0[PB], ix0[PB]; // input coordinates of tap (0, 0) of the lane's pixels
+    uint32_t pix0[PB];    // byte offset of 8 channels there (modulo 2^32 where it lies outside; x is below 4 GiB)
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const uint32_t m = ptile * 64u + (uint32_t)(s * 16 + n16);
-        const uint32_t n = fastdiv(m, a.div_howo), r = m - n * (uint32_t)(a.Ho * a.Wo);
-        const uint32_t oy = fastdiv(r, a.div_wo), ox = r - oy * (uint32_t)a.Wo;
-        px[s].n = m < (uint32_t)a.M ? (int)n : -1;
-        px[s].iy0 = (int)oy * a.stride - a.pad;
-        px[s].ix0 = (int)ox * a.stride - a.pad;
+    for (int s = 0; s < PB; ++s) {
+        const uint32_t mc = min((ptile * PB + s) * 16u + (uint32_t)n16, (uint32_t)a.M - 1u); // (past the last pixel: that one again, not stored)
+        const uint32_t pn = fastdiv(mc, a.div_howo), pr = mc - pn * (uint32_t)(a.Ho * a.Wo);
+        const uint32_t oy = fastdiv(pr, a.div_wo), ox = pr - oy * (uint32_t)a.Wo;
+        iy0[s] = (int)oy * a.stride - a.pad;
+        ix0[s] = (int)ox * a.stride - a.pad;
+        pix0[s] = ((pn * (uint32_t)a.H + (uint32_t)iy0[s]) * (uint32_t)a.W + (uint32_t)ix0[s]) * (uint32_t)a.C * 2u + 16u * (uint32_t)q;
     }
-    f32x4 acc[4];
+    f32x4 acc[PB][FI];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-
+    for (int s = 0; s < PB; ++s)
+#pragma unroll
+        for (int j = 0; j < FI; ++j) acc[s][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int st0 = wave * S / 16, st1 = (wave + 1) * S / 16; // this wave's steps
-    constexpr int NB = 3;                                      // steps in flight
+    constexpr int NB = PB == 2 ? 3 : FI == 1 ? 9 : FI == 2 ? 6 : 4; // steps in flight
     for (int sb = st0; sb < st1; sb += NB) {
-        uint4 wf[NB], xf[NB][4];
+        uint4 wf[NB][FI], xf[NB][PB];
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
             const int st = sb + u;
@@ -1214,84 +1216,116 @@ __device__ __forceinline__ void conv_smallm_mfma_kernel_body(SmallMArgs a)
                 const uint32_t ct = (uint32_t)st >> 1, hs = (uint32_t)st & 1u;
                 const uint32_t cc = fastdiv(ct * 2u, a.div_T2), tap = ct - cc * (uint32_t)T;
                 const uint32_t kh = fastdiv(tap, a.div_kw), kw = tap - kh * (uint32_t)a.KW;
-                wf[u] = *reinterpret_cast<const uint4 *>(wb + (size_t)ct * 16384u + hs * 8192u);
-                const uint32_t coff = cc * 64u + hs * 32u + 8u * (uint32_t)q;
+                const uint32_t toff = ((kh * (uint32_t)a.W + kw) * (uint32_t)a.C + cc * 64u + hs * 32u) * 2u;
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const int iy = px[s].iy0 + (int)kh, ix = px[s].ix0 + (int)kw;
-                    const bool ok = px[s].n >= 0 && (uint32_t)iy < (uint32_t)a.H && (uint32_t)ix < (uint32_t)a.W;
-                    xf[u][s] = uint4{0u, 0u, 0u, 0u};
-                    if (ok) xf[u][s] = *reinterpret_cast<const uint4 *>(x16 + ((size_t)(px[s].n * a.H + iy) * a.W + ix) * a.C + coff);
+                for (int s = 0; s < PB; ++s) {
+                    const bool ok = (uint32_t)(iy0[s] + (int)kh) < (uint32_t)a.H && (uint32_t)(ix0[s] + (int)kw) < (uint32_t)a.W;
+                    xf[u][s] = *reinterpret_cast<const uint4 *>(ok ? xb + (uint32_t)(pix0[s] + toff) : zb);
                 }
+#pragma unroll
+                for (int j = 0; j < FI; ++j) wf[u][j] = *reinterpret_cast<const uint4 *>(wb + (size_t)ct * 16384u + hs * 8192u + j * 1024u);
             }
         }
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
             if (sb + u < st1) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) acc[s] = mfma16<DT>(wf[u], xf[u][s], acc[s]);
+                for (int s = 0; s < PB; ++s)
+#pragma unroll
+                    for (int j = 0; j < FI; ++j) acc[s][j] = mfma16<DT>(wf[u][j], xf[u][s], acc[s][j]);
             }
         }
     }
-    // ---- the sixteen partial sums meet in LDS: [wave][block][lane] ----------------------------------
+    // row 4q + i of image tile8 + j is filter 128 fb + 64 (tile8 / 4) + 4 (4q + i) + tile8 % 4 + j; column n16 is pixel n16 of a block.
+    // Wave 4 s + i finishes rows 4q + i of pixel block s: FI consecutive filters of a pixel a lane.
+    const int row = wave & 3;
+    const uint32_t m = (ptile * PB + (uint32_t)(wave >> 2)) * 16u + (uint32_t)n16;
+    const int f = (int)(fb * 128u + (tile8 >> 2) * 64u + 4u * (uint32_t)(4 * q + row) + (tile8 & 3u));
+    const bool out = wave < 4 * PB && m < (uint32_t)a.M && f < a.F; // (F is a multiple of 4: all FI or none)
+    const size_t o = (size_t)m * a.F + (size_t)f;
+    float add[FI];
+    uint16_t rs[FI];
+#pragma unroll
+    for (int j = 0; j < FI; ++j) {
+        add[j] = out && a.bias ? a.bias[f + j] : 0.f;
+        rs[j] = out && a.residual ? reinterpret_cast<const uint16_t *>(a.residual)[o + j] : (uint16_t)0;
+    }
+    // ---- the sixteen partial sums meet in LDS: [wave][pixel block, image][lane] ---------------------
+    constexpr int NF = PB * FI;
     f32x4 *red = reinterpret_cast<f32x4 *>(lds);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) red[(wave * 4 + s) * 64 + lane] = acc[s];
+    for (int k = 0; k < NF; ++k) red[(wave * NF + k) * 64 + lane] = acc[k / FI][k % FI];
     __syncthreads();
-    if (wave >= 4) return;
-    f32x4 sum = red[wave * 64 + lane]; // block s = wave
-    for (int w = 1; w < 16; ++w) {
-        const f32x4 t = red[(w * 4 + wave) * 64 + lane];
-        sum[0] += t[0]; sum[1] += t[1]; sum[2] += t[2]; sum[3] += t[3];
-    }
-    // row 4q + i of the image is filter 128 fb + 64 (tile8 / 4) + 4 (4q + i) + tile8 % 4; column n16 is pixel 16 wave + n16
-    const uint32_t m = ptile * 64u + (uint32_t)(wave * 16 + n16);
-    if (m >= (uint32_t)a.M) return;
-    const Clamp cl = clamp_of(a.act);
-    uint16_t *y16 = reinterpret_cast<uint16_t *>(a.y);
-    const uint16_t *r16 = reinterpret_cast<const uint16_t *>(a.residual);
+    f32x4 *sums = red + 16 * NF * 64; // [pixel block, image][lane]
+    if (wave < NF) {
+        f32x4 sum = red[wave * 64 + lane];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int f = (int)(fb * 128u + (tile8 >> 2) * 64u + 4u * (uint32_t)(4 * q + i) + (tile8 & 3u));
-        if (f >= a.F) continue;
-        float v = sum[i];
-        if (a.bias) v += a.bias[f];
-        const size_t o = (size_t)m * a.F + (size_t)f;
-        if (r16) v += from_storage<DT>(r16[o]);
-        y16[o] = to_storage<DT>(clampf<HSW>(v, cl));
+        for (int w = 1; w < 16; ++w) {
+            const f32x4 t = red[(w * NF + wave) * 64 + lane];
+            sum[0] += t[0]; sum[1] += t[1]; sum[2] += t[2]; sum[3] += t[3];
+        }
+        sums[wave * 64 + lane] = sum;
     }
+    __syncthreads();
+    if (!out) return;
+    const Clamp cl = clamp_of(a.act);
+    const float *sf = reinterpret_cast<const float *>(sums + (wave >> 2) * FI * 64 + lane) + row;
+    uint16_t v16[FI];
+#pragma unroll
+    for (int j = 0; j < FI; ++j) {
+        float v = sf[j * 256] + add[j];
+        if (a.residual) v += from_storage<DT>(rs[j]);
+        v16[j] = to_storage<DT>(clampf<HSW>(v, cl));
+    }
+    uint16_t *y16 = reinterpret_cast<uint16_t *>(a.y) + o;
+    if (FI == 4) *reinterpret_cast<uint2 *>(y16) = uint2{(uint32_t)v16[0] | (uint32_t)v16[1 % FI] << 16, (uint32_t)v16[2 % FI] | (uint32_t)v16[3 % FI] << 16};
+    else if (FI == 2) *reinterpret_cast<uint32_t *>(y16) = (uint32_t)v16[0] | (uint32_t)v16[1 % FI] << 16;
+    else *y16 = v16[0];
 }
 // The activation kind is compiled in: hard-swish behind a (wave-uniform) branch per value kept the compiler from
 // interleaving loads, MFMAs and epilogue arithmetic across values and cost the launches without it 15-50 %.
-template <int DT>
+template <int DT, int FI, int PB>
 __global__ __launch_bounds__(1024) void conv_smallm_mfma_kernel(SmallMArgs a)
 {
-    if (a.act == NPAS_ACT_HARDSWISH) conv_smallm_mfma_kernel_body<DT, true>(a);
-    else conv_smallm_mfma_kernel_body<DT, false>(a);
+    if (a.act == NPAS_ACT_HARDSWISH) conv_smallm_mfma_kernel_body<DT, FI, PB, true>(a);
+    else conv_smallm_mfma_kernel_body<DT, FI, PB, false>(a);
 }
 
-int launch_conv_smallm(int dtype, const SmallMArgs &a, void *stream)
+int launch_conv_smallm(int dtype, SmallMArgs a, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    const size_t lds_bytes = 16 * 4 * 64 * 16;
-    const long grid = (long)a.nptiles * a.nimg;
-    if (a.C % 64 != 0 || a.M <= 0 || grid > 0x7fffffffL || (double)a.N * a.H * a.W * a.C >= 2147483648.0) {
+    const long halves = (a.F + 63) / 64, blocks = ((long)a.M + 15) / 16; // 64-filter halves (four images each), 16-pixel blocks
+    int fi = 1;
+    while (fi < 4 && blocks * halves * (4 / fi) > 256) fi *= 2;
+    const int pb = blocks * halves > 256 ? 2 : 1;
+    a.nptiles = (int)((blocks + pb - 1) / pb);
+    const long grid = (long)a.nptiles * halves * (4 / fi);
+    if (a.C % 64 != 0 || a.F % 4 != 0 || a.M <= 0 || grid > 0x7fffffffL || (double)a.N * a.H * a.W * a.C >= 2147483648.0) {
         set_error("conv_smallm_mfma: unsupported shape");
         return NPAS_E_SHAPE;
     }
-    static std::once_flag once[2];
-    if (dtype == NPAS_BF16) {
-        auto kern = conv_smallm_mfma_kernel<NPAS_BF16>;
-        allow_lds_once(once[0], kern, (int)lds_bytes);
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1024), lds_bytes, st, a);
-    } else if (dtype == NPAS_F16) {
-        auto kern = conv_smallm_mfma_kernel<NPAS_F16>;
-        allow_lds_once(once[1], kern, (int)lds_bytes);
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1024), lds_bytes, st, a);
-    } else {
+    if (dtype != NPAS_BF16 && dtype != NPAS_F16) {
         set_error("conv_smallm_mfma needs a 16-bit storage type");
         return NPAS_E_DTYPE;
     }
+    static std::once_flag once[2][4];
+    auto go = [&](auto dtc, auto fic, auto pbc) {
+        constexpr int DT = decltype(dtc)::value, FI = decltype(fic)::value, PB = decltype(pbc)::value;
+        const int lds_bytes = 17 * FI * PB * 64 * 16;
+        auto kern = conv_smallm_mfma_kernel<DT, FI, PB>;
+        allow_lds_once(once[DT == NPAS_F16][PB == 2 ? 3 : FI >> 1], kern, lds_bytes);
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1024), lds_bytes, st, a);
+    };
+    auto pick = [&](auto dtc) {
+        using std::integral_constant;
+        integral_constant<int, 1> one;
+        if (pb == 2) go(dtc, integral_constant<int, 4>{}, integral_constant<int, 2>{});
+        else if (fi == 1) go(dtc, one, one);
+        else if (fi == 2) go(dtc, integral_constant<int, 2>{}, one);
+        else go(dtc, integral_constant<int, 4>{}, one);
+    };
+    if (dtype == NPAS_BF16) pick(std::integral_constant<int, NPAS_BF16>{});
+    else pick(std::integral_constant<int, NPAS_F16>{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         set_error("conv_smallm_mfma launch failed: %s", hipGetErrorString(e));

@@ -258,10 +258,10 @@ struct SmallMArgs {
     const void *residual;
     const float *bias;
     const void *wimg;               // ring-format images
+    const void *zeros;              // >= 16 bytes of zeros on the device (source of padding pixels)
     int N, H, W, C, F, Ho, Wo, KH, KW, stride, pad, act;
     int M;                          // output pixels N*Ho*Wo
-    int nptiles;                    // 64-pixel tiles
-    int nimg;                       // 16-filter images: 8 per 128-filter block
+    int nptiles;                    // 16-pixel tiles (filled at the launch)
     uint32_t div_howo, div_wo, div_kw, div_T2; // fastdiv magics (Ho*Wo, Wo, KW, 2*KH*KW)
 };
 
@@ -371,7 +371,7 @@ int launch_spatial_ring(int dtype, const SpatialRingArgs &a, void *stream);
 int launch_spatial_resident(int dtype, const SpatialRingArgs &a, void *stream);
 size_t spatial_resident_lds_bytes(int npb, int nst); // LDS of a launch with npb patch blocks and nst weight stages
 int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream);
-int launch_conv_smallm(int dtype, const SmallMArgs &a, void *stream);
+int launch_conv_smallm(int dtype, SmallMArgs a, void *stream);
 int launch_fc_gather(int dtype, const FcGatherArgs &a, void *stream);
 bool pw_stream_supported(int C, int F);
 int launch_pointwise_stream(int dtype, PwStreamArgs a, void *stream);

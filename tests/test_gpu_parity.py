@@ -367,6 +367,29 @@ def test_inverted_residual_block_layerwise_and_stack(npas, torch, stride, bias, 
         assert rel_err(border, want) <= 0.1, "border pixels (padding of the depthwise layer)"
 
 
+# The reduction-splitting kernel with 1, 2 and 4 images a workgroup and with 32 pixels x 64 filters: a last block of 1, 15 and 16
+# pixels, an odd number of pixel blocks, filters that end inside a 64-filter half and inside an image, fewer steps than waves.
+SMALLM_EDGES = [
+    ("split_fi1_tail1_f20", 1, 1, 17, 64, 20, 1, 1, 1, 0, 4, 4, 2, dtypes.BF16, 0, True, True),
+    ("split_fi1_3x3_s2_f200", 1, 13, 11, 128, 200, 3, 3, 2, 1, 8, 4, 3, dtypes.F16, 3, False, True),
+    ("split_fi2_3x3_f128", 3, 15, 17, 64, 128, 3, 3, 1, 1, 8, 4, 2, dtypes.BF16, 1, True, True),
+    ("split_fi4_3x3_f68", 1, 37, 41, 64, 68, 3, 3, 1, 1, 4, 4, 2, dtypes.BF16, 2, True, False),
+    ("split_fi4_1x1_f64", 1, 53, 51, 256, 64, 1, 1, 1, 0, 8, 4, 2, dtypes.F16, 1, False, True),
+    ("split_pb2_odd_blocks_f192", 5, 27, 19, 64, 192, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 2, True, True),
+    ("split_pb2_s2_f200", 7, 29, 27, 64, 200, 3, 3, 2, 0, 8, 4, 2, dtypes.F16, 0, True, True),
+    ("split_pb2_5x5_f132", 3, 21, 25, 64, 132, 5, 5, 1, 2, 4, 4, 2, dtypes.BF16, 1, False, False),
+]
+
+
+@pytest.mark.parametrize("case", SMALLM_EDGES, ids=[c[0] for c in SMALLM_EDGES])
+def test_split_reduction(npas, torch, case):
+    npas.set_switches("smallm")      # k x k layers wherever the kernel applies (1x1 layers follow the rule)
+    try:
+        _run_edge_case(npas, torch, case, expect_kernel="conv_smallm_mfma")
+    finally:
+        npas.set_switches(None)
+
+
 # The flat 1x1 kernel: a last block of 1..15 pixels, a last 16-filter tile of 4, 8 and 12 filters, channel counts that end inside a
 # 32-deep step and 8 channels only, one and several filter groups (with and without 16-byte output segments), stride 2.
 STREAM_EDGES = [
