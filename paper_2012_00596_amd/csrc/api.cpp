@@ -420,13 +420,6 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
         const bool small = (double)N * Ho0 * Wo0 * p->fmt.nvg * 8.0 <= 4.0 * 1024 * 1024;
         return p->wavef.present && small && switches().force != FV_VALU ? R_WAVE_F32 : R_VALU;
     }
-    // sparse 1x1 / FC layer on few pixels: the exact per-tile lists (nothing pruned is multiplied, compact weights)
-    if (p->fc.present && p->KH == 1 && p->KW == 1 && pad == 0 && switches().force != FV_NOFCGATHER) {
-        const long M0 = (long)N * ((H - 1) / stride + 1) * ((W - 1) / stride + 1);
-        if (M0 <= 1024) return R_FC_GATHER;
-    }
-    SmallCArgs sc_local;
-    if (p->smallc.present && plan_smallc(p, N, H, W, stride, pad, sc ? sc : &sc_local)) return R_SMALLC;
     // A gather-format layer (few surviving positions) leaves the ring kernels, which multiply
     // everything, only the launches they win (measured on the 3x3 256 -> 256 rate sweep and the
     // 16 x 32-block FC layer): those above 1/8 density.
@@ -440,6 +433,18 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
     const long rounds = blocks * halves <= 256 ? 1 : ((blocks + 1) / 2 * halves + 255) / 256;
     const bool smallm_ok = ring_ok && (double)M1 * (Ho1 * Wo1) < 4294967296.0; // (its pixel decode divides by reciprocals)
     const double t_smallm = 1.7 + rounds * (2.2 + 0.08 * steps);
+    // sparse 1x1 / FC layer on few pixels: the exact per-tile lists (nothing pruned is multiplied, compact weights) ...
+    if (p->fc.present && p->KH == 1 && p->KW == 1 && pad == 0 && M1 <= 1024 && switches().force != FV_NOFCGATHER) {
+        // ... unless the weights are many and either little of them is skipped or there are few pixels to gather them for: the dense
+        // images are then quicker to stream than the lists to follow (1280 -> 1000 at 2x, 64 / 256 / 512 rows: 4.8 / 7.7 / 9.2 us ->
+        // 4.4 / 5.9 / 8.1, at 5x 4.6 / 5.6 / 5.9 against 4.4 / 5.8 / 8.1; 2048 -> 1000 at 5x, 128 rows 6.5 -> 5.9;
+        // 2432 -> 1372 at 5x, 256 rows 13.5 -> 11.0; 512 -> 1000 at 2x, 256 / 512 rows 4.8 / 5.1 against 4.4 / 5.4)
+        const bool dense = smallm_ok && rounds == 1 && p->C >= 256 && (double)p->C * p->F >= 131072.0 &&
+                           ((p->fmt.density > 0.3 && (p->C >= 1024 || blocks * halves <= 256)) || (p->C >= 1024 && (M1 <= 128 || p->C > 2048)));
+        return dense ? R_SMALLM : R_FC_GATHER;
+    }
+    SmallCArgs sc_local;
+    if (p->smallc.present && plan_smallc(p, N, H, W, stride, pad, sc ? sc : &sc_local)) return R_SMALLC;
     if (ring_ok && p->KH == 1 && p->KW == 1 && pad == 0) {
         // ahead of the ring's smallest tiles while it is one round and the reduction is long (512 -> 128 at 28 x 28, batch 1 / 4:
         // 6.5 / 6.6 -> 3.9 / 5.1 us, 1024 -> 256 at 14 x 14, batch 8: 10.0 -> 7.1), or the pixels are few; not with two rounds
