@@ -175,10 +175,14 @@ int launch_fc_gather(int dtype, const FcGatherArgs &a, void *stream)
 // ------------------------------------------------------------------------------
 // conv_wave_f32: eight consecutive lanes own one (output pixel, filter sub-group of VB <= 8 filters).  Lane l takes
 // list entries l, l + 8, l + 16, ... of the group's kept positions (the lists are padded to multiples of 8 with
-// zero weights), all its loads in flight at once, and accumulates in fp64 (products of two fp32 values are exact
-// there).  The eight partial sums per filter are added across lanes in a fixed tree (lane pairs 1, 2, 4 apart), so
-// the result does not vary from run to run; lanes 0 .. VB-1 then each finish one filter (bias, residual, activation)
-// and store it.
+// zero weights), U rounds of them in flight at once with the entries of the next U already asked for, and accumulates in
+// fp64 (products of two fp32 values are exact there).  The eight partial sums per filter are added across lanes in a fixed
+// tree (lane pairs 1, 2, 4 apart), so the result does not vary from run to run; lanes 0 .. VB-1 then each finish one filter
+// (bias, residual, activation) and store it.
+// Bound by load latency: entry, then activation, round after round; the entries asked for a step ahead take one of the two out
+// of the chain: 1 x 32 x 32 x 16 -> 32, 3 x 3 4.9 -> 4.1 us, 1 x 20 x 20 x 48 -> 64, 5 x 5 23.0 -> 16.6, 4 x 40 x 40 x 48 -> 64, 5 x 5
+// 74 -> 69.  (Two and four pixels a lane, sharing entry and weights, were slower, 91 and 89 us on the last and 6.1 and 9.0 on the
+// first; so were four and six rounds in flight and padding positions loaded without a branch.)
 constexpr int kWaveLanes = 8;
 
 __device__ __forceinline__ double lane_xor_add(double v, int mask)
@@ -198,31 +202,36 @@ __global__ __launch_bounds__(256) void conv_wave_f32_kernel(WaveF32Args a)
     const uint32_t ox = pc % (uint32_t)a.Wo, t = pc / (uint32_t)a.Wo;
     const uint32_t oy = t % (uint32_t)a.Ho, n = t / (uint32_t)a.Ho;
     const int f0 = a.vg_f0[vg];
-    const int k0 = a.wg_ptr[vg], k1 = a.wg_ptr[vg + 1];
+    const int k0 = a.wg_ptr[vg], rounds = (a.wg_ptr[vg + 1] - k0) / kWaveLanes; // (of eight entries: the same for the whole workgroup)
     const int by = (int)oy * a.stride - a.pad, bx = (int)ox * a.stride - a.pad;
     const float *xn = a.x + (size_t)n * a.H * a.W * a.C;
     double acc[VB];
 #pragma unroll
     for (int j = 0; j < VB; ++j) acc[j] = 0.0;
     constexpr int U = 3; // list rounds in flight
-    for (int kb = k0 + (int)l8; kb < k1; kb += kWaveLanes * U) {
+    const uint32_t *ents = a.kent + k0 + l8;
+    const float *ws = a.w + (size_t)(k0 + (int)l8) * VB;
+    uint32_t ent[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) ent[u] = u < rounds ? ents[kWaveLanes * u] : 0u;
+    for (int r = 0; r < rounds; r += U) {
         float xv[U];
         float wv[U][VB];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int k = kb + kWaveLanes * u;
             xv[u] = 0.0f;
 #pragma unroll
             for (int j = 0; j < VB; ++j) wv[u][j] = 0.0f;
-            if (k < k1) {
-                const uint32_t ent = a.kent[k];
-                const int iy = by + (int)(ent >> 24), ix = bx + (int)((ent >> 16) & 255u);
-                if (iy >= 0 && iy < a.H && ix >= 0 && ix < a.W) xv[u] = xn[(size_t)(iy * a.W + ix) * a.C + (ent & 0xffffu)];
-                const float *w = a.w + (size_t)k * VB;
+            if (r + u < rounds) { // (the same for the whole workgroup)
+                const int iy = by + (int)(ent[u] >> 24), ix = bx + (int)((ent[u] >> 16) & 255u);
+                if ((uint32_t)iy < (uint32_t)a.H && (uint32_t)ix < (uint32_t)a.W) xv[u] = xn[(size_t)(iy * a.W + ix) * a.C + (ent[u] & 0xffffu)];
+                const float *w = ws + (size_t)(r + u) * (kWaveLanes * VB);
 #pragma unroll
                 for (int j = 0; j < VB; ++j) wv[u][j] = w[j];
             }
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) ent[u] = r + U + u < rounds ? ents[kWaveLanes * (r + U + u)] : 0u;
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
