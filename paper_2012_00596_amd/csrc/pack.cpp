@@ -65,6 +65,9 @@ static inline void put_weight(uint8_t *dst, const uint8_t *src, int esz, bool ke
 
 static int check_mask_values(const uint8_t *m, size_t n)
 {
+    uint8_t bits = 0; // (a loop without an exit, vectorised; the offender is looked for only when there is one)
+    for (size_t i = 0; i < n; ++i) bits |= m[i];
+    if (bits <= 1) return NPAS_OK;
     for (size_t i = 0; i < n; ++i)
         if (m[i] > 1) {
             set_error("mask[%zu] = %d is neither 0 nor 1", i, (int)m[i]);
@@ -102,9 +105,19 @@ static int validate_fc_block(const uint8_t *m, int OUT, int IN, int Br, int Bcol
             int nr = std::min(Br, OUT - r0), nc = std::min(Bcol, IN - c0);
             std::fill(rowkeep.begin(), rowkeep.end(), 0);
             std::fill(colkeep.begin(), colkeep.end(), 0);
+            uint8_t bad = 0; // (no branch on a mask value: they are random; the offender is looked for only when there is one)
+            for (int r = 0; r < nr; ++r) {
+                const uint8_t *row = m + (size_t)(r0 + r) * IN + c0;
+                uint8_t any = 0;
+                for (int c = 0; c < nc; ++c) {
+                    any |= row[c];
+                    colkeep[c] |= row[c];
+                }
+                rowkeep[r] = any;
+            }
             for (int r = 0; r < nr; ++r)
-                for (int c = 0; c < nc; ++c)
-                    if (m[(size_t)(r0 + r) * IN + c0 + c]) rowkeep[r] = colkeep[c] = 1;
+                for (int c = 0; c < nc; ++c) bad |= m[(size_t)(r0 + r) * IN + c0 + c] ^ (rowkeep[r] & colkeep[c]);
+            if (!bad) continue;
             for (int r = 0; r < nr; ++r)
                 for (int c = 0; c < nc; ++c)
                     if (m[(size_t)(r0 + r) * IN + c0 + c] != (rowkeep[r] & colkeep[c])) {
