@@ -9,6 +9,7 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _CSRC = os.path.join(_HERE, "csrc")
 _LIB = os.path.join(_HERE, "libnpas.so")
+_CALLS = os.path.join(_HERE, "_pycalls.so")  # CPython entry points of the run calls, linked to libnpas.so
 SOURCES = ["pack.cpp", "api.cpp", "kernels.hip", "spatial_kernels.hip", "small_kernels.hip", "block_kernels.hip",
            "inverted_residual_kernel.hip", "pointwise_stream_kernel.hip", "noalloc.hip"]
 HEADER = os.path.join(os.path.dirname(_HERE), "include", "npas.h")
@@ -43,11 +44,14 @@ class NpasError(RuntimeError):
 
 
 def build(force: bool = True) -> str:
-    """Compile libnpas.so for gfx950 in-tree with hipcc (one object per source, compiled side by side)."""
+    """Compile libnpas.so for gfx950 in-tree with hipcc (one object per source, compiled side by side), and _pycalls.so."""
+    import sysconfig
     from concurrent.futures import ThreadPoolExecutor
     srcs = [os.path.join(_CSRC, s) for s in SOURCES]
     deps = srcs + [os.path.join(_CSRC, "npas_internal.h"), os.path.join(_CSRC, "device_util.h"), HEADER]
-    if not force and os.path.exists(_LIB) and all(os.path.getmtime(_LIB) >= os.path.getmtime(d) for d in deps):
+    calls = os.path.join(_CSRC, "pycalls.cpp")
+    if not force and os.path.exists(_LIB) and os.path.exists(_CALLS) and \
+            all(os.path.getmtime(_LIB) >= os.path.getmtime(d) for d in deps) and os.path.getmtime(_CALLS) >= os.path.getmtime(calls):
         return _LIB
     flags = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
              "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
@@ -63,6 +67,8 @@ def build(force: bool = True) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as pool:
         list(pool.map(compile_one, zip(srcs, objs)))
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", _LIB] + objs)
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], "-o", _CALLS, calls,
+                           "-L" + _HERE, "-l:libnpas.so", "-Wl,-rpath,$ORIGIN"])
     return _LIB
 
 
@@ -113,6 +119,25 @@ def lib():
         L.npas_debug_set_switches.restype = None
         _lib = L
     return _lib
+
+
+_calls = None
+
+
+def _load_calls():
+    """The CPython entry points (on the same loaded library as `lib()`)."""
+    global _calls
+    if _calls is None:
+        import importlib.util
+        lib()
+        if not os.path.exists(_CALLS):
+            raise RuntimeError(f"{_CALLS} is missing: run __graft_entry__.build() first; there is no fallback path")
+        spec = importlib.util.spec_from_file_location(__package__ + "._pycalls", _CALLS)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        mod.init(NpasError)
+        _calls = mod
+    return _calls
 
 
 def last_error() -> str:
@@ -224,13 +249,11 @@ def pack_depthwise3x3(w, dtype, stream=None):
 
 
 def depthwise3x3(packed, x, y, N, H, W, stride, bias=None, residual=None, act=ACT_NONE, stream=None):
-    _check(lib().npas_depthwise3x3(packed.handle, _dev(x), _dev(y), N, H, W, stride, _dev(bias), _dev(residual), act,
-                                   stream))
+    (_calls or _load_calls()).depthwise3x3(packed, x, y, N, H, W, stride, bias, residual, act, stream)
 
 
 def conv2d_sparse(packed, x, y, N, H, W, stride, pad, bias=None, residual=None, act=ACT_NONE, stream=None):
-    _check(lib().npas_conv2d_sparse(packed.handle, _dev(x), _dev(y), N, H, W, stride, pad, _dev(bias),
-                                    _dev(residual), act, stream))
+    (_calls or _load_calls()).conv2d_sparse(packed, x, y, N, H, W, stride, pad, bias, residual, act, stream)
 
 
 def conv2d_kernel_name(packed, N, H, W, stride, pad):
@@ -239,7 +262,7 @@ def conv2d_kernel_name(packed, N, H, W, stride, pad):
 
 
 def fc_sparse(packed, x, y, B, bias=None, act=ACT_NONE, stream=None):
-    _check(lib().npas_fc_sparse(packed.handle, _dev(x), _dev(y), B, _dev(bias), act, stream))
+    (_calls or _load_calls()).fc_sparse(packed, x, y, B, bias, act, stream)
 
 
 def maxpool3x3s2(x, y, N, H, W, Cc, dtype, stream=None):
@@ -293,4 +316,4 @@ class Stack:
         return [dict(zip(keys, (int(v) for v in rows[i]))) for i in range(got)]
 
     def run(self, x, y, N, workspace, workspace_bytes, stream=None):
-        _check(lib().npas_run_stack(self.handle, _dev(x), _dev(y), N, _dev(workspace), workspace_bytes, stream))
+        (_calls or _load_calls()).run_stack(self, x, y, N, workspace, workspace_bytes, stream)

@@ -286,3 +286,31 @@ def test_spatial_ring_is_not_planned_beyond_its_24_bit_pixel_count():
     assert npas.conv2d_kernel_name(p, 128, 28, 28, 1, 1) == "spatial_ring"
     assert 21400 * 28 * 28 >= 1 << 24
     assert npas.conv2d_kernel_name(p, 21400, 28, 28, 1, 1) != "spatial_ring"
+
+
+def test_run_calls_marshal_like_the_c_abi():
+    """The Python run calls: tensors, addresses and None as pointers, integers of any kind as sizes; library errors come back with
+    their code, wrong types are refused before the library is called."""
+    torch = pytest.importorskip("torch")
+    p = _bp_layer(64, 64, 1, 47)
+    x = torch.zeros((1, 8, 8, 64), dtype=torch.bfloat16)
+    # the library's own checks, in the order of its arguments: a missing output, an empty output, an unknown activation
+    for args, code in (((p, x, None, 1, 8, 8, 1, 0), npas.E_NULL), ((p, x, x, 1, np.int64(0), 8, 1, 0), npas.E_SHAPE),
+                       ((p, 256, 256, 1, 0, 0, 1, 0), npas.E_SHAPE)):
+        with pytest.raises(npas.NpasError) as e:
+            npas.conv2d_sparse(*args)
+        assert e.value.code == code and "libnpas error" in str(e.value)
+    with pytest.raises(npas.NpasError) as e:
+        npas.fc_sparse(p, x, x, B=-1, bias=None, act=npas.ACT_RELU)
+    assert e.value.code == npas.E_SHAPE
+    with pytest.raises(npas.NpasError) as e:
+        npas.depthwise3x3(p, x, x, 1, 8, 8, stride=1)          # not a depthwise handle
+    assert e.value.code == npas.E_SHAPE
+    with pytest.raises(AssertionError):
+        npas.conv2d_sparse(p, x.permute(0, 3, 1, 2), x, 1, 8, 8, 1, 0)
+    with pytest.raises(TypeError):
+        npas.conv2d_sparse(p, x, x, 1.0, 8, 8, 1, 0)
+    with pytest.raises(AttributeError):
+        npas.conv2d_sparse(p, "x", x, 1, 8, 8, 1, 0)
+    with pytest.raises(AttributeError):
+        npas.fc_sparse(None, x, x, 1)
