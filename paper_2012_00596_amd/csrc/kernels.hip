@@ -1295,9 +1295,10 @@ int launch_conv_smallm(int dtype, SmallMArgs a, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
     const long halves = (a.F + 63) / 64, blocks = ((long)a.M + 15) / 16; // 64-filter halves (four images each), 16-pixel blocks
+    const bool narrow = ((uintptr_t)a.y & 7u) != 0; // an output at less than 8-byte alignment: one image, 2-byte stores
     int fi = 1;
-    while (fi < 4 && blocks * halves * (4 / fi) > 256) fi *= 2;
-    const int pb = blocks * halves > 256 ? 2 : 1;
+    while (!narrow && fi < 4 && blocks * halves * (4 / fi) > 256) fi *= 2;
+    const int pb = !narrow && blocks * halves > 256 ? 2 : 1;
     a.nptiles = (int)((blocks + pb - 1) / pb);
     const long grid = (long)a.nptiles * halves * (4 / fi);
     if (a.C % 64 != 0 || a.F % 4 != 0 || a.M <= 0 || grid > 0x7fffffffL || (double)a.N * a.H * a.W * a.C >= 2147483648.0) {

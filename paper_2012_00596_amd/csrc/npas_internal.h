@@ -320,7 +320,7 @@ struct FcGatherArgs {
     uint32_t div_howo, div_wo;
 };
 
-// 16-bit 1x1 layer through the stream format: see pointwise_stream_kernel (nt, tpg, groups are filled at the launch)
+// 16-bit 1x1 layer through the stream format: see pointwise_stream_kernel (nt, tpg, groups, wide are filled at the launch)
 struct PwStreamArgs {
     const void *x;
     void *y;
@@ -331,6 +331,7 @@ struct PwStreamArgs {
     int H, W, Ho, Wo, stride, flat; // flat: stride 1, input pixel index == output pixel index
     int act;
     int nt, tpg, groups;          // 16-filter tiles; tiles per filter group; groups
+    int wide;                     // 16-byte stores
 };
 
 // fp32 layer with the reduction of every output split over 8 lanes: see conv_wave_f32_kernel

@@ -106,13 +106,13 @@ __global__ __launch_bounds__(256, NS <= 5 ? 4 : 3) void pointwise_stream_kernel(
         __builtin_amdgcn_wave_barrier();
         const uint32_t npx = min(16u, (uint32_t)a.M - blk * 16u); // pixels of this block
         uint8_t *yb = reinterpret_cast<uint8_t *>(a.y) + (size_t)blk * 32u * (uint32_t)a.F;
-        if (a.groups == 1) { // one contiguous run
+        if (a.wide) { // one contiguous run
             const uint32_t total = npx * (uint32_t)row_bytes; // (a multiple of 8)
             for (uint32_t o = lane * 16u; o < total; o += 1024u) {
                 if (o + 16u <= total) store_stream16(yb + o, *reinterpret_cast<const uint4 *>(stage + o));
                 else store_stream8(yb + o, *reinterpret_cast<const uint2 *>(stage + o));
             }
-        } else { // 8-byte vectors of each pixel's segment
+        } else { // 8-byte vectors of each pixel's segment (several groups, or y at 8-byte alignment)
             const uint32_t segv = (uint32_t)row_bytes >> 3;
             for (uint32_t v = lane; v < npx * segv; v += 64u) {
                 const uint32_t px = v / segv;
@@ -144,6 +144,7 @@ int launch_pointwise_stream(int dtype, PwStreamArgs a, void *stream)
     while (pw_stream_lds((a.nt + a.groups - 1) / a.groups, ns) > 80 * 1024) ++a.groups;
     a.tpg = (a.nt + a.groups - 1) / a.groups;
     a.groups = (a.nt + a.tpg - 1) / a.tpg;
+    a.wide = a.groups == 1 && ((uintptr_t)a.y & 15u) == 0;
     const size_t lds = pw_stream_lds(a.tpg, ns);
     const int fit = std::min<int>(ns <= 5 ? 4 : 3, (int)(160 * 1024 / lds));
     const long want = ((long)(a.M + 15) / 16 + 3) / 4;

@@ -407,6 +407,24 @@ def test_flat_pointwise(npas, torch, case):
     _run_edge_case(npas, torch, case)
 
 
+@pytest.mark.parametrize("C,F,N,HW,k,off", [(144, 40, 3, 29, 1, 8), (64, 128, 2, 21, 3, 2)], ids=["flat_8_bytes", "split_2_bytes"])
+def test_outputs_at_smaller_alignment(npas, torch, C, F, N, HW, k, off):
+    """An output that starts 8 (flat 1x1 kernel) or 2 bytes (split reduction) past an aligned address: narrower stores, same values."""
+    w = prng.normal(31, 1, F * C * k * k, 0.1).reshape(F, C, k, k)
+    ws, _ = dtypes.quantize(w, dtypes.BF16)
+    m = masks.block_punched_mask(F, C, k, k, 8, 8, 2, 31)
+    p = npas.pack_block_punched(ws, m, 8, 8, dtypes.BF16)
+    xs, _ = dtypes.quantize(prng.normal(31, 2, N * HW * HW * C).reshape(N, HW, HW, C), dtypes.BF16)
+    x, n = to_dev(xs, torch), N * HW * HW * F
+    y0 = torch.zeros(n, dtype=torch.int16, device="cuda")
+    y1 = torch.full((n + 16,), 0x7FC1, dtype=torch.int16, device="cuda")
+    npas.conv2d_sparse(p, x, y0, N, HW, HW, 1, k // 2)
+    npas.conv2d_sparse(p, x, y1.data_ptr() + off, N, HW, HW, 1, k // 2)
+    torch.cuda.synchronize()
+    assert torch.equal(y1[off // 2:off // 2 + n], y0)
+    assert (y1[:off // 2] == 0x7FC1).all() and (y1[off // 2 + n:] == 0x7FC1).all()
+
+
 # Every slot count the fused block is compiled for, partial tiles of 32, 64 and more pixels (the tile follows the number of
 # tiles in the batch), filter counts that leave a 16-filter tile partial, dense and pruned projections.
 @pytest.mark.parametrize("N,HW,C,t,stride,rate,dtype,bias,act",
