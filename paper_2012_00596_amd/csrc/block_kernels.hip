@@ -259,8 +259,10 @@ __global__ __launch_bounds__(256) void depthwise3x3_kernel(const void *x, void *
 // from the buffer descriptor's range check (an offset past the end reads zeros), which leaves no branch between the
 // loads.  The multiplies go column by column (kw): a tap's weights and an input vector are unpacked to fp32 once each
 // and feed up to three output rows; fp32 multiply-adds issue in half the time of a dot2 with one half zeroed.
-// Consecutive lanes are consecutive 16-byte channel vectors of a pixel, then consecutive pixels of a row; an XCD gets a
-// contiguous run of rows so that the rows two row blocks share come from its own L2.
+// Consecutive lanes are consecutive 16-byte channel vectors of a pixel, then consecutive pixels of a row; an XCD gets runs of
+// 16 workgroups (a few row blocks) so that most rows two row blocks share come from its own L2, while the chip as a whole
+// works on one stretch of the tensors: with inputs beyond the Infinity Cache 64 x 56 x 56 x 144 36.4 us against 38.1 with one run per
+// XCD and 36.3 with none, 60 x 60 x 60 x 480 119.5 / 125.3 / 122.1, inside it 32 x 57 x 57 x 144 17.8 / 17.8 / 19.2.
 // 64 x 56 x 56 x 144, bf16: stride 1 31 -> 28 us (a copy of the same bytes: 23), stride 2 57 -> 13 us (the thread of four
 // rows had spilled); 32 x 57 x 57 x 144 with a bias 23 -> 18 us; 1 x 46 x 28 x 272 at stride 2 16.5 -> 2.9 us.
 struct DwArgs {
@@ -288,7 +290,10 @@ template <int DT> __device__ __forceinline__ void unpack8(uint4 v, float *f)
 template <int DT, int STRIDE, int R, bool HSW>
 __global__ __launch_bounds__(256, R == 4 ? 2 : 3) void depthwise3x3_rows_kernel(DwArgs a)
 {
-    const uint32_t idx = xcd_remap(blockIdx.x, gridDim.x) * 256u + threadIdx.x;
+    // runs of 16 workgroups per XCD (see above); the last, partial window of eight runs stays as it is
+    const uint32_t win = blockIdx.x >> 7, in = blockIdx.x & 127u;
+    const uint32_t blk = (win + 1u) << 7 <= gridDim.x ? (win << 7) + (in & 7u) * 16u + (in >> 3) : blockIdx.x;
+    const uint32_t idx = blk * 256u + threadIdx.x;
     if (idx >= a.total) return;
     const uint32_t t = fastdiv(idx, a.div_cv);
     const uint32_t cv = idx - t * a.CV;
