@@ -135,9 +135,30 @@ def _load_calls():
         spec = importlib.util.spec_from_file_location(__package__ + "._pycalls", _CALLS)
         mod = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(mod)
-        mod.init(NpasError)
+        mod.init(NpasError, C.c_void_p, _conv2d_sparse, _fc_sparse, _depthwise3x3, _run_stack)
         _calls = mod
     return _calls
+
+
+# The run calls through ctypes: what the entry points above call with an argument that is neither a plain number nor a tensor
+# (a ctypes value, a stream object with `_as_parameter_`).
+
+def _conv2d_sparse(packed, x, y, N, H, W, stride, pad, bias, residual, act, stream):
+    _check(lib().npas_conv2d_sparse(packed.handle, _dev(x), _dev(y), N, H, W, stride, pad, _dev(bias), _dev(residual), act,
+                                    stream))
+
+
+def _fc_sparse(packed, x, y, B, bias, act, stream):
+    _check(lib().npas_fc_sparse(packed.handle, _dev(x), _dev(y), B, _dev(bias), act, stream))
+
+
+def _depthwise3x3(packed, x, y, N, H, W, stride, bias, residual, act, stream):
+    _check(lib().npas_depthwise3x3(packed.handle, _dev(x), _dev(y), N, H, W, stride, _dev(bias), _dev(residual), act,
+                                   stream))
+
+
+def _run_stack(stack, x, y, N, workspace, workspace_bytes, stream):
+    _check(lib().npas_run_stack(stack.handle, _dev(x), _dev(y), N, _dev(workspace), workspace_bytes, stream))
 
 
 def last_error() -> str:

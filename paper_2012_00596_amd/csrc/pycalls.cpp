@@ -9,64 +9,84 @@
 namespace {
 
 PyObject *error_class; // NpasError(code, message), set by init()
+PyObject *c_void_p;    // ctypes.c_void_p, set by init()
 PyObject *s_handle, *s_value, *s_is_contiguous, *s_data_ptr;
 
-// Device pointer of an argument: None, an address, or a contiguous tensor.
-bool device_pointer(PyObject *o, void **out)
-{
-    if (o == Py_None) {
-        *out = nullptr;
-        return true;
-    }
-    if (PyLong_Check(o)) {
-        *out = (void *)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
-        return !PyErr_Occurred();
-    }
-    PyObject *c = PyObject_CallMethodNoArgs(o, s_is_contiguous);
-    if (!c) return false;
-    const int yes = PyObject_IsTrue(c);
-    Py_DECREF(c);
-    if (yes < 0) return false;
-    if (!yes) {
-        PyErr_SetString(PyExc_AssertionError, "tensor is not contiguous");
-        return false;
-    }
-    PyObject *p = PyObject_CallMethodNoArgs(o, s_data_ptr);
-    if (!p) return false;
-    *out = (void *)(uintptr_t)PyLong_AsUnsignedLongLongMask(p);
-    Py_DECREF(p);
-    return !PyErr_Occurred();
-}
+// The arguments of one call, converted in their order.  Once one does not convert, the later conversions do nothing.
+struct Args {
+    PyObject *const *a;
+    enum { PLAIN, FAILED, OTHER } state = PLAIN; // all plain so far; a Python error is set; one is of a kind that is left to ctypes
 
-// Library handle of a Packed / Stack object: its `handle` is a ctypes c_void_p, or None once released.
-bool library_handle(PyObject *o, void **out)
-{
-    PyObject *h = PyObject_GetAttr(o, s_handle);
-    if (!h) return false;
-    *out = nullptr;
-    bool ok = true;
-    if (h != Py_None) {
-        PyObject *v = PyLong_Check(h) ? (Py_INCREF(h), h) : PyObject_GetAttr(h, s_value);
-        ok = v != nullptr;
-        if (ok && v != Py_None) {
-            *out = (void *)(uintptr_t)PyLong_AsUnsignedLongLongMask(v);
-            ok = !PyErr_Occurred();
+    // Device pointer: None, an address, or a contiguous tensor.
+    void *pointer(int i)
+    {
+        PyObject *o = a[i];
+        if (state != PLAIN || o == Py_None) return nullptr;
+        if (PyLong_Check(o)) return number(PyLong_AsUnsignedLongLongMask(o));
+        PyObject *c = PyObject_CallMethodNoArgs(o, s_is_contiguous);
+        const int yes = c ? PyObject_IsTrue(c) : -1;
+        Py_XDECREF(c);
+        if (yes == 0) PyErr_SetString(PyExc_AssertionError, "tensor is not contiguous");
+        PyObject *p = yes == 1 ? PyObject_CallMethodNoArgs(o, s_data_ptr) : nullptr;
+        if (!p) return fail();
+        void *v = PyLong_Check(p) ? number(PyLong_AsUnsignedLongLongMask(p)) : other();
+        Py_DECREF(p);
+        return v;
+    }
+
+    // Address that is not a tensor's, such as a stream: None or an integer; ctypes knows the rest (c_void_p, _as_parameter_).
+    void *address(int i)
+    {
+        PyObject *o = a[i];
+        if (state != PLAIN || o == Py_None) return nullptr;
+        return PyLong_Check(o) ? number(PyLong_AsUnsignedLongLongMask(o)) : other();
+    }
+
+    // Library handle of a Packed / Stack object: its `handle` is a ctypes c_void_p, or None once released.
+    void *handle(int i)
+    {
+        if (state != PLAIN) return nullptr;
+        PyObject *h = PyObject_GetAttr(a[i], s_handle);
+        if (!h) return fail();
+        void *v = nullptr;
+        if (PyLong_Check(h)) v = number(PyLong_AsUnsignedLongLongMask(h));
+        else if (h != Py_None) {
+            PyObject *p = PyObject_IsInstance(h, c_void_p) == 1 ? PyObject_GetAttr(h, s_value) : nullptr;
+            if (p && PyLong_Check(p)) v = number(PyLong_AsUnsignedLongLongMask(p));
+            else if (p != Py_None) v = PyErr_Occurred() ? fail() : other();
+            Py_XDECREF(p);
         }
-        Py_XDECREF(v);
+        Py_DECREF(h);
+        return v;
     }
-    Py_DECREF(h);
-    return ok;
-}
 
-bool c_int(PyObject *o, int *out) // (as ctypes: integers, reduced to 32 bits; no floats)
-{
-    if (PyFloat_Check(o)) {
-        PyErr_SetString(PyExc_TypeError, "int expected instead of float");
-        return false;
+    // As ctypes: anything with __index__, an int reduced to 32 bits; no floats.
+    int integer(int i) { return (int)(unsigned int)size(i); }
+    size_t size(int i)
+    {
+        if (state != PLAIN) return 0;
+        if (PyFloat_Check(a[i])) {
+            PyErr_SetString(PyExc_TypeError, "int expected instead of float");
+            fail();
+            return 0;
+        }
+        if (!PyIndex_Check(a[i])) return (size_t)(uintptr_t)other();
+        return (size_t)(uintptr_t)number(PyLong_AsUnsignedLongLongMask(a[i]));
     }
-    *out = (int)(unsigned int)PyLong_AsUnsignedLongMask(o);
-    return !PyErr_Occurred();
-}
+
+private:
+    void *fail()
+    {
+        state = FAILED;
+        return nullptr;
+    }
+    void *other()
+    {
+        state = OTHER;
+        return nullptr;
+    }
+    void *number(unsigned long long v) { return v == (unsigned long long)-1 && PyErr_Occurred() ? fail() : (void *)(uintptr_t)v; }
+};
 
 PyObject *result(int rc)
 {
@@ -79,6 +99,22 @@ PyObject *result(int rc)
     return nullptr;
 }
 
+// What follows the conversions: the library call without the interpreter lock, or, where an argument is of another kind, the
+// same call through ctypes (which accepts or refuses it).
+enum Call { CONV2D, FC, DEPTHWISE, STACK, CALLS };
+PyObject *by_ctypes[CALLS]; // set by init()
+
+template <typename F> PyObject *finish(const Args &g, Call which, Py_ssize_t n, F call)
+{
+    if (g.state == Args::FAILED) return nullptr;
+    if (g.state == Args::OTHER) return PyObject_Vectorcall(by_ctypes[which], g.a, (size_t)n, nullptr);
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = call();
+    Py_END_ALLOW_THREADS
+    return result(rc);
+}
+
 bool argc(Py_ssize_t n, Py_ssize_t want)
 {
     if (n == want) return true;
@@ -89,77 +125,75 @@ bool argc(Py_ssize_t n, Py_ssize_t want)
 // conv2d_sparse(packed, x, y, N, H, W, stride, pad, bias, residual, act, stream)
 PyObject *conv2d_sparse(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    void *p, *x, *y, *b, *r, *st;
-    int v[5], act, rc;
-    if (!argc(n, 12) || !library_handle(a[0], &p) || !device_pointer(a[1], &x) || !device_pointer(a[2], &y)) return nullptr;
-    for (int i = 0; i < 5; ++i)
-        if (!c_int(a[3 + i], &v[i])) return nullptr;
-    if (!device_pointer(a[8], &b) || !device_pointer(a[9], &r) || !c_int(a[10], &act) || !device_pointer(a[11], &st)) return nullptr;
-    Py_BEGIN_ALLOW_THREADS
-    rc = npas_conv2d_sparse((npas_packed *)p, x, y, v[0], v[1], v[2], v[3], v[4], b, r, (npas_act)act, st);
-    Py_END_ALLOW_THREADS
-    return result(rc);
+    if (!argc(n, 12)) return nullptr;
+    Args g{a};
+    npas_packed *p = (npas_packed *)g.handle(0);
+    void *x = g.pointer(1), *y = g.pointer(2);
+    const int N = g.integer(3), H = g.integer(4), W = g.integer(5), stride = g.integer(6), pad = g.integer(7);
+    void *b = g.pointer(8), *r = g.pointer(9);
+    const int act = g.integer(10);
+    void *st = g.address(11);
+    return finish(g, CONV2D, n, [&] { return npas_conv2d_sparse(p, x, y, N, H, W, stride, pad, b, r, (npas_act)act, st); });
 }
 
 // fc_sparse(packed, x, y, B, bias, act, stream)
 PyObject *fc_sparse(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    void *p, *x, *y, *b, *st;
-    int B, act, rc;
-    if (!argc(n, 7) || !library_handle(a[0], &p) || !device_pointer(a[1], &x) || !device_pointer(a[2], &y) || !c_int(a[3], &B) ||
-        !device_pointer(a[4], &b) || !c_int(a[5], &act) || !device_pointer(a[6], &st))
-        return nullptr;
-    Py_BEGIN_ALLOW_THREADS
-    rc = npas_fc_sparse((npas_packed *)p, x, y, B, b, (npas_act)act, st);
-    Py_END_ALLOW_THREADS
-    return result(rc);
+    if (!argc(n, 7)) return nullptr;
+    Args g{a};
+    npas_packed *p = (npas_packed *)g.handle(0);
+    void *x = g.pointer(1), *y = g.pointer(2);
+    const int B = g.integer(3);
+    void *b = g.pointer(4);
+    const int act = g.integer(5);
+    void *st = g.address(6);
+    return finish(g, FC, n, [&] { return npas_fc_sparse(p, x, y, B, b, (npas_act)act, st); });
 }
 
 // depthwise3x3(packed, x, y, N, H, W, stride, bias, residual, act, stream)
 PyObject *depthwise3x3(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    void *p, *x, *y, *b, *r, *st;
-    int v[4], act, rc;
-    if (!argc(n, 11) || !library_handle(a[0], &p) || !device_pointer(a[1], &x) || !device_pointer(a[2], &y)) return nullptr;
-    for (int i = 0; i < 4; ++i)
-        if (!c_int(a[3 + i], &v[i])) return nullptr;
-    if (!device_pointer(a[7], &b) || !device_pointer(a[8], &r) || !c_int(a[9], &act) || !device_pointer(a[10], &st)) return nullptr;
-    Py_BEGIN_ALLOW_THREADS
-    rc = npas_depthwise3x3((npas_packed *)p, x, y, v[0], v[1], v[2], v[3], b, r, (npas_act)act, st);
-    Py_END_ALLOW_THREADS
-    return result(rc);
+    if (!argc(n, 11)) return nullptr;
+    Args g{a};
+    npas_packed *p = (npas_packed *)g.handle(0);
+    void *x = g.pointer(1), *y = g.pointer(2);
+    const int N = g.integer(3), H = g.integer(4), W = g.integer(5), stride = g.integer(6);
+    void *b = g.pointer(7), *r = g.pointer(8);
+    const int act = g.integer(9);
+    void *st = g.address(10);
+    return finish(g, DEPTHWISE, n, [&] { return npas_depthwise3x3(p, x, y, N, H, W, stride, b, r, (npas_act)act, st); });
 }
 
 // run_stack(stack, x, y, N, workspace, workspace_bytes, stream)
 PyObject *run_stack(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    void *s, *x, *y, *w, *st;
-    int N, rc;
-    if (!argc(n, 7) || !library_handle(a[0], &s) || !device_pointer(a[1], &x) || !device_pointer(a[2], &y) || !c_int(a[3], &N) ||
-        !device_pointer(a[4], &w))
-        return nullptr;
-    if (PyFloat_Check(a[5])) {
-        PyErr_SetString(PyExc_TypeError, "int expected instead of float");
-        return nullptr;
-    }
-    const size_t bytes = (size_t)PyLong_AsUnsignedLongLongMask(a[5]);
-    if (PyErr_Occurred() || !device_pointer(a[6], &st)) return nullptr;
-    Py_BEGIN_ALLOW_THREADS
-    rc = npas_run_stack((npas_stack *)s, x, y, N, w, bytes, st);
-    Py_END_ALLOW_THREADS
-    return result(rc);
+    if (!argc(n, 7)) return nullptr;
+    Args g{a};
+    npas_stack *s = (npas_stack *)g.handle(0);
+    void *x = g.pointer(1), *y = g.pointer(2);
+    const int N = g.integer(3);
+    void *w = g.pointer(4);
+    const size_t bytes = g.size(5);
+    void *st = g.address(6);
+    return finish(g, STACK, n, [&] { return npas_run_stack(s, x, y, N, w, bytes, st); });
 }
 
-PyObject *init(PyObject *, PyObject *cls)
+// init(NpasError, c_void_p, conv2d_sparse, fc_sparse, depthwise3x3, run_stack): the last four are the calls through ctypes
+PyObject *init(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    Py_INCREF(cls);
-    Py_XDECREF(error_class);
-    error_class = cls;
+    if (!argc(n, 2 + CALLS)) return nullptr;
+    auto keep = [](PyObject *&slot, PyObject *o) {
+        Py_INCREF(o);
+        Py_XSETREF(slot, o);
+    };
+    keep(error_class, a[0]);
+    keep(c_void_p, a[1]);
+    for (int i = 0; i < CALLS; ++i) keep(by_ctypes[i], a[2 + i]);
     Py_RETURN_NONE;
 }
 
 PyMethodDef methods[] = {
-    {"init", init, METH_O, nullptr},
+    {"init", (PyCFunction)(void (*)(void))init, METH_FASTCALL, nullptr},
     {"conv2d_sparse", (PyCFunction)(void (*)(void))conv2d_sparse, METH_FASTCALL, nullptr},
     {"fc_sparse", (PyCFunction)(void (*)(void))fc_sparse, METH_FASTCALL, nullptr},
     {"depthwise3x3", (PyCFunction)(void (*)(void))depthwise3x3, METH_FASTCALL, nullptr},

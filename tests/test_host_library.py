@@ -314,3 +314,35 @@ def test_run_calls_marshal_like_the_c_abi():
         npas.conv2d_sparse(p, "x", x, 1, 8, 8, 1, 0)
     with pytest.raises(AttributeError):
         npas.fc_sparse(None, x, x, 1)
+
+
+def test_run_calls_take_ctypes_values_and_stream_objects():
+    """What ctypes accepts as a stream or a size, the run calls accept: a c_void_p, an object with `_as_parameter_` (torch's
+    stream objects), a c_int; a tensor is no stream."""
+    torch = pytest.importorskip("torch")
+    p, x = _bp_layer(64, 64, 1, 48), torch.zeros(64, dtype=torch.bfloat16)
+    dw = npas.pack_depthwise3x3(np.zeros((8, 3, 3), np.uint16), dtypes.BF16)
+    st = npas.Stack(helpers.stack_descs(npas, [_pw(6, 0, 16, 16, configs.ACT_NONE, 0)],
+                                        [helpers.pack_layer(npas, _pw(6, 0, 16, 16, configs.ACT_NONE, 0), dtypes.BF16)]), 4, 4)
+
+    class Stream:
+        def __init__(self, value):
+            self._as_parameter_ = value
+
+    for s in (ctypes.c_void_p(), ctypes.c_void_p(64), Stream(ctypes.c_void_p(64)), Stream(0), np.int64(0), None, 0):
+        N = ctypes.c_int(0) if not isinstance(s, np.int64) else 0    # refused by the library, on its own shape check
+        calls = [lambda: npas.conv2d_sparse(p, x, x, N, 1, 1, 1, 0, stream=s), lambda: npas.fc_sparse(p, x, x, N, stream=s),
+                 lambda: npas.depthwise3x3(dw, x, x, N, 1, 1, 1, stream=s), lambda: st.run(x, x, N, None, 0, s)]
+        for call in calls:
+            if isinstance(s, np.int64):                                  # ctypes takes no NumPy number as an address
+                with pytest.raises(ctypes.ArgumentError):
+                    call()
+                continue
+            with pytest.raises(npas.NpasError) as e:
+                call()
+            assert e.value.code == npas.E_SHAPE
+    for s in (x, 1.5, object()):
+        with pytest.raises(ctypes.ArgumentError):
+            npas.conv2d_sparse(p, x, x, 0, 1, 1, 1, 0, stream=s)
+        with pytest.raises(ctypes.ArgumentError):
+            st.run(x, x, 0, None, 0, s)
