@@ -971,7 +971,7 @@ static int run_depthwise(const npas_packed *p, const void *x, void *y, int N, in
         return NPAS_E_HIP;
     }
     const void *w = p->dtype == NPAS_F32 ? (const void *)p->dev.vw : p->dev.wfrag;
-    return launch_depthwise3x3(p->dtype, x, y, w, (const float *)bias, residual, N, H, W, p->C, stride, act, stream);
+    return launch_depthwise3x3(p->dtype, x, y, w, (const float *)bias, residual, N, H, W, p->C, stride, act, p->dev.zeros, stream);
 }
 
 int npas_depthwise3x3(const npas_packed *p, const void *x_dev, void *y_dev, int N, int H, int W, int stride,

@@ -271,8 +271,9 @@ struct DwArgs {
     const void *w;        // [9][C] storage type, tap-major
     const float *bias;
     const void *residual;
+    const void *zeros;                  // >= 16 bytes of zeros on the device
     int N, H, W, C, Ho, Wo, act;
-    uint32_t xbytes;                    // size of x (< 2 GiB: see launch_depthwise3x3)
+    uint32_t xbytes;                    // size of x (read where it is below 2 GiB: see launch_depthwise3x3)
     uint32_t CV, nyb, total;            // channel vectors, row blocks per image, threads
     uint32_t div_cv, div_wo, div_nyb;   // fastdiv magics
 };
@@ -287,7 +288,10 @@ template <int DT> __device__ __forceinline__ void unpack8(uint4 v, float *f)
     }
 }
 
-template <int DT, int STRIDE, int R, bool HSW>
+// BIG: the input does not fit a buffer descriptor's range check, or the reciprocals do not divide the thread index: 64-bit
+// addresses, a block of zeros for the padding, plain divisions.  Such launches took the one-output kernel: 65 x 256 x 256 x 256
+// 3380 -> 1216 us (3.6 TB/s), stride 2 924 -> 527; 32 x 512 x 512 x 64 at stride 2 (1 GiB, 2^32 as index times divisor) 404 -> 250.
+template <int DT, int STRIDE, int R, bool HSW, bool BIG>
 __global__ __launch_bounds__(256, R == 4 ? 2 : 3) void depthwise3x3_rows_kernel(DwArgs a)
 {
     // runs of 16 workgroups per XCD (see above); the last, partial window of eight runs stays as it is
@@ -295,11 +299,11 @@ __global__ __launch_bounds__(256, R == 4 ? 2 : 3) void depthwise3x3_rows_kernel(
     const uint32_t blk = (win + 1u) << 7 <= gridDim.x ? (win << 7) + (in & 7u) * 16u + (in >> 3) : blockIdx.x;
     const uint32_t idx = blk * 256u + threadIdx.x;
     if (idx >= a.total) return;
-    const uint32_t t = fastdiv(idx, a.div_cv);
+    const uint32_t t = BIG ? idx / a.CV : fastdiv(idx, a.div_cv);
     const uint32_t cv = idx - t * a.CV;
-    const uint32_t t2 = fastdiv(t, a.div_wo);
+    const uint32_t t2 = BIG ? t / (uint32_t)a.Wo : fastdiv(t, a.div_wo);
     const int ox = (int)(t - t2 * (uint32_t)a.Wo);
-    const uint32_t n = fastdiv(t2, a.div_nyb);
+    const uint32_t n = BIG ? t2 / a.nyb : fastdiv(t2, a.div_nyb);
     const int oy0 = (int)(t2 - n * a.nyb) * R;
     constexpr int NR = (R - 1) * STRIDE + 3; // input rows this thread reads
     const int ix0 = ox * STRIDE - 1, iy0 = oy0 * STRIDE - 1;
@@ -321,6 +325,11 @@ __global__ __launch_bounds__(256, R == 4 ? 2 : 3) void depthwise3x3_rows_kernel(
             wv[kw][kh] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(a.w) + (size_t)(kh * 3 + kw) * a.C + cv * 8u);
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
+            if (BIG) {
+                const uint8_t *px = reinterpret_cast<const uint8_t *>(a.x) + (((size_t)n * a.H + (size_t)(iy0 + r)) * a.W + (size_t)(ix0 + kw)) * pixb + cv * 16u;
+                xv[kw][r] = *reinterpret_cast<const uint4 *>(ok && (uint32_t)(iy0 + r) < (uint32_t)a.H ? px : reinterpret_cast<const uint8_t *>(a.zeros));
+                continue;
+            }
             const uint32_t off = ok && rowo[r] != 0x80000000u ? rowo[r] + (uint32_t)kw * pixb : 0x80000000u;
             xv[kw][r] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(xr, (int)off, 0, 0));
         }
@@ -380,13 +389,13 @@ __global__ __launch_bounds__(256, R == 4 ? 2 : 3) void depthwise3x3_rows_kernel(
 static uint32_t magic32(uint32_t d) { return d <= 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); }
 
 int launch_depthwise3x3(int dt, const void *x, void *y, const void *w, const float *bias, const void *residual, int N, int H,
-                        int W, int C, int stride, int act, void *stream)
+                        int W, int C, int stride, int act, const void *zeros, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
     const int Ho = (H - 1) / stride + 1, Wo = (W - 1) / stride + 1;
     const bool vec = dt != NPAS_F32 && C % 8 == 0;
     const size_t xbytes = (size_t)N * H * W * C * 2;
-    if (vec && (stride == 1 || stride == 2) && xbytes < 0x80000000u) { // (offset 2 GiB is past the end for the range check)
+    if (vec && (stride == 1 || stride == 2)) {
         const uint32_t CV = (uint32_t)C / 8;
         // Output rows per thread.  Four share input vectors (4.5 loads an output instead of 9) and are the faster form of a
         // launch that fills the chip anyway: 64 x 56 x 56 x 144 at stride 1 28.2 us (4.1 TB/s) against 36.1 with one row.
@@ -396,32 +405,34 @@ int launch_depthwise3x3(int dt, const void *x, void *y, const void *w, const flo
         const int R = stride == 1 && (double)N * Ho * Wo * CV > 256.0 * 12 * 64 ? 4 : 1;
         const uint32_t nyb = (uint32_t)((Ho + R - 1) / R);
         const double threads = (double)N * nyb * Wo * CV;
-        // the index decode divides by CV, Wo and nyb with 32-bit reciprocals: exact while index * divisor < 2^32
-        if (threads * std::max({CV, (uint32_t)Wo, nyb}) < 4294967296.0) {
-            DwArgs a{x, y, w, bias, residual, N, H, W, C, Ho, Wo, act, (uint32_t)xbytes, CV, nyb, (uint32_t)threads,
-                     magic32(CV), magic32((uint32_t)Wo), magic32(nyb)};
-            const unsigned grid = (a.total + 255u) / 256u;
-            auto go = [&](auto dtc, auto sc, auto rc) {
-                constexpr int DT = decltype(dtc)::value, S = decltype(sc)::value, RR = decltype(rc)::value;
-                if (act == NPAS_ACT_HARDSWISH) hipLaunchKernelGGL((depthwise3x3_rows_kernel<DT, S, RR, true>), dim3(grid), dim3(256), 0, st, a);
-                else hipLaunchKernelGGL((depthwise3x3_rows_kernel<DT, S, RR, false>), dim3(grid), dim3(256), 0, st, a);
-            };
-            auto rows = [&](auto dtc) {
-                using std::integral_constant;
-                integral_constant<int, 1> one;
-                if (stride == 2) go(dtc, integral_constant<int, 2>{}, one);
-                else if (R == 4) go(dtc, one, integral_constant<int, 4>{});
-                else go(dtc, one, one);
-            };
-            if (dt == NPAS_BF16) rows(std::integral_constant<int, NPAS_BF16>{});
-            else rows(std::integral_constant<int, NPAS_F16>{});
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) {
-                set_error("depthwise3x3_rows launch failed: %s", hipGetErrorString(e));
-                return NPAS_E_HIP;
-            }
-            return NPAS_OK;
+        // Offset 2 GiB is past the end for the descriptor's range check; the index decode divides by CV, Wo and nyb with 32-bit
+        // reciprocals, exact while index * divisor < 2^32.
+        const bool big = xbytes >= 0x80000000u || threads * std::max({CV, (uint32_t)Wo, nyb}) >= 4294967296.0;
+        DwArgs a{x, y, w, bias, residual, zeros, N, H, W, C, Ho, Wo, act, (uint32_t)xbytes, CV, nyb, (uint32_t)threads,
+                 magic32(CV), magic32((uint32_t)Wo), magic32(nyb)};
+        const unsigned grid = (a.total + 255u) / 256u;
+        auto go = [&](auto dtc, auto sc, auto rc) {
+            constexpr int DT = decltype(dtc)::value, S = decltype(sc)::value, RR = decltype(rc)::value;
+            auto run = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, a); };
+            const bool hsw = act == NPAS_ACT_HARDSWISH;
+            if (big) run(hsw ? depthwise3x3_rows_kernel<DT, S, RR, true, true> : depthwise3x3_rows_kernel<DT, S, RR, false, true>);
+            else run(hsw ? depthwise3x3_rows_kernel<DT, S, RR, true, false> : depthwise3x3_rows_kernel<DT, S, RR, false, false>);
+        };
+        auto rows = [&](auto dtc) {
+            using std::integral_constant;
+            integral_constant<int, 1> one;
+            if (stride == 2) go(dtc, integral_constant<int, 2>{}, one);
+            else if (R == 4) go(dtc, one, integral_constant<int, 4>{});
+            else go(dtc, one, one);
+        };
+        if (dt == NPAS_BF16) rows(std::integral_constant<int, NPAS_BF16>{});
+        else rows(std::integral_constant<int, NPAS_F16>{});
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) {
+            set_error("depthwise3x3_rows launch failed: %s", hipGetErrorString(e));
+            return NPAS_E_HIP;
         }
+        return NPAS_OK;
     }
     const size_t total = (size_t)N * Ho * Wo * (vec ? C / 8 : C);
     const unsigned grid = (unsigned)std::min<size_t>((total + 255) / 256, 256 * 32);

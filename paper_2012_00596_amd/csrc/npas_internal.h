@@ -395,7 +395,7 @@ struct IrLaunch {
 };
 int launch_fused_inverted_residual(int dtype, const IrLaunch &l, void *stream);
 int launch_depthwise3x3(int dt, const void *x, void *y, const void *w, const float *bias, const void *residual, int N, int H,
-                        int W, int C, int stride, int act, void *stream);
+                        int W, int C, int stride, int act, const void *zeros, void *stream);
 int launch_empty(int count, void *stream);
 int launch_maxpool(const void *x, void *y, int N, int H, int W, int C, int dt, void *stream);
 int launch_avgpool(const void *x, void *y, int N, int H, int W, int C, int dt, void *stream);

@@ -343,6 +343,30 @@ def test_depthwise3x3_row_blocks(npas, torch, N, H, W, C, stride, dtype):
     assert rel_err(from_dev(y, dtype), ref) <= TOL[dtype]
 
 
+# Inputs past the limits of the row-block kernel's 32-bit forms: 2 GiB and more (buffer range check), and thread counts that its
+# reciprocals do not divide (index times divisor 2^32 or more), four rows and one row a thread.
+@pytest.mark.parametrize("N,H,W,C,stride", [(65, 256, 256, 256, 1), (65, 257, 257, 256, 2), (2, 92801, 2, 8, 2), (2, 60000, 1, 8, 1),
+                                            (5, 4200, 120, 64, 1)],
+                         ids=["2gib", "2gib_s2", "index_s2", "index_one_row", "index_four_rows"])
+def test_depthwise3x3_past_32_bit_forms(npas, torch, N, H, W, C, stride):
+    """All images in one call give the same bits as one call per image (which the 32-bit forms serve): same kernel, same order of
+    additions."""
+    print(f"depthwise N={N} {H}x{W}x{C} stride {stride}", flush=True)
+    ws, _ = dtypes.quantize(prng.normal(19, 2, C * 9, 0.3).reshape(C, 3, 3), dtypes.BF16)
+    p = npas.pack_depthwise3x3(ws, dtypes.BF16)
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    g = torch.Generator(device="cuda").manual_seed(19)
+    x = torch.randn((N, H, W, C), generator=g, device="cuda", dtype=torch.bfloat16)
+    b = torch.randn(C, generator=g, device="cuda")
+    y = torch.full((N, Ho, Wo, C), float("nan"), dtype=torch.bfloat16, device="cuda")
+    npas.depthwise3x3(p, x, y, N, H, W, stride, b, None, npas.ACT_RELU6)
+    one = torch.full((Ho, Wo, C), float("nan"), dtype=torch.bfloat16, device="cuda")
+    for n in range(N):
+        npas.depthwise3x3(p, x[n], one, 1, H, W, stride, b, None, npas.ACT_RELU6)
+        torch.cuda.synchronize()
+        assert torch.equal(y[n].view(torch.int16), one.view(torch.int16)), f"image {n}"
+
+
 @pytest.mark.parametrize("stride,bias,act,HW", [(1, False, configs.ACT_RELU6, 13), (2, False, configs.ACT_RELU6, 13),
                                                 (1, True, configs.ACT_RELU6, 13), (2, True, configs.ACT_RELU6, 13),
                                                 (2, True, configs.ACT_HARDSWISH, 14), (1, True, configs.ACT_HARDSWISH, 9),
