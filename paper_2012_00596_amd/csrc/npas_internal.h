@@ -320,7 +320,8 @@ struct FcGatherArgs {
     uint32_t div_howo, div_wo;
 };
 
-// 16-bit 1x1 layer through the stream format: see pointwise_stream_kernel (nt, tpg, groups, wide are filled at the launch)
+// 16-bit 1x1 layer through the stream format: see pointwise_stream_kernel (what follows act is filled at the launch)
+enum { PW_SEG16, PW_SEG8, PW_RUN }; // how a wave writes 16 pixels: 16- or 8-byte vectors of each pixel's segment, or one contiguous run
 struct PwStreamArgs {
     const void *x;
     void *y;
@@ -331,7 +332,8 @@ struct PwStreamArgs {
     int H, W, Ho, Wo, stride, flat; // flat: stride 1, input pixel index == output pixel index
     int act;
     int nt, tpg, groups;          // 16-filter tiles; tiles per filter group; groups
-    int wide;                     // 16-byte stores
+    int store, pitch;             // PW_...; bytes from pixel to pixel in a wave's LDS rows
+    uint32_t div_segv[2];         // fastdiv magics: vectors of a segment in a full group and in the last one
 };
 
 // fp32 layer with the reduction of every output split over 8 lanes: see conv_wave_f32_kernel

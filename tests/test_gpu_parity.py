@@ -431,6 +431,27 @@ def test_flat_pointwise(npas, torch, case):
     _run_edge_case(npas, torch, case)
 
 
+# The same kernel's launch forms: a wave that walks two and three pixel blocks (in one run, in 16- and in 8-byte segments; with one, three
+# and five filter groups), a last block of 7 .. 11 pixels met on a later round, groups made because the pixels are few (the last of one
+# tile), dense layers of 8 channels, 4 filters and one pixel, and a density that would fit the gather format.
+STREAM_FORMS = [
+    ("flat_run_two_rounds", 24, 57, 57, 24, 12, 1, 1, 1, 0, 4, 8, 2, dtypes.BF16, 2, True, True),
+    ("flat_seg16_two_rounds", 23, 57, 57, 40, 32, 1, 1, 1, 0, 8, 8, 2, dtypes.F16, 3, True, True),
+    ("flat_3_groups_three_rounds", 7, 57, 57, 24, 960, 1, 1, 1, 0, 8, 8, 2, dtypes.BF16, 2, True, True),
+    ("flat_5_groups_seg8_three_rounds", 5, 53, 51, 40, 1276, 1, 1, 1, 0, 4, 8, 4, dtypes.BF16, 1, False, True),
+    ("flat_few_pixels_7_groups", 1, 3, 5, 24, 200, 1, 1, 1, 0, 8, 8, 1, dtypes.BF16, 0, True, True),
+    ("flat_few_pixels_seg8_last_4", 1, 9, 9, 16, 36, 1, 1, 1, 0, 4, 8, 1, dtypes.F16, 1, False, True),
+    ("flat_dense_c8_f4_one_pixel", 1, 1, 1, 8, 4, 1, 1, 1, 0, 4, 4, 1, dtypes.BF16, 0, False, True),
+    ("flat_dense_f20_run", 3, 9, 7, 16, 20, 1, 1, 1, 0, 4, 8, 1, dtypes.BF16, 3, True, False),
+    ("flat_low_density", 2, 33, 29, 72, 96, 1, 1, 1, 0, 8, 8, 10, dtypes.BF16, 2, False, True),
+]
+
+
+@pytest.mark.parametrize("case", STREAM_FORMS, ids=[c[0] for c in STREAM_FORMS])
+def test_flat_pointwise_launch_forms(npas, torch, case):
+    _run_edge_case(npas, torch, case, expect_kernel="conv_slab_mfma")
+
+
 @pytest.mark.parametrize("C,F,N,HW,k,off", [(144, 40, 3, 29, 1, 8), (64, 128, 2, 21, 3, 2)], ids=["flat_8_bytes", "split_2_bytes"])
 def test_outputs_at_smaller_alignment(npas, torch, C, F, N, HW, k, off):
     """An output that starts 8 (flat 1x1 kernel) or 2 bytes (split reduction) past an aligned address: narrower stores, same values."""
