@@ -438,9 +438,16 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
         // ... unless the weights are many and either little of them is skipped or there are few pixels to gather them for: the dense
         // images are then quicker to stream than the lists to follow (1280 -> 1000 at 2x, 64 / 256 / 512 rows: 4.8 / 7.7 / 9.2 us ->
         // 4.4 / 5.9 / 8.1, at 5x 4.6 / 5.6 / 5.9 against 4.4 / 5.8 / 8.1; 2048 -> 1000 at 5x, 128 rows 6.5 -> 5.9;
-        // 2432 -> 1372 at 5x, 256 rows 13.5 -> 11.0; 512 -> 1000 at 2x, 256 / 512 rows 4.8 / 5.1 against 4.4 / 5.4)
-        const bool dense = smallm_ok && rounds == 1 && p->C >= 256 && (double)p->C * p->F >= 131072.0 &&
-                           ((p->fmt.density > 0.3 && (p->C >= 1024 || blocks * halves <= 256)) || (p->C >= 1024 && (M1 <= 128 || p->C > 2048)));
+        // 2432 -> 1372 at 5x, 256 rows 13.5 -> 11.0; 512 -> 1000 at 2x, 256 / 512 rows 4.8 / 5.1 against 4.4 / 5.4).
+        // The lines within that, where the lists are the quicker ones again: 256 channels and few rows (256 -> 1000 at 3x, 64 rows: 4.2
+        // against 4.4), a third kept in two pixel blocks a workgroup (2048 -> 1000, 512 rows: 10.0 against 10.4), a fifth kept in a
+        // launch that fills the chip (1280 -> 4096, 128 rows: 6.6 against 8.1) or of few weights (4096 -> 100, 512 rows: 7.9 against 8.6).
+        const double d = p->fmt.density, weights = (double)p->C * p->F;
+        const long wgs = blocks * halves;
+        const bool full = d > 0.3 && weights >= 131072.0 && (p->C >= 512 || (p->C >= 256 && M1 >= 128)) &&
+                          (wgs <= 256 || (p->C >= 1024 && (d > 0.34 || M1 <= 128 || p->C > 2048)));
+        const bool sparse = d <= 0.3 && weights >= 524288.0 && p->C >= 1024 && (p->C > 2048 || (M1 <= 128 && wgs < 256));
+        const bool dense = smallm_ok && rounds == 1 && (full || sparse);
         return dense ? R_SMALLM : R_FC_GATHER;
     }
     SmallCArgs sc_local;

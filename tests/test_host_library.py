@@ -346,3 +346,15 @@ def test_run_calls_take_ctypes_values_and_stream_objects():
             npas.conv2d_sparse(p, x, x, 0, 1, 1, 1, 0, stream=s)
         with pytest.raises(ctypes.ArgumentError):
             st.run(x, x, 0, None, 0, s)
+
+
+@pytest.mark.parametrize("C,F,rate,B,dense", [(1280, 1000, 2, 256, True), (1280, 1000, 5, 256, False), (2048, 1000, 5, 64, True),
+                                              (256, 1000, 3, 64, False), (256, 1000, 3, 128, True), (2048, 1000, 3, 512, False),
+                                              (2048, 1000, 2, 512, True), (1280, 4096, 5, 128, False), (4096, 100, 5, 512, False),
+                                              (4096, 1000, 5, 512, True)])
+def test_fc_layers_take_the_dense_images_where_those_are_quicker(C, F, rate, B, dense):
+    """The lists of an FC layer or its dense images: the shapes on both sides of each line of the rule (host logic; the times
+    stand at the rule)."""
+    m = masks.fc_block_mask(F, C, 16, 32, rate, 49)
+    p = npas.pack_fc_block(np.zeros((F, C), np.uint16), m, 16, 32, dtypes.BF16)
+    assert npas.conv2d_kernel_name(p, B, 1, 1, 1, 0) == ("conv_smallm_mfma" if dense else "fc_gather_mfma")
