@@ -477,8 +477,11 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
     }
     // few output pixels (small batch, late stages): the tiled kernel would run a handful of workgroups, each walking the
     // whole reduction alone at about a third of a microsecond a step (28 x 28 x 128 at batch 2 / 8: 12.7 / 13.1 -> 5.4 / 12.0 us,
-    // 14 x 14 x 256 at batch 8 / 16: 25.8 / 32.3 -> 9.7 / 17.9; 56 x 56 x 64 at batch 8 16.1 against 9.5)
-    if (smallm_ok && (p->KH > 1 || p->KW > 1) && (fv == FV_SMALLM || t_smallm < 2.0 + 0.33 * steps)) return R_SMALLM;
+    // 14 x 14 x 256 at batch 8 / 16: 25.8 / 32.3 -> 9.7 / 17.9; 56 x 56 x 64 at batch 8 16.1 against 9.5).  The gather kernel, on maps of one
+    // small tile and one round of workgroups, takes a fifth of one (256 -> 256 at 7 x 7, batch 64, 10x pruned 16.8 against 18.3; on
+    // larger maps its tiles are larger: 14 x 14, batch 16 31.5 -> 18.9)
+    const double step = gather && rounds > 1 && Ho1 * Wo1 <= 64 && (long)N * ((p->F + 63) / 64) <= 256 ? 0.21 : 0.33;
+    if (smallm_ok && (p->KH > 1 || p->KW > 1) && (fv == FV_SMALLM || t_smallm < 2.0 + step * steps)) return R_SMALLM;
     return gather ? R_GATHER : R_SLAB;
 }
 

@@ -358,3 +358,12 @@ def test_fc_layers_take_the_dense_images_where_those_are_quicker(C, F, rate, B, 
     m = masks.fc_block_mask(F, C, 16, 32, rate, 49)
     p = npas.pack_fc_block(np.zeros((F, C), np.uint16), m, 16, 32, dtypes.BF16)
     assert npas.conv2d_kernel_name(p, B, 1, 1, 1, 0) == ("conv_smallm_mfma" if dense else "fc_gather_mfma")
+
+
+@pytest.mark.parametrize("C,F,N,HW,split", [(256, 256, 64, 7, False), (256, 256, 16, 14, True), (320, 320, 64, 7, True), (512, 512, 32, 7, True),
+                                            (256, 256, 16, 7, True)])
+def test_low_density_3x3_layers_split_their_reduction_where_that_is_quicker(C, F, N, HW, split):
+    """3x3 layers at 10x in the gather format: the split-reduction kernel, but for long launches on maps that the list kernel walks in one
+    round of small tiles (host logic; the times stand at the rule)."""
+    p = _bp_layer(C, F, 3, 50, rate=10)
+    assert npas.conv2d_kernel_name(p, N, HW, HW, 1, 1) == ("conv_smallm_mfma" if split else "conv_gather_mfma")
