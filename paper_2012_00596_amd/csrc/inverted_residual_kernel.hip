@@ -82,7 +82,19 @@ struct IrArgs {
     uint32_t div_tw, div_pw, div_tx, div_ty;
 };
 
-template <int DT, int NK, bool HSW> __global__ __launch_bounds__(256, fused_ir_wgs_per_cu(32 * NK)) void fused_inverted_residual_kernel(IrArgs a)
+// The activations compiled in: clamps (none, ReLU, ReLU6) on all three layers; hard-swish on the first two and a clamp on the
+// third; any mixture with hard-swish, behind a (wave-uniform) branch per value, which keeps the compiler from interleaving
+// loads, MFMAs and epilogue arithmetic across values (hard-swish blocks with it, fp16, stride 2: 1 x 28 x 28, 32 -> 192 -> 32 13.0 us,
+// now 8.9; the kernel with the depthwise layer on the vector ALUs 11.6).
+enum { IR_CLAMPS, IR_HS_HS_CLAMP, IR_MIXED };
+template <int ACT> __device__ __forceinline__ float ir_act12(float v, Clamp c)
+{
+    if (ACT == IR_HS_HS_CLAMP) return v * __builtin_amdgcn_fmed3f(v + 3.0f, 0.0f, 6.0f) * (1.0f / 6.0f);
+    return clampf<ACT == IR_MIXED>(v, c);
+}
+template <int ACT> __device__ __forceinline__ float ir_act3(float v, Clamp c) { return clampf<ACT == IR_MIXED>(v, c); }
+
+template <int DT, int NK, int ACT> __global__ __launch_bounds__(256, fused_ir_wgs_per_cu(32 * NK)) void fused_inverted_residual_kernel(IrArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     constexpr int NT1 = 2 * NK, NSLOTS = 32 * NK;
@@ -197,8 +209,8 @@ template <int DT, int NK, bool HSW> __global__ __launch_bounds__(256, fused_ir_w
                 // result register i: slot 32 k + 8 q + 4 h + i (the two tiles of a step interleaved: one 16-byte write)
                 const int t = 2 * k + h;
                 const f32x4 d = mfma16<DT>(w1r[t], xv[r], *reinterpret_cast<const f32x4 *>(lb1 + 32 * k + 8 * q + 4 * h));
-                o[2 * h] = pack2<DT>(clampf<HSW>(d[0], cl1), clampf<HSW>(d[1], cl1));
-                o[2 * h + 1] = pack2<DT>(clampf<HSW>(d[2], cl1), clampf<HSW>(d[3], cl1));
+                o[2 * h] = pack2<DT>(ir_act12<ACT>(d[0], cl1), ir_act12<ACT>(d[1], cl1));
+                o[2 * h + 1] = pack2<DT>(ir_act12<ACT>(d[2], cl1), ir_act12<ACT>(d[3], cl1));
             }
             *reinterpret_cast<uint4 *>(dst + k * 64) = uint4{o[0] & keep, o[1] & keep, o[2] & keep, o[3] & keep};
         }
@@ -257,8 +269,8 @@ template <int DT, int NK, bool HSW> __global__ __launch_bounds__(256, fused_ir_w
                 }
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
-                    b[j][2 * h] = pack2<DT>(clampf<HSW>(d[j][0], cl2), clampf<HSW>(d[j][1], cl2));
-                    b[j][2 * h + 1] = pack2<DT>(clampf<HSW>(d[j][2], cl2), clampf<HSW>(d[j][3], cl2));
+                    b[j][2 * h] = pack2<DT>(ir_act12<ACT>(d[j][0], cl2), ir_act12<ACT>(d[j][1], cl2));
+                    b[j][2 * h + 1] = pack2<DT>(ir_act12<ACT>(d[j][2], cl2), ir_act12<ACT>(d[j][3], cl2));
                 }
             }
 #pragma unroll
@@ -285,8 +297,8 @@ template <int DT, int NK, bool HSW> __global__ __launch_bounds__(256, fused_ir_w
                     v[3] += from_storage<DT>((uint16_t)(r.y >> 16));
                 }
                 uint2 o;
-                o.x = pack2<DT>(clampf<HSW>(v[0], cl3), clampf<HSW>(v[1], cl3));
-                o.y = pack2<DT>(clampf<HSW>(v[2], cl3), clampf<HSW>(v[3], cl3));
+                o.x = pack2<DT>(ir_act3<ACT>(v[0], cl3), ir_act3<ACT>(v[1], cl3));
+                o.y = pack2<DT>(ir_act3<ACT>(v[2], cl3), ir_act3<ACT>(v[3], cl3));
                 store_stream8(yimg + (pix[j] * (uint32_t)a.F3 + (uint32_t)f) * 2u, o);
             }
         }
@@ -305,17 +317,17 @@ size_t fused_ir_lds_bytes(int TH, int TW, int nslots, int stride)
     return ir_lds_front(nslots) + (size_t)((TH - 1) * stride + 3) * ir_row_pitch(nslots, stride, (TW - 1) * stride + 3) + ir_pitch(nslots, stride);
 }
 
-template <int DT, int NK> static void ir_launch(const IrArgs &a, bool hsw, unsigned grid, size_t lds_bytes, hipStream_t st)
+template <int DT, int NK> static void ir_launch(const IrArgs &a, unsigned grid, size_t lds_bytes, hipStream_t st)
 {
-    static std::once_flag once[2];
+    static std::once_flag once[3];
     auto go = [&](auto kern, std::once_flag &flag) {
         allow_lds_once(flag, kern, 160 * 1024);
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds_bytes, st, a);
     };
-    // the activation kind is compiled in: hard-swish behind a (wave-uniform) branch per value kept the compiler from
-    // interleaving loads, MFMAs and epilogue arithmetic across values
-    if (hsw) go(fused_inverted_residual_kernel<DT, NK, true>, once[0]);
-    else go(fused_inverted_residual_kernel<DT, NK, false>, once[1]);
+    const bool h1 = a.act1 == NPAS_ACT_HARDSWISH, h2 = a.act2 == NPAS_ACT_HARDSWISH, h3 = a.act3 == NPAS_ACT_HARDSWISH;
+    if (!h1 && !h2 && !h3) go(fused_inverted_residual_kernel<DT, NK, IR_CLAMPS>, once[0]);
+    else if (h1 && h2 && !h3) go(fused_inverted_residual_kernel<DT, NK, IR_HS_HS_CLAMP>, once[1]);
+    else go(fused_inverted_residual_kernel<DT, NK, IR_MIXED>, once[2]);
 }
 
 int launch_fused_inverted_residual(int dtype, const IrLaunch &l, void *stream)
@@ -348,19 +360,18 @@ int launch_fused_inverted_residual(int dtype, const IrLaunch &l, void *stream)
     a.div_ty = magic(a.tilesY);
     // a workgroup per CU for every copy of the kernel that fits there (LDS, and the registers its launch bounds allow)
     const int fit = std::min<int>((int)(160 * 1024 / lds_bytes), fused_ir_wgs_per_cu(nslots));
-    const bool hsw = l.act1 == NPAS_ACT_HARDSWISH || l.act2 == NPAS_ACT_HARDSWISH || l.act3 == NPAS_ACT_HARDSWISH;
     a.ntiles = (uint32_t)((long)N * a.tilesY * a.tilesX);
     a.fast = (uint64_t)a.ntiles * (uint64_t)std::max(a.tilesX, a.tilesY) < (1ull << 32);
     const unsigned grid = std::min<uint32_t>(a.ntiles, 256u * fit);
     auto go = [&](auto dtc) {
         constexpr int DT = decltype(dtc)::value;
         switch (nslots / 32) {
-        case 1: ir_launch<DT, 1>(a, hsw, grid, lds_bytes, st); break;
-        case 2: ir_launch<DT, 2>(a, hsw, grid, lds_bytes, st); break;
-        case 3: ir_launch<DT, 3>(a, hsw, grid, lds_bytes, st); break;
-        case 4: ir_launch<DT, 4>(a, hsw, grid, lds_bytes, st); break;
-        case 5: ir_launch<DT, 5>(a, hsw, grid, lds_bytes, st); break;
-        default: ir_launch<DT, 6>(a, hsw, grid, lds_bytes, st); break;
+        case 1: ir_launch<DT, 1>(a, grid, lds_bytes, st); break;
+        case 2: ir_launch<DT, 2>(a, grid, lds_bytes, st); break;
+        case 3: ir_launch<DT, 3>(a, grid, lds_bytes, st); break;
+        case 4: ir_launch<DT, 4>(a, grid, lds_bytes, st); break;
+        case 5: ir_launch<DT, 5>(a, grid, lds_bytes, st); break;
+        default: ir_launch<DT, 6>(a, grid, lds_bytes, st); break;
         }
     };
     if (dtype == NPAS_BF16) go(std::integral_constant<int, NPAS_BF16>{});

@@ -489,6 +489,23 @@ def test_fused_block_slots_and_tiles(npas, torch, N, HW, C, t, stride, rate, dty
     print(f"  norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
 
 
+# The activations are compiled in: hard-swish, hard-swish, clamp at the slot counts not above, and mixtures with hard-swish.
+@pytest.mark.parametrize("C,t,stride,acts,dtype", [(8, 4, 1, (3, 3, 0), dtypes.BF16), (24, 4, 2, (3, 3, 0), dtypes.F16), (16, 8, 1, (3, 3, 1), dtypes.BF16),
+                                                   (32, 5, 2, (3, 3, 2), dtypes.BF16), (24, 4, 1, (3, 2, 0), dtypes.BF16),
+                                                   (16, 4, 2, (1, 3, 0), dtypes.F16), (32, 6, 1, (2, 0, 3), dtypes.BF16)])
+def test_fused_block_activation_mixes(npas, torch, C, t, stride, acts, dtype):
+    from workloads import sweeps
+    print(f"fused block {C}->{C * t} stride {stride} activations {acts}", flush=True)
+    w = sweeps.inverted_residual_block(batch=3, HW=19, C=C, t=t, stride=stride, rate=1, dtype=dtype, bias=True)
+    for L, a in zip(w.layers, acts):
+        L.act = a
+    ref = oracle.run_stack(w.x_exact, w.layers, w.dtype)[0][-1]
+    got, st = _run_stack_gpu(npas, torch, w, npas.STACK_FUSE_INVERTED_RESIDUAL)
+    assert st.num_launches() == 1
+    norm, worst = helpers.check_stack_output(got.reshape(ref.shape), ref, STACK_NORM_TOL)
+    print(f"  norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
+
+
 def test_run_stack_in_a_hip_graph_replays_like_the_eager_call(npas, torch):
     """npas_run_stack allocates nothing and clears nothing during a run, so a caller may capture it.
     Several replays, with eager work and synchronisations in between, each against the eager result."""
