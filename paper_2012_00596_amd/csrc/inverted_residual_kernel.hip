@@ -136,7 +136,7 @@ template <int DT, int NK, int ACT> __global__ __launch_bounds__(256, fused_ir_wg
             const bool in = (int)(hpos[r] >> 16) < PH && (uint32_t)iy < (uint32_t)a.H && (uint32_t)ix < (uint32_t)a.W;
             inside |= in ? 1u << r : 0u;
             // no branch: outside the image some pixel of it (the result is replaced by zero), past the last channel the last ones
-            // again (their weights are zero)
+            // again (replaced by zeros below: their weights are zero, but infinity times zero is not)
             xv[r] = *reinterpret_cast<const uint4 *>(ximg + ((in ? (uint32_t)(iy * a.W + ix) * (uint32_t)a.C1 : 0u) + cq) * 2u);
         }
     };
@@ -201,6 +201,7 @@ template <int DT, int NK, int ACT> __global__ __launch_bounds__(256, fused_ir_wg
         const bool in_tile = (int)(hpos[r] >> 16) < PH; // otherwise written to the spare pixel behind the halo tile
         uint8_t *dst = y1 + (in_tile ? (hpos[r] >> 16) * rpitch + (hpos[r] & 0xffffu) * pitch : (uint32_t)PH * rpitch) + (uint32_t)q * 16u;
         const uint32_t keep = 0u - (inside >> r & 1u); // padding of the depthwise layer is zero, whatever the bias
+        const uint4 xr = 8 * q < a.C1 ? xv[r] : uint4{0u, 0u, 0u, 0u};
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
             uint32_t o[4];
@@ -208,7 +209,7 @@ template <int DT, int NK, int ACT> __global__ __launch_bounds__(256, fused_ir_wg
             for (int h = 0; h < 2; ++h) {
                 // result register i: slot 32 k + 8 q + 4 h + i (the two tiles of a step interleaved: one 16-byte write)
                 const int t = 2 * k + h;
-                const f32x4 d = mfma16<DT>(w1r[t], xv[r], *reinterpret_cast<const f32x4 *>(lb1 + 32 * k + 8 * q + 4 * h));
+                const f32x4 d = mfma16<DT>(w1r[t], xr, *reinterpret_cast<const f32x4 *>(lb1 + 32 * k + 8 * q + 4 * h));
                 o[2 * h] = pack2<DT>(ir_act12<ACT>(d[0], cl1), ir_act12<ACT>(d[1], cl1));
                 o[2 * h + 1] = pack2<DT>(ir_act12<ACT>(d[2], cl1), ir_act12<ACT>(d[3], cl1));
             }

@@ -506,6 +506,23 @@ def test_fused_block_activation_mixes(npas, torch, C, t, stride, acts, dtype):
     print(f"  norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
 
 
+@pytest.mark.parametrize("C", [8, 24])
+def test_fused_block_infinite_input_in_the_last_channels(npas, torch, C):
+    """The matrix steps are 32 channels deep; past the last channel they must meet zeros, not other channels of the pixel.  An
+    infinite input under kept weights then clamps to 0 or 6 like any other, as the oracle has it."""
+    from workloads import sweeps
+    w = sweeps.inverted_residual_block(batch=2, HW=11, C=C, t=4, stride=2, rate=1)
+    for n, y, x, c, v in ((0, 3, 4, C - 1, np.inf), (1, 0, 0, C - 5, -np.inf), (1, 10, 10, C - 8, np.inf)):
+        w.x_exact[n, y, x, c] = v
+    w.x_store, _ = dtypes.quantize(w.x_exact, w.dtype)
+    assert (w.layers[0].w_exact != 0).all()
+    ref = oracle.run_stack(w.x_exact, w.layers, w.dtype)[0][-1]
+    assert np.isfinite(ref).all()
+    got, st = _run_stack_gpu(npas, torch, w, npas.STACK_FUSE_INVERTED_RESIDUAL)
+    assert st.num_launches() == 1
+    helpers.check_stack_output(got.reshape(ref.shape), ref, STACK_NORM_TOL)
+
+
 def test_run_stack_in_a_hip_graph_replays_like_the_eager_call(npas, torch):
     """npas_run_stack allocates nothing and clears nothing during a run, so a caller may capture it.
     Several replays, with eager work and synchronisations in between, each against the eager result."""
