@@ -901,7 +901,7 @@ static IrPlan build_ir(const npas_packed *p1, const npas_packed *pdw, const npas
 // Output tile of at most `cap` pixels of the fused block for an Ho x Wo map: the shape that costs least, counting the
 // halo pixels expanded and the 16-pixel blocks of depthwise work (about four times dearer), among those whose LDS
 // footprint leaves room for as many workgroups per CU as their registers do.
-static void plan_ir_tile(int Ho, int Wo, int nslots, int stride, int cap, int *TH, int *TW)
+static void plan_ir_tile(int Ho, int Wo, int nslots, int stride, int act1, int act2, int act3, int cap, int *TH, int *TW)
 {
     double best = 1e300;
     *TH = 1; *TW = 1;
@@ -909,7 +909,7 @@ static void plan_ir_tile(int Ho, int Wo, int nslots, int stride, int cap, int *T
         for (int tw = 1; tw <= 64; ++tw) {
             const int ph = (th - 1) * stride + 3, pw = (tw - 1) * stride + 3; // input pixels under the tile, with halo
             if (th * tw > cap || ph * pw > 256) continue; // four 16-pixel halo blocks per wave at most
-            if (fused_ir_lds_bytes(th, tw, nslots, stride) > (size_t)160 * 1024 / fused_ir_wgs_per_cu(nslots)) continue;
+            if (fused_ir_lds_bytes(th, tw, nslots, stride, act1, act2, act3) > (size_t)160 * 1024 / fused_ir_wgs_per_cu(nslots)) continue;
             const double tiles = (double)((Ho + th - 1) / th) * ((Wo + tw - 1) / tw);
             const double cost = tiles * (1.0 * ((ph * pw + 15) / 16) + 4.0 * ((th * tw + 15) / 16) + 2.0);
             if (cost < best) {
@@ -1194,7 +1194,8 @@ int npas_stack_create(const npas_layer_desc *layers, int n_layers, int H, int W,
             }
             a.ir_nslots = ip.nslots; a.ir_residual = c.d.res >= 0;
             for (int t = 0; t < 3; ++t)
-                plan_ir_tile((a.H - 1) / b.d.stride + 1, (a.W - 1) / b.d.stride + 1, ip.nslots, b.d.stride, kIrTileCap[t], &a.ir_TH[t], &a.ir_TW[t]);
+                plan_ir_tile((a.H - 1) / b.d.stride + 1, (a.W - 1) / b.d.stride + 1, ip.nslots, b.d.stride, a.d.act, b.d.act, c.d.act, kIrTileCap[t],
+                             &a.ir_TH[t], &a.ir_TW[t]);
             b.fused_away = true;
             c.fused_away = true;
         }

@@ -55,14 +55,6 @@ __host__ __device__ constexpr uint32_t ir_row_pitch(int nslots, int stride, int 
     const uint32_t p = ir_pitch(nslots, stride);
     return (uint32_t)PW * p + 16u * ((stride == 1 ? 6u : 7u) * (p / 16u) % 8u); // -2 p or -p units, mod 8
 }
-// bytes in front of the halo tile: biases of the three layers, layer 3's images
-// (and, at 96 slots, the depthwise weights: there the registers of three workgroups per CU do not hold them)
-__host__ __device__ constexpr bool ir_wd_in_lds(int nslots) { return nslots == 96; }
-__host__ __device__ constexpr uint32_t ir_lds_front(int nslots)
-{
-    return (uint32_t)nslots * 8u + 128u + (uint32_t)nslots / 32u * 2048u + (ir_wd_in_lds(nslots) ? (uint32_t)nslots / 16u * 1280u : 0u);
-}
-
 struct IrArgs {
     const void *x;
     void *y;
@@ -82,15 +74,52 @@ struct IrArgs {
     uint32_t div_tw, div_pw, div_tx, div_ty;
 };
 
-// The activations compiled in: clamps (none, ReLU, ReLU6) on all three layers; hard-swish on the first two and a clamp on the
-// third; any mixture with hard-swish, behind a (wave-uniform) branch per value, which keeps the compiler from interleaving
-// loads, MFMAs and epilogue arithmetic across values (hard-swish blocks with it, fp16, stride 2: 1 x 28 x 28, 32 -> 192 -> 32 13.0 us,
-// now 8.9; the kernel with the depthwise layer on the vector ALUs 11.6).
-enum { IR_CLAMPS, IR_HS_HS_CLAMP, IR_MIXED };
-template <int ACT> __device__ __forceinline__ float ir_act12(float v, Clamp c)
+// The activations compiled in; a branch per value, as the last kind has it, keeps the compiler from interleaving loads, MFMAs and
+// epilogue arithmetic across values (hard-swish blocks with it, fp16, stride 2: 1 x 28 x 28, 32 -> 192 -> 32 13.0 us, now 8.9; the
+// kernel with the depthwise layer on the vector ALUs 11.6).
+// Where the first activation has no upper bound, an expanded value may be infinite in the storage type; the diagonal operand's
+// zeros then make NaN in all sixteen slots of a step, while the slot itself may be finite again after ReLU or ReLU6.  In such
+// kernels the second activation lets NaN pass (maximum, minimum instead of the median), so that layer 3's sums show it: a pixel with
+// a NaN among them is worked out again one product at a time.  With ReLU6 first there is nothing to look for, and without a
+// lower bound second (none, hard-swish) the pixel's results are not finite whatever its other slots are.
+enum { IR_PLAIN,              // clamps (none, ReLU, ReLU6), first ReLU6 or second none
+       IR_RELU,               // clamps, second ReLU
+       IR_HS_CLAMP, IR_CLAMP_HS, IR_HS_HS, // the first two; third a clamp
+       IR_MIXED };            // the rest
+__host__ __device__ constexpr bool ir_looks_for_nan(int act) { return act == IR_RELU || act == IR_HS_CLAMP || act == IR_MIXED; }
+static int ir_kind(int act1, int act2, int act3)
 {
-    if (ACT == IR_HS_HS_CLAMP) return v * __builtin_amdgcn_fmed3f(v + 3.0f, 0.0f, 6.0f) * (1.0f / 6.0f);
-    return clampf<ACT == IR_MIXED>(v, c);
+    const bool h1 = act1 == NPAS_ACT_HARDSWISH, h2 = act2 == NPAS_ACT_HARDSWISH;
+    if (act3 == NPAS_ACT_HARDSWISH) return IR_MIXED;
+    if (h1 || h2) return h1 && h2 ? IR_HS_HS : h1 ? IR_HS_CLAMP : IR_CLAMP_HS;
+    if (act1 == NPAS_ACT_RELU6 || act2 == NPAS_ACT_NONE) return IR_PLAIN;
+    return act2 == NPAS_ACT_RELU ? IR_RELU : IR_MIXED;
+}
+
+// bytes in front of the halo tile: biases of the three layers, layer 3's images
+// (and the depthwise weights where the registers of three workgroups per CU do not hold them: at 96 slots, and at 64 in a kernel that
+// looks for NaN, which spilled 16-24 of them otherwise: 64 x 56 x 56, 16 -> 64 -> 16 at stride 2 with ReLU 12.4 us, 9.3 so)
+__host__ __device__ constexpr bool ir_wd_in_lds(int nslots, int act) { return nslots == 96 || (nslots == 64 && ir_looks_for_nan(act)); }
+__host__ __device__ constexpr uint32_t ir_lds_front(int nslots, int act)
+{
+    return (uint32_t)nslots * 8u + 128u + (uint32_t)nslots / 32u * 2048u + (ir_wd_in_lds(nslots, act) ? (uint32_t)nslots / 16u * 1280u : 0u);
+}
+
+template <bool HS> __device__ __forceinline__ float ir_act(float v, Clamp c)
+{
+    if (HS) return v * __builtin_amdgcn_fmed3f(v + 3.0f, 0.0f, 6.0f) * (1.0f / 6.0f);
+    return __builtin_amdgcn_fmed3f(v, c.lo, c.hi);
+}
+template <int ACT> __device__ __forceinline__ float ir_act1(float v, Clamp c)
+{
+    return ACT == IR_MIXED ? clampf(v, c) : ir_act<ACT == IR_HS_CLAMP || ACT == IR_HS_HS>(v, c);
+}
+template <int ACT> __device__ __forceinline__ float ir_act2(float v, Clamp c)
+{
+    if (ACT == IR_RELU) return __builtin_elementwise_maximum(v, 0.0f);
+    if (ACT == IR_MIXED && c.hs) return ir_act<true>(v, c);
+    if (ACT == IR_HS_CLAMP || ACT == IR_MIXED) return __builtin_elementwise_minimum(__builtin_elementwise_maximum(v, c.lo), c.hi);
+    return ir_act<ACT == IR_CLAMP_HS || ACT == IR_HS_HS>(v, c);
 }
 template <int ACT> __device__ __forceinline__ float ir_act3(float v, Clamp c) { return clampf<ACT == IR_MIXED>(v, c); }
 
@@ -104,9 +133,9 @@ template <int DT, int NK, int ACT> __global__ __launch_bounds__(256, fused_ir_wg
     const uint32_t pitch = ir_pitch(NSLOTS, a.stride), rpitch = ir_row_pitch(NSLOTS, a.stride, PW);
     float *lb1 = reinterpret_cast<float *>(lds), *lb2 = lb1 + NSLOTS, *lb3 = lb2 + NSLOTS; // biases in slot / filter order
     uint4 *lw3 = reinterpret_cast<uint4 *>(lb3 + 32);                                      // [2][NK][64] layer 3's images
-    constexpr bool WDL = ir_wd_in_lds(NSLOTS);
+    constexpr bool WDL = ir_wd_in_lds(NSLOTS, ACT);
     uint32_t *lwd = reinterpret_cast<uint32_t *>(lw3 + 2 * NK * 64); // [NT1][5][64] depthwise weights
-    uint8_t *y1 = lds + ir_lds_front(NSLOTS);
+    uint8_t *y1 = lds + ir_lds_front(NSLOTS, ACT);
 
     // What the launch keeps for all its tiles: the weight images in registers (layer 3's in LDS), the biases in LDS.  Everything
     // is asked for here together with the first tile's activations: one memory latency instead of one per step.
@@ -210,8 +239,8 @@ template <int DT, int NK, int ACT> __global__ __launch_bounds__(256, fused_ir_wg
                 // result register i: slot 32 k + 8 q + 4 h + i (the two tiles of a step interleaved: one 16-byte write)
                 const int t = 2 * k + h;
                 const f32x4 d = mfma16<DT>(w1r[t], xr, *reinterpret_cast<const f32x4 *>(lb1 + 32 * k + 8 * q + 4 * h));
-                o[2 * h] = pack2<DT>(ir_act12<ACT>(d[0], cl1), ir_act12<ACT>(d[1], cl1));
-                o[2 * h + 1] = pack2<DT>(ir_act12<ACT>(d[2], cl1), ir_act12<ACT>(d[3], cl1));
+                o[2 * h] = pack2<DT>(ir_act1<ACT>(d[0], cl1), ir_act1<ACT>(d[1], cl1));
+                o[2 * h + 1] = pack2<DT>(ir_act1<ACT>(d[2], cl1), ir_act1<ACT>(d[3], cl1));
             }
             *reinterpret_cast<uint4 *>(dst + k * 64) = uint4{o[0] & keep, o[1] & keep, o[2] & keep, o[3] & keep};
         }
@@ -224,6 +253,7 @@ template <int DT, int NK, int ACT> __global__ __launch_bounds__(256, fused_ir_wg
     lds_barrier();
 
     // ---- 2. depthwise and 3. projection ---------------------------------------------------
+    uint64_t nan = 0; // lanes with a NaN among the tile's sums
     // NB 16-pixel blocks at a time (ob0 and ob0 + 4), so that a step's operand words are formed once for both
     auto blocks = [&](auto nbc, int ob0) __attribute__((always_inline)) {
         constexpr int NB = decltype(nbc)::value;
@@ -270,8 +300,8 @@ template <int DT, int NK, int ACT> __global__ __launch_bounds__(256, fused_ir_wg
                 }
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
-                    b[j][2 * h] = pack2<DT>(ir_act12<ACT>(d[j][0], cl2), ir_act12<ACT>(d[j][1], cl2));
-                    b[j][2 * h + 1] = pack2<DT>(ir_act12<ACT>(d[j][2], cl2), ir_act12<ACT>(d[j][3], cl2));
+                    b[j][2 * h] = pack2<DT>(ir_act2<ACT>(d[j][0], cl2), ir_act2<ACT>(d[j][1], cl2));
+                    b[j][2 * h + 1] = pack2<DT>(ir_act2<ACT>(d[j][2], cl2), ir_act2<ACT>(d[j][3], cl2));
                 }
             }
 #pragma unroll
@@ -282,6 +312,8 @@ template <int DT, int NK, int ACT> __global__ __launch_bounds__(256, fused_ir_wg
                 acc[j][1] = mfma16<DT>(w3b, bv, acc[j][1]);
             }
         }
+        // (a NaN slot makes NaN of all the pixel's sums)
+        if (ir_looks_for_nan(ACT)) nan |= __builtin_amdgcn_ballot_w64(__builtin_isunordered(acc[0][0][0], acc[NB - 1][0][0]));
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             if (!valid[j]) continue;
@@ -308,27 +340,69 @@ template <int DT, int NK, int ACT> __global__ __launch_bounds__(256, fused_ir_wg
         if (ob + 4 < nob) blocks(std::integral_constant<int, 2>{}, ob);
         else blocks(std::integral_constant<int, 1>{}, ob);
     }
+    if (ir_looks_for_nan(ACT) && nan) { // the wave's blocks again, four filters at a time, without products of zeros that are no weights
+        // (the arguments are read again here: kept for this they would take scalar registers from the loops above)
+        auto ka = (const __attribute__((address_space(4))) IrArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(ka));
+#pragma unroll 1
+        for (int i = 2 * wave; i < 2 * nob; i += i & 1 ? 7 : 1) {
+            const int u = i & 1, f = 16 * u + 4 * q;
+            const uint32_t p = (uint32_t)(i >> 1) * 16u + n16, ty = fastdiv(p, ka->div_tw), tx = p - ty * (uint32_t)ka->TW;
+            const int oy = oy0 + (int)ty, ox = ox0 + (int)tx;
+            if (f >= ka->F3 || (int)ty >= ka->TH || oy >= ka->Ho || ox >= ka->Wo) continue;
+            const uint8_t *px = y1 + (ty * rpitch + tx * pitch) * (uint32_t)ka->stride;
+            f32x4 v = *reinterpret_cast<const f32x4 *>(lb3 + f);
+#pragma unroll 1
+            for (int s = 0; s < NSLOTS; ++s) {
+                const int r = s & 15;
+                float d = lb2[s];
+#pragma unroll 1
+                for (int tap = 0; tap < 9; ++tap) {
+                    const uint32_t w = ka->wdw[((s >> 4) * 5 + (tap >> 1)) * 64 + (2 * (tap & 1) + (r >> 3)) * 16 + r] >> (16 * (r & 1));
+                    const uint16_t e = *reinterpret_cast<const uint16_t *>(px + (uint32_t)(tap / 3) * rpitch + (uint32_t)(tap % 3) * pitch + 2 * s);
+                    d = fmaf(from_storage<DT>((uint16_t)(w & 0xffffu)), from_storage<DT>(e), d);
+                }
+                d = from_storage<DT>(to_storage<DT>(clampf(d, clamp_of(ka->act2))));
+                // slot s is element 4 (s / 16 % 2) + s % 4 of lanes 16 (s / 4 % 4) + filter in layer 3's image of step s / 32
+                const uint16_t *w3 = reinterpret_cast<const uint16_t *>(lw3 + (u * NK + (s >> 5)) * 64 + (r >> 2) * 16 + 4 * q) + 4 * (s >> 4 & 1) + (s & 3);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (w3[8 * k] & 0x7fffu) v[k] = fmaf(from_storage<DT>(w3[8 * k]), d, v[k]);
+            }
+            const uint32_t pix = (uint32_t)(oy * ka->Wo + ox);
+            uint16_t *yp = reinterpret_cast<uint16_t *>(yimg) + pix * (uint32_t)ka->F3 + (uint32_t)f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (ka->residual) v[k] += from_storage<DT>(reinterpret_cast<const uint16_t *>(ximg)[pix * (uint32_t)ka->C1 + f + k]);
+                yp[k] = to_storage<DT>(ir_act3<ACT>(v[k], clamp_of(ka->act3)));
+            }
+        }
+    }
     if (item >= a.ntiles) break; // (the same for the whole workgroup)
     lds_barrier(); // the halo tile is free again
     }
 }
 
-size_t fused_ir_lds_bytes(int TH, int TW, int nslots, int stride)
+size_t fused_ir_lds_bytes(int TH, int TW, int nslots, int stride, int act1, int act2, int act3)
 {
-    return ir_lds_front(nslots) + (size_t)((TH - 1) * stride + 3) * ir_row_pitch(nslots, stride, (TW - 1) * stride + 3) + ir_pitch(nslots, stride);
+    return ir_lds_front(nslots, ir_kind(act1, act2, act3)) + (size_t)((TH - 1) * stride + 3) * ir_row_pitch(nslots, stride, (TW - 1) * stride + 3) + ir_pitch(nslots, stride);
 }
 
 template <int DT, int NK> static void ir_launch(const IrArgs &a, unsigned grid, size_t lds_bytes, hipStream_t st)
 {
-    static std::once_flag once[3];
+    static std::once_flag once[6];
     auto go = [&](auto kern, std::once_flag &flag) {
         allow_lds_once(flag, kern, 160 * 1024);
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds_bytes, st, a);
     };
-    const bool h1 = a.act1 == NPAS_ACT_HARDSWISH, h2 = a.act2 == NPAS_ACT_HARDSWISH, h3 = a.act3 == NPAS_ACT_HARDSWISH;
-    if (!h1 && !h2 && !h3) go(fused_inverted_residual_kernel<DT, NK, IR_CLAMPS>, once[0]);
-    else if (h1 && h2 && !h3) go(fused_inverted_residual_kernel<DT, NK, IR_HS_HS_CLAMP>, once[1]);
-    else go(fused_inverted_residual_kernel<DT, NK, IR_MIXED>, once[2]);
+    switch (ir_kind(a.act1, a.act2, a.act3)) {
+    case IR_PLAIN: go(fused_inverted_residual_kernel<DT, NK, IR_PLAIN>, once[0]); break;
+    case IR_RELU: go(fused_inverted_residual_kernel<DT, NK, IR_RELU>, once[1]); break;
+    case IR_HS_CLAMP: go(fused_inverted_residual_kernel<DT, NK, IR_HS_CLAMP>, once[2]); break;
+    case IR_CLAMP_HS: go(fused_inverted_residual_kernel<DT, NK, IR_CLAMP_HS>, once[3]); break;
+    case IR_HS_HS: go(fused_inverted_residual_kernel<DT, NK, IR_HS_HS>, once[4]); break;
+    default: go(fused_inverted_residual_kernel<DT, NK, IR_MIXED>, once[5]); break;
+    }
 }
 
 int launch_fused_inverted_residual(int dtype, const IrLaunch &l, void *stream)
@@ -346,7 +420,7 @@ int launch_fused_inverted_residual(int dtype, const IrLaunch &l, void *stream)
     const int PH = (TH - 1) * stride + 3, PW = (TW - 1) * stride + 3;
     a.div_tw = TW <= 1 ? 0u : (uint32_t)(((1ull << 32) + TW - 1) / TW);
     a.div_pw = (uint32_t)(((1ull << 32) + PW - 1) / PW);
-    const size_t lds_bytes = fused_ir_lds_bytes(TH, TW, nslots, stride);
+    const size_t lds_bytes = fused_ir_lds_bytes(TH, TW, nslots, stride, l.act1, l.act2, l.act3);
     if (nslots <= 0 || nslots % 32 || nslots > 192 || TH < 1 || TW < 1 || PH * PW > 256 || a.nt3 < 1 || a.nt3 > 2 || C1 > 32 || C1 % 8 || F3 % 4 ||
         lds_bytes > 160 * 1024 || (stride != 1 && stride != 2) || (l.residual && (F3 != C1 || stride != 1)) || !l.perm) {
         set_error("fused inverted residual: unsupported shape (slots %d, C1 %d, F3 %d, stride %d, LDS %zu)", nslots, C1, F3, stride, lds_bytes);

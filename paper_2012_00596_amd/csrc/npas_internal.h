@@ -382,7 +382,7 @@ int launch_conv_wave_f32(const WaveF32Args &a, void *stream);
 bool fpp_supported(int nt1, int nt2);
 int launch_fused_pointwise_pair(int dtype, const void *x, void *y, const void *wblob, int M, int C1, int nt1, int F2,
                                 int act1, int act2, uint32_t use0, uint32_t use1, void *stream);
-size_t fused_ir_lds_bytes(int TH, int TW, int nslots, int stride);
+size_t fused_ir_lds_bytes(int TH, int TW, int nslots, int stride, int act1, int act2, int act3);
 constexpr int fused_ir_wgs_per_cu(int nslots) { return nslots <= 96 ? 3 : 2; } // what the kernel's launch bounds allow
 // One launch of the fused 1x1 -> depthwise 3x3 -> 1x1 block (all pointers device memory).
 struct IrLaunch {

@@ -523,6 +523,31 @@ def test_fused_block_infinite_input_in_the_last_channels(npas, torch, C):
     helpers.check_stack_output(got.reshape(ref.shape), ref, STACK_NORM_TOL)
 
 
+@pytest.mark.parametrize("C,t,stride,acts,HW", [(8, 4, 1, (1, 1, 0), 9), (16, 4, 2, (3, 2, 0), 23), (24, 4, 1, (1, 2, 1), 13), (32, 4, 2, (1, 1, 0), 15),
+                                                (32, 5, 1, (3, 2, 3), 21), (32, 6, 1, (1, 1, 0), 17), (32, 6, 2, (3, 1, 0), 17)])
+def test_fused_block_expanded_values_that_overflow(npas, torch, C, t, stride, acts, HW):
+    """fp16, finite input: two expanded channels overflow to infinity at scattered pixels, and the depthwise layer (negative weights, then
+    ReLU or ReLU6) turns them into finite values again.  The other channels of their matrix step must not notice."""
+    from workloads import sweeps
+    w = sweeps.inverted_residual_block(batch=3, HW=HW, C=C, t=t, stride=stride, rate=1, dtype=dtypes.F16, bias=True)
+    mid = C * t
+    for L, a in zip(w.layers, acts):
+        L.act = a
+    for c in (1, mid - 6):
+        w.layers[0].w_exact[c] = 0.0
+        w.layers[0].w_exact[c, 0, 0, 0] = 32768.0            # times an input above 2: infinite in fp16
+        w.layers[0].bias[c] = 0.0
+        w.layers[1].w_exact[c] = -np.abs(w.layers[1].w_exact[c]) - 0.0625
+        w.layers[1].bias[c] = 0.0
+    for L in w.layers[:2]:
+        L.w_store, L.w_exact = dtypes.quantize(L.w_exact, w.dtype)
+    rounded, _ = oracle.run_stack(w.x_exact, w.layers, w.dtype)
+    assert np.isinf(rounded[1]).any() and np.isfinite(rounded[-1]).all()
+    got, st = _run_stack_gpu(npas, torch, w, npas.STACK_FUSE_INVERTED_RESIDUAL)
+    assert st.num_launches() == 1
+    helpers.check_stack_output(got.reshape(rounded[-1].shape), rounded[-1], TOL[dtypes.F16])
+
+
 def test_run_stack_in_a_hip_graph_replays_like_the_eager_call(npas, torch):
     """npas_run_stack allocates nothing and clears nothing during a run, so a caller may capture it.
     Several replays, with eager work and synchronisations in between, each against the eager result."""
