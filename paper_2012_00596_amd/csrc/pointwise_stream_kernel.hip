@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256, NS <= 5 ? 4 : 3) void pointwise_stream_kernel(
         }
         const uint8_t *row = xb + (size_t)ip * (uint32_t)(2 * a.C);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) // (past the last channel: the last ones again, their weights are zero)
+        for (int s = 0; s < NS; ++s) // (past the last channel the last ones again, replaced by zeros below)
             v[s] = *reinterpret_cast<const uint4 *>(row + 2u * (uint32_t)min(32 * s + 8 * q, a.C - 8));
     };
     uint32_t blk = wg * 4u + (uint32_t)wave;
@@ -71,6 +71,8 @@ __global__ __launch_bounds__(256, NS <= 5 ? 4 : 3) void pointwise_stream_kernel(
     const Clamp cl = clamp_of(a.act);
     const int row_bytes = nf * 2;
     for (; blk < nblk; blk += step) {
+        // past the last channel the weights are zero, but infinity times zero is not
+        if (32 * (NS - 1) + 8 * q >= a.C) cur[NS - 1] = uint4{0u, 0u, 0u, 0u};
         if (blk + step < nblk) load_x(blk + step, nxt);
         const uint32_t p = min(blk * 16u + n16, (uint32_t)a.M - 1u);
         const uint8_t *rrow = reinterpret_cast<const uint8_t *>(a.residual) + ((size_t)p * (uint32_t)a.F + (uint32_t)f0) * 2u;

@@ -452,6 +452,23 @@ def test_flat_pointwise_launch_forms(npas, torch, case):
     _run_edge_case(npas, torch, case, expect_kernel="conv_slab_mfma")
 
 
+@pytest.mark.parametrize("C,F,HW", [(8, 20, 9), (24, 144, 37), (144, 40, 33), (312, 96, 33)])
+def test_flat_pointwise_infinite_input_in_the_last_channels(npas, torch, C, F, HW):
+    """The matrix steps are 32 channels deep; past the last channel they must meet zeros, not other channels of the pixel: an infinite
+    input under kept weights clamps to 0 or 6, as the oracle has it."""
+    L = configs._bp_conv(52, 0, C, F, 1, 1, 0, 4, 8, 1, 0.2, dtypes.BF16, configs.ACT_RELU6)
+    assert (L.w_exact != 0).all()
+    xs, xe = configs._tensor(52, 1, (2, HW, HW, C), 1.0, dtypes.BF16)
+    for n, y, x, c, v in ((0, 0, 0, C - 1, np.inf), (0, 5, 7, C - 8, -np.inf), (1, HW - 1, HW - 1, C - 3, np.inf)):
+        xe[n, y, x, c] = v
+    xs, xe = dtypes.quantize(xe, dtypes.BF16)
+    ref = oracle.round_to(oracle.conv2d_masked(xe, L.w_exact, L.mask, 1, 0, None, None, L.act), dtypes.BF16)
+    p = pack_layer(npas, L, dtypes.BF16)
+    assert npas.conv2d_kernel_name(p, 2, HW, HW, 1, 0) == "conv_slab_mfma"
+    y = run_layer_gpu(npas, torch, L, p, to_dev(xs, torch), xe.shape, dtypes.BF16)
+    assert rel_err(from_dev(y, dtypes.BF16).reshape(ref.shape), ref) <= TOL[dtypes.BF16]
+
+
 @pytest.mark.parametrize("C,F,N,HW,k,off", [(144, 40, 3, 29, 1, 8), (64, 128, 2, 21, 3, 2)], ids=["flat_8_bytes", "split_2_bytes"])
 def test_outputs_at_smaller_alignment(npas, torch, C, F, N, HW, k, off):
     """An output that starts 8 (flat 1x1 kernel) or 2 bytes (split reduction) past an aligned address: narrower stores, same values."""
