@@ -1174,7 +1174,33 @@ int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream)
 // A fragment load touches 16 lines where an image load touches 8 whole ones: the work is cut along the pixels first (16 a
 // workgroup, as 64 pixels x 16 filters the same layers spent their time in the address path of a quarter of the CUs), then as
 // few filters each as keeps the launch within one workgroup per CU.
-// MEASURED
+// Past 256 workgroups of 16 pixels x 64 filters, PB = 2 pixel blocks share a workgroup's images: eight waves add up, eight finish.
+// An infinite input meets the zeros that stand for pruned weights; a sum that is NaN is formed again over the kept weights alone, as the
+// exact lists give it that some of these layers take on other pixel counts.
+
+// The sum of one output over its kept weights, in channel order: pixel m, row r of image img of the 128-filter block fb.
+// (The arguments are read again here: kept for this they would take registers from the loop.)
+template <int DT> __device__ __forceinline__ float smallm_kept_sum(uint32_t m, uint32_t fb, uint32_t img, int r)
+{
+    auto ka = (const __attribute__((address_space(4))) SmallMArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ka));
+    const auto &a = *ka;
+    const uint32_t n = m / (uint32_t)(a.Ho * a.Wo), p = m - n * (uint32_t)(a.Ho * a.Wo), oy = p / (uint32_t)a.Wo, ox = p - oy * (uint32_t)a.Wo;
+    const int T = a.KH * a.KW, nch = a.C >> 6;
+    const uint16_t *w = reinterpret_cast<const uint16_t *>(a.wimg) + ((size_t)fb * nch * T * 16 + img) * 512 + r * 8;
+    float v = 0.f;
+    for (int t = 0; t < T; ++t) {
+        const int iy = (int)oy * a.stride - a.pad + t / a.KW, ix = (int)ox * a.stride - a.pad + t % a.KW;
+        if ((uint32_t)iy >= (uint32_t)a.H || (uint32_t)ix >= (uint32_t)a.W) continue;
+        const uint16_t *x = reinterpret_cast<const uint16_t *>(a.x) + (((size_t)n * a.H + iy) * a.W + ix) * a.C;
+        for (int c = 0; c < a.C; ++c) {
+            const uint16_t wc = w[((size_t)(c >> 6) * T + t) * 8192 + (c >> 5 & 1) * 4096 + (c >> 3 & 3) * 128 + (c & 7)];
+            if (wc & 0x7fffu) v = fmaf(from_storage<DT>(wc), from_storage<DT>(x[c]), v);
+        }
+    }
+    return v;
+}
+
 template <int DT, int FI, int PB, bool HSW>
 __device__ __forceinline__ void conv_smallm_mfma_kernel_body(SmallMArgs a)
 {
@@ -1273,7 +1299,9 @@ __device__ __forceinline__ void conv_smallm_mfma_kernel_body(SmallMArgs a)
     uint16_t v16[FI];
 #pragma unroll
     for (int j = 0; j < FI; ++j) {
-        float v = sf[j * 256] + add[j];
+        float v = sf[j * 256];
+        if (v != v) v = smallm_kept_sum<DT>(m, fb, tile8 + j, 4 * q + row);
+        v += add[j];
         if (a.residual) v += from_storage<DT>(rs[j]);
         v16[j] = to_storage<DT>(clampf<HSW>(v, cl));
     }

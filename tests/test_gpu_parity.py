@@ -469,6 +469,40 @@ def test_flat_pointwise_infinite_input_in_the_last_channels(npas, torch, C, F, H
     assert rel_err(from_dev(y, dtypes.BF16).reshape(ref.shape), ref) <= TOL[dtypes.BF16]
 
 
+def _infinite_input_under_pruned_weights(npas, torch, L, N, H, W, dtype, res, kernel):
+    """An input that is infinite where a filter's weight is pruned does not reach that filter: outputs against the oracle, which skips
+    pruned positions; the infinite inputs clamp to 0 or 6 where the weight is kept."""
+    xs, xe = configs._tensor(53, 1, (N, H, W, L.C), 1.0, dtype)
+    Ho, Wo = (H + 2 * L.pad - L.KH) // L.stride + 1, (W + 2 * L.pad - L.KW) // L.stride + 1
+    for i in range(4):
+        xe[i % N, (5 * i) % H // L.stride * L.stride, (7 * i) % W // L.stride * L.stride, (37 * i + 11) % L.C] = np.inf if i & 1 else -np.inf
+    xs, xe = dtypes.quantize(xe, dtype)
+    rs = re = None
+    if res:
+        rs, re = configs._tensor(53, 2, (N, Ho, Wo, L.F), 1.0, dtype)
+    we = L.w_exact * L.mask
+    # the oracle's sum without the pruned terms: finite inputs through the oracle, the infinite ones by their sign
+    fin = np.isfinite(xe)
+    acc = oracle.conv2d_masked(np.where(fin, xe, 0.0), L.w_exact, L.mask, L.stride, L.pad, None, re, configs.ACT_NONE)
+    inf = oracle.conv2d_masked(np.where(fin, 0.0, np.sign(xe)), np.sign(we), L.mask, L.stride, L.pad, None, None, configs.ACT_NONE)
+    ref = oracle.round_to(np.clip(np.where(inf > 0, np.inf, np.where(inf < 0, -np.inf, acc)), 0.0, 6.0), dtype)
+    assert (inf != 0).any() and (inf == 0).any()
+    p = pack_layer(npas, L, dtype)
+    assert npas.conv2d_kernel_name(p, N, H, W, L.stride, L.pad) == kernel
+    y = run_layer_gpu(npas, torch, L, p, to_dev(xs, torch), xe.shape, dtype, None if rs is None else to_dev(rs, torch))
+    assert rel_err(from_dev(y, dtype).reshape(ref.shape), ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("C,F,N,HW,k,stride,rate,dtype,res", [(1280, 200, 37, 1, 1, 1, 2, dtypes.BF16, False), (1024, 1000, 300, 1, 1, 1, 2, dtypes.F16, False),
+                                                               (256, 128, 3, 11, 1, 2, 3, dtypes.BF16, True), (128, 72, 2, 9, 3, 1, 5, dtypes.F16, True),
+                                                               (64, 200, 5, 28, 3, 2, 3, dtypes.BF16, False), (64, 192, 5, 25, 3, 1, 3, dtypes.BF16, True)],
+                         ids=["fc", "fc_64_filters", "1x1_s2", "3x3", "3x3_s2", "3x3_two_pixel_blocks"])
+def test_split_reduction_infinite_input_under_pruned_weights(npas, torch, C, F, N, HW, k, stride, rate, dtype, res, force_variant):
+    force_variant("smallm")
+    L = configs._bp_conv(53, 0, C, F, k, stride, k // 2, 4, 4, rate, 0.2, dtype, configs.ACT_RELU6)
+    _infinite_input_under_pruned_weights(npas, torch, L, N, HW, HW, dtype, res, "conv_smallm_mfma")
+
+
 @pytest.mark.parametrize("C,F,N,HW,k,off", [(144, 40, 3, 29, 1, 8), (64, 128, 2, 21, 3, 2)], ids=["flat_8_bytes", "split_2_bytes"])
 def test_outputs_at_smaller_alignment(npas, torch, C, F, N, HW, k, off):
     """An output that starts 8 (flat 1x1 kernel) or 2 bytes (split reduction) past an aligned address: narrower stores, same values."""
