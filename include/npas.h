@@ -36,8 +36,8 @@
  *   - Every function returns 0 (NPAS_OK) or a negative npas_status;
  *     npas_last_error() gives a thread-local message for the last failure.
  *   - Activations must be finite: a stored zero weight (padding of a partial
- *     group or of a position shared with a neighbouring group) times an infinite
- *     activation would give NaN where the definition gives a finite value.
+ *     group, or a pruned position of a layer whose kernel multiplies them) times an
+ *     infinite activation would give NaN where the definition gives a finite value.
  */
 #ifndef NPAS_H
 #define NPAS_H
@@ -78,6 +78,9 @@ const char *npas_last_error(void);
  * overrides the format / kernel choice, nothing else) and NPAS_NO_BALANCE (pointwise tiles of full height).
  * This call replaces them for the process (force_variant NULL or "" = none); it must not race with pack / run calls. */
 void npas_debug_set_switches(const char *force_variant, int no_balance);
+/* Testing aid: name of the device function of that launch, as a profiler lists it ("conv_slab_mfma_kernel",
+ * "pointwise_stream_kernel", ...); tells the two forms of the slab route apart.  Static string, NULL for a NULL handle. */
+const char *npas_debug_device_kernel(const npas_packed *p, int N, int H, int W, int stride, int pad);
 /* Measurement aid: enqueues `count` launches of an empty kernel (one wave) on the stream, so that a report can
  * state the launch-to-launch floor of the machine next to the kernels' times. */
 int npas_debug_launch_empty(int count, void *hip_stream);
@@ -153,7 +156,8 @@ int npas_conv2d_sparse(const npas_packed *p, const void *x_dev, void *y_dev, int
 /* Name of the kernel npas_conv2d_sparse / npas_fc_sparse launch for this layer and geometry
  * ("conv_valu_f32", "conv_wave_f32", "conv_gather_mfma", "conv_slab_mfma", "pointwise_ring",
  * "spatial_ring", "spatial_resident", "conv_smallc_mfma", "conv_smallm_mfma", "fc_gather_mfma";
- * "conv_slab_mfma" names both forms of the slab route: the tiled kernel, and the flat one of 1x1 layers);
+ * "conv_slab_mfma" names both forms of the slab route: the tiled kernel, and the flat one that 1x1 layers on at most 320
+ * channels, no multiple of 64, take in either list format);
  * a static string, NULL for a NULL handle.  For reports and tests:
  * the choice depends on the packed format and on how well the problem fills the chip. */
 const char *npas_conv2d_kernel_name(const npas_packed *p, int N, int H, int W, int stride, int pad);

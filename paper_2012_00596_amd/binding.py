@@ -31,7 +31,7 @@ EXPORTS = [
     "npas_fc_sparse",
     "npas_maxpool3x3s2", "npas_global_avgpool", "npas_stack_create", "npas_stack_workspace_bytes",
     "npas_run_stack", "npas_stack_num_launches", "npas_stack_free", "npas_stack_describe", "npas_debug_set_switches",
-    "npas_run_stack_static", "npas_debug_launch_empty",
+    "npas_run_stack_static", "npas_debug_launch_empty", "npas_debug_device_kernel",
 ]
 STATIC_WORKSPACE_BYTES = 32 << 20
 DESCRIBE_COLS = 11
@@ -115,6 +115,8 @@ def lib():
         L.npas_stack_describe.argtypes = [vp, ip, vp, ip]
         L.npas_run_stack_static.argtypes = [vp, vp, vp, ip, vp]
         L.npas_debug_launch_empty.argtypes = [ip, vp]
+        L.npas_debug_device_kernel.argtypes = [vp, ip, ip, ip, ip, ip]
+        L.npas_debug_device_kernel.restype = C.c_char_p
         L.npas_debug_set_switches.argtypes = [C.c_char_p, ip]
         L.npas_debug_set_switches.restype = None
         _lib = L
@@ -279,6 +281,12 @@ def conv2d_sparse(packed, x, y, N, H, W, stride, pad, bias=None, residual=None, 
 
 def conv2d_kernel_name(packed, N, H, W, stride, pad):
     name = lib().npas_conv2d_kernel_name(packed.handle, N, H, W, stride, pad)
+    return name.decode() if name else None
+
+
+def device_kernel(packed, N, H, W, stride, pad):
+    """Testing aid: the device function conv2d_sparse / fc_sparse launch, as a profiler lists it."""
+    name = lib().npas_debug_device_kernel(packed.handle, N, H, W, stride, pad)
     return name.decode() if name else None
 
 

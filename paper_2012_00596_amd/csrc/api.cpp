@@ -485,21 +485,25 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
     return gather ? R_GATHER : R_SLAB;
 }
 
-const char *route_name(const npas_packed *p, int N, int H, int W, int stride, int pad)
+// Name of a route in reports, and of the device function behind it.
+struct RouteNames {
+    const char *report, *kernel;
+};
+RouteNames route_names(const npas_packed *p, int N, int H, int W, int stride, int pad)
 {
     SpatialRingArgs sp;
     switch (choose_route(p, N, H, W, stride, pad, &sp)) {
-    case R_VALU: return "conv_valu_f32";
-    case R_WAVE_F32: return "conv_wave_f32";
-    case R_FC_GATHER: return "fc_gather_mfma";
-    case R_POINTWISE_RING: return "pointwise_ring";
-    case R_SPATIAL_RING: return "spatial_ring";
-    case R_SPATIAL_RESIDENT: return "spatial_resident";
-    case R_SMALLC: return "conv_smallc_mfma";
-    case R_SMALLM: return "conv_smallm_mfma";
-    case R_STREAM: // the slab route's flat form
-    case R_SLAB: return "conv_slab_mfma";
-    default: return "conv_gather_mfma";
+    case R_VALU: return {"conv_valu_f32", "conv_valu_f32_kernel"};
+    case R_WAVE_F32: return {"conv_wave_f32", "conv_wave_f32_kernel"};
+    case R_FC_GATHER: return {"fc_gather_mfma", "fc_gather_mfma_kernel"};
+    case R_POINTWISE_RING: return {"pointwise_ring", "pointwise_ring_kernel"};
+    case R_SPATIAL_RING: return {"spatial_ring", "spatial_ring_kernel"};
+    case R_SPATIAL_RESIDENT: return {"spatial_resident", "spatial_resident_kernel"};
+    case R_SMALLC: return {"conv_smallc_mfma", "conv_smallc_mfma_kernel"};
+    case R_SMALLM: return {"conv_smallm_mfma", "conv_smallm_mfma_kernel"};
+    case R_STREAM: return {"conv_slab_mfma", "pointwise_stream_kernel"}; // the slab route's flat form
+    case R_SLAB: return {"conv_slab_mfma", "conv_slab_mfma_kernel"};
+    default: return {"conv_gather_mfma", "conv_gather_mfma_kernel"};
     }
 }
 
@@ -942,7 +946,13 @@ int npas_conv2d_sparse(const npas_packed *p, const void *x_dev, void *y_dev, int
 const char *npas_conv2d_kernel_name(const npas_packed *p, int N, int H, int W, int stride, int pad)
 {
     if (!p || N <= 0 || H <= 0 || W <= 0 || stride <= 0 || pad < 0) return nullptr;
-    return route_name(p, N, H, W, stride, pad);
+    return route_names(p, N, H, W, stride, pad).report;
+}
+
+const char *npas_debug_device_kernel(const npas_packed *p, int N, int H, int W, int stride, int pad)
+{
+    if (!p || N <= 0 || H <= 0 || W <= 0 || stride <= 0 || pad < 0) return nullptr;
+    return route_names(p, N, H, W, stride, pad).kernel;
 }
 
 int npas_fc_sparse(const npas_packed *p, const void *x_dev, void *y_dev, int B, const void *bias_dev, npas_act act,

@@ -367,7 +367,6 @@ int run_stack_impl(const npas_stack *s, const void *x_dev, void *y_dev, int N, v
 int launch_conv_mfma(int dtype, int variant, const ConvMfmaArgs &a, unsigned grid, size_t lds_bytes, void *stream);
 int launch_conv_valu(const ConvValuArgs &a, void *stream);
 int launch_pointwise_ring(int dtype, const RingArgs &a, void *stream);
-const char *route_name(const npas_packed *p, int N, int H, int W, int stride, int pad);
 // Tile plan of the k x k streaming kernel (geometry fields of *a); false: use another kernel.
 bool plan_spatial(const npas_packed *p, int N, int H, int W, int pad, int stride, SpatialRingArgs *a);
 int launch_spatial_ring(int dtype, const SpatialRingArgs &a, void *stream);

@@ -164,7 +164,7 @@ EDGE = [
 ]
 
 
-def _run_edge_case(npas, torch, case, expect_kernel=None):
+def _run_edge_case(npas, torch, case, expect_kernel=None, device_kernel=None):
     name, N, H, W, C, F, KH, KW, stride, pad, Bf, Bc, rate, dtype, act, use_res, use_bias = case
     print(f"edge {name}", flush=True)
     xs, xe = dtypes.quantize(prng.normal(7, 1, N * H * W * C).reshape(N, H, W, C), dtype)
@@ -182,6 +182,8 @@ def _run_edge_case(npas, torch, case, expect_kernel=None):
     helpers.check_metadata(oracle, L, p, dtype)
     if expect_kernel is not None:
         assert npas.conv2d_kernel_name(p, N, H, W, stride, pad) == expect_kernel
+    if device_kernel is not None:
+        assert npas.device_kernel(p, N, H, W, stride, pad) == device_kernel
     y = run_layer_gpu(npas, torch, L, p, to_dev(xs, torch), (N, H, W, C), dtype,
                       None if rs is None else to_dev(rs, torch), None if bias is None else to_dev(bias, torch))
     got = from_dev(y, dtype).reshape(oshape)
@@ -343,6 +345,31 @@ def test_depthwise3x3_row_blocks(npas, torch, N, H, W, C, stride, dtype):
     assert rel_err(from_dev(y, dtype), ref) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("stride,N,off", [(1, 1, 2), (1, 40, 2), (2, 2, 2), (1, 40, 8), (2, 2, 4)])
+def test_depthwise3x3_at_smaller_alignment(npas, torch, stride, N, off):
+    """Tensors that start 2, 4 or 8 bytes past an aligned address (input, output and residual): same values as aligned ones."""
+    H, W, C = 29, 31, 48
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    ws, _ = dtypes.quantize(prng.normal(20, 2, C * 9, 0.3).reshape(C, 3, 3), dtypes.BF16)
+    p = npas.pack_depthwise3x3(ws, dtypes.BF16)
+    g = torch.Generator(device="cuda").manual_seed(20)
+    x = torch.randn((N, H, W, C), generator=g, device="cuda", dtype=torch.bfloat16)
+    r = torch.randn((N, Ho, Wo, C), generator=g, device="cuda", dtype=torch.bfloat16)
+    y = torch.empty((N, Ho, Wo, C), dtype=torch.bfloat16, device="cuda")
+    npas.depthwise3x3(p, x, y, N, H, W, stride, None, r, npas.ACT_NONE)
+
+    def shifted(t):
+        b = torch.zeros(t.numel() + 16, dtype=torch.int16, device="cuda")
+        b[off // 2:off // 2 + t.numel()] = t.reshape(-1).view(torch.int16)
+        return b
+
+    xo, ro, yo = shifted(x), shifted(r), shifted(torch.zeros_like(y))
+    npas.depthwise3x3(p, xo.data_ptr() + off, yo.data_ptr() + off, N, H, W, stride, None, ro.data_ptr() + off, npas.ACT_NONE)
+    torch.cuda.synchronize()
+    assert torch.equal(yo[off // 2:off // 2 + y.numel()], y.reshape(-1).view(torch.int16))
+    assert not yo[:off // 2].any() and not yo[off // 2 + y.numel():].any()
+
+
 # Inputs past the limits of the row-block kernel's 32-bit forms: 2 GiB and more (buffer range check), and thread counts that its
 # reciprocals do not divide (index times divisor 2^32 or more), four rows and one row a thread.
 @pytest.mark.parametrize("N,H,W,C,stride", [(65, 256, 256, 256, 1), (65, 257, 257, 256, 2), (2, 92801, 2, 8, 2), (2, 60000, 1, 8, 1),
@@ -414,8 +441,9 @@ def test_split_reduction(npas, torch, case):
         npas.set_switches(None)
 
 
-# The flat 1x1 kernel: a last block of 1..15 pixels, a last 16-filter tile of 4, 8 and 12 filters, channel counts that end inside a
-# 32-deep step and 8 channels only, one and several filter groups (with and without 16-byte output segments), stride 2.
+# The flat 1x1 kernel: a last block of 1..15 pixels, a last 16-filter tile of 8 and 12 filters, channel counts that end inside a
+# 32-deep step, one and several filter groups (with and without 16-byte output segments), stride 2.  (One pixel of a layer at 2x
+# takes the exact lists; the dense one, 8 channels, 4-filter tiles and waves of several blocks are in STREAM_FORMS.)
 STREAM_EDGES = [
     ("flat_c8_f4_one_pixel", 1, 1, 1, 8, 4, 1, 1, 1, 0, 4, 4, 2, dtypes.BF16, 0, False, True),
     ("flat_c24_f144_tail1", 3, 7, 83, 24, 144, 1, 1, 1, 0, 8, 8, 2, dtypes.BF16, 2, False, False),
@@ -428,7 +456,8 @@ STREAM_EDGES = [
 
 @pytest.mark.parametrize("case", STREAM_EDGES, ids=[c[0] for c in STREAM_EDGES])
 def test_flat_pointwise(npas, torch, case):
-    _run_edge_case(npas, torch, case)
+    lists = case[0] == "flat_c8_f4_one_pixel"
+    _run_edge_case(npas, torch, case, device_kernel="fc_gather_mfma_kernel" if lists else "pointwise_stream_kernel")
 
 
 # The same kernel's launch forms: a wave that walks two and three pixel blocks (in one run, in 16- and in 8-byte segments; with one, three
@@ -449,7 +478,7 @@ STREAM_FORMS = [
 
 @pytest.mark.parametrize("case", STREAM_FORMS, ids=[c[0] for c in STREAM_FORMS])
 def test_flat_pointwise_launch_forms(npas, torch, case):
-    _run_edge_case(npas, torch, case, expect_kernel="conv_slab_mfma")
+    _run_edge_case(npas, torch, case, device_kernel="pointwise_stream_kernel")
 
 
 @pytest.mark.parametrize("C,F,HW", [(8, 20, 9), (24, 144, 37), (144, 40, 33), (312, 96, 33)])
@@ -464,7 +493,7 @@ def test_flat_pointwise_infinite_input_in_the_last_channels(npas, torch, C, F, H
     xs, xe = dtypes.quantize(xe, dtypes.BF16)
     ref = oracle.round_to(oracle.conv2d_masked(xe, L.w_exact, L.mask, 1, 0, None, None, L.act), dtypes.BF16)
     p = pack_layer(npas, L, dtypes.BF16)
-    assert npas.conv2d_kernel_name(p, 2, HW, HW, 1, 0) == "conv_slab_mfma"
+    assert npas.device_kernel(p, 2, HW, HW, 1, 0) == "pointwise_stream_kernel"
     y = run_layer_gpu(npas, torch, L, p, to_dev(xs, torch), xe.shape, dtypes.BF16)
     assert rel_err(from_dev(y, dtypes.BF16).reshape(ref.shape), ref) <= TOL[dtypes.BF16]
 
@@ -503,14 +532,17 @@ def test_split_reduction_infinite_input_under_pruned_weights(npas, torch, C, F, 
     _infinite_input_under_pruned_weights(npas, torch, L, N, HW, HW, dtype, res, "conv_smallm_mfma")
 
 
-@pytest.mark.parametrize("C,F,N,HW,k,off", [(144, 40, 3, 29, 1, 8), (64, 128, 2, 21, 3, 2)], ids=["flat_8_bytes", "split_2_bytes"])
+@pytest.mark.parametrize("C,F,N,HW,k,off", [(144, 40, 3, 29, 1, 8), (64, 128, 2, 21, 3, 2), (144, 40, 3, 29, 1, 2), (24, 960, 3, 29, 1, 8),
+                                              (24, 960, 3, 29, 1, 2)],
+                         ids=["flat_8_bytes", "split_2_bytes", "flat_2_bytes", "flat_groups_8_bytes", "flat_groups_2_bytes"])
 def test_outputs_at_smaller_alignment(npas, torch, C, F, N, HW, k, off):
-    """An output that starts 8 (flat 1x1 kernel) or 2 bytes (split reduction) past an aligned address: narrower stores, same values."""
+    """An output that starts 8 or 2 bytes past an aligned address: narrower stores, same values."""
     w = prng.normal(31, 1, F * C * k * k, 0.1).reshape(F, C, k, k)
     ws, _ = dtypes.quantize(w, dtypes.BF16)
     m = masks.block_punched_mask(F, C, k, k, 8, 8, 2, 31)
     p = npas.pack_block_punched(ws, m, 8, 8, dtypes.BF16)
     xs, _ = dtypes.quantize(prng.normal(31, 2, N * HW * HW * C).reshape(N, HW, HW, C), dtypes.BF16)
+    assert npas.device_kernel(p, N, HW, HW, 1, k // 2) == ("pointwise_stream_kernel" if k == 1 else "conv_smallm_mfma_kernel")
     x, n = to_dev(xs, torch), N * HW * HW * F
     y0 = torch.zeros(n, dtype=torch.int16, device="cuda")
     y1 = torch.full((n + 16,), 0x7FC1, dtype=torch.int16, device="cuda")

@@ -179,6 +179,21 @@ def test_kernel_choice_follows_layer_and_launch_shape():
     assert name(p, 64, 56, 56, 1, 0) == "conv_slab_mfma"         # channels not a multiple of 64
 
 
+def test_device_kernel_tells_the_forms_of_the_slab_route_apart():
+    """1x1 layers on at most 320 channels, no multiple of 64, take the flat kernel in either list format; with padding, wider layers
+    and k x k layers the kernel of their format."""
+    name, kernel = npas.conv2d_kernel_name, npas.device_kernel
+    p = _bp_layer(24, 144, 1, 45, rate=4)
+    assert (name(p, 64, 56, 56, 1, 0), kernel(p, 64, 56, 56, 1, 0)) == ("conv_slab_mfma", "pointwise_stream_kernel")
+    assert kernel(p, 64, 56, 56, 1, 1) == "conv_slab_mfma_kernel"
+    p = _bp_layer(144, 64, 1, 45, rate=20)
+    assert kernel(p, 64, 56, 56, 1, 0) == "pointwise_stream_kernel" and kernel(p, 64, 56, 56, 1, 1) == "conv_gather_mfma_kernel"
+    p = _bp_layer(328, 64, 1, 45, rate=2)
+    assert kernel(p, 64, 56, 56, 1, 0) == "conv_slab_mfma_kernel"
+    p = _bp_layer(64, 64, 3, 41)
+    assert kernel(p, 8, 56, 56, 1, 1) == "conv_slab_mfma_kernel" and kernel(p, 1, 56, 56, 1, 1) == "conv_smallm_mfma_kernel"
+
+
 # ---- workspace placement of fused stacks (host logic: works without a GPU) -----------------------------------
 
 def _pw(seed, idx, C, F, act, src, res=-1):
