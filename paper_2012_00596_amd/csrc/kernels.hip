@@ -1297,11 +1297,11 @@ __device__ __forceinline__ void conv_smallm_mfma_kernel_body(SmallMArgs a)
     const Clamp cl = clamp_of(a.act);
     const float *sf = reinterpret_cast<const float *>(sums + (wave >> 2) * FI * 64 + lane) + row;
     uint16_t v16[FI];
+    float vs[FI];
 #pragma unroll
     for (int j = 0; j < FI; ++j) {
-        float v = sf[j * 256];
-        if (v != v) v = smallm_kept_sum<DT>(m, fb, tile8 + j, 4 * q + row);
-        v += add[j];
+        vs[j] = sf[j * 256];
+        float v = vs[j] + add[j];
         if (a.residual) v += from_storage<DT>(rs[j]);
         v16[j] = to_storage<DT>(clampf<HSW>(v, cl));
     }
@@ -1309,6 +1309,18 @@ __device__ __forceinline__ void conv_smallm_mfma_kernel_body(SmallMArgs a)
     if (FI == 4) *reinterpret_cast<uint2 *>(y16) = uint2{(uint32_t)v16[0] | (uint32_t)v16[1 % FI] << 16, (uint32_t)v16[2 % FI] | (uint32_t)v16[3 % FI] << 16};
     else if (FI == 2) *reinterpret_cast<uint32_t *>(y16) = (uint32_t)v16[0] | (uint32_t)v16[1 % FI] << 16;
     else *y16 = v16[0];
+    // (after the stores and in one copy: in front of them, per value, the check cost the batch-1 network 4 us of 268)
+    bool nan = false;
+#pragma unroll
+    for (int j = 0; j < FI; j += 2) nan |= __builtin_isunordered(vs[j], vs[(j + 1) % FI]);
+    if (__builtin_expect(!__any(nan), 1)) return;
+#pragma unroll 1
+    for (int j = 0; j < FI; ++j) {
+        if (sf[j * 256] == sf[j * 256]) continue;
+        float v = smallm_kept_sum<DT>(m, fb, tile8 + j, 4 * q + row) + (a.bias ? a.bias[f + j] : 0.f);
+        if (a.residual) v += from_storage<DT>(reinterpret_cast<const uint16_t *>(a.residual)[o + j]);
+        y16[j] = to_storage<DT>(clampf<HSW>(v, cl));
+    }
 }
 // The activation kind is compiled in: hard-swish behind a (wave-uniform) branch per value kept the compiler from
 // interleaving loads, MFMAs and epilogue arithmetic across values and cost the launches without it 15-50 %.
