@@ -263,8 +263,9 @@ __global__ __launch_bounds__(256) void depthwise3x3_kernel(const void *x, void *
 // 16 workgroups (a few row blocks) so that most rows two row blocks share come from its own L2, while the chip as a whole
 // works on one stretch of the tensors: with inputs beyond the Infinity Cache 64 x 56 x 56 x 144 36.4 us against 38.1 with one run per
 // XCD and 36.3 with none, 60 x 60 x 60 x 480 119.5 / 125.3 / 122.1, inside it 32 x 57 x 57 x 144 17.8 / 17.8 / 19.2.
-// 64 x 56 x 56 x 144, bf16: stride 1 31 -> 28 us (a copy of the same bytes: 23), stride 2 57 -> 13 us (the thread of four
-// rows had spilled); 32 x 57 x 57 x 144 with a bias 23 -> 18 us; 1 x 46 x 28 x 272 at stride 2 16.5 -> 2.9 us.
+// 64 x 56 x 56 x 144, bf16, launches over three sets of tensors in turn: stride 1 31 -> 28 us (a copy of the same bytes: 23), stride 2
+// 57 -> 13 us (the thread of four rows had spilled); 32 x 57 x 57 x 144 with a bias 23 -> 17.2 us (22.6 -> 16.8 on one set, warm);
+// 1 x 46 x 28 x 272 at stride 2 16.5 -> 2.9 us.
 struct DwArgs {
     const void *x;
     void *y;

@@ -42,8 +42,9 @@ namespace npas {
 // zero, tap weights read from LDS beside the activations), was bound by both: 27 16-byte LDS reads and 109 vector
 // instructions per 16 pixels x 32 slots, where there are now 10 reads and about 50 (the masks shared by two pixel blocks).  It is
 // now a mix: of 18 us the vector ALUs are busy 7.5, the LDS 6 and the matrix cores 3.6, on three waves per SIMD that
-// work in step.  64 x 56 x 56, 24 -> 144 (83 live) -> 24, bf16: 28.7 -> 18.2 us with biases, 25.2 -> 17.9 without, 41 -> 29
-// with hard-swish, stride 2 19.6 -> 13.0; 32 -> 192 -> 32 (all live) 70.6 -> 32.4; one image 10.7 -> 4.8.
+// work in step.  64 x 56 x 56, 24 -> 144 (83 live) -> 24, bf16, launches over three sets of tensors in turn: 28.7 -> 18.0 us with biases
+// (26.9 -> 16.3 on one set, warm), 25.2 -> 17.5 without, 41 -> 20.8 with hard-swish, stride 2 19.6 -> 12.8; 32 -> 192 -> 32 (all live)
+// 70.6 -> 33.1; one image 10.7 -> 4.8.
 
 // Pitches in LDS.  A 16-byte access is served eight lanes at a time, four neighbouring lanes of one quarter wave with four of
 // the next, whose 16 bytes lie one unit further: neighbouring output pixels have to be 2 or 6 units of 16 bytes apart

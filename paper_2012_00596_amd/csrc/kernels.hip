@@ -1173,7 +1173,8 @@ int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream)
 // that.  Stride and kernel size are free (every address is formed per lane).
 // A fragment load touches 16 lines where an image load touches 8 whole ones: the work is cut along the pixels first (16 a
 // workgroup, as 64 pixels x 16 filters the same layers spent their time in the address path of a quarter of the CUs), then as
-// few filters each as keeps the launch within one workgroup per CU.
+// few filters each as keeps the launch within one workgroup per CU: bf16, 14 x 14 x 256 3x3 at batch 1 11.0 -> 5.3 us, at batch 8 25.8 -> 9.7,
+// 7 x 7 x 512 at batch 16 34.6 -> 15.6, 2048 -> 512 at 7 x 7 9.2 -> 5.0; the 50-layer stack at batch 1 382 -> 275.
 // Past 256 workgroups of 16 pixels x 64 filters, PB = 2 pixel blocks share a workgroup's images: eight waves add up, eight finish.
 // An infinite input meets the zeros that stand for pruned weights; a sum that is NaN is formed again over the kept weights alone, as the
 // exact lists give it that some of these layers take on other pixel counts.
