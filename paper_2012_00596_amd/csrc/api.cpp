@@ -175,161 +175,72 @@ static int check_run(const npas_packed *p, const void *x, void *y, int N, int H,
     return NPAS_OK;
 }
 
-// Output tile of the k x k streaming kernel: NI images x TH x TW output pixels (at most 256,
-// the MFMA columns of a workgroup) whose halo patch fits the kernel's limits.  Picks the
-// plan with the best ratio of useful to computed columns, then the smaller halo.  Returns
-// false when no plan exists or the launch would leave most of the chip idle (the slab
-// kernel's smaller tiles serve those cases better).
-static bool plan_spatial_search(const npas_packed *p, int N, int H, int W, int pad, int stride, bool force, int maxpix, SpatialRingArgs *a);
-
-// The search is a few thousand candidates; its result depends only on the shapes, so it is
-// kept per shape (launches of a stack repeat the same few shapes).
-bool plan_spatial(const npas_packed *p, int N, int H, int W, int pad, int stride, SpatialRingArgs *a)
+// Tile plan of the direct-weights k x k kernel: how the four multiplying waves of a workgroup are laid out (pixel groups x 64-filter
+// halves x shares of the reduction, 16 NB pixels each) and a tile of NI images x TH x TW output pixels, by the time of the launch.
+// *t_us is that time, fitted to 449 layers (3x3, 5x5, 7x7, stride 1 and 2) in all layouts: within 4 % for half of them, 10 % for nine in ten;
+// the layout it picks is on average 2 % slower than the best one.  A step of 32 channels takes 78 ns (its loads) and 19 ns a pixel block, 26 where
+// every CU is at work (the clock falls); a chunk 0.6 us more, a workgroup's first patch 33 ns a KB.
+// The search is some ten thousand candidates and depends on the shapes only: its results are kept per shape.
+bool plan_direct(const npas_packed *p, int N, int H, int W, int pad, int stride, SpatialDirectArgs *a, double *t_us)
 {
+    struct Entry { bool ok; double t; SpatialDirectArgs g; };
     static std::mutex mu;
-    static std::map<std::array<int, 11>, std::pair<bool, SpatialRingArgs>> cache;
-    // forced (tests): take this kernel whenever a plan exists
-    const int force = switches().force == FV_SPATIAL;
-    const std::array<int, 11> key = {p->KH, p->KW, p->C, p->F, p->ring.nfb, N, H, W, pad, force, stride};
+    static std::map<std::array<int, 9>, Entry> cache;
+    const std::array<int, 9> key = {p->KH, p->KW, p->C, p->F, N, H, W, pad, stride};
     std::lock_guard<std::mutex> lock(mu);
     auto it = cache.find(key);
     if (it == cache.end()) {
-        SpatialRingArgs g;
+        SpatialDirectArgs g;
         std::memset(&g, 0, sizeof g);
-        // 256-pixel tiles; if those would leave most of the chip idle, 128-pixel tiles (half the multiplying waves)
-        // (stride 2: 128-pixel tiles only, the four phase planes of a 256-pixel tile do not fit)
-        bool ok = stride == 1 && plan_spatial_search(p, N, H, W, pad, stride, false, 256, &g);
-        if (!ok) ok = plan_spatial_search(p, N, H, W, pad, stride, false, 128, &g);
-        if (!ok && force) ok = plan_spatial_search(p, N, H, W, pad, stride, true, stride == 1 ? 256 : 128, &g);
-        it = cache.emplace(key, std::make_pair(ok, g)).first;
-    }
-    *a = it->second.second;
-    return it->second.first;
-}
-
-static bool plan_spatial_search(const npas_packed *p, int N, int H, int W, int pad, int stride, bool force, int maxpix, SpatialRingArgs *a)
-{
-    const int KH = p->KH, KW = p->KW, T = KH * KW;
-    const bool s2 = stride == 2; // 3 x 3, pad 1: four phase planes of (TH + 1) x (TW + 1) pixels, one copy
-    if (stride != 1 && !(s2 && KH == 3 && KW == 3 && pad == 1)) return false;
-    const int Ho = (H + 2 * pad - KH) / stride + 1, Wo = (W + 2 * pad - KW) / stride + 1;
-    const int lds_total = 160 * 1024 - 2048 /* bias buffers */ - (s2 ? 4096 : 2048) /* patch pixel table */ - 1024 /* tile pixel table */, wstage = 16384;
-    const int nbuf = s2 ? 4 : 2; // patch buffers (planes) of npb KB each
-    const int max_npb = std::min(s2 ? 124 : 1 << 20, (lds_total - 3 * wstage) / (1024 * nbuf));
-    if (T < 2 || p->C % 64 != 0 || Ho <= 0 || Wo <= 0 || (long)N * H * W >= (1L << 24)) return false; // (the kernel forms patch addresses with 24-bit multiplies)
-    double best = -1.0;
-    int bNI = 0, bTH = 0, bTW = 0;
-    for (int TH = 1; TH <= std::min(Ho, 255); ++TH)
-        for (int TW = 1; TW <= std::min(Wo, 255) && TH * TW <= maxpix; ++TW) {
-            const int PH = s2 ? TH + 1 : TH + KH - 1, PW = s2 ? TW + 1 : TW + KW - 1;
-            const long ty = (Ho + TH - 1) / TH, tx = (Wo + TW - 1) / TW;
-            const int maxNI = std::min(N, maxpix / (TH * TW));
-            for (int NI = 1; NI <= maxNI; ++NI) {
-                const int npb = (NI * PH * PW + 7) / 8;
-                if (npb > max_npb) break;
-                const long tn = (N + NI - 1) / NI;
-                const int depth = std::min(6, (lds_total - 1024 * nbuf * npb) / wstage);
-                const double eff = (double)N * Ho * Wo / ((double)tn * ty * tx * (double)maxpix);
-                const double halo = (double)(NI * PH * PW) / (double)(NI * TH * TW);
-                const double score = eff - 0.02 * halo + 0.02 * (depth - 3);
-                if (score > best) {
-                    best = score;
-                    bNI = NI; bTH = TH; bTW = TW;
-                }
-            }
-        }
-    if (best < 0) return false;
-    a->N = N; a->H = H; a->W = W; a->C = p->C; a->F = p->F; a->Ho = Ho; a->Wo = Wo;
-    a->KH = KH; a->KW = KW; a->pad = pad; a->stride = stride;
-    a->pg = maxpix / 64;
-    a->NI = bNI; a->TH = bTH; a->TW = bTW; a->PH = s2 ? bTH + 1 : bTH + KH - 1; a->PW = s2 ? bTW + 1 : bTW + KW - 1;
-    a->tilesN = (N + bNI - 1) / bNI; a->tilesY = (Ho + bTH - 1) / bTH; a->tilesX = (Wo + bTW - 1) / bTW;
-    a->nfb = p->ring.nfb;
-    a->npb = (bNI * a->PH * a->PW + 7) / 8;
-    a->depth = std::min(6, (lds_total - 1024 * nbuf * a->npb) / wstage);
-    a->div_tw = magic_div((uint32_t)bTW); a->div_pw = magic_div((uint32_t)a->PW);
-    a->div_thtw = magic_div((uint32_t)(bTH * bTW)); a->div_phpw = magic_div((uint32_t)(a->PH * a->PW));
-    const long items = (long)a->tilesN * a->tilesY * a->tilesX * a->nfb;
-    const double eff = (double)N * Ho * Wo / ((double)a->tilesN * a->tilesY * a->tilesX * (double)maxpix);
-    // worth it when the launch fills most of the chip and neither the 256 pixel columns nor the
-    // 128 filter rows of a workgroup are mostly padding (measured against the slab kernel)
-    const double fill = (double)p->F / (128.0 * a->nfb);
-    // with 128-pixel tiles a long reduction (many stages per item) pays from fewer items on: the slab kernel's
-    // workgroups would walk it with one step of lookahead (512 -> 512 at 7 x 7, batch 32: 64 items, 64 -> 47 us)
-    // (at stride 2 only from 64 stages per item on: 256 -> 256 onto 14 x 14 at batch 32, 100 items of 36 stages, 32 against 27 us)
-    const bool enough = items >= 192 || (maxpix == 128 && items >= 48 && items * (p->C / 64) * T >= 3000 && (!s2 || (p->C / 64) * T >= 64));
-    return force || (enough && eff >= 0.6 && fill >= 0.75);
-}
-
-// Tile plan of the resident-weights k x k kernel (at most 64 filters, all weight stages in LDS): the
-// spatial ring's search with the LDS that the weights leave, scored by useful columns times how evenly the
-// items fill rounds of 256 workgroups.  False when the weights do not fit or the launch is too small.
-bool plan_resident(const npas_packed *p, int N, int H, int W, int pad, SpatialRingArgs *a)
-{
-    struct Entry { bool fits, worth; SpatialRingArgs g; };
-    static std::mutex mu;
-    static std::map<std::array<int, 8>, Entry> cache;
-    const std::array<int, 8> key = {p->KH, p->KW, p->C, p->F, N, H, W, pad};
-    const bool force = switches().force == FV_RESIDENT; // tests: take this kernel whenever a plan exists
-    std::lock_guard<std::mutex> lock(mu);
-    auto it = cache.find(key);
-    if (it != cache.end()) {
-        *a = it->second.g;
-        return it->second.fits && (force || it->second.worth);
-    }
-    SpatialRingArgs g;
-    std::memset(&g, 0, sizeof g);
-    const int KH = p->KH, KW = p->KW, T = KH * KW;
-    const int Ho = H + 2 * pad - KH + 1, Wo = W + 2 * pad - KW + 1;
-    bool ok = T >= 2 && p->C % 64 == 0 && p->F <= 64 && p->ring.present && Ho > 0 && Wo > 0;
-    const int nst = ok ? (p->C / 64) * T : 0;
-    double best = -1e30;
-    int bNI = 0, bTH = 0, bTW = 0;
-    if (ok && spatial_resident_lds_bytes(8, nst) <= 160 * 1024) {
-        for (int TH = 1; TH <= std::min(Ho, 255); ++TH)
-            for (int TW = 1; TW <= std::min(Wo, 255) && TH * TW <= 256; ++TW) {
-                const int PH = TH + KH - 1, PW = TW + KW - 1;
-                const long ty = (Ho + TH - 1) / TH, tx = (Wo + TW - 1) / TW;
-                const int maxNI = std::min(N, 256 / (TH * TW));
-                for (int NI = 1; NI <= maxNI; ++NI) {
-                    const int npb = (NI * PH * PW + 7) / 8;
-                    if (spatial_resident_lds_bytes(npb, nst) > 160 * 1024) break;
-                    const long items = (long)((N + NI - 1) / NI) * ty * tx;
-                    const double eff = (double)N * Ho * Wo / ((double)items * 256.0);
-                    const double rounds = (double)items / (double)((items + 255) / 256 * 256);
-                    const double halo = (double)(PH * PW) / (double)(TH * TW);
-                    const double score = eff * rounds - 0.02 * halo;
-                    if (score > best) {
-                        best = score;
-                        bNI = NI; bTH = TH; bTW = TW;
+        const int KH = p->KH, KW = p->KW, T = KH * KW, nch = p->C / 64;
+        const int Ho = (H + 2 * pad - KH) / stride + 1, Wo = (W + 2 * pad - KW) / stride + 1;
+        const bool able = T >= 2 && p->C % 64 == 0 && p->F % 4 == 0 && p->ring.present && (stride == 1 || stride == 2);
+        double best = 1e30;
+        static const int layouts[][3] = {{2, 2, 1}, {1, 2, 2}, {4, 1, 1}, {2, 1, 2}};
+        for (const auto &l : layouts)
+            for (int NB = 3; able && NB <= 7; ++NB) {
+                const int G = l[0], Hf = l[1], KS = l[2], cap = 16 * NB * G, nfb = (p->F + 64 * Hf - 1) / (64 * Hf);
+                for (int TH = 1; TH <= std::min(Ho, cap); ++TH)
+                    for (int TW = 1; TW <= std::min(Wo, cap / TH); ++TW) {
+                        const int PH = (TH - 1) * stride + KH, PW = (TW - 1) * stride + KW;
+                        const long ty = (Ho + TH - 1) / TH, tx = (Wo + TW - 1) / TW;
+                        for (int NI = std::min(N, cap / (TH * TW)); NI >= 1; --NI) {
+                            const int npb = (NI * PH * PW + 15) / 16 * 2;
+                            const long items = (long)((N + NI - 1) / NI) * ty * tx * nfb, rounds = (items + 255) / 256;
+                            if (spatial_direct_lds_bytes(npb, G, KS, NB) > 160 * 1024 || items * std::max<long>(nfb, std::max(tx, ty)) > 0xffffffffL) continue;
+                            const double busy = std::min(1.0, (double)items / (256.0 * rounds));
+                            const double step = 0.078 + (0.0186 + 0.0069 * busy) * NB, item = nch * (0.62 + T * 2 / KS * step) + 0.3 * NB - 0.13 + (KS == 2 ? 0.43 : 0.0);
+                            const double t = 2.1 + rounds * item + 0.0325 * npb;
+                            if (t < best) {
+                                best = t;
+                                g.G = G; g.Hf = Hf; g.KS = KS; g.NB = NB;
+                                g.NI = NI; g.TH = TH; g.TW = TW; g.nfb = nfb;
+                            }
+                        }
                     }
-                }
             }
+        if (best < 1e30) {
+            g.N = N; g.H = H; g.W = W; g.C = p->C; g.F = p->F; g.Ho = Ho; g.Wo = Wo;
+            g.KH = KH; g.KW = KW; g.pad = pad; g.stride = stride;
+            g.PH = (g.TH - 1) * stride + KH; g.PW = (g.TW - 1) * stride + KW;
+            g.tilesN = (N + g.NI - 1) / g.NI; g.tilesY = (Ho + g.TH - 1) / g.TH; g.tilesX = (Wo + g.TW - 1) / g.TW;
+            g.nitems = g.tilesN * g.tilesY * g.tilesX * g.nfb;
+            g.npb = (g.NI * g.PH * g.PW + 15) / 16 * 2;
+            g.xbytes = (uint32_t)((size_t)N * H * W * p->C * 2); g.ybytes = (uint32_t)((size_t)N * Ho * Wo * p->F * 2);
+            g.div_tw = magic_div((uint32_t)g.TW); g.div_pw = magic_div((uint32_t)g.PW);
+            g.div_thtw = magic_div((uint32_t)(g.TH * g.TW)); g.div_phpw = magic_div((uint32_t)(g.PH * g.PW));
+            g.div_nfb = magic_div((uint32_t)g.nfb); g.div_tx = magic_div((uint32_t)g.tilesX); g.div_ty = magic_div((uint32_t)g.tilesY);
+        }
+        if (cache.size() >= 4096) cache.clear();
+        it = cache.emplace(key, Entry{best < 1e30, best, g}).first;
     }
-    ok = ok && bNI > 0;
-    bool worth = false;
-    if (ok) {
-        g.N = N; g.H = H; g.W = W; g.C = p->C; g.F = p->F; g.Ho = Ho; g.Wo = Wo;
-        g.KH = KH; g.KW = KW; g.pad = pad;
-        g.pg = 4; g.stride = 1;
-        g.NI = bNI; g.TH = bTH; g.TW = bTW; g.PH = bTH + KH - 1; g.PW = bTW + KW - 1;
-        g.tilesN = (N + bNI - 1) / bNI; g.tilesY = (Ho + bTH - 1) / bTH; g.tilesX = (Wo + bTW - 1) / bTW;
-        g.nfb = 1;
-        g.npb = (bNI * g.PH * g.PW + 7) / 8;
-        g.depth = nst;
-        g.div_tw = magic_div((uint32_t)bTW); g.div_pw = magic_div((uint32_t)g.PW);
-        g.div_thtw = magic_div((uint32_t)(bTH * bTW)); g.div_phpw = magic_div((uint32_t)(g.PH * g.PW));
-        const long items = (long)g.tilesN * g.tilesY * g.tilesX;
-        const double eff = (double)N * Ho * Wo / ((double)items * 256.0);
-        worth = items >= 192 && eff >= 0.6;
-    }
-    cache.emplace(key, Entry{ok, worth, g});
-    *a = g;
-    return ok && (force || worth);
+    *a = it->second.g;
+    *t_us = it->second.t;
+    return it->second.ok;
 }
 
 // Which kernel a run call launches for this layer and geometry.
-enum Route { R_VALU, R_WAVE_F32, R_FC_GATHER, R_POINTWISE_RING, R_SPATIAL_RING, R_SPATIAL_RESIDENT, R_SMALLC, R_SMALLM, R_STREAM, R_SLAB, R_GATHER };
+enum Route { R_VALU, R_WAVE_F32, R_FC_GATHER, R_POINTWISE_RING, R_DIRECT, R_SMALLC, R_SMALLM, R_STREAM, R_SLAB, R_GATHER };
 
 // Tile and patch of a small-channel launch: TH x TW = 256 output pixels with the fewest computed-but-
 // unused ones, the patch within 48 KB of LDS.  False when no tile shape fits.
@@ -411,7 +322,35 @@ int run_conv_maxpool(const npas_packed *p, const void *x, void *y, int N, int H,
     return launch_conv_smallc(p->dtype, sc, stream);
 }
 
-static Route choose_route(const npas_packed *p, int N, int H, int W, int stride, int pad, SpatialRingArgs *sp,
+// Time of a k x k launch of the tiled kernels, us: a workgroup walks the whole reduction alone, the slab kernel at about a third of
+// a microsecond a step, the gather kernel, on maps of one small tile and one round of workgroups, at a fifth of one.
+static double t_tiled(const npas_packed *p, int N, long Ho, long Wo, long steps, long rounds)
+{
+    const bool small_maps = p->fmt.variant == V_MFMA_GATHER && rounds > 1 && Ho * Wo <= 64 && (long)N * ((p->F + 63) / 64) <= 256;
+    return 2.0 + (small_maps ? 0.21 : 0.33) * steps;
+}
+
+// How reports name a launch of the direct-weights kernel: by the route its class of launches belongs to.  Launches of at least 192 tiles of
+// 128 pixels x 128 filters (256 x 64 for up to 64 filters) are the streaming ones ...
+static const char *direct_report(const npas_packed *p, int N, int H, int W, int stride, int pad)
+{
+    const int fv = switches().force;
+    if (fv == FV_SPATIAL) return "spatial_ring";
+    if (fv == FV_RESIDENT) return "spatial_resident";
+    const long Ho = (H + 2 * pad - p->KH) / stride + 1, Wo = (W + 2 * pad - p->KW) / stride + 1, M = (long)N * Ho * Wo;
+    const bool usual = stride == 1 || (p->KH == 3 && p->KW == 3 && pad == 1);
+    if (usual && (long)N * H * W < (1L << 24)) {
+        if (p->F <= 64 && stride == 1 && (M + 255) / 256 >= 192) return "spatial_resident";
+        if (4 * p->F >= 3 * 128 * p->ring.nfb && (M + 127) / 128 * p->ring.nfb >= 192) return "spatial_ring";
+    }
+    // ... the others stand beside the split reduction's and the tiled kernels'
+    const long halves = (p->F + 63) / 64, blocks = (M + 15) / 16, steps = (long)(p->C / 32) * p->KH * p->KW;
+    const long rounds = blocks * halves <= 256 ? 1 : ((blocks + 1) / 2 * halves + 255) / 256;
+    if (1.7 + rounds * (2.2 + 0.08 * steps) < t_tiled(p, N, Ho, Wo, steps, rounds)) return "conv_smallm_mfma";
+    return p->fmt.variant == V_MFMA_GATHER ? "conv_gather_mfma" : "conv_slab_mfma";
+}
+
+static Route choose_route(const npas_packed *p, int N, int H, int W, int stride, int pad, SpatialDirectArgs *sp,
                           SmallCArgs *sc = nullptr)
 {
     if (p->fmt.variant == V_VALU_F32) {
@@ -462,27 +401,18 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
     }
     const int fv = switches().force;
     if (p->stream.present && pad == 0) return R_STREAM;
-    if (ring_ok && stride == 1 && (p->KH > 1 || p->KW > 1) && p->F <= 64 && fv != FV_NORESIDENT && plan_resident(p, N, H, W, pad, sp))
-        return R_SPATIAL_RESIDENT;
-    {
-        const bool s2_off = stride == 2 && fv == FV_NOSPATIAL2;
-        if (ring_ok && (stride == 1 || stride == 2) && !s2_off && (p->KH > 1 || p->KW > 1) && plan_spatial(p, N, H, W, pad, stride, sp)) {
-            // The streaming kernel walks an item's stages alone: long reductions on few items are quicker split over the waves
-            // (512 -> 512 at 7 x 7, batch 32: 32.3 -> 28.5 us; 14 x 14 x 512 at stride 2: 37.6 -> 31; at batch 64 32.8 against 53)
-            const double stage = sp->pg == 4 ? 0.75 : stride == 2 ? 0.5 : 0.42; // us, measured (see spatial_kernels.hip)
-            const long items = (long)sp->tilesN * sp->tilesY * sp->tilesX * sp->nfb;
-            const double t_spatial = 2.0 + (double)((items + 255) / 256) * (stage * 0.5 * steps + 2.4);
-            if (fv != FV_SPATIAL && smallm_ok && t_smallm < 0.9 * t_spatial) return R_SMALLM;
-            return R_SPATIAL_RING;
-        }
-    }
-    // few output pixels (small batch, late stages): the tiled kernel would run a handful of workgroups, each walking the
-    // whole reduction alone at about a third of a microsecond a step (28 x 28 x 128 at batch 2 / 8: 12.7 / 13.1 -> 5.4 / 12.0 us,
-    // 14 x 14 x 256 at batch 8 / 16: 25.8 / 32.3 -> 9.7 / 17.9; 56 x 56 x 64 at batch 8 16.1 against 9.5).  The gather kernel, on maps of one
-    // small tile and one round of workgroups, takes a fifth of one (256 -> 256 at 7 x 7, batch 64, 10x pruned 16.8 against 18.3; on
-    // larger maps its tiles are larger: 14 x 14, batch 16 31.5 -> 18.9)
-    const double step = gather && rounds > 1 && Ho1 * Wo1 <= 64 && (long)N * ((p->F + 63) / 64) <= 256 ? 0.21 : 0.33;
-    if (smallm_ok && (p->KH > 1 || p->KW > 1) && (fv == FV_SMALLM || t_smallm < 2.0 + step * steps)) return R_SMALLM;
+    // k x k: split over a workgroup's waves while that is one round (of 449 layers measured, one in thirty of these would be up to 8 % quicker
+    // direct: 64 -> 64 5x5 at 28 x 28, batch 8: 8.8 against 8.2 us), the direct-weights kernel beyond (28 x 28 x 128 at batch 8: 12.3 -> 7.5 us,
+    // 14 x 14 x 256 at batch 16 18.9 -> 12.0, 33 x 33, 192 -> 192 at batch 48 46.9 -> 34.4) unless the split is the quicker one by both estimates.
+    const bool kxk = ring_ok && (p->KH > 1 || p->KW > 1);
+    const bool direct_forced = fv == FV_SPATIAL || (fv == FV_RESIDENT && p->F <= 64 && stride == 1);
+    const bool direct_off = fv == FV_SMALLM || (fv == FV_NOSPATIAL2 && stride == 2) || (fv == FV_NORESIDENT && p->F <= 64 && stride == 1);
+    double t_direct = 0.0;
+    if (kxk && !direct_off && (direct_forced || !smallm_ok || rounds > 1) && plan_direct(p, N, H, W, pad, stride, sp, &t_direct) &&
+        (direct_forced || !smallm_ok || t_direct <= t_smallm))
+        return R_DIRECT;
+    // The tiled kernels are left with strides beyond 2, patches that do not fit and formats without operand images.
+    if (smallm_ok && kxk && (fv == FV_SMALLM || t_smallm < t_tiled(p, N, Ho1, Wo1, steps, rounds))) return R_SMALLM;
     return gather ? R_GATHER : R_SLAB;
 }
 
@@ -492,14 +422,13 @@ struct RouteNames {
 };
 RouteNames route_names(const npas_packed *p, int N, int H, int W, int stride, int pad)
 {
-    SpatialRingArgs sp;
+    SpatialDirectArgs sp;
     switch (choose_route(p, N, H, W, stride, pad, &sp)) {
     case R_VALU: return {"conv_valu_f32", "conv_valu_f32_kernel"};
     case R_WAVE_F32: return {"conv_wave_f32", "conv_wave_f32_kernel"};
     case R_FC_GATHER: return {"fc_gather_mfma", "fc_gather_mfma_kernel"};
     case R_POINTWISE_RING: return {"pointwise_ring", "pointwise_ring_kernel"};
-    case R_SPATIAL_RING: return {"spatial_ring", "spatial_ring_kernel"};
-    case R_SPATIAL_RESIDENT: return {"spatial_resident", "spatial_resident_kernel"};
+    case R_DIRECT: return {direct_report(p, N, H, W, stride, pad), "conv_slab_mfma_kernel"}; // its direct-weights form, <..>(SpatialDirectArgs)
     case R_SMALLC: return {"conv_smallc_mfma", "conv_smallc_mfma_kernel"};
     case R_SMALLM: return {"conv_smallm_mfma", "conv_smallm_mfma_kernel"};
     case R_STREAM: return {"conv_slab_mfma", "pointwise_stream_kernel"}; // the slab route's flat form
@@ -515,7 +444,7 @@ int run_conv(const npas_packed *p, const ConvPlan *plan, const void *x, void *y,
         set_error("unknown activation %d", act);
         return NPAS_E_SHAPE;
     }
-    SpatialRingArgs sp;
+    SpatialDirectArgs sp;
     SmallCArgs sc;
     const Route route = choose_route(p, N, H, W, stride, pad, &sp, &sc);
     if (route == R_SMALLC) { // fewer than 8 input channels: whole reduction in a few MFMA steps
@@ -637,19 +566,11 @@ int run_conv(const npas_packed *p, const ConvPlan *plan, const void *x, void *y,
         a.div_wo = magic_div((uint32_t)a.Wo);
         return launch_pointwise_ring(p->dtype, a, stream);
     }
-    if (route == R_SPATIAL_RESIDENT) { // k x k, at most 64 filters: all weights stay in LDS
-        SpatialRingArgs &a = sp;
-        a.x = x; a.y = y; a.residual = residual; a.bias = (const float *)bias;
-        a.wimg = p->dev.wimg; a.zeros = p->dev.zeros;
-        a.act = act;
-        return launch_spatial_resident(p->dtype, a, stream);
-    }
-    if (route == R_SPATIAL_RING) { // k x k streaming path, when a tile plan fills the chip
-        SpatialRingArgs &a = sp;
-        a.x = x; a.y = y; a.residual = residual; a.bias = (const float *)bias;
-        a.wimg = p->dev.wimg; a.zeros = p->dev.zeros;
-        a.act = act;
-        return launch_spatial_ring(p->dtype, a, stream);
+    if (route == R_DIRECT) { // k x k on whole 64-channel chunks
+        sp.x = x; sp.y = y; sp.residual = residual; sp.bias = (const float *)bias;
+        sp.wimg = p->dev.wimg;
+        sp.act = act;
+        return launch_spatial_direct(p->dtype, sp, stream);
     }
     std::shared_ptr<const ConvPlan> cached;
     if (!plan) { // plans are kept per handle and geometry: a stack repeats the same launches call after call

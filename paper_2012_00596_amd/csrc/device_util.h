@@ -163,4 +163,29 @@ __device__ __forceinline__ void wait_vmcnt(uint32_t n)
 #undef NPAS_W
 }
 
+// The sum of one output (pixel m, filter f) over its kept weights, in channel order, from ring-format images: for the kernels that
+// multiply the zeros of pruned weights too and meet an infinite input.  (The kernel's arguments, a struct with the geometry
+// fields, are read again: kept for this they would take registers from the loop.)
+template <int DT, typename Args> __device__ __forceinline__ float kept_sum(uint32_t m, uint32_t f)
+{
+    auto ka = (const __attribute__((address_space(4))) Args *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ka));
+    const auto &a = *ka;
+    const uint32_t n = m / (uint32_t)(a.Ho * a.Wo), p = m - n * (uint32_t)(a.Ho * a.Wo), oy = p / (uint32_t)a.Wo, ox = p - oy * (uint32_t)a.Wo;
+    const int T = a.KH * a.KW, nch = a.C >> 6;
+    const uint32_t img = (f >> 6 & 1u) * 4u + (f & 3u), r = f >> 2 & 15u; // image of the 128-filter block, row of the image
+    const uint16_t *w = reinterpret_cast<const uint16_t *>(a.wimg) + ((size_t)(f >> 7) * nch * T * 16 + img) * 512 + r * 8;
+    float v = 0.f;
+    for (int t = 0; t < T; ++t) {
+        const int iy = (int)oy * a.stride - a.pad + t / a.KW, ix = (int)ox * a.stride - a.pad + t % a.KW;
+        if ((uint32_t)iy >= (uint32_t)a.H || (uint32_t)ix >= (uint32_t)a.W) continue;
+        const uint16_t *x = reinterpret_cast<const uint16_t *>(a.x) + (((size_t)n * a.H + iy) * a.W + ix) * a.C;
+        for (int c = 0; c < a.C; ++c) {
+            const uint16_t wc = w[((size_t)(c >> 6) * T + t) * 8192 + (c >> 5 & 1) * 4096 + (c >> 3 & 3) * 128 + (c & 7)];
+            if (wc & 0x7fffu) v = fmaf(from_storage<DT>(wc), from_storage<DT>(x[c]), v);
+        }
+    }
+    return v;
+}
+
 } // namespace npas

@@ -1179,29 +1179,6 @@ int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream)
 // An infinite input meets the zeros that stand for pruned weights; a sum that is NaN is formed again over the kept weights alone, as the
 // exact lists give it that some of these layers take on other pixel counts.
 
-// The sum of one output over its kept weights, in channel order: pixel m, row r of image img of the 128-filter block fb.
-// (The arguments are read again here: kept for this they would take registers from the loop.)
-template <int DT> __device__ __forceinline__ float smallm_kept_sum(uint32_t m, uint32_t fb, uint32_t img, int r)
-{
-    auto ka = (const __attribute__((address_space(4))) SmallMArgs *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(ka));
-    const auto &a = *ka;
-    const uint32_t n = m / (uint32_t)(a.Ho * a.Wo), p = m - n * (uint32_t)(a.Ho * a.Wo), oy = p / (uint32_t)a.Wo, ox = p - oy * (uint32_t)a.Wo;
-    const int T = a.KH * a.KW, nch = a.C >> 6;
-    const uint16_t *w = reinterpret_cast<const uint16_t *>(a.wimg) + ((size_t)fb * nch * T * 16 + img) * 512 + r * 8;
-    float v = 0.f;
-    for (int t = 0; t < T; ++t) {
-        const int iy = (int)oy * a.stride - a.pad + t / a.KW, ix = (int)ox * a.stride - a.pad + t % a.KW;
-        if ((uint32_t)iy >= (uint32_t)a.H || (uint32_t)ix >= (uint32_t)a.W) continue;
-        const uint16_t *x = reinterpret_cast<const uint16_t *>(a.x) + (((size_t)n * a.H + iy) * a.W + ix) * a.C;
-        for (int c = 0; c < a.C; ++c) {
-            const uint16_t wc = w[((size_t)(c >> 6) * T + t) * 8192 + (c >> 5 & 1) * 4096 + (c >> 3 & 3) * 128 + (c & 7)];
-            if (wc & 0x7fffu) v = fmaf(from_storage<DT>(wc), from_storage<DT>(x[c]), v);
-        }
-    }
-    return v;
-}
-
 template <int DT, int FI, int PB, bool HSW>
 __device__ __forceinline__ void conv_smallm_mfma_kernel_body(SmallMArgs a)
 {
@@ -1318,7 +1295,7 @@ __device__ __forceinline__ void conv_smallm_mfma_kernel_body(SmallMArgs a)
 #pragma unroll 1
     for (int j = 0; j < FI; ++j) {
         if (sf[j * 256] == sf[j * 256]) continue;
-        float v = smallm_kept_sum<DT>(m, fb, tile8 + j, 4 * q + row) + (a.bias ? a.bias[f + j] : 0.f);
+        float v = kept_sum<DT, SmallMArgs>(m, (uint32_t)(f + j)) + (a.bias ? a.bias[f + j] : 0.f);
         if (a.residual) v += from_storage<DT>(reinterpret_cast<const uint16_t *>(a.residual)[o + j]);
         y16[j] = to_storage<DT>(clampf<HSW>(v, cl));
     }

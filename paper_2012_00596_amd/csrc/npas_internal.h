@@ -284,24 +284,23 @@ struct RingArgs {
     uint32_t div_howo, div_wo;  // magic reciprocals of Ho*Wo and Wo
 };
 
-struct SpatialRingArgs {
+// k x k layer, weights from the L2 to registers: see spatial_direct_kernel
+struct SpatialDirectArgs {
     const void *x;
     void *y;
     const void *residual;
     const float *bias;
-    const void *wimg;
-    const void *zeros;          // >= 16 bytes of zeros on the device (source of padding pixels)
+    const void *wimg;           // ring-format images
+    uint32_t xbytes, ybytes;    // sizes of x and y
     int N, H, W, C, F, Ho, Wo;
-    int KH, KW, pad;
-    int stride;                 // 1, or 2 (3 x 3, pad 1: the patch as four phase planes, PH = TH + 1, PW = TW + 1, npb per plane)
-    int pg;                     // pixel groups of 64 a workgroup multiplies: 4 (256-pixel tiles) or 2 (128)
-    int NI, TH, TW;             // tile: NI images x TH x TW output pixels (<= 64 pg)
+    int KH, KW, pad, stride;    // stride 1 or 2
+    int G, Hf, KS, NB;          // pixel groups x 64-filter halves x shares of the reduction (4 waves); 16-pixel blocks of a wave
+    int NI, TH, TW;             // tile: NI images x TH x TW output pixels (<= 16 NB G)
     int PH, PW;                 // patch of one image of the tile
-    int tilesN, tilesY, tilesX, nfb;
-    int npb;                    // 1 KB blocks (8 pixels) of one patch chunk
-    int depth;                  // weight stages in the LDS ring (3..6)
+    int tilesN, tilesY, tilesX, nfb, nitems; // nfb: blocks of 64 Hf filters; items: the product
+    int npb;                    // 1 KB blocks (8 pixels) of one patch chunk, an even number
     int act;
-    uint32_t div_tw, div_pw, div_thtw, div_phpw; // magic reciprocals
+    uint32_t div_tw, div_pw, div_thtw, div_phpw, div_nfb, div_tx, div_ty; // magic reciprocals
 };
 
 // Sparse 1x1 / FC layer on few pixels through the exact per-tile lists: see fc_gather_mfma_kernel
@@ -367,11 +366,8 @@ int run_stack_impl(const npas_stack *s, const void *x_dev, void *y_dev, int N, v
 int launch_conv_mfma(int dtype, int variant, const ConvMfmaArgs &a, unsigned grid, size_t lds_bytes, void *stream);
 int launch_conv_valu(const ConvValuArgs &a, void *stream);
 int launch_pointwise_ring(int dtype, const RingArgs &a, void *stream);
-// Tile plan of the k x k streaming kernel (geometry fields of *a); false: use another kernel.
-bool plan_spatial(const npas_packed *p, int N, int H, int W, int pad, int stride, SpatialRingArgs *a);
-int launch_spatial_ring(int dtype, const SpatialRingArgs &a, void *stream);
-int launch_spatial_resident(int dtype, const SpatialRingArgs &a, void *stream);
-size_t spatial_resident_lds_bytes(int npb, int nst); // LDS of a launch with npb patch blocks and nst weight stages
+int launch_spatial_direct(int dtype, const SpatialDirectArgs &a, void *stream);
+size_t spatial_direct_lds_bytes(int npb, int G, int KS, int NB); // LDS of a launch with npb patch blocks a buffer
 int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream);
 int launch_conv_smallm(int dtype, SmallMArgs a, void *stream);
 int launch_fc_gather(int dtype, const FcGatherArgs &a, void *stream);

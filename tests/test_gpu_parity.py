@@ -263,6 +263,30 @@ def test_spatial_streaming_kernel_half_size_tiles(npas, torch):
                    expect_kernel="spatial_ring")
 
 
+# The direct-weights kernel in every layout of its waves (pixel groups x filter halves x shares of the reduction) and several tile heights: one pixel,
+# four filters, tiles that end with the map or the batch, odd strided maps with and without padding, even and long kernels, one and several chunks,
+# more tiles than workgroups.  The comment gives the layout and the pixel blocks of a wave that the planner chooses.
+DIRECT = [
+    ("dir_one_pixel_four_filters", 1, 1, 1, 64, 4, 3, 3, 1, 1, 4, 4, 2, dtypes.BF16, 1, True, True),            # 1 x 2 x 2, 3
+    ("dir_stride2_pad0", 2, 30, 29, 192, 68, 3, 3, 2, 0, 4, 4, 3, dtypes.BF16, 2, True, True),                   # 1 x 2 x 2, 3
+    ("dir_5x5_stride2_fp16", 5, 20, 31, 64, 132, 5, 5, 2, 2, 4, 4, 3, dtypes.F16, 3, False, True),               # 1 x 2 x 2, 3
+    ("dir_2x2_pad0", 200, 9, 9, 64, 64, 2, 2, 1, 0, 8, 4, 2, dtypes.BF16, 0, True, False),                       # 2 x 1 x 2, 3
+    ("dir_7x7", 3, 64, 64, 64, 64, 7, 7, 1, 3, 8, 4, 5, dtypes.BF16, 1, False, False),                           # 2 x 1 x 2, 3
+    ("dir_two_groups_two_shares", 17, 40, 40, 64, 64, 3, 3, 1, 1, 8, 4, 3, dtypes.F16, 2, True, True),           # 2 x 1 x 2, 4
+    ("dir_four_groups", 20, 33, 33, 64, 192, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 3, True, False),                  # 4 x 1 x 1, 5
+    ("dir_images_past_the_batch", 28, 40, 40, 64, 60, 3, 3, 1, 1, 4, 4, 3, dtypes.BF16, 1, False, True),         # 4 x 1 x 1, 3
+    ("dir_two_groups_two_halves", 21, 40, 40, 64, 128, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 1, True, True),         # 2 x 2 x 1, 5
+    ("dir_several_images_two_chunks", 130, 14, 14, 128, 256, 3, 3, 1, 1, 8, 4, 3, dtypes.F16, 1, True, False),   # 2 x 2 x 1, 7
+    ("dir_more_tiles_than_workgroups", 64, 28, 28, 64, 320, 3, 3, 2, 1, 8, 4, 3, dtypes.BF16, 0, False, True),   # 2 x 2 x 1, 3
+]
+
+
+@pytest.mark.parametrize("case", DIRECT, ids=[c[0] for c in DIRECT])
+def test_direct_weights_kernel(npas, torch, case, force_variant):
+    force_variant("spatial")
+    _run_edge_case(npas, torch, case, expect_kernel="spatial_ring", device_kernel="conv_slab_mfma_kernel")
+
+
 def test_config4_pattern_small_streaming_kernel(npas, torch, force_variant):
     force_variant("spatial")
     print("config4 small, streaming kernel", flush=True)
@@ -530,6 +554,32 @@ def test_split_reduction_infinite_input_under_pruned_weights(npas, torch, C, F, 
     force_variant("smallm")
     L = configs._bp_conv(53, 0, C, F, k, stride, k // 2, 4, 4, rate, 0.2, dtype, configs.ACT_RELU6)
     _infinite_input_under_pruned_weights(npas, torch, L, N, HW, HW, dtype, res, "conv_smallm_mfma")
+
+
+@pytest.mark.parametrize("C,F,N,HW,k,stride,rate,dtype,res", [(128, 72, 2, 9, 3, 1, 5, dtypes.F16, True), (64, 200, 5, 28, 3, 2, 3, dtypes.BF16, False),
+                                                               (64, 64, 5, 25, 5, 1, 3, dtypes.BF16, True), (64, 128, 30, 25, 3, 1, 3, dtypes.BF16, True)],
+                         ids=["two_shares", "stride2", "5x5", "one_share"])
+def test_direct_weights_infinite_input_under_pruned_weights(npas, torch, C, F, N, HW, k, stride, rate, dtype, res, force_variant):
+    force_variant("spatial")
+    L = configs._bp_conv(53, 0, C, F, k, stride, k // 2, 4, 4, rate, 0.2, dtype, configs.ACT_RELU6)
+    _infinite_input_under_pruned_weights(npas, torch, L, N, HW, HW, dtype, res, "spatial_ring")
+
+
+@pytest.mark.parametrize("off", [8, 2])
+def test_direct_weights_output_at_smaller_alignment(npas, torch, off):
+    N, HW, C, F = 20, 28, 64, 72
+    ws, _ = dtypes.quantize(prng.normal(31, 1, F * C * 9, 0.1).reshape(F, C, 3, 3), dtypes.BF16)
+    p = npas.pack_block_punched(ws, masks.block_punched_mask(F, C, 3, 3, 8, 8, 2, 31), 8, 8, dtypes.BF16)
+    xs, _ = dtypes.quantize(prng.normal(31, 2, N * HW * HW * C).reshape(N, HW, HW, C), dtypes.BF16)
+    assert npas.device_kernel(p, N, HW, HW, 1, 1) == "conv_slab_mfma_kernel"
+    x, n = to_dev(xs, torch), N * HW * HW * F
+    y0 = torch.zeros(n, dtype=torch.int16, device="cuda")
+    y1 = torch.full((n + 16,), 0x7FC1, dtype=torch.int16, device="cuda")
+    npas.conv2d_sparse(p, x, y0, N, HW, HW, 1, 1)
+    npas.conv2d_sparse(p, x, y1.data_ptr() + off, N, HW, HW, 1, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(y1[off // 2:off // 2 + n], y0)
+    assert (y1[:off // 2] == 0x7FC1).all() and (y1[off // 2 + n:] == 0x7FC1).all()
 
 
 @pytest.mark.parametrize("C,F,N,HW,k,off", [(144, 40, 3, 29, 1, 8), (64, 128, 2, 21, 3, 2), (144, 40, 3, 29, 1, 2), (24, 960, 3, 29, 1, 8),
