@@ -145,6 +145,15 @@ __device__ __forceinline__ void lds_dma16(const void *gptr, uint32_t lds_addr)
                  : "memory"); // m0 is reserved: the compiler keeps nothing in it across statements
 }
 
+// The same with 4 bytes a lane (256 bytes of LDS).
+__device__ __forceinline__ void lds_dma4(const void *gptr, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
+                 :
+                 : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(gptr)
+                 : "memory");
+}
+
 // "At most n vector-memory operations of this wave outstanding" for a wave-uniform n < 64
 // (the instruction takes an immediate).
 __device__ __forceinline__ void wait_vmcnt(uint32_t n)

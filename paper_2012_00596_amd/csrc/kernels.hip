@@ -1,4 +1,4 @@
-// gfx950 kernels of libnpas for one layer per launch (k x k layers on whole 64-channel chunks: spatial_kernels.hip; exact lists
+// gfx950 kernels of libnpas for one layer per launch (k x k layers on whole 64-channel chunks: spatial_direct_kernel.hip; exact lists
 // for sparse FC and small fp32 blocks: small_kernels.hip; fused pairs / blocks and the depthwise layer: block_kernels.hip).
 //
 // conv_gather_mfma: block-punched / block-based / pattern layers in bf16 or fp16.

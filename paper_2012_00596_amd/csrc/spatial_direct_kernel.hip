@@ -1,10 +1,27 @@
 // gfx950 kernel of libnpas for k x k layers with whole 64-channel chunks on many pixels: weights from the L2 straight into
-// registers, activations through LDS.
+// registers, activations through LDS (the direct-weights form of the slab kernel: an operand is 8 channels of one tap).
+//
+// What bounds such a layer is feeding the matrix cores.  With weights and activations both in LDS, 64 x 64 outputs a wave and a barrier
+// per 64-channel tap, a tap took 1.7-1.9 k cycles for 1024 of MFMAs: operand reads, their waits on both sides of every barrier, and
+// an epilogue and a prologue that nothing hides.  Here
+//   * a workgroup has four multiplying waves, one per SIMD, each up to 112 pixels x 64 filters: a step of 32 channels is 28 MFMAs
+//     against 7 operand reads from LDS (a quarter of an LDS byte per multiply of the 64 x 64 tiling with weights in LDS) and 4 KB of
+//     weight images, asked for three steps ahead in registers, from the L2;
+//   * a barrier per 64-channel chunk (18 steps of a 3x3 layer), whose patch four more waves fetch while the chunk before is multiplied;
+//   * every MFMA hides three other instructions, so all of a step's addresses, loads and bookkeeping are put between its MFMAs
+//     (scheduling groups); behind them they cost a third of the step (815 -> 520-660 cycles for 448 of MFMAs);
+//   * the four waves are 2 pixel groups x 2 filter halves, 4 x 1, or 1 x 2 and 2 x 1 with the reduction split over two waves that
+//     meet in LDS once per tile: with the tile's height free this fits one round of 256 workgroups to a map (14 x 14 x 256 at
+//     batch 128: one image x 128 filters each, 13 pixel blocks of 16 instead of 16).
+// bf16, alone: 14 x 14 x 256 at batch 128 31.9 -> 28.8 us, 28 x 28 x 128 34.5 -> 31.0, 7 x 7 x 512 36.6 -> 30.5, 56 x 56 x 64 40.1 -> 39.4; at stride 2
+// 256 -> 256 onto 14 x 14 43.6 -> 34.4; 256 -> 256 at 14 x 14, batch 16 18.9 -> 12.0; 192 -> 192 at 33 x 33, batch 48 46.9 -> 34.4.  At full batch the chip is then
+// power bound: 2.0 GHz under this kernel against 2.35 with a quarter of the CUs at work.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 
 #include "npas_internal.h"
 #include "device_util.h"
@@ -75,8 +92,10 @@ __device__ __forceinline__ void direct_store_tile(const SpatialDirectArgs &a, co
     const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(a.y, 0, (int)a.ybytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.residual), 0, (int)a.ybytes, 0x00020000);
     typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+    asm volatile("" : "+v"(b4.x), "+v"(b4.y), "+v"(b4.z), "+v"(b4.w)); // (keeps the variants' common sums from being formed ahead of the branch: 112 registers)
 #pragma unroll
     for (int s = S0; s < S1; ++s) {
+        __builtin_amdgcn_sched_barrier(0); // (a block's values and addresses one after the other: interleaved they spill beside the next item's weights)
         const uint4 p4 = *reinterpret_cast<const uint4 *>(ot + s * 64);
         const uint32_t o[4] = {add_sat(p4.x, fbyte), add_sat(p4.y, fbyte), add_sat(p4.z, fbyte), add_sat(p4.w, fbyte)};
         u32x2 r2[4];
@@ -106,6 +125,7 @@ template <int DT, int S0, int S1, int NB, bool RES>
 __device__ __forceinline__ void direct_mend_nan(const uint8_t *ot, const f32x4 (&acc)[4][NB], int fcol)
 {
     float any = 0.f;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = S0; s < S1; ++s)
 #pragma unroll
@@ -219,31 +239,59 @@ __global__ __launch_bounds__(kDirectThreads) void conv_slab_mfma_kernel(SpatialD
             const int f = pi.fb * (64 * H) + (lane & (16 * H - 1)) * 4;
             lds_dma16(a.bias + (f < a.F ? f : 0), lbase + lbias + buf * 1024u);
         };
+        // The next chunk's weights into the XCD's L2 ahead of their use (its workgroups share the lines; the loaded words land in
+        // 256 bytes that nobody reads): in a network the weights come from memory, and three steps of lookahead do not cover that
+        // (14 x 14 x 256 inside the 50-layer stack 31.1 -> 28.5 us, 7 x 7 x 512 32.3 -> 30.3; with the weights in a cache no difference).  Not with
+        // two chunks (28 x 28 x 128 in the stack and alone: no difference), nor at stride 2, where four times the patch is on its way (56 x
+        // 56 x 128 46.4 -> 47.5).  Returns the loads issued.
+        auto touch = [&](int cc) __attribute__((always_inline)) -> uint32_t {
+            uint32_t count = 0;
+            const uint32_t lines = (uint32_t)T * 128u, all = (uint32_t)((a.F + 127) >> 7) * lines; // of a 128-filter block, of all
+            const uint32_t per = all / ((nwg + 7u) >> 3) + 1u, l0 = (blockIdx.x >> 3) * per, l1 = min(l0 + per, all);
+            for (uint32_t k = l0 + (uint32_t)wl * 64u; k < l1; k += kDirectFetchWaves * 64u, ++count) {
+                const uint32_t l = min(k + (uint32_t)lane, l1 - 1u), fb = l / lines;
+                lds_dma4(reinterpret_cast<const uint8_t *>(a.wimg) + ((size_t)(fb * (uint32_t)nch + (uint32_t)cc) * lines + (l - fb * lines)) * 128u, lbase + lptab + 2u * npx * 4u);
+            }
+            return count;
+        };
         bias_block(it, 0);
         uint32_t pbuf = 0, par = 0;
-        for (;;) {
+        // One item (false: it was the last).  TOUCH: the workgroup's first item of a long reduction.
+        auto fetch_item = [&](auto touching) __attribute__((always_inline)) -> bool {
+            constexpr bool TOUCH = decltype(touching)::value;
+            uint32_t pending = 0; // loads behind the patch's: a wave's loads return in order, so these need not be awaited
             const bool more_items = c_item + nwg < nitems;
             if (more_items) it = direct_item(a, c_item + nwg);
             for (int cc = 0; cc < nch; ++cc) {
-                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); // this chunk's patch (and the tables) have landed
-                __builtin_amdgcn_s_barrier();                               // ... and the other buffer has been multiplied
+                if (TOUCH) wait_vmcnt(pending); // this chunk's patch (and the tables) have landed
+                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier(); // ... and the other buffer has been multiplied
                 asm volatile("" ::: "memory");
                 if (cc == 0 && more_items) { // (the other parity was last read in the epilogue before this item)
                     tables(it, par ^ 1u, wl, kDirectFetchWaves);
                     bias_block(it, par ^ 1u);
                 }
-                if (cc + 1 < nch) patch(cc + 1, pbuf ^ 1u, par, wl, kDirectFetchWaves);
-                else if (more_items) patch(0, pbuf ^ 1u, par ^ 1u, wl, kDirectFetchWaves);
+                if (cc + 1 < nch) {
+                    patch(cc + 1, pbuf ^ 1u, par, wl, kDirectFetchWaves);
+                    if (TOUCH) pending = touch(cc + 1);
+                } else {
+                    if (more_items) patch(0, pbuf ^ 1u, par ^ 1u, wl, kDirectFetchWaves);
+                    pending = 0;
+                }
                 pbuf ^= 1u;
             }
             if (KS == 2) { // the multiplying waves' exchange
                 __builtin_amdgcn_s_barrier();
                 __builtin_amdgcn_s_barrier();
             }
-            if (!more_items) break;
             c_item += nwg;
             par ^= 1u;
-        }
+            return more_items;
+        };
+        // (later items find the weights in the L2)
+        bool more = nch >= 4 && !sh ? fetch_item(std::true_type{}) : fetch_item(std::false_type{});
+        while (more) more = fetch_item(std::false_type{});
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         return;
     }
@@ -415,7 +463,7 @@ __global__ __launch_bounds__(kDirectThreads) void conv_slab_mfma_kernel(SpatialD
 
 size_t spatial_direct_lds_bytes(int npb, int G, int KS, int NB)
 {
-    return (size_t)2 * npb * 1024 + (KS == 2 ? kDirectExchange : 0) + 2048 + (size_t)npb * 64 + (size_t)G * NB * 192;
+    return (size_t)2 * npb * 1024 + (KS == 2 ? kDirectExchange : 0) + 2048 + (size_t)npb * 64 + 256 + (size_t)G * NB * 192;
 }
 
 template <int DT, int G, int H, int KS, int NB> static void launch_direct_inst(const SpatialDirectArgs &a, unsigned grid, size_t lds_bytes, hipStream_t st)
