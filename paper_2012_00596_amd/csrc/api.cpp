@@ -393,10 +393,10 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
     SmallCArgs sc_local;
     if (p->smallc.present && plan_smallc(p, N, H, W, stride, pad, sc ? sc : &sc_local)) return R_SMALLC;
     if (ring_ok && p->KH == 1 && p->KW == 1 && pad == 0) {
-        // ahead of the ring's smallest tiles while it is one round and the reduction is long (512 -> 128 at 28 x 28, batch 1 / 4:
-        // 6.5 / 6.6 -> 3.9 / 5.1 us, 1024 -> 256 at 14 x 14, batch 8: 10.0 -> 7.1), or the pixels are few; not with two rounds
-        // (2048 -> 512 at 7 x 7, batch 32: 18.6 against 18.0) nor with four steps to split (128 -> 512 at 28 x 28: 6.3 against 4.4)
-        if (smallm_ok && rounds == 1 && (p->C >= 256 || M1 <= 256)) return R_SMALLM;
+        // ahead of the ring's smallest tiles while it is one round (512 -> 128 at 28 x 28, batch 1: 6.5 -> 3.2 us, 128 -> 128 4.0 -> 2.7, 64 -> 256
+        // 3.9 -> 3.1; equal where the round is nearly full: 128 -> 512 at 28 x 28, batch 2: 4.5); not with two (64 -> 256 at 56 x 56: 6.2
+        // against 4.4, 512 -> 256 at 56 x 56 8.6 against 6.8)
+        if (smallm_ok && rounds == 1) return R_SMALLM;
         return R_POINTWISE_RING;
     }
     const int fv = switches().force;
@@ -430,7 +430,11 @@ RouteNames route_names(const npas_packed *p, int N, int H, int W, int stride, in
     case R_POINTWISE_RING: return {"pointwise_ring", "pointwise_ring_kernel"};
     case R_DIRECT: return {direct_report(p, N, H, W, stride, pad), "conv_slab_mfma_kernel"}; // its direct-weights form, <..>(SpatialDirectArgs)
     case R_SMALLC: return {"conv_smallc_mfma", "conv_smallc_mfma_kernel"};
-    case R_SMALLM: return {"conv_smallm_mfma", "conv_smallm_mfma_kernel"};
+    case R_SMALLM: {
+        // (1x1 layers of few channels on more than 256 pixels belong to the streaming route whichever of its kernels they take)
+        const bool streaming = p->KH == 1 && p->KW == 1 && pad == 0 && p->C < 256 && (long)N * ((H - 1) / stride + 1) * ((W - 1) / stride + 1) > 256;
+        return {streaming ? "pointwise_ring" : "conv_smallm_mfma", "conv_smallm_mfma_kernel"};
+    }
     case R_STREAM: return {"conv_slab_mfma", "pointwise_stream_kernel"}; // the slab route's flat form
     case R_SLAB: return {"conv_slab_mfma", "conv_slab_mfma_kernel"};
     default: return {"conv_gather_mfma", "conv_gather_mfma_kernel"};
@@ -456,7 +460,6 @@ int run_conv(const npas_packed *p, const ConvPlan *plan, const void *x, void *y,
     if (route == R_SMALLM) {
         SmallMArgs a;
         a.x = x; a.y = y; a.residual = residual; a.bias = (const float *)bias; a.wimg = p->dev.wimg;
-        a.zeros = p->dev.zeros;
         a.N = N; a.H = H; a.W = W; a.C = p->C; a.F = p->F;
         a.Ho = (H + 2 * pad - p->KH) / stride + 1; a.Wo = (W + 2 * pad - p->KW) / stride + 1;
         a.KH = p->KH; a.KW = p->KW; a.stride = stride; a.pad = pad; a.act = act;

@@ -1165,74 +1165,111 @@ int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream)
 // conv_smallm_mfma: layers (C a multiple of 64, ring-format weights) on few output pixels: batch 1, the late stages of a
 // network.  The tiled kernels then run a handful of workgroups that each walk the whole reduction (C*KH*KW / 32 MFMA
 // steps) alone, one load latency after the other.  Here a workgroup owns 16 output pixels x FI weight images (16 filters
-// each; FI = 1, 2 or 4, four make 64 consecutive filters) and its sixteen waves split the reduction: a wave takes a
+// each; FI = 1, 2 or 4, four make 64 consecutive filters) and its eight waves split the reduction: a wave takes a
 // contiguous run of steps, fetches each step's images (1 KB, coalesced) and activation fragment (lane = pixel n16, 8
-// channels = 16 bytes at the tap's input pixel; padding reads a block of zeros) straight from memory, NB steps in
-// flight, and accumulates FI MFMA tiles.  The sixteen partial sums meet in LDS, are added up in a fixed order by FI waves
-// and exchanged once more so that a lane writes FI consecutive filters of a pixel.  Bias and residual are asked for before
-// that.  Stride and kernel size are free (every address is formed per lane).
+// channels = 16 bytes at the tap's input pixel; padding lies past the buffer descriptor's range) straight from memory, NB steps in
+// flight, and accumulates FI MFMA tiles.  The eight partial sums meet in LDS and are added up in wave order, FI consecutive filters
+// of a pixel a lane.  Bias and residual are asked for before that.  Stride and kernel size are free (every address is formed per lane).
+// What bounds such a launch is a chain: launch, addresses, one load latency, two barriers' worth of skew.  Its addresses are instructions of
+// every wave of the workgroup, so there are few of them (the steps are linear in the images and, for 1x1, in the pixels; a tap moves on from
+// the one before; the tile comes from a reciprocal) and eight waves instead of sixteen, whose prologues alone took 1700 of 6000 cycles; the
+// sums need one barrier: 56 x 56, 256 -> 64 at batch 1 4.1 -> 3.2 us, 14 x 14 x 256 3x3 5.3 -> 4.9, the 50-layer stack 267 -> 250.  Four waves 263; two
+// workgroups a CU (half the filters each) 259, half the CUs (twice the filters) 262.
 // A fragment load touches 16 lines where an image load touches 8 whole ones: the work is cut along the pixels first (16 a
-// workgroup, as 64 pixels x 16 filters the same layers spent their time in the address path of a quarter of the CUs), then as
-// few filters each as keeps the launch within one workgroup per CU: bf16, 14 x 14 x 256 3x3 at batch 1 11.0 -> 5.3 us, at batch 8 25.8 -> 9.7,
-// 7 x 7 x 512 at batch 16 34.6 -> 15.6, 2048 -> 512 at 7 x 7 9.2 -> 5.0; the 50-layer stack at batch 1 382 -> 275.
-// Past 256 workgroups of 16 pixels x 64 filters, PB = 2 pixel blocks share a workgroup's images: eight waves add up, eight finish.
+// workgroup), then as few filters each as keeps the launch within one workgroup per CU.
+// Past 256 workgroups of 16 pixels x 64 filters, PB = 2 pixel blocks share a workgroup's images.
 // An infinite input meets the zeros that stand for pruned weights; a sum that is NaN is formed again over the kept weights alone, as the
 // exact lists give it that some of these layers take on other pixel counts.
 
-template <int DT, int FI, int PB, bool HSW>
-__device__ __forceinline__ void conv_smallm_mfma_kernel_body(SmallMArgs a)
+// ONE: 1x1 without padding (steps are linear in both operands and no tap lies outside).
+constexpr int kSmallMWaves = 8;
+template <int DT, int FI, int PB, bool ONE>
+__global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(SmallMArgs a)
 {
+    constexpr int NW = kSmallMWaves;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n16 = lane & 15, q = lane >> 4;
     // an XCD's workgroups are neighbours: the pixel tiles of one filter tile find its weights in their L2
     const uint32_t id = xcd_remap(blockIdx.x, gridDim.x);
-    const uint32_t ft = id / (uint32_t)a.nptiles, ptile = id - ft * (uint32_t)a.nptiles;
+    const uint32_t ft = a.div_np ? fastdiv(id, a.div_np) : id / (uint32_t)a.nptiles, ptile = id - ft * (uint32_t)a.nptiles;
     const uint32_t img = ft * FI, fb = img >> 3, tile8 = img & 7u; // first image: 128-filter block, image in it
-    const int T = a.KH * a.KW, nch = a.C >> 6, S = nch * T * 2;
-    const uint8_t *wb = reinterpret_cast<const uint8_t *>(a.wimg) + (size_t)fb * nch * T * 16384u + tile8 * 1024u + (uint32_t)lane * 16u;
-    const uint8_t *xb = reinterpret_cast<const uint8_t *>(a.x), *zb = reinterpret_cast<const uint8_t *>(a.zeros);
+    const uint32_t S = (uint32_t)a.S;                              // 32-deep steps: (chunk * KH * KW + tap) * 2 + half
+    const uint32_t st0 = (uint32_t)wave * S / NW, st1 = (uint32_t)(wave + 1) * S / NW; // this wave's
+    const uint8_t *wb = reinterpret_cast<const uint8_t *>(a.wimg) + ((size_t)fb * S + st0) * 8192u + tile8 * 1024u;
+    const uint32_t lane16 = (uint32_t)lane * 16u;
+    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, (int)a.xbytes, 0x00020000);
 
-    int iy0[PB], ix0[PB]; // input coordinates of tap (0, 0) of the lane's pixels
-    uint32_t pix0[PB];    // byte offset of 8 channels there (modulo 2^32 where it lies outside; x is below 4 GiB)
+    uint32_t pix0[PB];    // byte of the lane's 8 channels in step 0, at tap (0, 0) (modulo 2^32 where it lies outside)
+    int iy0[PB], ix0[PB]; // input coordinates of that tap
 #pragma unroll
     for (int s = 0; s < PB; ++s) {
         const uint32_t mc = min((ptile * PB + s) * 16u + (uint32_t)n16, (uint32_t)a.M - 1u); // (past the last pixel: that one again, not stored)
-        const uint32_t pn = fastdiv(mc, a.div_howo), pr = mc - pn * (uint32_t)(a.Ho * a.Wo);
-        const uint32_t oy = fastdiv(pr, a.div_wo), ox = pr - oy * (uint32_t)a.Wo;
-        iy0[s] = (int)oy * a.stride - a.pad;
-        ix0[s] = (int)ox * a.stride - a.pad;
-        pix0[s] = ((pn * (uint32_t)a.H + (uint32_t)iy0[s]) * (uint32_t)a.W + (uint32_t)ix0[s]) * (uint32_t)a.C * 2u + 16u * (uint32_t)q;
+        uint32_t in = mc;
+        if (!ONE || a.stride != 1) {
+            const uint32_t pn = fastdiv(mc, a.div_howo), pr = mc - pn * (uint32_t)(a.Ho * a.Wo);
+            const uint32_t oy = fastdiv(pr, a.div_wo), ox = pr - oy * (uint32_t)a.Wo;
+            iy0[s] = (int)(oy * (uint32_t)a.stride) - a.pad;
+            ix0[s] = (int)(ox * (uint32_t)a.stride) - a.pad;
+            in = (pn * (uint32_t)a.H + (uint32_t)iy0[s]) * (uint32_t)a.W + (uint32_t)ix0[s];
+        }
+        pix0[s] = in * (uint32_t)a.C * 2u + 16u * (uint32_t)q;
     }
     f32x4 acc[PB][FI];
 #pragma unroll
     for (int s = 0; s < PB; ++s)
 #pragma unroll
         for (int j = 0; j < FI; ++j) acc[s][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int st0 = wave * S / 16, st1 = (wave + 1) * S / 16; // this wave's steps
-    constexpr int NB = PB == 2 ? 3 : FI == 1 ? 9 : FI == 2 ? 6 : 4; // steps in flight
-    for (int sb = st0; sb < st1; sb += NB) {
+    // tap of the step at hand (wave-uniform, moved on from step to step) and its byte offset from tap (0, 0) of channel 0
+    uint32_t kh = 0, kw = 0, c0 = 0, toff = 0;
+    if (!ONE) {
+        const uint32_t T = (uint32_t)(a.KH * a.KW), ct = st0 >> 1, cc = fastdiv(ct * 2u, a.div_T2), tap = ct - cc * T;
+        kh = fastdiv(tap, a.div_kw);
+        kw = tap - kh * (uint32_t)a.KW;
+        c0 = cc * 128u;
+        toff = (kh * (uint32_t)a.W + kw) * (uint32_t)a.C * 2u + c0;
+    }
+    constexpr int NB = PB == 2 ? 6 : FI == 4 ? 8 : 9; // steps in flight
+    uint32_t off[PB];
+    for (uint32_t sb = st0; sb < st1; sb += NB, wb += NB * 8192u) {
         uint4 wf[NB][FI], xf[NB][PB];
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
-            const int st = sb + u;
+            const uint32_t st = sb + (uint32_t)u;
             if (st < st1) { // wave-uniform
-                // step st = (chunk * T + tap) * 2 + half
-                const uint32_t ct = (uint32_t)st >> 1, hs = (uint32_t)st & 1u;
-                const uint32_t cc = fastdiv(ct * 2u, a.div_T2), tap = ct - cc * (uint32_t)T;
-                const uint32_t kh = fastdiv(tap, a.div_kw), kw = tap - kh * (uint32_t)a.KW;
-                const uint32_t toff = ((kh * (uint32_t)a.W + kw) * (uint32_t)a.C + cc * 64u + hs * 32u) * 2u;
+                typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 #pragma unroll
                 for (int s = 0; s < PB; ++s) {
-                    const bool ok = (uint32_t)(iy0[s] + (int)kh) < (uint32_t)a.H && (uint32_t)(ix0[s] + (int)kw) < (uint32_t)a.W;
-                    xf[u][s] = *reinterpret_cast<const uint4 *>(ok ? xb + (uint32_t)(pix0[s] + toff) : zb);
+                    uint32_t o;
+                    if (ONE) o = pix0[s] + st * 64u;
+                    else {
+                        if (u == 0 || !(st & 1u)) { // a tap begins: outside the map nothing is loaded (past the descriptor's range: zeros)
+                            const bool ok = (uint32_t)(iy0[s] + (int)kh) < (uint32_t)a.H && (uint32_t)(ix0[s] + (int)kw) < (uint32_t)a.W;
+                            off[s] = ok ? pix0[s] + toff : 0xffffffffu;
+                        }
+                        o = off[s] | (st & 1u) * 64u; // (chunks are 128 bytes)
+                    }
+                    xf[u][s] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(xr, (int)o, 0, 0));
                 }
 #pragma unroll
-                for (int j = 0; j < FI; ++j) wf[u][j] = *reinterpret_cast<const uint4 *>(wb + (size_t)ct * 16384u + hs * 8192u + j * 1024u);
+                for (int j = 0; j < FI; ++j) wf[u][j] = *reinterpret_cast<const uint4 *>(wb + (size_t)u * 8192u + (lane16 + (uint32_t)j * 1024u));
+                if (!ONE && (st & 1u)) {
+                    ++kw;
+                    toff += (uint32_t)a.C * 2u;
+                    if (kw == (uint32_t)a.KW) {
+                        kw = 0;
+                        ++kh;
+                        toff += (uint32_t)(a.W - a.KW) * (uint32_t)a.C * 2u;
+                        if (kh == (uint32_t)a.KH) {
+                            kh = 0;
+                            toff = c0 += 128u;
+                        }
+                    }
+                }
             }
         }
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
-            if (sb + u < st1) {
+            if (sb + (uint32_t)u < st1) {
 #pragma unroll
                 for (int s = 0; s < PB; ++s)
 #pragma unroll
@@ -1254,34 +1291,38 @@ __device__ __forceinline__ void conv_smallm_mfma_kernel_body(SmallMArgs a)
         add[j] = out && a.bias ? a.bias[f + j] : 0.f;
         rs[j] = out && a.residual ? reinterpret_cast<const uint16_t *>(a.residual)[o + j] : (uint16_t)0;
     }
-    // ---- the sixteen partial sums meet in LDS: [wave][pixel block, image][lane] ---------------------
+    // ---- the partial sums meet in LDS: [wave][pixel block, image][row of the quarter][lane], added in wave order -----------
     constexpr int NF = PB * FI;
-    f32x4 *red = reinterpret_cast<f32x4 *>(lds);
+    float *red = reinterpret_cast<float *>(lds);
 #pragma unroll
-    for (int k = 0; k < NF; ++k) red[(wave * NF + k) * 64 + lane] = acc[k / FI][k % FI];
-    __syncthreads();
-    f32x4 *sums = red + 16 * NF * 64; // [pixel block, image][lane]
-    if (wave < NF) {
-        f32x4 sum = red[wave * 64 + lane];
+    for (int k = 0; k < NF; ++k)
 #pragma unroll
-        for (int w = 1; w < 16; ++w) {
-            const f32x4 t = red[(w * NF + wave) * 64 + lane];
-            sum[0] += t[0]; sum[1] += t[1]; sum[2] += t[2]; sum[3] += t[3];
-        }
-        sums[wave * 64 + lane] = sum;
-    }
+        for (int i = 0; i < 4; ++i) red[((wave * NF + k) * 4 + i) * 64 + lane] = acc[k / FI][k % FI][i];
     __syncthreads();
     if (!out) return;
-    const Clamp cl = clamp_of(a.act);
-    const float *sf = reinterpret_cast<const float *>(sums + (wave >> 2) * FI * 64 + lane) + row;
-    uint16_t v16[FI];
+    const float *rf = red + ((wave >> 2) * FI * 4 + row) * 64 + lane;
     float vs[FI];
 #pragma unroll
     for (int j = 0; j < FI; ++j) {
-        vs[j] = sf[j * 256];
-        float v = vs[j] + add[j];
-        if (a.residual) v += from_storage<DT>(rs[j]);
-        v16[j] = to_storage<DT>(clampf<HSW>(v, cl));
+        float sum = rf[j * 256];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += rf[(w * NF + j) * 256];
+        vs[j] = sum;
+    }
+    const Clamp cl = clamp_of(a.act);
+    uint16_t v16[FI];
+    float v[FI];
+#pragma unroll
+    for (int j = 0; j < FI; ++j) {
+        v[j] = vs[j] + add[j];
+        if (a.residual) v[j] += from_storage<DT>(rs[j]);
+    }
+    if (cl.hs) {
+#pragma unroll
+        for (int j = 0; j < FI; ++j) v16[j] = to_storage<DT>(clampf<true>(v[j], cl));
+    } else {
+#pragma unroll
+        for (int j = 0; j < FI; ++j) v16[j] = to_storage<DT>(clampf<false>(v[j], cl));
     }
     uint16_t *y16 = reinterpret_cast<uint16_t *>(a.y) + o;
     if (FI == 4) *reinterpret_cast<uint2 *>(y16) = uint2{(uint32_t)v16[0] | (uint32_t)v16[1 % FI] << 16, (uint32_t)v16[2 % FI] | (uint32_t)v16[3 % FI] << 16};
@@ -1294,19 +1335,13 @@ __device__ __forceinline__ void conv_smallm_mfma_kernel_body(SmallMArgs a)
     if (__builtin_expect(!__any(nan), 1)) return;
 #pragma unroll 1
     for (int j = 0; j < FI; ++j) {
-        if (sf[j * 256] == sf[j * 256]) continue;
-        float v = kept_sum<DT, SmallMArgs>(m, (uint32_t)(f + j)) + (a.bias ? a.bias[f + j] : 0.f);
-        if (a.residual) v += from_storage<DT>(reinterpret_cast<const uint16_t *>(a.residual)[o + j]);
-        y16[j] = to_storage<DT>(clampf<HSW>(v, cl));
+        float sum = rf[j * 256];
+        for (int w = 1; w < NW; ++w) sum += rf[(w * NF + j) * 256];
+        if (sum == sum) continue;
+        float r = kept_sum<DT, SmallMArgs>(m, (uint32_t)(f + j)) + (a.bias ? a.bias[f + j] : 0.f);
+        if (a.residual) r += from_storage<DT>(reinterpret_cast<const uint16_t *>(a.residual)[o + j]);
+        y16[j] = to_storage<DT>(clampf(r, cl));
     }
-}
-// The activation kind is compiled in: hard-swish behind a (wave-uniform) branch per value kept the compiler from
-// interleaving loads, MFMAs and epilogue arithmetic across values and cost the launches without it 15-50 %.
-template <int DT, int FI, int PB>
-__global__ __launch_bounds__(1024) void conv_smallm_mfma_kernel(SmallMArgs a)
-{
-    if (a.act == NPAS_ACT_HARDSWISH) conv_smallm_mfma_kernel_body<DT, FI, PB, true>(a);
-    else conv_smallm_mfma_kernel_body<DT, FI, PB, false>(a);
 }
 
 int launch_conv_smallm(int dtype, SmallMArgs a, void *stream)
@@ -1327,24 +1362,32 @@ int launch_conv_smallm(int dtype, SmallMArgs a, void *stream)
         set_error("conv_smallm_mfma needs a 16-bit storage type");
         return NPAS_E_DTYPE;
     }
-    static std::once_flag once[2][4];
-    auto go = [&](auto dtc, auto fic, auto pbc) {
+    a.S = a.C / 32 * a.KH * a.KW;
+    a.xbytes = (uint32_t)((size_t)a.N * a.H * a.W * a.C * 2);
+    a.div_np = a.nptiles > 1 && grid * a.nptiles <= 0xffffffffL ? (uint32_t)(((1ull << 32) + a.nptiles - 1) / a.nptiles) : 0u; // (0: by division)
+    static std::once_flag once[2][4][2];
+    auto go = [&](auto dtc, auto fic, auto pbc, auto onec) {
         constexpr int DT = decltype(dtc)::value, FI = decltype(fic)::value, PB = decltype(pbc)::value;
-        const int lds_bytes = 17 * FI * PB * 64 * 16;
-        auto kern = conv_smallm_mfma_kernel<DT, FI, PB>;
-        allow_lds_once(once[DT == NPAS_F16][PB == 2 ? 3 : FI >> 1], kern, lds_bytes);
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1024), lds_bytes, st, a);
+        constexpr bool ONE = decltype(onec)::value;
+        const int lds_bytes = kSmallMWaves * FI * PB * 1024;
+        auto kern = conv_smallm_mfma_kernel<DT, FI, PB, ONE>;
+        allow_lds_once(once[DT == NPAS_F16][PB == 2 ? 3 : FI >> 1][ONE], kern, lds_bytes);
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kSmallMWaves * 64), lds_bytes, st, a);
+    };
+    using std::integral_constant;
+    auto shape = [&](auto dtc, auto fic, auto pbc) {
+        if (a.KH == 1 && a.KW == 1 && a.pad == 0) go(dtc, fic, pbc, std::true_type{});
+        else go(dtc, fic, pbc, std::false_type{});
     };
     auto pick = [&](auto dtc) {
-        using std::integral_constant;
-        integral_constant<int, 1> one;
-        if (pb == 2) go(dtc, integral_constant<int, 4>{}, integral_constant<int, 2>{});
-        else if (fi == 1) go(dtc, one, one);
-        else if (fi == 2) go(dtc, integral_constant<int, 2>{}, one);
-        else go(dtc, integral_constant<int, 4>{}, one);
+        integral_constant<int, 1> c1;
+        if (pb == 2) shape(dtc, integral_constant<int, 4>{}, integral_constant<int, 2>{});
+        else if (fi == 1) shape(dtc, c1, c1);
+        else if (fi == 2) shape(dtc, integral_constant<int, 2>{}, c1);
+        else shape(dtc, integral_constant<int, 4>{}, c1);
     };
-    if (dtype == NPAS_BF16) pick(std::integral_constant<int, NPAS_BF16>{});
-    else pick(std::integral_constant<int, NPAS_F16>{});
+    if (dtype == NPAS_BF16) pick(integral_constant<int, NPAS_BF16>{});
+    else pick(integral_constant<int, NPAS_F16>{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         set_error("conv_smallm_mfma launch failed: %s", hipGetErrorString(e));

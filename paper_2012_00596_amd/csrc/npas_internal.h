@@ -258,11 +258,12 @@ struct SmallMArgs {
     const void *residual;
     const float *bias;
     const void *wimg;               // ring-format images
-    const void *zeros;              // >= 16 bytes of zeros on the device (source of padding pixels)
     int N, H, W, C, F, Ho, Wo, KH, KW, stride, pad, act;
     int M;                          // output pixels N*Ho*Wo
-    int nptiles;                    // 16-pixel tiles (filled at the launch)
     uint32_t div_howo, div_wo, div_kw, div_T2; // fastdiv magics (Ho*Wo, Wo, KW, 2*KH*KW)
+    // filled at the launch: 16 PB-pixel tiles and their magic (0: divide), 32-deep steps of the reduction, bytes of x
+    int nptiles, S;
+    uint32_t div_np, xbytes;
 };
 
 struct RingArgs {

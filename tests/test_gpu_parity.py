@@ -88,6 +88,14 @@ def test_config2_pointwise_stack_small(npas, torch):
     layerwise(npas, torch, configs.config2(batch=2, HW=23))        # 1058 pixels: several tiles + ragged tail
 
 
+@pytest.mark.parametrize("N,HW,C,F,dtype,res,kernel", [(3, 10, 128, 136, dtypes.F16, True, "conv_smallm_mfma_kernel"), (1, 17, 64, 40, dtypes.BF16, False, "conv_smallm_mfma_kernel"),
+                                                       (2, 25, 192, 200, dtypes.BF16, True, "conv_smallm_mfma_kernel"), (13, 29, 128, 136, dtypes.F16, True, "pointwise_ring_kernel"),
+                                                       (6, 29, 64, 200, dtypes.F16, False, "pointwise_ring_kernel")])
+def test_pointwise_layers_of_few_channels(npas, torch, N, HW, C, F, dtype, res, kernel):
+    """1x1 layers on 64 .. 192 channels: split over the waves up to one round of workgroups, the streaming kernel beyond."""
+    _run_edge_case(npas, torch, (f"pw_c{C}_f{F}", N, HW, HW, C, F, 1, 1, 1, 0, 8, 4, 2, dtype, 2, res, True), device_kernel=kernel)
+
+
 def test_config3_fc_block_full(npas, torch):
     print("config3 full", flush=True)
     w = configs.config3()
