@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <array>
 #include <cstring>
@@ -307,10 +308,46 @@ static bool plan_smallc_pool(const npas_packed *p, int N, int H, int W, int stri
     return true;
 }
 
+// The stride-2 form of both on at most 3 channels whose rows are whole 4-byte words (conv_smallc_rows_kernel): waves walk down 16 conv columns each.
+// An image's rows of pairs are cut into as many bands as keep two waves on every SIMD busy: a wave's time is taken as its pairs times the waves
+// that share its SIMD, and three pairs' worth of start.
+static bool plan_smallc_rows(const npas_packed *p, int N, int H, int W, int stride, int pad, bool pool, SmallCRowsArgs *a)
+{
+    if (!p->smallc.present || !smallc_rows_layer(p->C, p->KH, p->KW) || stride != 2 || (W * p->C) % 2) return false;
+    const int Ho = (H + 2 * pad - p->KH) / 2 + 1, Wo = (W + 2 * pad - p->KW) / 2 + 1;
+    if (H + 2 * pad < p->KH || W + 2 * pad < p->KW || N < 1) return false;
+    a->H = H; a->W = W; a->C = p->C; a->F = p->F; a->Ho = Ho; a->Wo = Wo; a->KH = p->KH; a->pad = pad; a->kwc = p->KW * p->C;
+    a->pool = pool; a->PHo = (Ho - 1) / 2 + 1; a->PWo = (Wo - 1) / 2 + 1;
+    a->nsteps = a->PHo; // = pairs of conv rows
+    a->nblk = pool ? (a->PWo + 6) / 7 : (Wo + 15) / 16;
+    const double cols = (double)N * a->nblk; // bytes of an image within a buffer descriptor's range, items within exact reciprocals
+    if ((double)H * W * p->C * 2.0 >= 2147483648.0 || (double)Ho * Wo * p->F * 2.0 >= 2147483648.0 || cols * a->nsteps * a->nblk * a->nsteps >= 4294967296.0) return false;
+    double best = 0;
+    for (int b = 1; b <= a->nsteps; ++b) {
+        const int band = (a->nsteps + b - 1) / b, nband = (a->nsteps + band - 1) / band;
+        const double waves = cols * nband, t = std::ceil(waves / 1024.0) * band + std::ceil(waves / 2048.0) * 3.0;
+        if (b == 1 || t <= best) { best = t; a->band = band; a->nband = nband; }
+    }
+    a->nitems = (uint32_t)(N * a->nblk * a->nband);
+    a->div_img = magic_div((uint32_t)(a->nblk * a->nband));
+    a->div_blk = magic_div((uint32_t)a->nblk);
+    return true;
+}
+static int run_smallc_rows(const npas_packed *p, SmallCRowsArgs &a, const void *x, void *y, const void *bias, const void *residual, int act, void *stream)
+{
+    a.x = x; a.y = y; a.residual = residual; a.bias = (const float *)bias;
+    a.wimg = (const uint16_t *)p->dev.srimg + (size_t)((a.pad * a.C) & 1) * p->KH * 4 * 512;
+    a.act = act;
+    return launch_conv_smallc_rows(p->dtype, a, stream);
+}
+static bool words(const void *x, const void *y, const void *residual) { return (((uintptr_t)x | (uintptr_t)y | (uintptr_t)residual) & 3u) == 0; }
+
 // conv (small-channel kernel) + max pool 3 x 3 / 2 as one launch; y is the pooled tensor
 int run_conv_maxpool(const npas_packed *p, const void *x, void *y, int N, int H, int W, int stride, int pad, const void *bias,
                      int act, void *stream)
 {
+    SmallCRowsArgs rows;
+    if (words(x, y, nullptr) && plan_smallc_rows(p, N, H, W, stride, pad, true, &rows)) return run_smallc_rows(p, rows, x, y, bias, nullptr, act, stream);
     SmallCArgs sc;
     if (!plan_smallc_pool(p, N, H, W, stride, pad, &sc)) {
         set_error("conv + max pool: the layer does not fit the small-channel kernel");
@@ -429,7 +466,10 @@ RouteNames route_names(const npas_packed *p, int N, int H, int W, int stride, in
     case R_FC_GATHER: return {"fc_gather_mfma", "fc_gather_mfma_kernel"};
     case R_POINTWISE_RING: return {"pointwise_ring", "pointwise_ring_kernel"};
     case R_DIRECT: return {direct_report(p, N, H, W, stride, pad), "conv_slab_mfma_kernel"}; // its direct-weights form, <..>(SpatialDirectArgs)
-    case R_SMALLC: return {"conv_smallc_mfma", "conv_smallc_mfma_kernel"};
+    case R_SMALLC: {
+        SmallCRowsArgs rows;
+        return {"conv_smallc_mfma", plan_smallc_rows(p, N, H, W, stride, pad, false, &rows) ? "conv_smallc_rows_kernel" : "conv_smallc_mfma_kernel"};
+    }
     case R_SMALLM: {
         // (1x1 layers of few channels on more than 256 pixels belong to the streaming route whichever of its kernels they take)
         const bool streaming = p->KH == 1 && p->KW == 1 && pad == 0 && p->C < 256 && (long)N * ((H - 1) / stride + 1) * ((W - 1) / stride + 1) > 256;
@@ -452,6 +492,8 @@ int run_conv(const npas_packed *p, const ConvPlan *plan, const void *x, void *y,
     SmallCArgs sc;
     const Route route = choose_route(p, N, H, W, stride, pad, &sp, &sc);
     if (route == R_SMALLC) { // fewer than 8 input channels: whole reduction in a few MFMA steps
+        SmallCRowsArgs rows;
+        if (words(x, y, residual) && plan_smallc_rows(p, N, H, W, stride, pad, false, &rows)) return run_smallc_rows(p, rows, x, y, bias, residual, act, stream);
         sc.x = x; sc.y = y; sc.residual = residual; sc.bias = (const float *)bias;
         sc.wimg = p->dev.scimg;
         sc.act = act;

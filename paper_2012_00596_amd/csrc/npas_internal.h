@@ -99,10 +99,12 @@ struct RingFormat {
 // most 64 filters and C*KH*KW <= 160.  The whole reduction, k = (kh*KW + kw)*C + c, is padded to
 // nsteps * 32; wimg holds per step four column-operand images of 1 KB: image step*4 + j, lane
 // 16*q + r, value i = W[4 r + j][k = 32 step + 8 q + i] (zero where pruned, past F or past K).
+// rimg, for 3x3, 5x5 and 7x7 layers of at most 3 channels, is the same by kernel rows of 32 slots: set s (0 or 1), kernel row kh, image
+// (s KH + kh)*4 + j, lane 16*q + r, value i = W[4 r + j][kh, slot 8 q + i - s of the row's KW*C values].
 struct SmallCFormat {
     bool present = false;
     int nsteps = 0;
-    std::vector<uint16_t> wimg;
+    std::vector<uint16_t> wimg, rimg;
 };
 
 // ---- exact-list format of sparse 1x1 / FC layers (fc_gather_mfma): per 16-filter tile the list of input channels
@@ -151,6 +153,7 @@ struct DeviceCopy {
     const uint32_t *rg_chunk = nullptr;
     const void *wimg = nullptr;
     const void *scimg = nullptr; // small-channel images
+    const void *srimg = nullptr; // the same by kernel rows
     const int32_t *fc_tptr = nullptr; // exact-list format
     const uint16_t *fc_koff = nullptr;
     const void *fc_wimg = nullptr;
@@ -249,6 +252,21 @@ struct SmallCArgs {
     // (TH x TW, at most 256) starting one conv row / column before 2 x the pooled origin.
     int pool, PTH, PTW, PHo, PWo;
     uint32_t div_ptw;
+};
+
+// k x k layer at stride 2 on at most 3 channels, alone or with the max pool: see conv_smallc_rows_kernel
+inline bool smallc_rows_layer(int C, int KH, int KW) { return C <= 3 && KH == KW && (KH == 3 || KH == 5 || KH == 7); }
+struct SmallCRowsArgs {
+    const void *x;
+    void *y;
+    const void *residual;
+    const float *bias;
+    const void *wimg;               // by kernel rows, the set of the padding's parity
+    int H, W, C, F, Ho, Wo, KH, pad, act;
+    int kwc;                        // KW*C
+    int pool, PHo, PWo;             // pool != 0: y is the pooled tensor
+    int nsteps, nblk, band, nband;  // pairs of conv rows of an image; 16-column blocks; pairs a wave walks and walks per block
+    uint32_t nitems, div_img, div_blk; // N*nband*nblk; fastdiv magics (nband*nblk, nblk)
 };
 
 // k x k layer on few output pixels (small batch, small maps): see conv_smallm_mfma_kernel
@@ -370,6 +388,7 @@ int launch_pointwise_ring(int dtype, const RingArgs &a, void *stream);
 int launch_spatial_direct(int dtype, const SpatialDirectArgs &a, void *stream);
 size_t spatial_direct_lds_bytes(int npb, int G, int KS, int NB); // LDS of a launch with npb patch blocks a buffer
 int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream);
+int launch_conv_smallc_rows(int dtype, const SmallCRowsArgs &a, void *stream);
 int launch_conv_smallm(int dtype, SmallMArgs a, void *stream);
 int launch_fc_gather(int dtype, const FcGatherArgs &a, void *stream);
 bool pw_stream_supported(int C, int F);

@@ -351,6 +351,16 @@ static void build_smallc(npas_packed *p, const uint8_t *m, const uint8_t *w)
                     const size_t wi = ((size_t)f * C + c) * T + tap;
                     if (m[wi]) sc.wimg[((size_t)(step * 4 + j) * 64 + lane) * 8 + i] = w16[wi];
                 }
+    if (!smallc_rows_layer(C, p->KH, p->KW)) return;
+    sc.rimg.assign((size_t)2 * p->KH * 4 * 512, 0);
+    for (int img = 0; img < 2 * p->KH * 4; ++img)
+        for (int lane = 0; lane < 64; ++lane)
+            for (int i = 0; i < 8; ++i) {
+                const int set = img / (4 * p->KH), kh = img / 4 % p->KH, f = 4 * (lane & 15) + img % 4, k = 8 * (lane >> 4) + i - set;
+                if (f >= F || k < 0 || k >= p->KW * C) continue;
+                const size_t wi = ((size_t)f * C + k % C) * T + kh * p->KW + k / C;
+                if (m[wi]) sc.rimg[((size_t)img * 64 + lane) * 8 + i] = w16[wi];
+            }
 }
 
 // Exact-list format (see npas_internal.h): built for 16-bit 1x1 / FC layers sparse enough for it to pay.
@@ -528,7 +538,7 @@ int upload(npas_packed *p, void *hip_stream)
     size_t o_vp = place(blob, d.vg_ptr), o_vf = place(blob, d.vg_f0), o_vk = place(blob, d.vkent),
            o_vw = place(blob, d.vw);
     size_t o_rp = place(blob, p->ring.rg_ptr), o_rc = place(blob, p->ring.rg_chunk), o_ri = place(blob, p->ring.wimg);
-    size_t o_sc = place(blob, p->smallc.wimg);
+    size_t o_sc = place(blob, p->smallc.wimg), o_sr = place(blob, p->smallc.rimg);
     size_t o_ft = place(blob, p->fc.tptr), o_fk = place(blob, p->fc.koff), o_fw = place(blob, p->fc.wimg);
     size_t o_sw = place(blob, p->stream.wimg);
     size_t o_wp = place(blob, p->wavef.wg_ptr), o_wk = place(blob, p->wavef.kent), o_ww = place(blob, p->wavef.w);
@@ -562,6 +572,7 @@ int upload(npas_packed *p, void *hip_stream)
     p->dev.rg_chunk = (const uint32_t *)(b + o_rc);
     p->dev.wimg = b + o_ri;
     p->dev.scimg = b + o_sc;
+    p->dev.srimg = b + o_sr;
     p->dev.fc_tptr = (const int32_t *)(b + o_ft);
     p->dev.fc_koff = (const uint16_t *)(b + o_fk);
     p->dev.fc_wimg = b + o_fw;

@@ -766,6 +766,43 @@ def test_small_channel_kernel(npas, torch, case):
     _run_edge_case(npas, torch, case, expect_kernel="conv_smallc_mfma")
 
 
+# Stride 2 on at most 3 channels and whole 4-byte rows: the kernel by kernel rows.  Partial column blocks and filter quads, one or an odd
+# number of conv rows, images smaller than the kernel's reach, both parities of the padding, bands of one pair and of many.
+SMALLC_ROWS = [
+    ("rows_7x7_s2_ragged", 2, 37, 42, 3, 64, 7, 7, 2, 3, 8, 3, 3, dtypes.BF16, 1, False, True),
+    ("rows_7x7_no_pad_res", 3, 29, 46, 3, 36, 7, 7, 2, 0, 4, 3, 2, dtypes.F16, 0, True, False),
+    ("rows_5x5_hs_c2", 2, 31, 35, 2, 20, 5, 5, 2, 2, 4, 2, 2, dtypes.BF16, 3, True, True),
+    ("rows_3x3_c1_wide_pad", 1, 5, 6, 1, 4, 3, 3, 2, 3, 4, 1, 1, dtypes.F16, 2, False, True),
+    ("rows_one_conv_row", 2, 3, 64, 3, 8, 3, 3, 2, 0, 8, 3, 2, dtypes.BF16, 1, False, False),
+    ("rows_many_bands", 70, 128, 128, 3, 8, 3, 3, 2, 1, 8, 3, 2, dtypes.BF16, 1, False, True),
+]
+
+
+@pytest.mark.parametrize("case", SMALLC_ROWS, ids=[c[0] for c in SMALLC_ROWS])
+def test_small_channel_kernel_by_rows(npas, torch, case):
+    _run_edge_case(npas, torch, case, expect_kernel="conv_smallc_mfma", device_kernel="conv_smallc_rows_kernel")
+
+
+@pytest.mark.parametrize("pool", [False, True])
+def test_small_channel_rows_infinite_input_stays_in_its_windows(npas, torch, pool):
+    """The slots beside a kernel row's values hold neighbouring pixels: an infinite one must not reach outputs whose window is without it."""
+    N, H, W, C, F, k = 1, 32, 36, 3, 16, 7
+    layers = [configs._bp_conv(78, 0, C, F, k, 2, 3, 8, C, 2, 0.2, dtypes.BF16, configs.ACT_NONE, 0, -1, "stem")]
+    if pool:
+        layers.append(configs.Layer("maxpool", src=1, C=F, F=F, KH=3, KW=3, stride=2, pad=1, name="maxpool"))
+    xs, xe = configs._tensor(78, 1, (N, H, W, C), 1.0, dtypes.BF16)
+    clean, _ = _run_stack_gpu(npas, torch, configs.Workload("clean", dtypes.BF16, xs.shape, xs, xe, layers), npas.STACK_FUSE_CONV_MAXPOOL)
+    for iy, ix in ((16, 17), (15, 18), (0, 0), (31, 35)):
+        x2 = xs.copy().reshape(N, H, W, C)
+        x2[0, iy, ix] = 0x7f80
+        got, _ = _run_stack_gpu(npas, torch, configs.Workload("inf", dtypes.BF16, x2.shape, x2, xe, layers), npas.STACK_FUSE_CONV_MAXPOOL)
+        oy, ox = np.arange(16)[:, None], np.arange(18)[None, :]
+        hit = (np.abs(2 * oy - iy) <= 3) & (np.abs(2 * ox - ix) <= 3)   # conv outputs that see the pixel
+        if pool:
+            hit = np.array([[hit[max(0, 2 * y - 1):2 * y + 2, max(0, 2 * c - 1):2 * c + 2].any() for c in range(9)] for y in range(8)])
+        np.testing.assert_array_equal(got[0][~hit], clean[0][~hit])
+
+
 # Few output pixels (batch 1, late stages): the kernel that splits the reduction over the waves of a workgroup.
 # Stride 2, non-square kernels, filter counts off the 16- and 128-filter grids, ragged pixel tiles, fp16.
 SMALLM = [
@@ -886,6 +923,11 @@ STEM_POOL = [
     ("stem7x7_no_activation_fp16", 2, 64, 64, 3, 40, 7, 2, 3, 3, configs.ACT_NONE, dtypes.F16),
     ("conv3x3_stride1_4_channels", 2, 30, 33, 4, 32, 3, 1, 1, 4, configs.ACT_RELU6, dtypes.BF16),
     ("more_tiles_than_workgroups", 9, 224, 224, 3, 64, 7, 2, 3, 3, configs.ACT_RELU, dtypes.BF16),
+    # by kernel rows: partial blocks of 7 pooled columns, odd conv heights and widths, one pooled pixel, hard-swish
+    ("rows_7x7_ragged", 3, 39, 58, 3, 64, 7, 2, 3, 3, configs.ACT_RELU, dtypes.BF16),
+    ("rows_5x5_hard_swish_fp16", 2, 33, 62, 2, 44, 5, 2, 2, 2, configs.ACT_HARDSWISH, dtypes.F16),
+    ("rows_3x3_one_pooled_pixel", 2, 3, 4, 3, 8, 3, 2, 1, 3, configs.ACT_RELU6, dtypes.BF16),
+    ("rows_3x3_odd_width", 1, 20, 30, 1, 12, 3, 2, 0, 1, configs.ACT_NONE, dtypes.BF16),
 ]
 
 
