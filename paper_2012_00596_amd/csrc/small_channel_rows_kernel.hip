@@ -11,9 +11,10 @@
 //     by direct loads (a 256-byte row each, padding by the buffer descriptor's range) five steps ahead: no barrier, no staging arithmetic;
 //   * the pool is three maxima per conv value in registers: rows as they come, columns within a lane's four plus one from the next quarter
 //     wave; activation and rounding, which are monotone (hard-swish is not and comes first), are left to the pooled value.
-// 56 MFMAs of 16 cycles stand against about 120 vector instructions a step; two waves a SIMD (216 registers) leave part of a step's chain of
-// reads, MFMAs and maxima uncovered.  7 x 7 x 3 -> 64 with the pool at 224 x 224, batch 128, in the 50-layer stack 103 -> 50 us (matrix floor
-// 22, HBM 18); the stack 1905 -> 1874 us at batch 128, 248 -> 244 at batch 1.
+//   * operand words are read four kernel rows ahead, and the step's loads, the columns' maxima of the step before and its stores lie between MFMAs (in front
+//     of them and behind them: 47 us instead of 41, of which four rows ahead were worth 2.7).
+// 56 MFMAs of 16 cycles stand against about 110 vector instructions a step, on two waves a SIMD (235 registers).  7 x 7 x 3 -> 64 with the pool at
+// 224 x 224, batch 128, inside the 50-layer stack 103 -> 45 us (41 where clocks are up; matrix floor 22, HBM 18); the stack 1888 -> 1827 us, at batch 1 247 -> 244.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -40,6 +41,19 @@ __device__ __forceinline__ void lds_buffer4(rows_u32x4 rsrc, uint32_t voff, uint
                  : "memory"); // m0 is reserved: the compiler keeps nothing in it across statements
 }
 
+// The maximum of three, a NaN counting as nothing (fmaxf quiets every operand first, an instruction each: MFMA results need that as little as activated ones).
+// The compiler does not keep an asm statement's distance from the MFMAs whose results it reads: results_ready() stands between.
+__device__ __forceinline__ float max3(float a, float b, float c)
+{
+    float d;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+__device__ __forceinline__ void results_ready(f32x4 (&A)[4], f32x4 (&B)[4])
+{
+    asm volatile("s_nop 15\n\ts_nop 7" : "+v"(A[0]), "+v"(A[1]), "+v"(A[2]), "+v"(A[3]), "+v"(B[0]), "+v"(B[1]), "+v"(B[2]), "+v"(B[3]));
+}
+
 template <int DT, int KH, bool POOL, bool HSW>
 __device__ __forceinline__ void conv_smallc_rows_kernel_body(const SmallCRowsArgs &a)
 {
@@ -61,7 +75,7 @@ __device__ __forceinline__ void conv_smallc_rows_kernel_body(const SmallCRowsArg
     const rows_u32x4 xr = {(uint32_t)xb, (uint32_t)(xb >> 32) & 0xffffu, (uint32_t)a.H * rowbytes, 0x00020000u};
     const int iy0 = (2 * t0 - 1) * 2 - a.pad, nrows = KH + 4 * (t1 - t0);
     const int v0 = (((ox0 * 2 - a.pad) * a.C) & ~1) + 2 * lane; // the lane's first value of a row (an even one: both or neither in the row)
-    const uint32_t xv = v0 >= 0 && v0 < a.W * a.C ? (uint32_t)v0 * 2u : kRowsOutside;
+    const uint32_t xv = v0 >= 0 && v0 < a.W * a.C && lane < 60 ? (uint32_t)v0 * 2u : kRowsOutside; // (a row's last 16 bytes are zeros: see lrow)
     auto ask = [&](int i) __attribute__((always_inline)) {
         const bool in = (uint32_t)(iy0 + i) < (uint32_t)a.H && i < nrows;
         lds_buffer4(xr, in ? xv : kRowsOutside, in ? (uint32_t)(iy0 + i) * rowbytes : 0u, ring + (uint32_t)(i & (kRowsRing - 1)) * 256u);
@@ -89,11 +103,16 @@ __device__ __forceinline__ void conv_smallc_rows_kernel_body(const SmallCRowsArg
         const int k = 8 * q + 2 * i - ph;
         mask[i] = ((uint32_t)k < (uint32_t)a.kwc ? 0xffffu : 0u) | ((uint32_t)(k + 1) < (uint32_t)a.kwc ? 0xffff0000u : 0u);
     }
-    const uint8_t *lrow = lds + ring + (uint32_t)(n16 * 2 * a.C) * 2u + (uint32_t)q * 16u;
-    auto fragment = [&](int i) __attribute__((always_inline)) {
+    // (lanes without any such slot read zeros: pixels and their slots end 228 bytes into a row)
+    const uint8_t *lrow = lds + ring + (8 * q < a.kwc + ph ? (uint32_t)(n16 * 2 * a.C) * 2u + (uint32_t)q * 16u : 240u);
+    auto words = [&](int i) __attribute__((always_inline)) {
         const uint32_t *p = reinterpret_cast<const uint32_t *>(lrow + (uint32_t)(i & (kRowsRing - 1)) * 256u); // (4-byte aligned)
-        return uint4{p[0] & mask[0], p[1] & mask[1], p[2] & mask[2], p[3] & mask[3]};
+        return uint4{p[0], p[1], p[2], p[3]};
     };
+    auto own = [&](uint4 v) __attribute__((always_inline)) {
+        return uint4{v.x & mask[0], KH == 7 ? v.y : v.y & mask[1], v.z & mask[2], v.w & mask[3]}; // (7, 8, 14, 21 or 22 slots leave no pair 1 incomplete)
+    };
+    auto fragment = [&](int i) __attribute__((always_inline)) { return own(words(i)); };
 
     // ---- output ----
     const int oH = POOL ? a.PHo : a.Ho, oW = POOL ? a.PWo : a.Wo;
@@ -127,15 +146,51 @@ __device__ __forceinline__ void conv_smallc_rows_kernel_body(const SmallCRowsArg
 #pragma unroll
             for (int j = 0; j < 4; ++j) prev[j] = activate(prev[j]);
     }
-    for (int t = t0, i0 = 2; t < t1; ++t, i0 += 4) { // i0: the input row of conv row 2 t's first kernel row
-        // The slots filled here were last read in the step before at the latest, whose stores needed what was read.
+    // POOL: the vertical maxima of the step before, whose columns are taken among this step's MFMAs, and where they go
+    f32x4 v[4] = {none, none, none, none};
+    uint32_t pv0 = kRowsOutside, pv1 = kRowsOutside;
+    float right[4], p0[4], p1[4];
+    auto columns_right = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) ask(i0 - 2 + KH + 4 * kRowsAhead + i);
-        asm volatile("s_waitcnt vmcnt(20)" ::: "memory"); // all but the rows of the kRowsAhead steps to come (4 each) have landed
+        for (int j = 0; j < 4; ++j) right[j] = __int_as_float(__builtin_amdgcn_ds_bpermute((lane + 16) * 4, __float_as_int(v[j][0]))); // column 4 (q + 1)
+    };
+    auto columns_finish = [&](float (&p)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p[j] = HSW ? fmaxf(p[j], -INFINITY) /* a window of nothing but NaN */ : clampf<false>(p[j], cl);
+    };
+    auto columns0 = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p0[j] = max3(v[j][0], v[j][1], v[j][2]);
+        columns_finish(p0);
+    };
+    auto columns1 = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p1[j] = max3(v[j][2], v[j][3], right[j]);
+        columns_finish(p1);
+    };
+    auto columns_store = [&](int t) __attribute__((always_inline)) {
+        const rows_u32x2 o0 = {pack2<DT>(p0[0], p0[1]), pack2<DT>(p0[2], p0[3])}, o1 = {pack2<DT>(p1[0], p1[1]), pack2<DT>(p1[2], p1[3])};
+        __builtin_amdgcn_raw_buffer_store_b64(o0, yr, (int)pv0, (int)((uint32_t)t * orow), 0);
+        __builtin_amdgcn_raw_buffer_store_b64(o1, yr, (int)pv1, (int)((uint32_t)t * orow), 0);
+    };
+    for (int t = t0, i0 = 2; t < t1; ++t, i0 += 4) { // i0: the input row of conv row 2 t's first kernel row
+        asm volatile("s_waitcnt vmcnt(16)" ::: "memory"); // all but the rows of kRowsAhead - 1 steps to come (4 each) have landed
         f32x4 A[4], B[4];
+        uint4 raw[KH + 2];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) raw[r] = words(i0 + r);
 #pragma unroll
         for (int r = 0; r < KH + 2; ++r) {
-            const uint4 f = fragment(i0 + r);
+            __builtin_amdgcn_sched_barrier(0);
+            if (r + 4 < KH + 2) raw[r + 4 < KH + 2 ? r + 4 : 0] = words(i0 + r + 4);
+            const uint4 f = own(raw[r]);
+            // The step's other work lies between its MFMAs.  The slots filled here were last read in the step before at the latest, whose
+            // maxima or stores needed what was read.
+            if (r >= 1 && r <= 4) ask(i0 - 2 + KH + 4 * kRowsAhead + r - 1);
+            if (POOL && r == 1) columns_right();
+            if (POOL && r == 2) columns0();
+            if (POOL && r == 3) columns1();
+            if (POOL && r == 4) columns_store(t - 1);
             if (r < KH)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) A[j] = mfma16<DT>(f, w[r < KH ? r : 0][j], r == 0 ? bias[j] : A[j]);
@@ -151,11 +206,11 @@ __device__ __forceinline__ void conv_smallc_rows_kernel_body(const SmallCRowsArg
             if (!rowB)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) B[j] = none;
-            f32x4 v[4];
+            results_ready(A, B);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[j][i] = fmaxf(fmaxf(A[j][i], B[j][i]), prev[j][i]);
+                for (int i = 0; i < 4; ++i) v[j][i] = max3(A[j][i], B[j][i], prev[j][i]);
                 prev[j] = B[j];
             }
             if (edge)
@@ -163,18 +218,8 @@ __device__ __forceinline__ void conv_smallc_rows_kernel_body(const SmallCRowsArg
                 for (int j = 0; j < 4; ++j)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) v[j][i] = colok[i] ? v[j][i] : -INFINITY;
-            float p0[4], p1[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float right = __int_as_float(__builtin_amdgcn_ds_bpermute((lane + 16) * 4, __float_as_int(v[j][0]))); // column 4 (q + 1)
-                p0[j] = fmaxf(fmaxf(v[j][0], v[j][1]), v[j][2]);
-                p1[j] = fmaxf(fmaxf(v[j][2], v[j][3]), right);
-                if (HSW) { p0[j] = fmaxf(p0[j], -INFINITY); p1[j] = fmaxf(p1[j], -INFINITY); } // (a window of nothing but NaN)
-                else { p0[j] = clampf<false>(p0[j], cl); p1[j] = clampf<false>(p1[j], cl); }
-            }
-            const rows_u32x2 o0 = {pack2<DT>(p0[0], p0[1]), pack2<DT>(p0[2], p0[3])}, o1 = {pack2<DT>(p1[0], p1[1]), pack2<DT>(p1[2], p1[3])};
-            __builtin_amdgcn_raw_buffer_store_b64(o0, yr, (int)ov[0], (int)((uint32_t)t * orow), 0);
-            __builtin_amdgcn_raw_buffer_store_b64(o1, yr, (int)ov[1], (int)((uint32_t)t * orow), 0);
+            pv0 = ov[0];
+            pv1 = ov[1];
         } else {
             const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((uint8_t *)const_cast<void *>(a.residual) + (uint64_t)n * obytes, 0, (int)obytes, 0x00020000);
 #pragma unroll
@@ -195,6 +240,12 @@ __device__ __forceinline__ void conv_smallc_rows_kernel_body(const SmallCRowsArg
                 }
             }
         }
+    }
+    if (POOL) {
+        columns_right();
+        columns0();
+        columns1();
+        columns_store(t1 - 1);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // nothing lands in LDS that is no longer this workgroup's
 }
