@@ -309,7 +309,7 @@ static bool plan_smallc_pool(const npas_packed *p, int N, int H, int W, int stri
 }
 
 // The stride-2 form of both on at most 3 channels whose rows are whole 4-byte words (conv_smallc_rows_kernel): waves walk down 16 conv columns each.
-// An image's rows of pairs are cut into as many bands as keep two waves on every SIMD busy: a wave's time is taken as its pairs times the waves
+// An image's pairs of conv rows are cut into as many bands as keep two waves on every SIMD busy: a wave's time is taken as its pairs times the waves
 // that share its SIMD, and three pairs' worth of start.
 static bool plan_smallc_rows(const npas_packed *p, int N, int H, int W, int stride, int pad, bool pool, SmallCRowsArgs *a)
 {
@@ -320,15 +320,16 @@ static bool plan_smallc_rows(const npas_packed *p, int N, int H, int W, int stri
     a->pool = pool; a->PHo = (Ho - 1) / 2 + 1; a->PWo = (Wo - 1) / 2 + 1;
     a->nsteps = a->PHo; // = pairs of conv rows
     a->nblk = pool ? (a->PWo + 6) / 7 : (Wo + 15) / 16;
-    const double cols = (double)N * a->nblk; // bytes of an image within a buffer descriptor's range, items within exact reciprocals
-    if ((double)H * W * p->C * 2.0 >= 2147483648.0 || (double)Ho * Wo * p->F * 2.0 >= 2147483648.0 || cols * a->nsteps * a->nblk * a->nsteps >= 4294967296.0) return false;
+    if ((double)H * W * p->C * 2.0 >= 2147483648.0 || (double)Ho * Wo * p->F * 2.0 >= 2147483648.0) return false; // an image within a buffer descriptor's range
+    const double cols = (double)N * a->nblk;
     double best = 0;
     for (int b = 1; b <= a->nsteps; ++b) {
         const int band = (a->nsteps + b - 1) / b, nband = (a->nsteps + band - 1) / band;
         const double waves = cols * nband, t = std::ceil(waves / 1024.0) * band + std::ceil(waves / 2048.0) * 3.0;
         if (b == 1 || t <= best) { best = t; a->band = band; a->nband = nband; }
     }
-    a->nitems = (uint32_t)(N * a->nblk * a->nband);
+    if (cols * a->nband * a->nblk * a->nband >= 4294967296.0) return false; // the kernel's reciprocals are exact below that
+    a->nitems = (uint32_t)N * (uint32_t)(a->nblk * a->nband);
     a->div_img = magic_div((uint32_t)(a->nblk * a->nband));
     a->div_blk = magic_div((uint32_t)a->nblk);
     return true;
@@ -568,6 +569,7 @@ int run_conv(const npas_packed *p, const ConvPlan *plan, const void *x, void *y,
         a.H = H; a.W = W; a.stride = stride;
         a.Ho = (H - 1) / stride + 1; a.Wo = (W - 1) / stride + 1;
         a.M = N * a.Ho * a.Wo;
+        a.xbytes = (uint32_t)((size_t)N * H * W * p->C * 2);
         a.nptiles = (a.M + 255) / 256;
         a.nfb = p->ring.nfb;
         a.small = 0;

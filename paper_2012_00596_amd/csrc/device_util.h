@@ -154,6 +154,22 @@ __device__ __forceinline__ void lds_dma4(const void *gptr, uint32_t lds_addr)
                  : "memory");
 }
 
+// Raw buffer descriptor of `bytes` bytes at p: loads past them give zeros, stores past them vanish.
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+__device__ __forceinline__ u32x4 buffer_of(const void *p, uint32_t bytes)
+{
+    const uint64_t u = (uint64_t)(uintptr_t)p;
+    return u32x4{(uint32_t)u, (uint32_t)(u >> 32) & 0xffffu, bytes, 0x00020000u};
+}
+// Direct buffer -> LDS load: 64 lanes x 16 bytes land lane-linearly in the 1 KB block at lds_addr.
+__device__ __forceinline__ void lds_buffer16(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory"); // m0 is reserved: the compiler keeps nothing in it across statements
+}
+
 // "At most n vector-memory operations of this wave outstanding" for a wave-uniform n < 64
 // (the instruction takes an immediate).
 __device__ __forceinline__ void wait_vmcnt(uint32_t n)

@@ -301,6 +301,7 @@ struct RingArgs {
     int act;
     int flat;                   // 1: stride 1, input pixel index == output pixel index
     uint32_t div_howo, div_wo;  // magic reciprocals of Ho*Wo and Wo
+    uint32_t xbytes;                // of x
 };
 
 // k x k layer, weights from the L2 to registers: see spatial_direct_kernel

@@ -29,11 +29,10 @@ constexpr int kRowsRing = 32;  // input rows of a wave's ring, 256 bytes each
 constexpr int kRowsAhead = 5;  // steps (of 4 input rows) whose rows are asked for ahead: k + 2 rows in use, 4 per step in flight, k + 2 + 20 <= 32
 constexpr uint32_t kRowsOutside = 0xffffffffu; // past any buffer descriptor's range: loads give zeros, stores vanish
 
-typedef __attribute__((ext_vector_type(4))) uint32_t rows_u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t rows_u32x2;
 
 // Direct buffer -> LDS load of 64 lanes x 4 bytes to lds_addr.
-__device__ __forceinline__ void lds_buffer4(rows_u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr)
+__device__ __forceinline__ void lds_buffer4(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr)
 {
     asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen lds"
                  :
@@ -71,8 +70,7 @@ __device__ __forceinline__ void conv_smallc_rows_kernel_body(const SmallCRowsArg
     // ---- input rows: row i of the wave is image row iy0 + i and lies at ring slot i % 32 ----
     const uint32_t ring = wave * (uint32_t)(kRowsRing * 256);
     const uint32_t rowbytes = (uint32_t)(a.W * a.C) * 2u;
-    const uint64_t xb = (uint64_t)(uintptr_t)a.x + (uint64_t)n * (uint64_t)a.H * rowbytes;
-    const rows_u32x4 xr = {(uint32_t)xb, (uint32_t)(xb >> 32) & 0xffffu, (uint32_t)a.H * rowbytes, 0x00020000u};
+    const u32x4 xr = buffer_of(reinterpret_cast<const uint8_t *>(a.x) + (uint64_t)n * (uint64_t)a.H * rowbytes, (uint32_t)a.H * rowbytes);
     const int iy0 = (2 * t0 - 1) * 2 - a.pad, nrows = KH + 4 * (t1 - t0);
     const int v0 = (((ox0 * 2 - a.pad) * a.C) & ~1) + 2 * lane; // the lane's first value of a row (an even one: both or neither in the row)
     const uint32_t xv = v0 >= 0 && v0 < a.W * a.C && lane < 60 ? (uint32_t)v0 * 2u : kRowsOutside; // (a row's last 16 bytes are zeros: see lrow)

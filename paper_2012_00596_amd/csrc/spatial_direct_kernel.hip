@@ -43,22 +43,7 @@ __device__ __forceinline__ DirectItem direct_item(const SpatialDirectArgs &a, ui
     return it;
 }
 
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 constexpr uint32_t kOutside = 0xffffffffu; // byte offset of what lies outside a tensor: past the buffer descriptor's range, so loads give zeros and stores vanish
-
-__device__ __forceinline__ u32x4 buffer_of(const void *p, uint32_t bytes)
-{
-    const uint64_t u = (uint64_t)(uintptr_t)p;
-    return u32x4{(uint32_t)u, (uint32_t)(u >> 32) & 0xffffu, bytes, 0x00020000u};
-}
-// Direct buffer -> LDS load: 64 lanes x 16 bytes land lane-linearly in the 1 KB block at lds_addr.
-__device__ __forceinline__ void lds_buffer16(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr)
-{
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory"); // m0 is reserved: the compiler keeps nothing in it across statements
-}
 __device__ __forceinline__ uint32_t add_sat(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
 
 // Byte offset in the input of patch pixel pp of an item (channel 0; a multiple of 128), kOutside for padding; bits 4-6 hold the

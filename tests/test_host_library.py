@@ -179,6 +179,16 @@ def test_kernel_choice_follows_layer_and_launch_shape():
     assert name(p, 64, 56, 56, 1, 0) == "conv_slab_mfma"         # channels not a multiple of 64
 
 
+def test_device_kernel_tells_the_stem_kernels_apart():
+    """By kernel rows: stride 2, at most 3 channels, rows of whole 4-byte words; everything else stays with the whole-reduction kernel."""
+    p = _bp_layer(3, 64, 7, 44)
+    assert npas.device_kernel(p, 2, 224, 224, 2, 3) == "conv_smallc_rows_kernel"
+    assert npas.device_kernel(p, 128, 224, 224, 2, 0) == "conv_smallc_rows_kernel"
+    for W, stride in ((225, 2), (224, 1)):
+        assert npas.device_kernel(p, 2, 224, W, stride, 3) == "conv_smallc_mfma_kernel"
+    assert npas.device_kernel(_bp_layer(4, 64, 5, 47), 2, 64, 64, 2, 2) == "conv_smallc_mfma_kernel"
+
+
 def test_device_kernel_tells_the_forms_of_the_slab_route_apart():
     """1x1 layers on at most 320 channels, no multiple of 64, take the flat kernel in either list format; with padding, wider layers
     and k x k layers the kernel of their format."""
