@@ -136,19 +136,23 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t wg, uint32_t nwg)
     return xcd * q + (xcd < r ? xcd : r) + idx;
 }
 
+// Direct loads take their LDS address from M0, which the ISA wants written a wait state before a load to LDS reads it; inside an asm statement
+// the compiler does not see to that.  (M0 is reserved: the compiler keeps nothing in it across statements.)
+#define NPAS_M0_FROM_ARG0 "s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+
 // Direct global -> LDS load: 64 lanes x 16 bytes land lane-linearly in the 1 KB block at lds_addr; nothing is held in registers.
 __device__ __forceinline__ void lds_dma16(const void *gptr, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+    asm volatile(NPAS_M0_FROM_ARG0 "global_load_lds_dwordx4 %1, off"
                  :
                  : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(gptr)
-                 : "memory"); // m0 is reserved: the compiler keeps nothing in it across statements
+                 : "memory");
 }
 
 // The same with 4 bytes a lane (256 bytes of LDS).
 __device__ __forceinline__ void lds_dma4(const void *gptr, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
+    asm volatile(NPAS_M0_FROM_ARG0 "global_load_lds_dword %1, off"
                  :
                  : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(gptr)
                  : "memory");
@@ -164,10 +168,10 @@ __device__ __forceinline__ u32x4 buffer_of(const void *p, uint32_t bytes)
 // Direct buffer -> LDS load: 64 lanes x 16 bytes land lane-linearly in the 1 KB block at lds_addr.
 __device__ __forceinline__ void lds_buffer16(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+    asm volatile(NPAS_M0_FROM_ARG0 "buffer_load_dwordx4 %1, %2, %3 offen lds"
                  :
                  : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory"); // m0 is reserved: the compiler keeps nothing in it across statements
+                 : "memory");
 }
 
 // "At most n vector-memory operations of this wave outstanding" for a wave-uniform n < 64

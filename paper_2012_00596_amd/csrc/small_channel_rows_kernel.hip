@@ -34,10 +34,10 @@ typedef __attribute__((ext_vector_type(2))) uint32_t rows_u32x2;
 // Direct buffer -> LDS load of 64 lanes x 4 bytes to lds_addr.
 __device__ __forceinline__ void lds_buffer4(u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+    asm volatile(NPAS_M0_FROM_ARG0 "buffer_load_dword %1, %2, %3 offen lds"
                  :
                  : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory"); // m0 is reserved: the compiler keeps nothing in it across statements
+                 : "memory");
 }
 
 // The maximum of three, a NaN counting as nothing (fmaxf quiets every operand first, an instruction each: MFMA results need that as little as activated ones).

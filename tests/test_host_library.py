@@ -4,6 +4,8 @@ illegal masks, and fails loudly instead of computing without a GPU."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -392,3 +394,42 @@ def test_low_density_3x3_layers_split_their_reduction_where_that_is_quicker(C, F
     round of small tiles (host logic; the times stand at the rule)."""
     p = _bp_layer(C, F, 3, 50, rate=10)
     assert npas.conv2d_kernel_name(p, N, HW, HW, 1, 1) == ("conv_smallm_mfma" if split else "conv_gather_mfma")
+
+
+def _sgprs(text):
+    return {n for a, b, one in re.findall(r"\bs\[(\d+):(\d+)\]|\bs(\d+)\b", text) for n in (range(int(a), int(b) + 1) if a else (int(one),))}
+
+
+def test_scalar_operands_of_vector_memory_instructions_keep_their_wait_states(tmp_path):
+    """The ISA's manually inserted wait states around vector memory instructions, in every kernel of the built library: one between a scalar write of M0
+    and a load to LDS, five between a vector instruction's write of a scalar register and a vector memory instruction that reads it.  The
+    compiler keeps them for its own instructions only, not within or around inline assembly."""
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    shutil.copy(npas.binding._LIB, tmp_path)
+    subprocess.run([objdump, "--offloading", "libnpas.so"], cwd=tmp_path, check=True, capture_output=True)
+    loads = 0
+    for code in sorted(tmp_path.glob("*gfx950")):
+        asm = subprocess.run([objdump, "-d", "--no-show-raw-insn", code], check=True, capture_output=True, text=True).stdout
+        kernel, before = "", []  # (op, operands, wait states it stands for)
+        for line in asm.splitlines():
+            label = re.match(r"[0-9a-f]+ <(.*)>:", line)
+            if label:
+                kernel, before = label.group(1), []
+                continue
+            op, _, args = line.split("//")[0].strip().partition(" ")
+            if not op:
+                continue
+            if re.match(r"(buffer|global|flat|scratch)_", op):
+                if op.startswith("global_load_lds") or (op.startswith("buffer_load") and re.search(r"\blds\b", args)):
+                    loads += 1
+                    assert not (before and before[-1][0].startswith("s_") and before[-1][1].split(",")[0].strip() == "m0"), (kernel, before[-3:], line)
+                read, states = _sgprs(args), 0
+                for o, a, n in reversed(before[-5:]):
+                    if states >= 5:
+                        break
+                    if o.startswith("v_"):
+                        written = a.split(",")[:2 if re.match(r"v_(add|sub|subrev)c?_co|v_mad_[ui]64|v_div_scale", o) else 1]
+                        assert not _sgprs(",".join(written)) & read, (kernel, before[-6:], line)
+                    states += n
+            before = before[-7:] + [(op, args, int(args, 0) + 1 if op == "s_nop" else 1)]
+    assert loads > 500  # (direct loads are in the library, and the scan has seen them)
