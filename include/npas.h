@@ -74,13 +74,17 @@ typedef enum {
 const char *npas_last_error(void);
 
 /* Testing aid.  The library reads two environment switches once, when it is loaded: NPAS_FORCE_VARIANT
- * (gather | slab | noring | nosmallc | spatial | nospatial2 | smallm | resident | noresident | nofcgather | valu:
+ * (gather | slab | noring | nosmallc | spatial | smallm | nofcgather | valu:
  * overrides the format / kernel choice, nothing else) and NPAS_NO_BALANCE (pointwise tiles of full height).
  * This call replaces them for the process (force_variant NULL or "" = none); it must not race with pack / run calls. */
 void npas_debug_set_switches(const char *force_variant, int no_balance);
 /* Testing aid: name of the device function of that launch, as a profiler lists it ("conv_slab_mfma_kernel",
- * "pointwise_stream_kernel", ...); tells the two forms of the slab route apart.  Static string, NULL for a NULL handle. */
+ * "pointwise_stream_kernel", ...); tells the forms of a route apart.  Static string, NULL for a NULL handle. */
 const char *npas_debug_device_kernel(const npas_packed *p, int N, int H, int W, int stride, int pad);
+/* Testing aid: how the "spatial_direct" kernel would cut that launch, plan[0..8) = { pixel groups, 64-filter halves, shares of the reduction
+ * (the layout of a workgroup's four multiplying waves), 16-pixel blocks of a wave, images, rows and columns of a tile, tiles
+ * x filter blocks }.  NPAS_OK, or NPAS_E_SHAPE where the launch takes another kernel. */
+int npas_debug_direct_plan(const npas_packed *p, int N, int H, int W, int stride, int pad, int plan[8]);
 /* Measurement aid: enqueues `count` launches of an empty kernel (one wave) on the stream, so that a report can
  * state the launch-to-launch floor of the machine next to the kernels' times. */
 int npas_debug_launch_empty(int count, void *hip_stream);
@@ -155,9 +159,9 @@ int npas_conv2d_sparse(const npas_packed *p, const void *x_dev, void *y_dev, int
 
 /* Name of the kernel npas_conv2d_sparse / npas_fc_sparse launch for this layer and geometry
  * ("conv_valu_f32", "conv_wave_f32", "conv_gather_mfma", "conv_slab_mfma", "pointwise_ring",
- * "spatial_ring", "spatial_resident", "conv_smallc_mfma", "conv_smallm_mfma", "fc_gather_mfma";
+ * "spatial_direct", "conv_smallc_mfma", "conv_smallm_mfma", "fc_gather_mfma";
  * "conv_slab_mfma" names both forms of the slab route: the tiled kernel, and the flat one that 1x1 layers on at most 320
- * channels, no multiple of 64, take in either list format);
+ * channels, no multiple of 64, take in either list format; "conv_smallc_mfma" both forms of the small-channel route);
  * a static string, NULL for a NULL handle.  For reports and tests:
  * the choice depends on the packed format and on how well the problem fills the chip. */
 const char *npas_conv2d_kernel_name(const npas_packed *p, int N, int H, int W, int stride, int pad);

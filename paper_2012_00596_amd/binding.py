@@ -31,7 +31,7 @@ EXPORTS = [
     "npas_fc_sparse",
     "npas_maxpool3x3s2", "npas_global_avgpool", "npas_stack_create", "npas_stack_workspace_bytes",
     "npas_run_stack", "npas_stack_num_launches", "npas_stack_free", "npas_stack_describe", "npas_debug_set_switches",
-    "npas_run_stack_static", "npas_debug_launch_empty", "npas_debug_device_kernel",
+    "npas_run_stack_static", "npas_debug_launch_empty", "npas_debug_device_kernel", "npas_debug_direct_plan",
 ]
 STATIC_WORKSPACE_BYTES = 32 << 20
 DESCRIBE_COLS = 11
@@ -117,6 +117,7 @@ def lib():
         L.npas_debug_launch_empty.argtypes = [ip, vp]
         L.npas_debug_device_kernel.argtypes = [vp, ip, ip, ip, ip, ip]
         L.npas_debug_device_kernel.restype = C.c_char_p
+        L.npas_debug_direct_plan.argtypes = [vp, ip, ip, ip, ip, ip, C.POINTER(ip)]
         L.npas_debug_set_switches.argtypes = [C.c_char_p, ip]
         L.npas_debug_set_switches.restype = None
         _lib = L
@@ -288,6 +289,14 @@ def device_kernel(packed, N, H, W, stride, pad):
     """Testing aid: the device function conv2d_sparse / fc_sparse launch, as a profiler lists it."""
     name = lib().npas_debug_device_kernel(packed.handle, N, H, W, stride, pad)
     return name.decode() if name else None
+
+
+def direct_plan(packed, N, H, W, stride, pad):
+    """Testing aid: (pixel groups, 64-filter halves, shares of the reduction, 16-pixel blocks of a wave), (images, rows, columns of a
+    tile) and number of items of a launch of the direct-weights kernel."""
+    v = (C.c_int * 8)()
+    _check(lib().npas_debug_direct_plan(packed.handle, N, H, W, stride, pad, v))
+    return tuple(v[:4]), tuple(v[4:7]), v[7]
 
 
 def fc_sparse(packed, x, y, B, bias=None, act=ACT_NONE, stream=None):

@@ -368,26 +368,6 @@ static double t_tiled(const npas_packed *p, int N, long Ho, long Wo, long steps,
     return 2.0 + (small_maps ? 0.21 : 0.33) * steps;
 }
 
-// How reports name a launch of the direct-weights kernel: by the route its class of launches belongs to.  Launches of at least 192 tiles of
-// 128 pixels x 128 filters (256 x 64 for up to 64 filters) are the streaming ones ...
-static const char *direct_report(const npas_packed *p, int N, int H, int W, int stride, int pad)
-{
-    const int fv = switches().force;
-    if (fv == FV_SPATIAL) return "spatial_ring";
-    if (fv == FV_RESIDENT) return "spatial_resident";
-    const long Ho = (H + 2 * pad - p->KH) / stride + 1, Wo = (W + 2 * pad - p->KW) / stride + 1, M = (long)N * Ho * Wo;
-    const bool usual = stride == 1 || (p->KH == 3 && p->KW == 3 && pad == 1);
-    if (usual && (long)N * H * W < (1L << 24)) {
-        if (p->F <= 64 && stride == 1 && (M + 255) / 256 >= 192) return "spatial_resident";
-        if (4 * p->F >= 3 * 128 * p->ring.nfb && (M + 127) / 128 * p->ring.nfb >= 192) return "spatial_ring";
-    }
-    // ... the others stand beside the split reduction's and the tiled kernels'
-    const long halves = (p->F + 63) / 64, blocks = (M + 15) / 16, steps = (long)(p->C / 32) * p->KH * p->KW;
-    const long rounds = blocks * halves <= 256 ? 1 : ((blocks + 1) / 2 * halves + 255) / 256;
-    if (1.7 + rounds * (2.2 + 0.08 * steps) < t_tiled(p, N, Ho, Wo, steps, rounds)) return "conv_smallm_mfma";
-    return p->fmt.variant == V_MFMA_GATHER ? "conv_gather_mfma" : "conv_slab_mfma";
-}
-
 static Route choose_route(const npas_packed *p, int N, int H, int W, int stride, int pad, SpatialDirectArgs *sp,
                           SmallCArgs *sc = nullptr)
 {
@@ -443,8 +423,7 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
     // direct: 64 -> 64 5x5 at 28 x 28, batch 8: 8.8 against 8.2 us), the direct-weights kernel beyond (28 x 28 x 128 at batch 8: 12.3 -> 7.5 us,
     // 14 x 14 x 256 at batch 16 18.9 -> 12.0, 33 x 33, 192 -> 192 at batch 48 46.9 -> 34.4) unless the split is the quicker one by both estimates.
     const bool kxk = ring_ok && (p->KH > 1 || p->KW > 1);
-    const bool direct_forced = fv == FV_SPATIAL || (fv == FV_RESIDENT && p->F <= 64 && stride == 1);
-    const bool direct_off = fv == FV_SMALLM || (fv == FV_NOSPATIAL2 && stride == 2) || (fv == FV_NORESIDENT && p->F <= 64 && stride == 1);
+    const bool direct_forced = fv == FV_SPATIAL, direct_off = fv == FV_SMALLM;
     double t_direct = 0.0;
     if (kxk && !direct_off && (direct_forced || !smallm_ok || rounds > 1) && plan_direct(p, N, H, W, pad, stride, sp, &t_direct) &&
         (direct_forced || !smallm_ok || t_direct <= t_smallm))
@@ -466,16 +445,12 @@ RouteNames route_names(const npas_packed *p, int N, int H, int W, int stride, in
     case R_WAVE_F32: return {"conv_wave_f32", "conv_wave_f32_kernel"};
     case R_FC_GATHER: return {"fc_gather_mfma", "fc_gather_mfma_kernel"};
     case R_POINTWISE_RING: return {"pointwise_ring", "pointwise_ring_kernel"};
-    case R_DIRECT: return {direct_report(p, N, H, W, stride, pad), "conv_slab_mfma_kernel"}; // its direct-weights form, <..>(SpatialDirectArgs)
+    case R_DIRECT: return {"spatial_direct", "spatial_direct_kernel"};
     case R_SMALLC: {
         SmallCRowsArgs rows;
         return {"conv_smallc_mfma", plan_smallc_rows(p, N, H, W, stride, pad, false, &rows) ? "conv_smallc_rows_kernel" : "conv_smallc_mfma_kernel"};
     }
-    case R_SMALLM: {
-        // (1x1 layers of few channels on more than 256 pixels belong to the streaming route whichever of its kernels they take)
-        const bool streaming = p->KH == 1 && p->KW == 1 && pad == 0 && p->C < 256 && (long)N * ((H - 1) / stride + 1) * ((W - 1) / stride + 1) > 256;
-        return {streaming ? "pointwise_ring" : "conv_smallm_mfma", "conv_smallm_mfma_kernel"};
-    }
+    case R_SMALLM: return {"conv_smallm_mfma", "conv_smallm_mfma_kernel"};
     case R_STREAM: return {"conv_slab_mfma", "pointwise_stream_kernel"}; // the slab route's flat form
     case R_SLAB: return {"conv_slab_mfma", "conv_slab_mfma_kernel"};
     default: return {"conv_gather_mfma", "conv_gather_mfma_kernel"};
@@ -922,6 +897,22 @@ const char *npas_debug_device_kernel(const npas_packed *p, int N, int H, int W, 
 {
     if (!p || N <= 0 || H <= 0 || W <= 0 || stride <= 0 || pad < 0) return nullptr;
     return route_names(p, N, H, W, stride, pad).kernel;
+}
+
+int npas_debug_direct_plan(const npas_packed *p, int N, int H, int W, int stride, int pad, int plan[8])
+{
+    if (!p || !plan) {
+        set_error("NULL argument (p=%p plan=%p)", (const void *)p, (void *)plan);
+        return NPAS_E_NULL;
+    }
+    SpatialDirectArgs sp;
+    if (N <= 0 || H <= 0 || W <= 0 || stride <= 0 || pad < 0 || choose_route(p, N, H, W, stride, pad, &sp) != R_DIRECT) {
+        set_error("this launch does not take the direct-weights kernel");
+        return NPAS_E_SHAPE;
+    }
+    const int v[8] = {sp.G, sp.Hf, sp.KS, sp.NB, sp.NI, sp.TH, sp.TW, sp.nitems};
+    std::copy(v, v + 8, plan);
+    return NPAS_OK;
 }
 
 int npas_fc_sparse(const npas_packed *p, const void *x_dev, void *y_dev, int B, const void *bias_dev, npas_act act,

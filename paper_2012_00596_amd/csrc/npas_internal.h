@@ -20,8 +20,7 @@ inline int dtype_size(int dt) { return dt == NPAS_F32 ? 4 : 2; }
 
 // Testing switches (NPAS_FORCE_VARIANT / NPAS_NO_BALANCE): read from the environment once, at load;
 // npas_debug_set_switches replaces them.
-enum ForceVariant { FV_NONE = 0, FV_GATHER, FV_SLAB, FV_NORING, FV_NOSMALLC, FV_SPATIAL, FV_NOSPATIAL2, FV_SMALLM,
-                    FV_RESIDENT, FV_NORESIDENT, FV_NOFCGATHER, FV_VALU };
+enum ForceVariant { FV_NONE = 0, FV_GATHER, FV_SLAB, FV_NORING, FV_NOSMALLC, FV_SPATIAL, FV_SMALLM, FV_NOFCGATHER, FV_VALU };
 struct Switches {
     int force = FV_NONE;
     bool no_balance = false;

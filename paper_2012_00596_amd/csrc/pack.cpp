@@ -30,8 +30,7 @@ const char *last_error() { return g_err; }
 
 static int parse_force(const char *v)
 {
-    static const char *names[] = {"", "gather", "slab", "noring", "nosmallc", "spatial", "nospatial2", "smallm",
-                                  "resident", "noresident", "nofcgather", "valu"};
+    static const char *names[] = {"", "gather", "slab", "noring", "nosmallc", "spatial", "smallm", "nofcgather", "valu"};
     if (!v) return FV_NONE;
     for (int i = 1; i < (int)(sizeof(names) / sizeof(names[0])); ++i)
         if (strcmp(v, names[i]) == 0) return i;

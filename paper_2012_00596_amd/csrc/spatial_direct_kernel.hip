@@ -1,5 +1,5 @@
 // gfx950 kernel of libnpas for k x k layers with whole 64-channel chunks on many pixels: weights from the L2 straight into
-// registers, activations through LDS (the direct-weights form of the slab kernel: an operand is 8 channels of one tap).
+// registers, activations through LDS.
 //
 // What bounds such a layer is feeding the matrix cores.  With weights and activations both in LDS, 64 x 64 outputs a wave and a barrier
 // per 64-channel tap, a tap took 1.7-1.9 k cycles for 1024 of MFMAs: operand reads, their waits on both sides of every barrier, and
@@ -165,7 +165,7 @@ constexpr int kDirectFetchWaves = 4, kDirectThreads = (4 + kDirectFetchWaves) * 
 constexpr uint32_t kDirectExchange = 2u * 16384u; // LDS of the partial sums' exchange (KS == 2): 16 KB per filter half
 
 template <int DT, int G, int H, int KS, int NB>
-__global__ __launch_bounds__(kDirectThreads) void conv_slab_mfma_kernel(SpatialDirectArgs a)
+__global__ __launch_bounds__(kDirectThreads) void spatial_direct_kernel(SpatialDirectArgs a)
 {
     static_assert(G * H * KS == 4 && (KS == 1 || (NB <= 8 && G * H == 2)), "four multiplying waves, one per SIMD");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -453,7 +453,7 @@ size_t spatial_direct_lds_bytes(int npb, int G, int KS, int NB)
 
 template <int DT, int G, int H, int KS, int NB> static void launch_direct_inst(const SpatialDirectArgs &a, unsigned grid, size_t lds_bytes, hipStream_t st)
 {
-    auto kern = conv_slab_mfma_kernel<DT, G, H, KS, NB>;
+    auto kern = spatial_direct_kernel<DT, G, H, KS, NB>;
     static std::once_flag once; // one per instantiation
     allow_lds_once(once, kern, 160 * 1024);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kDirectThreads), lds_bytes, st, a);

@@ -209,9 +209,9 @@ def test_edge_cases(npas, torch, case):
     _run_edge_case(npas, torch, case)
 
 
-# k x k, stride 1, whole 64-channel chunks: the streaming kernel (forced, so that small
+# k x k, stride 1, whole 64-channel chunks: the direct-weights kernel (forced, so that small
 # problems take it too): several images per tile, ragged tiles in every direction, filter
-# counts off the 128-filter block, more work items than workgroups.
+# counts off the 128-filter block, many work items.
 SPATIAL = [
     ("sp_7x7_images_per_tile", 11, 7, 7, 64, 136, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 1, True, True),
     ("sp_14x14_two_chunks", 3, 14, 14, 128, 64, 3, 3, 1, 1, 8, 4, 2, dtypes.BF16, 2, False, True),
@@ -223,9 +223,9 @@ SPATIAL = [
 
 
 @pytest.mark.parametrize("case", SPATIAL, ids=[c[0] for c in SPATIAL])
-def test_spatial_streaming_kernel(npas, torch, case, force_variant):
+def test_direct_weights_kernel_stride1(npas, torch, case, force_variant):
     force_variant("spatial")
-    _run_edge_case(npas, torch, case, expect_kernel="spatial_ring")
+    _run_edge_case(npas, torch, case, expect_kernel="spatial_direct")
 
 
 RESIDENT = [
@@ -238,15 +238,15 @@ RESIDENT = [
 
 
 @pytest.mark.parametrize("case", RESIDENT, ids=[c[0] for c in RESIDENT])
-def test_spatial_resident_weights_kernel(npas, torch, case, force_variant):
-    force_variant("resident")
-    _run_edge_case(npas, torch, case, expect_kernel="spatial_resident")
+def test_direct_weights_kernel_up_to_64_filters(npas, torch, case, force_variant):
+    force_variant("spatial")
+    _run_edge_case(npas, torch, case, expect_kernel="spatial_direct")
 
 
-def test_spatial_resident_weights_kernel_chosen_for_a_full_launch(npas, torch):
-    """56 x 56, 64 -> 64 at batch 16: 224 tiles of 8 x 28 pixels, chosen by the library itself."""
+def test_direct_weights_kernel_chosen_for_a_full_launch(npas, torch):
+    """56 x 56, 64 -> 64 at batch 16, chosen by the library itself."""
     _run_edge_case(npas, torch, ("res_full_launch", 16, 56, 56, 64, 64, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 1, False, True),
-                   expect_kernel="spatial_resident")
+                   expect_kernel="spatial_direct")
 
 
 SPATIAL_STRIDE2 = [
@@ -259,16 +259,15 @@ SPATIAL_STRIDE2 = [
 
 
 @pytest.mark.parametrize("case", SPATIAL_STRIDE2, ids=[c[0] for c in SPATIAL_STRIDE2])
-def test_spatial_streaming_kernel_stride2(npas, torch, case, force_variant):
+def test_direct_weights_kernel_stride2(npas, torch, case, force_variant):
     force_variant("spatial")
-    _run_edge_case(npas, torch, case, expect_kernel="spatial_ring")
+    _run_edge_case(npas, torch, case, expect_kernel="spatial_direct")
 
 
-def test_spatial_streaming_kernel_half_size_tiles(npas, torch):
-    """104 tiles of 256 pixels would leave most CUs idle; 256 tiles of 128 pixels (two 7x7 images each) do not:
-    the streaming kernel with half the multiplying waves, chosen by the library itself."""
+def test_direct_weights_kernel_on_7x7_maps(npas, torch):
+    """Two 7 x 7 images a tile, 128 filters: one round of 256 items, chosen by the library itself."""
     _run_edge_case(npas, torch, ("sp_7x7_half_tiles", 128, 7, 7, 64, 512, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 1, True, True),
-                   expect_kernel="spatial_ring")
+                   expect_kernel="spatial_direct")
 
 
 # The direct-weights kernel in every layout of its waves (pixel groups x filter halves x shares of the reduction) and several tile heights: one pixel,
@@ -292,12 +291,12 @@ DIRECT = [
 @pytest.mark.parametrize("case", DIRECT, ids=[c[0] for c in DIRECT])
 def test_direct_weights_kernel(npas, torch, case, force_variant):
     force_variant("spatial")
-    _run_edge_case(npas, torch, case, expect_kernel="spatial_ring", device_kernel="conv_slab_mfma_kernel")
+    _run_edge_case(npas, torch, case, expect_kernel="spatial_direct")
 
 
-def test_config4_pattern_small_streaming_kernel(npas, torch, force_variant):
+def test_config4_pattern_small_direct_weights_kernel(npas, torch, force_variant):
     force_variant("spatial")
-    print("config4 small, streaming kernel", flush=True)
+    print("config4 small, direct-weights kernel", flush=True)
     layerwise(npas, torch, configs.config4(batch=3, HW=12))
 
 
@@ -570,7 +569,7 @@ def test_split_reduction_infinite_input_under_pruned_weights(npas, torch, C, F, 
 def test_direct_weights_infinite_input_under_pruned_weights(npas, torch, C, F, N, HW, k, stride, rate, dtype, res, force_variant):
     force_variant("spatial")
     L = configs._bp_conv(53, 0, C, F, k, stride, k // 2, 4, 4, rate, 0.2, dtype, configs.ACT_RELU6)
-    _infinite_input_under_pruned_weights(npas, torch, L, N, HW, HW, dtype, res, "spatial_ring")
+    _infinite_input_under_pruned_weights(npas, torch, L, N, HW, HW, dtype, res, "spatial_direct")
 
 
 @pytest.mark.parametrize("off", [8, 2])
@@ -579,7 +578,7 @@ def test_direct_weights_output_at_smaller_alignment(npas, torch, off):
     ws, _ = dtypes.quantize(prng.normal(31, 1, F * C * 9, 0.1).reshape(F, C, 3, 3), dtypes.BF16)
     p = npas.pack_block_punched(ws, masks.block_punched_mask(F, C, 3, 3, 8, 8, 2, 31), 8, 8, dtypes.BF16)
     xs, _ = dtypes.quantize(prng.normal(31, 2, N * HW * HW * C).reshape(N, HW, HW, C), dtypes.BF16)
-    assert npas.device_kernel(p, N, HW, HW, 1, 1) == "conv_slab_mfma_kernel"
+    assert npas.device_kernel(p, N, HW, HW, 1, 1) == "spatial_direct_kernel"
     x, n = to_dev(xs, torch), N * HW * HW * F
     y0 = torch.zeros(n, dtype=torch.int16, device="cuda")
     y1 = torch.full((n + 16,), 0x7FC1, dtype=torch.int16, device="cuda")
@@ -900,8 +899,10 @@ def test_fp16_storage_through_the_fused_kernels_and_the_pointwise_ring(npas, tor
     norm, worst = helpers.check_stack_output(got, rounded[-1], TOL[dtypes.F16])
     print(f"  launches={st.num_launches()} norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
     assert st.num_launches() == 1
-    _run_edge_case(npas, torch, ("fp16_pointwise_ring", 3, 9, 11, 128, 136, 1, 1, 1, 0, 8, 4, 3, dtypes.F16, 2, True, True),
+    _run_edge_case(npas, torch, ("fp16_pointwise_ring", 13, 29, 27, 128, 136, 1, 1, 1, 0, 8, 4, 3, dtypes.F16, 2, True, True),
                    expect_kernel="pointwise_ring")
+    _run_edge_case(npas, torch, ("fp16_pointwise_split", 3, 9, 11, 128, 136, 1, 1, 1, 0, 8, 4, 3, dtypes.F16, 2, True, True),
+                   expect_kernel="conv_smallm_mfma")
 
 
 def test_config5_run_stack_end_to_end(npas, torch):
@@ -1094,18 +1095,19 @@ def test_chained_fused_launches_against_the_oracle(npas, torch):
 HS_CASES = [
     # hard-swish through every epilogue: name, N, H, W, C, F, KH, KW, stride, pad, Bf, Bc, rate, dtype, act, res, bias, variant, kernel
     (("hs_slab", 2, 11, 9, 24, 40, 3, 3, 1, 1, 8, 4, 2, dtypes.BF16, 3, True, True), None, "conv_slab_mfma"),
-    (("hs_pointwise_ring", 3, 9, 11, 128, 136, 1, 1, 1, 0, 8, 4, 3, dtypes.BF16, 3, True, True), None, "pointwise_ring"),
-    (("hs_spatial_ring", 3, 14, 14, 128, 64, 3, 3, 1, 1, 8, 4, 2, dtypes.BF16, 3, False, True), "spatial", "spatial_ring"),
-    (("hs_resident_fp16", 2, 13, 11, 64, 40, 3, 3, 1, 1, 8, 4, 2, dtypes.F16, 3, True, False), "resident", "spatial_resident"),
+    (("hs_pointwise_ring", 13, 29, 27, 128, 136, 1, 1, 1, 0, 8, 4, 3, dtypes.BF16, 3, True, True), None, "pointwise_ring"),
+    (("hs_pointwise_split", 3, 9, 11, 128, 136, 1, 1, 1, 0, 8, 4, 3, dtypes.BF16, 3, True, True), None, "conv_smallm_mfma"),
+    (("hs_spatial", 3, 14, 14, 128, 64, 3, 3, 1, 1, 8, 4, 2, dtypes.BF16, 3, False, True), "spatial", "spatial_direct"),
+    (("hs_spatial_f40_fp16", 2, 13, 11, 64, 40, 3, 3, 1, 1, 8, 4, 2, dtypes.F16, 3, True, False), "spatial", "spatial_direct"),
     (("hs_smallm", 1, 7, 7, 128, 72, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 3, True, True), None, "conv_smallm_mfma"),
     (("hs_smallc", 2, 21, 23, 3, 32, 5, 5, 2, 2, 8, 3, 2, dtypes.BF16, 3, False, True), None, "conv_smallc_mfma"),
     (("hs_gather", 1, 8, 8, 20, 18, 3, 3, 1, 1, 6, 4, 2, dtypes.BF16, 3, False, True), None, "conv_gather_mfma"),
     (("hs_fp32", 2, 9, 9, 8, 12, 3, 3, 1, 1, 4, 4, 2, dtypes.F32, 3, True, True), None, None),
     # the compiled epilogue variants of the spatial kernels (activation kind x residual), partial filter blocks, stride 2
-    (("epi_spatial_hs_res", 3, 14, 14, 128, 128, 3, 3, 1, 1, 8, 4, 2, dtypes.BF16, 3, True, True), "spatial", "spatial_ring"),
-    (("epi_spatial_s2_relu_res", 2, 28, 28, 64, 128, 3, 3, 2, 1, 8, 4, 2, dtypes.BF16, 1, True, True), "spatial", "spatial_ring"),
-    (("epi_spatial_relu6_res_fp16_f200", 2, 9, 9, 64, 200, 3, 3, 1, 1, 8, 4, 3, dtypes.F16, 2, True, False), "spatial", "spatial_ring"),
-    (("epi_resident_none_nores", 2, 12, 10, 64, 64, 3, 3, 1, 1, 8, 4, 2, dtypes.BF16, 0, False, True), "resident", "spatial_resident"),
+    (("epi_spatial_hs_res", 3, 14, 14, 128, 128, 3, 3, 1, 1, 8, 4, 2, dtypes.BF16, 3, True, True), "spatial", "spatial_direct"),
+    (("epi_spatial_s2_relu_res", 2, 28, 28, 64, 128, 3, 3, 2, 1, 8, 4, 2, dtypes.BF16, 1, True, True), "spatial", "spatial_direct"),
+    (("epi_spatial_relu6_res_fp16_f200", 2, 9, 9, 64, 200, 3, 3, 1, 1, 8, 4, 3, dtypes.F16, 2, True, False), "spatial", "spatial_direct"),
+    (("epi_spatial_none_nores", 2, 12, 10, 64, 64, 3, 3, 1, 1, 8, 4, 2, dtypes.BF16, 0, False, True), "spatial", "spatial_direct"),
     (("epi_pointwise_hs_nores_partial", 2, 7, 9, 64, 72, 1, 1, 1, 0, 8, 4, 2, dtypes.BF16, 3, False, False), None, None),
 ]
 
@@ -1134,15 +1136,15 @@ def test_full_size_config4_sampled_images(npas, torch):
 
 def test_config5_batch128_sampled_images(npas, torch):
     """The 50-layer stack's layers in the launch configuration the per-layer report times (batch 128: big tiles,
-    both tile sizes of the streaming kernels, their stride-2 mode, the resident-weights kernel, the stem kernel), each on a seeded input of its real shape, checked
+    the streaming pointwise kernel, the direct-weights kernel at both strides, the stem kernel), each on a seeded input of its real shape, checked
     on three of the 128 images (a layer's output for one image depends on that image only)."""
     w = configs.config5(batch=128)
     shapes = {0: w.x_shape}
     for i, L in enumerate(w.layers):
         shapes[i + 1] = helpers.out_shape(L, shapes[L.src])
-    want = {"stem7x7": "conv_smallc_mfma", "s0b0_c3": "pointwise_ring", "s1b0_sc": "pointwise_ring", "s1b1_c2": "spatial_ring",
-            "s2b1_c3": "pointwise_ring", "s2b0_c2": "spatial_ring", "s3b1_c1": "pointwise_ring", "s3b1_c2": "spatial_ring",
-            "s0b1_c2": "spatial_resident"}
+    want = {"stem7x7": "conv_smallc_mfma", "s0b0_c3": "pointwise_ring", "s1b0_sc": "pointwise_ring", "s1b1_c2": "spatial_direct",
+            "s2b1_c3": "pointwise_ring", "s2b0_c2": "spatial_direct", "s3b1_c1": "pointwise_ring", "s3b1_c2": "spatial_direct",
+            "s0b1_c2": "spatial_direct"}
     seen = set()
     for i, L in enumerate(w.layers):
         if L.name not in want:

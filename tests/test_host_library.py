@@ -159,18 +159,21 @@ def _bp_layer(C, F, k, seed, rate=3):
 def test_kernel_choice_follows_layer_and_launch_shape():
     """Host logic only: which kernel a layer gets depends on its shape and on how many tiles the launch has."""
     name = npas.conv2d_kernel_name
-    p = _bp_layer(64, 64, 3, 41)                       # 3x3 on 64 channels, 64 filters: all weight stages fit in LDS
-    assert name(p, 128, 56, 56, 1, 1) == "spatial_resident"
-    assert name(p, 8, 56, 56, 1, 1) == "conv_slab_mfma"          # 112 tiles: too few for the persistent kernels
+    p = _bp_layer(64, 64, 3, 41)                       # k x k on whole 64-channel chunks
+    assert name(p, 128, 56, 56, 1, 1) == "spatial_direct"
+    assert name(p, 8, 56, 56, 1, 1) == "spatial_direct"          # more than one round of the split reduction
     assert name(p, 1, 56, 56, 1, 1) == "conv_smallm_mfma"        # little work in all: reduction split over the waves
     p = _bp_layer(128, 128, 3, 42)
-    assert name(p, 128, 28, 28, 1, 1) == "spatial_ring"
-    assert name(p, 128, 56, 56, 2, 1) == "spatial_ring"          # stride 2: phase planes
-    assert name(p, 128, 56, 56, 2, 0) == "conv_slab_mfma"        # ... for pad 1 only
+    assert name(p, 128, 28, 28, 1, 1) == "spatial_direct"
+    assert name(p, 8, 28, 28, 1, 1) == "spatial_direct"
+    assert name(p, 128, 56, 56, 2, 1) == "spatial_direct"        # stride 2, with any padding
+    assert name(p, 128, 56, 56, 2, 0) == "spatial_direct"
+    assert name(p, 128, 56, 56, 3, 1) == "conv_slab_mfma"        # ... but no more
     assert name(p, 1, 28, 28, 1, 1) == "conv_smallm_mfma"
     p = _bp_layer(64, 256, 1, 43)
     assert name(p, 128, 56, 56, 1, 0) == "pointwise_ring"
     assert name(p, 1, 14, 14, 1, 0) == "conv_smallm_mfma"        # up to 256 output pixels
+    assert name(p, 1, 28, 28, 1, 0) == "conv_smallm_mfma"        # 4 x 49 workgroups: still one round
     assert name(p, 1, 56, 56, 1, 0) == "pointwise_ring"
     p = _bp_layer(1024, 256, 1, 46)
     assert name(p, 8, 7, 7, 1, 0) == "conv_smallm_mfma"          # long reduction, 7 x 16 workgroups: one round
@@ -203,7 +206,8 @@ def test_device_kernel_tells_the_forms_of_the_slab_route_apart():
     p = _bp_layer(328, 64, 1, 45, rate=2)
     assert kernel(p, 64, 56, 56, 1, 0) == "conv_slab_mfma_kernel"
     p = _bp_layer(64, 64, 3, 41)
-    assert kernel(p, 8, 56, 56, 1, 1) == "conv_slab_mfma_kernel" and kernel(p, 1, 56, 56, 1, 1) == "conv_smallm_mfma_kernel"
+    assert kernel(p, 8, 56, 56, 1, 1) == "spatial_direct_kernel" and kernel(p, 1, 56, 56, 1, 1) == "conv_smallm_mfma_kernel"
+    assert kernel(p, 64, 56, 56, 3, 1) == "conv_slab_mfma_kernel"
 
 
 # ---- workspace placement of fused stacks (host logic: works without a GPU) -----------------------------------
@@ -295,24 +299,46 @@ def test_a_layer_joins_one_fused_launch_only():
     assert {r["out"] for r in rows} == {1, 4}
 
 
+def test_device_functions_have_names_of_their_own():
+    """A profile or device_kernel() names a kernel: no two sources define the same one, and each name the dispatch gives is defined."""
+    defined = []
+    for src in npas.binding.SOURCES:
+        text = open(os.path.join(npas.binding._CSRC, src)).read()
+        defined += set(re.findall(r"__global__[^;{]*?\b(\w+_kernel)\(", text))
+    assert len(defined) == len(set(defined)), sorted(n for n in defined if defined.count(n) > 1)
+    api = open(os.path.join(npas.binding._CSRC, "api.cpp")).read()
+    assert set(re.findall(r'"(\w+_kernel)"', api)) <= set(defined)
+
+
 def test_switches_are_read_once_and_can_be_replaced():
     p = _bp_layer(128, 128, 3, 42)
     assert npas.conv2d_kernel_name(p, 2, 14, 14, 1, 1) == "conv_smallm_mfma"
     npas.set_switches("spatial")
     try:
-        assert npas.conv2d_kernel_name(p, 2, 14, 14, 1, 1) == "spatial_ring"
+        assert npas.conv2d_kernel_name(p, 2, 14, 14, 1, 1) == "spatial_direct"
     finally:
         npas.set_switches(None)
     assert npas.conv2d_kernel_name(p, 2, 14, 14, 1, 1) == "conv_smallm_mfma"
 
 
-def test_spatial_ring_is_not_planned_beyond_its_24_bit_pixel_count():
-    """The spatial ring forms its patch addresses with 24-bit multiplies: a launch with 2^24 input pixels or more
-    gets another kernel (the planner's rule, checked on the host)."""
-    p = _bp_layer(128, 128, 3, 43)
-    assert npas.conv2d_kernel_name(p, 128, 28, 28, 1, 1) == "spatial_ring"
-    assert 21400 * 28 * 28 >= 1 << 24
-    assert npas.conv2d_kernel_name(p, 21400, 28, 28, 1, 1) != "spatial_ring"
+def test_direct_weights_kernel_is_planned_within_its_limits():
+    """Launches beyond 2^24 input pixels take it too (byte offsets are 32-bit, tensors below 4 GiB); a patch of a 64-channel chunk has to fit in LDS
+    twice, so the largest kernels go elsewhere, and strides beyond 2 do."""
+    p = _bp_layer(64, 128, 3, 43)
+    assert 42700 * 28 * 28 * 64 <= 2 ** 31 - 1 and 42700 * 28 * 28 >= 1 << 24
+    for N, pad in ((128, 1), (42700, 0)):
+        layout, tile, items = npas.direct_plan(p, N, 28, 28, 1, pad)
+        Ho = 26 + 2 * pad
+        assert layout[0] * layout[1] * layout[2] == 4 and np.prod(tile) <= 16 * layout[3] * layout[0]
+        assert items == -(-N // tile[0]) * -(-Ho // tile[1]) * -(-Ho // tile[2]) * (2 // layout[1])
+    with pytest.raises(npas.NpasError):
+        npas.direct_plan(p, 128, 56, 56, 3, 1)
+    npas.set_switches("spatial")
+    try:
+        assert npas.conv2d_kernel_name(_bp_layer(64, 8, 23, 44), 64, 56, 56, 1, 11) == "spatial_direct"
+        assert npas.conv2d_kernel_name(_bp_layer(64, 8, 25, 44), 64, 56, 56, 1, 12) != "spatial_direct"   # one pixel's patch: 79 KB
+    finally:
+        npas.set_switches(None)
 
 
 def test_run_calls_marshal_like_the_c_abi():
@@ -387,13 +413,13 @@ def test_fc_layers_take_the_dense_images_where_those_are_quicker(C, F, rate, B, 
     assert npas.conv2d_kernel_name(p, B, 1, 1, 1, 0) == ("conv_smallm_mfma" if dense else "fc_gather_mfma")
 
 
-@pytest.mark.parametrize("C,F,N,HW,split", [(256, 256, 64, 7, False), (256, 256, 16, 14, True), (320, 320, 64, 7, True), (512, 512, 32, 7, True),
-                                            (256, 256, 16, 7, True)])
-def test_low_density_3x3_layers_split_their_reduction_where_that_is_quicker(C, F, N, HW, split):
-    """3x3 layers at 10x in the gather format: the split-reduction kernel, but for long launches on maps that the list kernel walks in one
-    round of small tiles (host logic; the times stand at the rule)."""
+@pytest.mark.parametrize("C,F,N,HW,kernel", [(256, 256, 64, 7, "spatial_direct"), (256, 256, 16, 14, "spatial_direct"), (320, 320, 64, 7, "spatial_direct"),
+                                             (512, 512, 32, 7, "spatial_direct"), (256, 256, 16, 7, "conv_smallm_mfma")])
+def test_low_density_3x3_layers_split_their_reduction_where_that_is_quicker(C, F, N, HW, kernel):
+    """3x3 layers at 10x in the gather format: the split-reduction kernel in one round of workgroups, the direct-weights kernel beyond, as at other
+    densities above an eighth (host logic; the times stand at the rule)."""
     p = _bp_layer(C, F, 3, 50, rate=10)
-    assert npas.conv2d_kernel_name(p, N, HW, HW, 1, 1) == ("conv_smallm_mfma" if split else "conv_gather_mfma")
+    assert npas.conv2d_kernel_name(p, N, HW, HW, 1, 1) == kernel
 
 
 def _sgprs(text):
