@@ -181,7 +181,9 @@ static int check_run(const npas_packed *p, const void *x, void *y, int N, int H,
 // *t_us is that time, fitted to 449 layers (3x3, 5x5, 7x7, stride 1 and 2) in all layouts: within 4 % for half of them, 10 % for nine in ten;
 // the layout it picks is on average 2 % slower than the best one.  A step of 32 channels takes 78 ns (its loads) and 19 ns a pixel block, 26 where
 // every CU is at work (the clock falls); a chunk 0.6 us more, a workgroup's first patch 33 ns a KB.
-// The search is some ten thousand candidates and depends on the shapes only: its results are kept per shape.
+// Of the sizes that cut a side into the same number of parts only the smallest is a candidate (its patch is the smallest), and tiles that
+// would lose with every item at its quickest are passed over: a shape's first call takes some 50 us, a tenth of
+// what it takes over all sizes.  It depends on the shapes only: the results are kept per shape.
 bool plan_direct(const npas_packed *p, int N, int H, int W, int pad, int stride, SpatialDirectArgs *a, double *t_us)
 {
     struct Entry { bool ok; double t; SpatialDirectArgs g; };
@@ -197,28 +199,52 @@ bool plan_direct(const npas_packed *p, int N, int H, int W, int pad, int stride,
         const int Ho = (H + 2 * pad - KH) / stride + 1, Wo = (W + 2 * pad - KW) / stride + 1;
         const bool able = T >= 2 && p->C % 64 == 0 && p->F % 4 == 0 && p->ring.present && (stride == 1 || stride == 2);
         double best = 1e30;
+        // the ways to cut a side into parts of equal size: per number of parts the smallest size
+        struct Cut { int size, parts; };
+        auto cuts = [](int n) {
+            std::vector<Cut> c;
+            for (int size = 1; size <= std::min(n, 16 * 7 * 4);) {
+                const int parts = (n + size - 1) / size;
+                c.push_back(Cut{size, parts});
+                size = parts > 1 ? (n + parts - 2) / (parts - 1) : n + 1;
+            }
+            return c;
+        };
+        const std::vector<Cut> hs = cuts(Ho), ws = cuts(Wo), ns = cuts(N);
         static const int layouts[][3] = {{2, 2, 1}, {1, 2, 2}, {4, 1, 1}, {2, 1, 2}};
         for (const auto &l : layouts)
             for (int NB = 3; able && NB <= 7; ++NB) {
                 const int G = l[0], Hf = l[1], KS = l[2], cap = 16 * NB * G, nfb = (p->F + 64 * Hf - 1) / (64 * Hf);
-                for (int TH = 1; TH <= std::min(Ho, cap); ++TH)
-                    for (int TW = 1; TW <= std::min(Wo, cap / TH); ++TW) {
-                        const int PH = (TH - 1) * stride + KH, PW = (TW - 1) * stride + KW;
-                        const long ty = (Ho + TH - 1) / TH, tx = (Wo + TW - 1) / TW;
-                        for (int NI = std::min(N, cap / (TH * TW)); NI >= 1; --NI) {
-                            const int npb = (NI * PH * PW + 15) / 16 * 2;
-                            const long items = (long)((N + NI - 1) / NI) * ty * tx * nfb, rounds = (items + 255) / 256;
-                            if (spatial_direct_lds_bytes(npb, G, KS, NB) > 160 * 1024 || items * std::max<long>(nfb, std::max(tx, ty)) > 0xffffffffL) continue;
-                            const double busy = std::min(1.0, (double)items / (256.0 * rounds));
-                            const double step = 0.078 + (0.0186 + 0.0069 * busy) * NB, item = nch * (0.62 + T * 2 / KS * step) + 0.3 * NB - 0.13 + (KS == 2 ? 0.43 : 0.0);
-                            const double t = 2.1 + rounds * item + 0.0325 * npb;
+                auto item_us = [&](double busy) {
+                    const double step = 0.078 + (0.0186 + 0.0069 * busy) * NB;
+                    return nch * (0.62 + T * 2 / KS * step) + 0.3 * NB - 0.13 + (KS == 2 ? 0.43 : 0.0);
+                };
+                const double item0 = item_us(0.0);
+                const size_t lds0 = spatial_direct_lds_bytes(0, G, KS, NB), lds1 = spatial_direct_lds_bytes(1, G, KS, NB) - lds0;
+                const int max_npb = (int)((160 * 1024 - lds0) / lds1);
+                for (const Cut &h : hs) {
+                    if (h.size > cap) break;
+                    for (const Cut &w : ws) {
+                        const int px = h.size * w.size;
+                        if (px > cap) break;
+                        const long per_image = (long)h.parts * w.parts * nfb;
+                        if (2.1 + std::max(1.0, (double)N * px / cap * per_image / 256.0) * item0 >= best) continue; // (as if images filled the tiles)
+                        const int patch = ((h.size - 1) * stride + KH) * ((w.size - 1) * stride + KW);
+                        for (const Cut &n : ns) {
+                            if (n.size * px > cap) break;
+                            const int npb = (n.size * patch + 15) / 16 * 2;
+                            if (npb > max_npb) break;
+                            const long items = n.parts * per_image, rounds = (items + 255) / 256;
+                            if (2.1 + rounds * item0 + 0.0325 * npb >= best || items * std::max(nfb, std::max(w.parts, h.parts)) > 0xffffffffL) continue;
+                            const double t = 2.1 + rounds * item_us(std::min(1.0, (double)items / (256.0 * rounds))) + 0.0325 * npb;
                             if (t < best) {
                                 best = t;
                                 g.G = G; g.Hf = Hf; g.KS = KS; g.NB = NB;
-                                g.NI = NI; g.TH = TH; g.TW = TW; g.nfb = nfb;
+                                g.NI = n.size; g.TH = h.size; g.TW = w.size; g.nfb = nfb;
                             }
                         }
                     }
+                }
             }
         if (best < 1e30) {
             g.N = N; g.H = H; g.W = W; g.C = p->C; g.F = p->F; g.Ho = Ho; g.Wo = Wo;

@@ -6,6 +6,7 @@ import os
 import re
 import shutil
 import subprocess
+import time
 
 import numpy as np
 import pytest
@@ -339,6 +340,18 @@ def test_direct_weights_kernel_is_planned_within_its_limits():
         assert npas.conv2d_kernel_name(_bp_layer(64, 8, 25, 44), 64, 56, 56, 1, 12) != "spatial_direct"   # one pixel's patch: 79 KB
     finally:
         npas.set_switches(None)
+
+
+def test_planning_a_new_shape_is_quick():
+    """A batch size or map that a program has not run before is planned in its first call, on the caller's time: 40-70 us here (400-700 without
+    passing over sizes that cannot win)."""
+    p = _bp_layer(128, 128, 3, 45)
+    us = []
+    for N in range(33, 97):
+        t = time.perf_counter()
+        npas.conv2d_kernel_name(p, N, 28, 28, 1, 1)
+        us.append((time.perf_counter() - t) * 1e6)
+    assert sorted(us)[len(us) // 2] < 250
 
 
 def test_run_calls_marshal_like_the_c_abi():
