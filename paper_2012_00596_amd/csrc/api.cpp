@@ -349,10 +349,11 @@ static bool plan_smallc_rows(const npas_packed *p, int N, int H, int W, int stri
     if ((double)H * W * p->C * 2.0 >= 2147483648.0 || (double)Ho * Wo * p->F * 2.0 >= 2147483648.0) return false; // an image within a buffer descriptor's range
     const double cols = (double)N * a->nblk;
     double best = 0;
-    for (int b = 1; b <= a->nsteps; ++b) {
+    for (int b = 1; b <= a->nsteps;) { // (every length of a band once: this is part of each run call)
         const int band = (a->nsteps + b - 1) / b, nband = (a->nsteps + band - 1) / band;
         const double waves = cols * nband, t = std::ceil(waves / 1024.0) * band + std::ceil(waves / 2048.0) * 3.0;
         if (b == 1 || t <= best) { best = t; a->band = band; a->nband = nband; }
+        b = band > 1 ? (a->nsteps - 1) / (band - 1) + 1 : a->nsteps + 1; // the first number of bands that makes them shorter
     }
     if (cols * a->nband * a->nblk * a->nband >= 4294967296.0) return false; // the kernel's reciprocals are exact below that
     a->nitems = (uint32_t)N * (uint32_t)(a->nblk * a->nband);
