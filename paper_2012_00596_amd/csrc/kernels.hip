@@ -1335,13 +1335,11 @@ __global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(Sma
 #pragma unroll
     for (int j = 0; j < FI; j += 2) nan |= __builtin_isunordered(vs[j], vs[(j + 1) % FI]);
     if (__builtin_expect(!__any(nan), 1)) return;
-#pragma unroll 1
+#pragma unroll
     for (int j = 0; j < FI; ++j) {
-        float sum = rf[j * 256];
-        for (int w = 1; w < NW; ++w) sum += rf[(w * NF + j) * 256];
-        if (sum == sum) continue;
-        float r = kept_sum<DT, SmallMArgs>(m, (uint32_t)(f + j)) + (a.bias ? a.bias[f + j] : 0.f);
-        if (a.residual) r += from_storage<DT>(reinterpret_cast<const uint16_t *>(a.residual)[o + j]);
+        if (vs[j] == vs[j]) continue;
+        float r = kept_sum<DT, SmallMArgs>(m, (uint32_t)(f + j)) + add[j];
+        if (a.residual) r += from_storage<DT>(rs[j]); // (y may be the residual's own place)
         y16[j] = to_storage<DT>(clampf(r, cl));
     }
 }

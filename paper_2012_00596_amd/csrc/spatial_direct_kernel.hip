@@ -71,8 +71,9 @@ __device__ __forceinline__ uint32_t direct_out_entry(const SpatialDirectArgs &a,
 // register i of acc[j][s] is tile pixel m0 + 16 s + i (m0 = the wave's first pixel + 4 q), filter fcol + j: a lane
 // writes 4 consecutive filters of a pixel, the 16 lanes of a quarter wave one whole 128-byte run of its row.  `ot`
 // points at the lane's entry m0 of the item's output offsets.  The activation kind and the residual are wave-uniform and compiled in.
+// HELD (wave-uniform): pixels with a sum that is NaN are not stored; their shortcut, which lies in y, is still to be read.
 template <int DT, int S0, int S1, int NB, bool HS, bool RES>
-__device__ __forceinline__ void direct_store_tile(const SpatialDirectArgs &a, const uint8_t *ot, const f32x4 (&acc)[4][NB], float4 b4, uint32_t fbyte, Clamp cl)
+__device__ __forceinline__ void direct_store_tile(const SpatialDirectArgs &a, const uint8_t *ot, const f32x4 (&acc)[4][NB], float4 b4, uint32_t fbyte, Clamp cl, bool held = false)
 {
     const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(a.y, 0, (int)a.ybytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.residual), 0, (int)a.ybytes, 0x00020000);
@@ -82,11 +83,14 @@ __device__ __forceinline__ void direct_store_tile(const SpatialDirectArgs &a, co
     for (int s = S0; s < S1; ++s) {
         __builtin_amdgcn_sched_barrier(0); // (a block's values and addresses one after the other: interleaved they spill beside the next item's weights)
         const uint4 p4 = *reinterpret_cast<const uint4 *>(ot + s * 64);
-        const uint32_t o[4] = {add_sat(p4.x, fbyte), add_sat(p4.y, fbyte), add_sat(p4.z, fbyte), add_sat(p4.w, fbyte)};
+        uint32_t o[4] = {add_sat(p4.x, fbyte), add_sat(p4.y, fbyte), add_sat(p4.z, fbyte), add_sat(p4.w, fbyte)};
         u32x2 r2[4];
         if (RES)
 #pragma unroll
             for (int i = 0; i < 4; ++i) r2[i] = (u32x2)__builtin_amdgcn_raw_buffer_load_b64(rr, (int)o[i], 0, 0);
+        if (RES && __builtin_expect(held, 0))
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = __builtin_isunordered(acc[0][s][i], acc[1][s][i]) || __builtin_isunordered(acc[2][s][i], acc[3][s][i]) ? kOutside : o[i];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float v[4] = {acc[0][s][i] + b4.x, acc[1][s][i] + b4.y, acc[2][s][i] + b4.z, acc[3][s][i] + b4.w};
@@ -104,10 +108,8 @@ __device__ __forceinline__ void direct_store_tile(const SpatialDirectArgs &a, co
         }
     }
 }
-// A sum that is NaN (an infinite input against the zero of a pruned weight) is formed again over the kept weights, behind the
-// stores.  One running maximum that lets NaN pass tells whether a lane has any.
-template <int DT, int S0, int S1, int NB, bool RES>
-__device__ __forceinline__ void direct_mend_nan(const uint8_t *ot, const f32x4 (&acc)[4][NB], int fcol)
+// Whether a sum of the wave is NaN: one running maximum that lets NaN pass.
+template <int S0, int S1, int NB> __device__ __forceinline__ bool direct_any_nan(const f32x4 (&acc)[4][NB])
 {
     float any = 0.f;
     __builtin_amdgcn_sched_barrier(0);
@@ -118,17 +120,30 @@ __device__ __forceinline__ void direct_mend_nan(const uint8_t *ot, const f32x4 (
             any = __builtin_elementwise_maximum(__builtin_elementwise_maximum(any, acc[0][s][i]), acc[1][s][i]);
             any = __builtin_elementwise_maximum(__builtin_elementwise_maximum(any, acc[2][s][i]), acc[3][s][i]);
         }
-    if (__builtin_expect(!__any(any != any), 1)) return;
-    auto ka = (const __attribute__((address_space(4))) SpatialDirectArgs *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(ka)); // (the arguments are read again: kept for this they would take registers from the loop)
-    const auto &a = *ka;
-    if (fcol >= a.F) return;
-    uint32_t todo = 0; // bit 4 s + i: one of that pixel's four sums is NaN
+    return __any(any != any);
+}
+// The lane's pixels (bit 4 s + i) one of whose four sums is NaN.
+template <int S0, int S1, int NB> __device__ __forceinline__ uint32_t direct_nan_pixels(const f32x4 (&acc)[4][NB])
+{
+    uint32_t todo = 0;
+    if (__builtin_expect(!direct_any_nan<S0, S1, NB>(acc), 1)) return todo;
 #pragma unroll
     for (int s = S0; s < S1; ++s)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             todo |= __builtin_isunordered(acc[0][s][i], acc[1][s][i]) || __builtin_isunordered(acc[2][s][i], acc[3][s][i]) ? 1u << (4 * s + i) : 0u;
+    return todo;
+}
+// A sum that is NaN (an infinite input against the zero of a pruned weight) is formed again over the kept weights, behind the
+// stores, and with it the other three of its pixel.  (In one place for all variants of the epilogue, by the bits alone: within one of
+// them the sums stayed in registers for the others.)
+template <int DT> __device__ __forceinline__ void direct_mend_nan(const uint8_t *ot, uint32_t todo, int fcol)
+{
+    if (__builtin_expect(!__any(todo), 1)) return;
+    auto ka = (const __attribute__((address_space(4))) SpatialDirectArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ka)); // (the arguments are read again: kept for this they would take registers from the loop)
+    const auto &a = *ka;
+    if (fcol >= a.F) return;
     const Clamp cl = clamp_of(a.act);
     const uint16_t *rp = reinterpret_cast<const uint16_t *>(a.residual);
     uint16_t *yp = reinterpret_cast<uint16_t *>(a.y);
@@ -141,24 +156,24 @@ __device__ __forceinline__ void direct_mend_nan(const uint8_t *ot, const f32x4 (
 #pragma unroll 1
         for (int j = 0; j < 4; ++j) {
             float v = kept_sum<DT, SpatialDirectArgs>(m, (uint32_t)fcol + j) + (a.bias ? a.bias[fcol + j] : 0.f);
-            if (RES) v += from_storage<DT>(rp[e + j]);
+            if (rp) v += from_storage<DT>(rp[e + j]);
             yp[e + j] = to_storage<DT>(clampf(v, cl));
         }
     }
 }
 template <int DT, int S0, int S1, int NB>
-__device__ __forceinline__ void direct_epilogue(const SpatialDirectArgs &a, const uint8_t *ot, const f32x4 (&acc)[4][NB], float4 b4, int fcol, Clamp cl)
+__device__ __forceinline__ uint32_t direct_epilogue(const SpatialDirectArgs &a, const uint8_t *ot, const f32x4 (&acc)[4][NB], float4 b4, int fcol, Clamp cl)
 {
     const uint32_t fbyte = fcol < a.F ? (uint32_t)fcol * 2u : kOutside;
-    if (a.residual) {
-        if (cl.hs) direct_store_tile<DT, S0, S1, NB, true, true>(a, ot, acc, b4, fbyte, cl);
-        else direct_store_tile<DT, S0, S1, NB, false, true>(a, ot, acc, b4, fbyte, cl);
-        direct_mend_nan<DT, S0, S1, NB, true>(ot, acc, fcol);
+    if (__builtin_expect(!a.residual, 1)) {
+        if (__builtin_expect(!cl.hs, 1)) direct_store_tile<DT, S0, S1, NB, false, false>(a, ot, acc, b4, fbyte, cl);
+        else direct_store_tile<DT, S0, S1, NB, true, false>(a, ot, acc, b4, fbyte, cl);
     } else {
-        if (cl.hs) direct_store_tile<DT, S0, S1, NB, true, false>(a, ot, acc, b4, fbyte, cl);
-        else direct_store_tile<DT, S0, S1, NB, false, false>(a, ot, acc, b4, fbyte, cl);
-        direct_mend_nan<DT, S0, S1, NB, false>(ot, acc, fcol);
+        const bool held = a.residual == a.y && direct_any_nan<S0, S1, NB>(acc); // (the shortcut added in place)
+        if (cl.hs) direct_store_tile<DT, S0, S1, NB, true, true>(a, ot, acc, b4, fbyte, cl, held);
+        else direct_store_tile<DT, S0, S1, NB, false, true>(a, ot, acc, b4, fbyte, cl, held);
     }
+    return direct_nan_pixels<S0, S1, NB>(acc);
 }
 
 constexpr int kDirectFetchWaves = 4, kDirectThreads = (4 + kDirectFetchWaves) * 64;
@@ -398,6 +413,7 @@ __global__ __launch_bounds__(kDirectThreads) void spatial_direct_kernel(SpatialD
         float4 b4 = float4{0.f, 0.f, 0.f, 0.f};
         if (a.bias) b4 = *reinterpret_cast<const float4 *>(lds + lbias + par * 1024u + (uint32_t)(wh * 64 + 4 * n16) * 4u);
         const uint8_t *ot = lds + lotab + (par * kPix + (uint32_t)(wg * NB * 16 + 4 * q)) * 4u;
+        uint32_t nan_pixels;
         if (KS == 2) {
             // the two shares of the reduction meet: wave 0 of a pair finishes pixel blocks 0 .. K0-1, wave 1 the others
             constexpr int K0 = (NB + 1) / 2;
@@ -425,7 +441,7 @@ __global__ __launch_bounds__(kDirectThreads) void spatial_direct_kernel(SpatialD
             }
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
-            if (wk == 0) direct_epilogue<DT, 0, K0, NB>(a, ot, acc, b4, fcol, cl);
+            if (wk == 0) nan_pixels = direct_epilogue<DT, 0, K0, NB>(a, ot, acc, b4, fcol, cl);
             else {
 #pragma unroll
                 for (int s = K0; s < NB; ++s)
@@ -435,10 +451,11 @@ __global__ __launch_bounds__(kDirectThreads) void spatial_direct_kernel(SpatialD
 #pragma unroll
                         for (int i = 0; i < 4; ++i) acc[j][s][i] += o[i];
                     }
-                direct_epilogue<DT, K0, NB, NB>(a, ot, acc, b4, fcol, cl);
+                nan_pixels = direct_epilogue<DT, K0, NB, NB>(a, ot, acc, b4, fcol, cl);
             }
         } else
-            direct_epilogue<DT, 0, NB, NB>(a, ot, acc, b4, fcol, cl);
+            nan_pixels = direct_epilogue<DT, 0, NB, NB>(a, ot, acc, b4, fcol, cl);
+        direct_mend_nan<DT>(ot, nan_pixels, fcol);
         if (!more_items) break;
         load_w(Wt[2]);
         c_item += nwg;

@@ -551,6 +551,11 @@ def _infinite_input_under_pruned_weights(npas, torch, L, N, H, W, dtype, res, ke
     assert npas.conv2d_kernel_name(p, N, H, W, L.stride, L.pad) == kernel
     y = run_layer_gpu(npas, torch, L, p, to_dev(xs, torch), xe.shape, dtype, None if rs is None else to_dev(rs, torch))
     assert rel_err(from_dev(y, dtype).reshape(ref.shape), ref) <= TOL[dtype]
+    if res:  # the shortcut added in place
+        y = to_dev(rs, torch)
+        npas.conv2d_sparse(p, to_dev(xs, torch), y, N, H, W, L.stride, L.pad, residual=y, act=L.act)
+        torch.cuda.synchronize()
+        assert rel_err(from_dev(y, dtype).reshape(ref.shape), ref) <= TOL[dtype]
 
 
 @pytest.mark.parametrize("C,F,N,HW,k,stride,rate,dtype,res", [(1280, 200, 37, 1, 1, 1, 2, dtypes.BF16, False), (1024, 1000, 300, 1, 1, 1, 2, dtypes.F16, False),
