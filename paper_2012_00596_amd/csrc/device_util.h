@@ -192,29 +192,50 @@ __device__ __forceinline__ void wait_vmcnt(uint32_t n)
 #undef NPAS_W
 }
 
-// The sum of one output (pixel m, filter f) over its kept weights, in channel order, from ring-format images: for the kernels that
-// multiply the zeros of pruned weights too and meet an infinite input.  (The kernel's arguments, a struct with the geometry
-// fields, are read again: kept for this they would take registers from the loop.)
-template <int DT, typename Args> __device__ __forceinline__ float kept_sum(uint32_t m, uint32_t f)
+// The sums of NF consecutive outputs (pixel m, filters f .. f + NF - 1 of one quad) over their kept weights, in channel order, from
+// ring-format images: for the kernels that multiply the zeros of pruned weights too and meet an infinite input.  16 bytes a load (in a plain
+// loop: it needs few registers beside the next item's weights), and an end as soon as all sums are NaN, because a map that has overflowed comes here
+// with all its outputs: 14 x 14 x 256 3x3 at batch 128, all inputs NaN 45 ms -> 0.11, one infinite channel 45 -> 4.4, one infinite value 8 -> 1.1.
+// (The kernel's arguments, a struct with the geometry fields, are read again: kept for this they would take registers from the loop.)
+template <int DT, typename Args, int NF> __device__ __forceinline__ void kept_sums(uint32_t m, uint32_t f, float (&v)[NF])
 {
     auto ka = (const __attribute__((address_space(4))) Args *)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(ka));
     const auto &a = *ka;
     const uint32_t n = m / (uint32_t)(a.Ho * a.Wo), p = m - n * (uint32_t)(a.Ho * a.Wo), oy = p / (uint32_t)a.Wo, ox = p - oy * (uint32_t)a.Wo;
     const int T = a.KH * a.KW, nch = a.C >> 6;
-    const uint32_t img = (f >> 6 & 1u) * 4u + (f & 3u), r = f >> 2 & 15u; // image of the 128-filter block, row of the image
+    const uint32_t img = (f >> 6 & 1u) * 4u + (f & 3u), r = f >> 2 & 15u; // first image of the 128-filter block, row of the images
     const uint16_t *w = reinterpret_cast<const uint16_t *>(a.wimg) + ((size_t)(f >> 7) * nch * T * 16 + img) * 512 + r * 8;
-    float v = 0.f;
-    for (int t = 0; t < T; ++t) {
+#pragma unroll
+    for (int j = 0; j < NF; ++j) v[j] = 0.f;
+    bool all = false;
+#pragma unroll 1
+    for (int t = 0; t < T && !all; ++t) {
         const int iy = (int)oy * a.stride - a.pad + t / a.KW, ix = (int)ox * a.stride - a.pad + t % a.KW;
-        if ((uint32_t)iy >= (uint32_t)a.H || (uint32_t)ix >= (uint32_t)a.W) continue;
-        const uint16_t *x = reinterpret_cast<const uint16_t *>(a.x) + (((size_t)n * a.H + iy) * a.W + ix) * a.C;
-        for (int c = 0; c < a.C; ++c) {
-            const uint16_t wc = w[((size_t)(c >> 6) * T + t) * 8192 + (c >> 5 & 1) * 4096 + (c >> 3 & 3) * 128 + (c & 7)];
-            if (wc & 0x7fffu) v = fmaf(from_storage<DT>(wc), from_storage<DT>(x[c]), v);
+        const bool in = (uint32_t)iy < (uint32_t)a.H && (uint32_t)ix < (uint32_t)a.W;
+        const uint16_t *x = reinterpret_cast<const uint16_t *>(a.x) + (((size_t)n * a.H + iy) * a.W + ix) * a.C, *wt = w + (size_t)t * 8192;
+#pragma unroll 1
+        for (int s = in ? 0 : 8 * nch; s < 8 * nch && !all; ++s) { // 8 channels
+            const uint4 xv = *reinterpret_cast<const uint4 *>(x + s * 8);
+            const uint32_t xs[4] = {xv.x, xv.y, xv.z, xv.w};
+            const uint16_t *ws = wt + (size_t)(s >> 3) * T * 8192 + (s >> 2 & 1) * 4096 + (s & 3) * 128;
+            uint4 wv[NF];
+#pragma unroll
+            for (int j = 0; j < NF; ++j) wv[j] = *reinterpret_cast<const uint4 *>(ws + j * 512);
+            all = true;
+#pragma unroll
+            for (int j = 0; j < NF; ++j) {
+                const uint32_t wc[4] = {wv[j].x, wv[j].y, wv[j].z, wv[j].w};
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const uint16_t c = (uint16_t)(wc[i >> 1] >> (i & 1) * 16);
+                    const float sum = fmaf(from_storage<DT>(c), from_storage<DT>((uint16_t)(xs[i >> 1] >> (i & 1) * 16)), v[j]);
+                    v[j] = c & 0x7fffu ? sum : v[j];
+                }
+                all = all && v[j] != v[j];
+            }
         }
     }
-    return v;
 }
 
 } // namespace npas

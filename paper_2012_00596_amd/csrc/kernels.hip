@@ -1334,11 +1334,13 @@ __global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(Sma
     bool nan = false;
 #pragma unroll
     for (int j = 0; j < FI; j += 2) nan |= __builtin_isunordered(vs[j], vs[(j + 1) % FI]);
-    if (__builtin_expect(!__any(nan), 1)) return;
+    if (__builtin_expect(!nan, 1)) return;
+    float kept[FI];
+    kept_sums<DT, SmallMArgs>(m, (uint32_t)f, kept);
 #pragma unroll
     for (int j = 0; j < FI; ++j) {
         if (vs[j] == vs[j]) continue;
-        float r = kept_sum<DT, SmallMArgs>(m, (uint32_t)(f + j)) + add[j];
+        float r = kept[j] + add[j];
         if (a.residual) r += from_storage<DT>(rs[j]); // (y may be the residual's own place)
         y16[j] = to_storage<DT>(clampf(r, cl));
     }

@@ -152,10 +152,11 @@ template <int DT> __device__ __forceinline__ void direct_mend_nan(const uint8_t 
         const uint32_t k = (uint32_t)__builtin_ctz(todo), o = *reinterpret_cast<const uint32_t *>(ot + (k >> 2) * 64u + (k & 3u) * 4u);
         if (o == kOutside) continue;
         const size_t e = (size_t)(o >> 1) + (size_t)(uint32_t)fcol;
-        const uint32_t m = (o >> 1) / (uint32_t)a.F;
-#pragma unroll 1
+        float sum[4];
+        kept_sums<DT, SpatialDirectArgs>((o >> 1) / (uint32_t)a.F, (uint32_t)fcol, sum);
+#pragma unroll
         for (int j = 0; j < 4; ++j) {
-            float v = kept_sum<DT, SpatialDirectArgs>(m, (uint32_t)fcol + j) + (a.bias ? a.bias[fcol + j] : 0.f);
+            float v = sum[j] + (a.bias ? a.bias[fcol + j] : 0.f);
             if (rp) v += from_storage<DT>(rp[e + j]);
             yp[e + j] = to_storage<DT>(clampf(v, cl));
         }

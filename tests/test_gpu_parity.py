@@ -577,6 +577,29 @@ def test_direct_weights_infinite_input_under_pruned_weights(npas, torch, C, F, N
     _infinite_input_under_pruned_weights(npas, torch, L, N, HW, HW, dtype, res, "spatial_direct")
 
 
+def test_direct_weights_on_a_map_that_has_overflowed(npas, torch):
+    """All outputs of a launch come to the sums over kept weights: about 60 us where all inputs are NaN, 1.4 ms where one channel is infinite (13 ms
+    each by loads of 2 bytes and to the end of every sum; 12 us for a finite map).  The bounds leave a factor of three and more."""
+    N, HW, C = 32, 28, 128
+    ws, _ = dtypes.quantize(prng.normal(33, 1, C * C * 9, 0.1).reshape(C, C, 3, 3), dtypes.BF16)
+    p = npas.pack_block_punched(ws, masks.block_punched_mask(C, C, 3, 3, 8, 1, 3, 33), 8, 1, dtypes.BF16)
+    assert npas.device_kernel(p, N, HW, HW, 1, 1) == "spatial_direct_kernel"
+    y = torch.empty(N, HW, HW, C, dtype=torch.bfloat16, device="cuda")
+    plane = torch.ones_like(y)
+    plane[..., 3] = float("inf")
+    for x, ms in ((torch.full_like(y, float("nan")), 0.5), (plane, 5.0)):
+        best = 1e9
+        for _ in range(3):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            npas.conv2d_sparse(p, x, y, N, HW, HW, 1, 1)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        print(f"  {best * 1e3:.0f} us", flush=True)
+        assert best < ms
+
+
 @pytest.mark.parametrize("off", [8, 2])
 def test_direct_weights_output_at_smaller_alignment(npas, torch, off):
     N, HW, C, F = 20, 28, 64, 72
