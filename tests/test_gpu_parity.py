@@ -172,7 +172,7 @@ EDGE = [
 ]
 
 
-def _run_edge_case(npas, torch, case, expect_kernel=None, device_kernel=None):
+def _run_edge_case(npas, torch, case, expect_kernel=None, device_kernel=None, direct_plan=None):
     name, N, H, W, C, F, KH, KW, stride, pad, Bf, Bc, rate, dtype, act, use_res, use_bias = case
     print(f"edge {name}", flush=True)
     xs, xe = dtypes.quantize(prng.normal(7, 1, N * H * W * C).reshape(N, H, W, C), dtype)
@@ -192,6 +192,9 @@ def _run_edge_case(npas, torch, case, expect_kernel=None, device_kernel=None):
         assert npas.conv2d_kernel_name(p, N, H, W, stride, pad) == expect_kernel
     if device_kernel is not None:
         assert npas.device_kernel(p, N, H, W, stride, pad) == device_kernel
+    if direct_plan is not None:
+        layout, _, items = npas.direct_plan(p, N, H, W, stride, pad)
+        assert (layout, items) == direct_plan
     y = run_layer_gpu(npas, torch, L, p, to_dev(xs, torch), (N, H, W, C), dtype,
                       None if rs is None else to_dev(rs, torch), None if bias is None else to_dev(bias, torch))
     got = from_dev(y, dtype).reshape(oshape)
@@ -233,7 +236,7 @@ RESIDENT = [
     ("res_ragged_filters_fp16", 2, 13, 11, 64, 40, 3, 3, 1, 1, 8, 4, 2, dtypes.F16, 2, False, True),
     ("res_two_chunks_2x2_pad0", 5, 9, 9, 128, 32, 2, 2, 1, 0, 4, 4, 2, dtypes.BF16, 0, True, False),
     ("res_several_images_per_tile", 37, 7, 7, 64, 64, 3, 3, 1, 1, 8, 4, 5, dtypes.BF16, 1, False, False),
-    ("res_more_items_than_workgroups", 20, 56, 56, 64, 16, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 1, False, True),
+    ("res_one_round_16_filters", 20, 56, 56, 64, 16, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 1, False, True),
 ]
 
 
@@ -270,28 +273,113 @@ def test_direct_weights_kernel_on_7x7_maps(npas, torch):
                    expect_kernel="spatial_direct")
 
 
-# The direct-weights kernel in every layout of its waves (pixel groups x filter halves x shares of the reduction) and several tile heights: one pixel,
-# four filters, tiles that end with the map or the batch, odd strided maps with and without padding, even and long kernels, one and several chunks,
-# more tiles than workgroups.  The comment gives the layout and the pixel blocks of a wave that the planner chooses.
+# The direct-weights kernel where its tiles and loops can go wrong: one pixel, four filters, tiles that end with the map or the batch, odd strided maps
+# with and without padding, even and long kernels, one and several chunks, more tiles than workgroups.  With the layout of the waves (pixel groups,
+# filter halves, shares of the reduction, pixel blocks of a wave) and the number of items that the planner chooses.
 DIRECT = [
-    ("dir_one_pixel_four_filters", 1, 1, 1, 64, 4, 3, 3, 1, 1, 4, 4, 2, dtypes.BF16, 1, True, True),            # 1 x 2 x 2, 3
-    ("dir_stride2_pad0", 2, 30, 29, 192, 68, 3, 3, 2, 0, 4, 4, 3, dtypes.BF16, 2, True, True),                   # 1 x 2 x 2, 3
-    ("dir_5x5_stride2_fp16", 5, 20, 31, 64, 132, 5, 5, 2, 2, 4, 4, 3, dtypes.F16, 3, False, True),               # 1 x 2 x 2, 3
-    ("dir_2x2_pad0", 200, 9, 9, 64, 64, 2, 2, 1, 0, 8, 4, 2, dtypes.BF16, 0, True, False),                       # 2 x 1 x 2, 3
-    ("dir_7x7", 3, 64, 64, 64, 64, 7, 7, 1, 3, 8, 4, 5, dtypes.BF16, 1, False, False),                           # 2 x 1 x 2, 3
-    ("dir_two_groups_two_shares", 17, 40, 40, 64, 64, 3, 3, 1, 1, 8, 4, 3, dtypes.F16, 2, True, True),           # 2 x 1 x 2, 4
-    ("dir_four_groups", 20, 33, 33, 64, 192, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 3, True, False),                  # 4 x 1 x 1, 5
-    ("dir_images_past_the_batch", 28, 40, 40, 64, 60, 3, 3, 1, 1, 4, 4, 3, dtypes.BF16, 1, False, True),         # 4 x 1 x 1, 3
-    ("dir_two_groups_two_halves", 21, 40, 40, 64, 128, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 1, True, True),         # 2 x 2 x 1, 5
-    ("dir_several_images_two_chunks", 130, 14, 14, 128, 256, 3, 3, 1, 1, 8, 4, 3, dtypes.F16, 1, True, False),   # 2 x 2 x 1, 7
-    ("dir_more_tiles_than_workgroups", 64, 28, 28, 64, 320, 3, 3, 2, 1, 8, 4, 3, dtypes.BF16, 0, False, True),   # 2 x 2 x 1, 3
+    (("dir_one_pixel_four_filters", 1, 1, 1, 64, 4, 3, 3, 1, 1, 4, 4, 2, dtypes.BF16, 1, True, True), (1, 2, 2, 3), 1),
+    (("dir_stride2_pad0", 2, 30, 29, 192, 68, 3, 3, 2, 0, 4, 4, 3, dtypes.BF16, 2, True, True), (1, 2, 2, 3), 56),
+    (("dir_5x5_stride2_fp16", 5, 20, 31, 64, 132, 5, 5, 2, 2, 4, 4, 3, dtypes.F16, 3, False, True), (1, 2, 2, 3), 160),
+    (("dir_2x2_pad0", 200, 9, 9, 64, 64, 2, 2, 1, 0, 8, 4, 2, dtypes.BF16, 0, True, False), (2, 1, 2, 3), 200),
+    (("dir_7x7", 3, 64, 64, 64, 64, 7, 7, 1, 3, 8, 4, 5, dtypes.BF16, 1, False, False), (2, 1, 2, 3), 144),
+    (("dir_two_groups_two_shares", 17, 40, 40, 64, 64, 3, 3, 1, 1, 8, 4, 3, dtypes.F16, 2, True, True), (2, 1, 2, 4), 255),
+    (("dir_four_groups", 20, 33, 33, 64, 192, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 3, True, False), (4, 1, 1, 5), 240),
+    (("dir_images_past_the_batch", 28, 40, 40, 64, 60, 3, 3, 1, 1, 4, 4, 3, dtypes.BF16, 1, False, True), (4, 1, 1, 3), 250),
+    (("dir_two_groups_two_halves", 21, 40, 40, 64, 128, 3, 3, 1, 1, 8, 4, 3, dtypes.BF16, 1, True, True), (2, 2, 1, 5), 252),
+    (("dir_several_images_two_chunks", 130, 14, 14, 128, 256, 3, 3, 1, 1, 8, 4, 3, dtypes.F16, 1, True, False), (2, 2, 1, 7), 238),
+    (("dir_more_tiles_than_workgroups", 64, 28, 28, 64, 320, 3, 3, 2, 1, 8, 4, 3, dtypes.BF16, 0, False, True), (2, 2, 1, 3), 480),
 ]
 
 
-@pytest.mark.parametrize("case", DIRECT, ids=[c[0] for c in DIRECT])
-def test_direct_weights_kernel(npas, torch, case, force_variant):
+@pytest.mark.parametrize("case,layout,items", DIRECT, ids=[c[0][0] for c in DIRECT])
+def test_direct_weights_kernel(npas, torch, case, layout, items, force_variant):
     force_variant("spatial")
-    _run_edge_case(npas, torch, case, expect_kernel="spatial_direct")
+    _run_edge_case(npas, torch, case, expect_kernel="spatial_direct", direct_plan=(layout, items))
+
+
+# Every layout that is compiled, in both 16-bit types, with more items than workgroups (a workgroup's second item: the other parity of its tables, the
+# exchange of the partial sums used again, the patch and weights asked for across the items): layout, items, N, H, W, C, F, k, stride, pad.  With 256
+# channels at stride 1 the first item asks for the next chunks' weights ahead and the second does not.
+DIRECT_LAYOUTS = [
+    ((1, 2, 2, 3), 510, 102, 30, 30, 64, 64, 5, 2, 2), ((1, 2, 2, 4), 504, 48, 37, 37, 64, 132, 3, 2, 0), ((1, 2, 2, 5), 754, 79, 31, 28, 256, 72, 3, 1, 0),
+    ((1, 2, 2, 6), 432, 81, 33, 33, 128, 132, 3, 2, 0), ((1, 2, 2, 7), 510, 104, 17, 16, 256, 196, 3, 1, 1),
+    ((2, 1, 2, 3), 500, 115, 39, 38, 64, 4, 2, 2, 1), ((2, 1, 2, 4), 477, 53, 33, 33, 64, 132, 3, 2, 1), ((2, 1, 2, 5), 512, 94, 28, 28, 256, 4, 5, 1, 2),
+    ((2, 1, 2, 6), 486, 89, 20, 20, 256, 132, 3, 1, 0), ((2, 1, 2, 7), 495, 87, 35, 34, 256, 4, 2, 1, 1),
+    ((2, 2, 1, 3), 490, 91, 28, 26, 64, 132, 2, 2, 1), ((2, 2, 1, 4), 510, 64, 32, 29, 256, 72, 2, 1, 1), ((2, 2, 1, 5), 460, 46, 38, 36, 64, 72, 2, 1, 0),
+    ((2, 2, 1, 6), 512, 64, 36, 33, 64, 72, 2, 1, 1), ((2, 2, 1, 7), 486, 90, 37, 34, 256, 72, 2, 1, 0),
+    ((4, 1, 1, 3), 507, 65, 39, 37, 64, 4, 3, 1, 1), ((4, 1, 1, 4), 460, 115, 30, 30, 256, 4, 2, 1, 1), ((4, 1, 1, 5), 460, 115, 36, 35, 256, 4, 3, 1, 1),
+    ((4, 1, 1, 6), 420, 105, 39, 37, 64, 4, 2, 1, 1), ((4, 1, 1, 7), 444, 111, 40, 40, 64, 4, 5, 1, 2),
+]
+
+
+@pytest.mark.parametrize("dtype,infinite", [(dtypes.BF16, False), (dtypes.F16, True)], ids=["bf16", "fp16_infinite_inputs"])
+@pytest.mark.parametrize("case", DIRECT_LAYOUTS, ids=["x".join(map(str, c[0])) for c in DIRECT_LAYOUTS])
+def test_direct_weights_kernel_in_every_layout(npas, torch, case, dtype, infinite, force_variant):
+    """All images against the split-reduction kernel, the first, the middle and the last one (an item beyond the first 256) against the oracle, with
+    infinite inputs over pruned weights there too."""
+    layout, items, N, H, W, C, F, k, stride, pad = case
+    print(f"direct layout {layout}", flush=True)
+    L = configs._bp_conv(61, 0, C, F, k, stride, pad, 4, 4, 3, 0.1, dtype, configs.ACT_RELU6)
+    p = pack_layer(npas, L, dtype)
+    force_variant("spatial")
+    chosen, tile, n_items = npas.direct_plan(p, N, H, W, stride, pad)
+    assert (chosen, n_items) == (layout, items) and items > 256
+    Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+    td = torch.bfloat16 if dtype == dtypes.BF16 else torch.float16
+    g = torch.Generator(device="cuda").manual_seed(61)
+    x, res = torch.randn(N, H, W, C, generator=g, device="cuda").to(td), torch.randn(N, Ho, Wo, F, generator=g, device="cuda").to(td)
+    bias = torch.randn(F, generator=g, device="cuda")
+    if infinite:
+        for n in (0, N // 2, N - 1):
+            for i in range(4):
+                x[n, (5 * i) % Ho * stride, (7 * i + 3) % Wo * stride, (37 * i + 11) % C] = float("inf") if i & 1 else -float("inf")
+
+    def run():
+        y = torch.full((N, Ho, Wo, F), float("nan"), device="cuda").to(td)
+        npas.conv2d_sparse(p, x, y, N, H, W, stride, pad, bias=bias, residual=res, act=L.act)
+        torch.cuda.synchronize()
+        return y
+
+    y = run()
+    assert torch.equal(y.view(torch.int16), run().view(torch.int16))
+    force_variant("smallm")
+    other = run().double()
+    floor = 1e-3 * other.abs().max()
+    assert float(((y.double() - other).abs() / other.abs().clamp(min=floor)).max()) <= 2 * TOL[dtype]   # (each of the two within TOL)
+    for n in (0, N // 2, N - 1):
+        xe, fin = x[n:n + 1].double().cpu().numpy(), torch.isfinite(x[n:n + 1]).cpu().numpy()
+        acc = oracle.conv2d_masked(np.where(fin, xe, 0.0), L.w_exact, L.mask, stride, pad, bias.double().cpu().numpy(), res[n:n + 1].double().cpu().numpy(), configs.ACT_NONE)
+        inf = oracle.conv2d_masked(np.where(fin, 0.0, np.sign(xe)), np.sign(L.w_exact * L.mask), L.mask, stride, pad, None, None, configs.ACT_NONE)
+        assert (inf != 0).any() == infinite
+        ref = oracle.round_to(np.clip(np.where(inf > 0, np.inf, np.where(inf < 0, -np.inf, acc)), 0.0, 6.0), dtype)
+        err = rel_err(y[n:n + 1].double().cpu().numpy(), ref)
+        print(f"  image {n} err={err:.3e}", flush=True)
+        assert err <= TOL[dtype]
+
+
+def test_direct_weights_kernel_beyond_2_gib(npas, torch):
+    """Input and output of 3.96 GiB each, just below 2^31 elements: byte offsets beyond 2^31, those of padding beyond the tensors' ends.  200 times the same
+    53 images: each group of outputs has to be the first one's, whose images are checked against the oracle."""
+    N, HW, C = 10600, 56, 64
+    assert 2 ** 31 - 2 ** 25 < N * HW * HW * C < 2 ** 31
+    print("direct, 3.96 GiB", flush=True)
+    L = configs._bp_conv(62, 0, C, C, 3, 1, 1, 8, 4, 3, 0.1, dtypes.BF16, configs.ACT_NONE)
+    p = pack_layer(npas, L, dtypes.BF16)
+    assert npas.device_kernel(p, N, HW, HW, 1, 1) == "spatial_direct_kernel"
+    g = torch.Generator(device="cuda").manual_seed(62)
+    base = torch.randn(53, HW, HW, C, generator=g, device="cuda").to(torch.bfloat16)
+    x = base.repeat(200, 1, 1, 1)
+    y = torch.full_like(x, float("nan"))
+    npas.conv2d_sparse(p, x, y, N, HW, HW, 1, 1)
+    torch.cuda.synchronize()
+    for n in (0, 52):
+        ref = oracle.round_to(oracle.conv2d_masked(base[n:n + 1].double().cpu().numpy(), L.w_exact, L.mask, 1, 1), dtypes.BF16)
+        assert rel_err(y[n:n + 1].double().cpu().numpy(), ref) <= TOL[dtypes.BF16]
+    groups = y.view(200, -1).view(torch.int16)
+    for i in range(1, 200):
+        assert torch.equal(groups[i], groups[0]), i
+    del x, y, groups
+    torch.cuda.empty_cache()
 
 
 def test_config4_pattern_small_direct_weights_kernel(npas, torch, force_variant):
@@ -952,6 +1040,7 @@ STEM_POOL = [
     ("stem7x7_no_activation_fp16", 2, 64, 64, 3, 40, 7, 2, 3, 3, configs.ACT_NONE, dtypes.F16),
     ("conv3x3_stride1_4_channels", 2, 30, 33, 4, 32, 3, 1, 1, 4, configs.ACT_RELU6, dtypes.BF16),
     ("more_tiles_than_workgroups", 9, 224, 224, 3, 64, 7, 2, 3, 3, configs.ACT_RELU, dtypes.BF16),
+    ("more_tiles_than_workgroups_odd_width", 12, 224, 223, 3, 64, 7, 2, 3, 3, configs.ACT_RELU, dtypes.BF16),   # 672 tiles of the kernel that is not by rows
     # by kernel rows: partial blocks of 7 pooled columns, odd conv heights and widths, one pooled pixel, hard-swish
     ("rows_7x7_ragged", 3, 39, 58, 3, 64, 7, 2, 3, 3, configs.ACT_RELU, dtypes.BF16),
     ("rows_5x5_hard_swish_fp16", 2, 33, 62, 2, 44, 5, 2, 2, 2, configs.ACT_HARDSWISH, dtypes.F16),
