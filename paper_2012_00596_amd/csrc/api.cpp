@@ -178,8 +178,8 @@ static int check_run(const npas_packed *p, const void *x, void *y, int N, int H,
 
 // Tile plan of the direct-weights k x k kernel: how the four multiplying waves of a workgroup are laid out (pixel groups x 64-filter
 // halves x shares of the reduction, 16 NB pixels each) and a tile of NI images x TH x TW output pixels, by the time of the launch.
-// *t_us is that time, fitted to 449 layers (3x3, 5x5, 7x7, stride 1 and 2) in all layouts: within 4 % for half of them, 10 % for nine in ten;
-// the layout it picks is on average 2 % slower than the best one.  A step of 32 channels takes 78 ns (its loads) and 19 ns a pixel block, 26 where
+// *t_us is that time, fitted to layers of 3x3, 5x5 and 7x7 at stride 1 and 2 in all layouts: on 180 others within 6 % of the time for half of them, 13 % for nine
+// in ten; the layout it picks is on average 2 % slower than the best one, 7 % at nine in ten.  A step of 32 channels takes 78 ns (its loads) and 19 ns a pixel block, 26 where
 // every CU is at work (the clock falls); a chunk 0.6 us more, a workgroup's first patch 33 ns a KB.
 // Of the sizes that cut a side into the same number of parts only the smallest is a candidate (its patch is the smallest), and tiles that
 // would lose with every item at its quickest are passed over: a shape's first call takes some 50 us, a tenth of
@@ -336,7 +336,8 @@ static bool plan_smallc_pool(const npas_packed *p, int N, int H, int W, int stri
 
 // The stride-2 form of both on at most 3 channels whose rows are whole 4-byte words (conv_smallc_rows_kernel): waves walk down 16 conv columns each.
 // An image's pairs of conv rows are cut into as many bands as keep two waves on every SIMD busy: a wave's time is taken as its pairs times the waves
-// that share its SIMD, and three pairs' worth of start.
+// that share its SIMD, and three pairs' worth of start.  Of 232 layers against the whole-reduction kernel 1.37x on average; five took longer by 3 to 13 %
+// (one channel at 5 x 5 and 7 x 7, which that kernel does in one or two steps; 63 x 86 x 86 x 3 with a shortcut, 10.9 -> 12.5 us).
 static bool plan_smallc_rows(const npas_packed *p, int N, int H, int W, int stride, int pad, bool pool, SmallCRowsArgs *a)
 {
     if (!p->smallc.present || !smallc_rows_layer(p->C, p->KH, p->KW) || stride != 2 || (W * p->C) % 2) return false;
@@ -410,9 +411,9 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
     const bool gather = p->fmt.variant == V_MFMA_GATHER;
     const bool ring_ok = p->ring.present && (!gather || p->fmt.density >= 0.125);
     // Rounds of the kernel that splits the reduction over a workgroup's waves (one workgroup of 16 pixels x 16 .. 64
-    // filters or of 32 x 64 per CU, see launch_conv_smallm), and what it takes (us; fitted to 5.3 .. 57 us measured on the layers
-    // of the 50-layer stack at batch 2 .. 64, within a tenth there; over 1338 other layers with warm caches 0.82 .. 2.2 of the time,
-    // 1.23 in the middle: what follows from it was measured shape by shape, none slower than its former kernel by more than 5 %).
+    // filters or of 32 x 64 per CU, see launch_conv_smallm), and what it takes, us: 0.95 .. 1.17 of the time of 72 k x k launches of two
+    // rounds and more.  In one round it is high (1.0 .. 2.7 of 744, fitted as it is to sixteen waves), which decides nothing: the direct-weights
+    // kernel is compared beyond one round only, and the tiled kernels take longer still.
     const long Ho1 = (H + 2 * pad - p->KH) / stride + 1, Wo1 = (W + 2 * pad - p->KW) / stride + 1, M1 = (long)N * Ho1 * Wo1;
     const long halves = (p->F + 63) / 64, blocks = (M1 + 15) / 16, steps = (long)(p->C / 32) * p->KH * p->KW;
     const long rounds = blocks * halves <= 256 ? 1 : ((blocks + 1) / 2 * halves + 255) / 256;
@@ -421,12 +422,12 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
     // sparse 1x1 / FC layer on few pixels: the exact per-tile lists (nothing pruned is multiplied, compact weights) ...
     if (p->fc.present && p->KH == 1 && p->KW == 1 && pad == 0 && M1 <= 1024 && switches().force != FV_NOFCGATHER) {
         // ... unless the weights are many and either little of them is skipped or there are few pixels to gather them for: the dense
-        // images are then quicker to stream than the lists to follow (1280 -> 1000 at 2x, 64 / 256 / 512 rows: 4.8 / 7.7 / 9.2 us ->
-        // 4.4 / 5.9 / 8.1, at 5x 4.6 / 5.6 / 5.9 against 4.4 / 5.8 / 8.1; 2048 -> 1000 at 5x, 128 rows 6.5 -> 5.9;
-        // 2432 -> 1372 at 5x, 256 rows 13.5 -> 11.0; 512 -> 1000 at 2x, 256 / 512 rows 4.8 / 5.1 against 4.4 / 5.4).
-        // The lines within that, where the lists are the quicker ones again: 256 channels and few rows (256 -> 1000 at 3x, 64 rows: 4.2
-        // against 4.4), a third kept in two pixel blocks a workgroup (2048 -> 1000, 512 rows: 10.0 against 10.4), a fifth kept in a
-        // launch that fills the chip (1280 -> 4096, 128 rows: 6.6 against 8.1) or of few weights (4096 -> 100, 512 rows: 7.9 against 8.6).
+        // images are then quicker to stream than the lists to follow (1280 -> 1000 at 5x, 64 rows: 4.6 -> 3.9 us; 2048 -> 1000 at 5x, 128 rows
+        // 6.2 -> 5.2; 4096 -> 1000 at 5x, 256 rows 14.1 -> 10.1; 256 -> 1000 at 3x, 128 rows 3.9 -> 3.0).  The lines within that were drawn
+        // where the lists were quicker than a split reduction of sixteen waves.  With eight, some still are right (1280 -> 1000 at 5x, 512 rows:
+        // 6.0 against 6.7; 1280 -> 4096 at 5x, 128 rows 6.1 against 6.6; 4096 -> 100 at 5x, 512 rows 7.1 against 7.6; 2048 -> 1000 at 3x,
+        // 512 rows 8.7 against 8.8), others keep the lists where they take longer: 110 of 306 launches of one round, by 5 % and more (256 -> 1000 at 3x, 64
+        // rows: 3.5 against 2.8).
         const double d = p->fmt.density, weights = (double)p->C * p->F;
         const long wgs = blocks * halves;
         const bool full = d > 0.3 && weights >= 131072.0 && (p->C >= 512 || (p->C >= 256 && M1 >= 128)) &&
@@ -438,17 +439,18 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
     SmallCArgs sc_local;
     if (p->smallc.present && plan_smallc(p, N, H, W, stride, pad, sc ? sc : &sc_local)) return R_SMALLC;
     if (ring_ok && p->KH == 1 && p->KW == 1 && pad == 0) {
-        // ahead of the ring's smallest tiles while it is one round (512 -> 128 at 28 x 28, batch 1: 6.5 -> 3.2 us, 128 -> 128 4.0 -> 2.7, 64 -> 256
-        // 3.9 -> 3.1; equal where the round is nearly full: 128 -> 512 at 28 x 28, batch 2: 4.5); not with two (64 -> 256 at 56 x 56: 6.2
-        // against 4.4, 512 -> 256 at 56 x 56 8.6 against 6.8)
+        // ahead of the ring's smallest tiles while it is one round (128 -> 128 at 28 x 28, batch 1: 3.9 -> 2.7 us, 64 -> 256 3.6 -> 2.8; of 357 launches
+        // none is quicker by more than 2 % on the ring); not with two (64 -> 256 at 56 x 56: 5.1 against 3.8, 512 -> 512 at 14 x 14, batch 8 7.6
+        // against 5.9)
         if (smallm_ok && rounds == 1) return R_SMALLM;
         return R_POINTWISE_RING;
     }
     const int fv = switches().force;
     if (p->stream.present && pad == 0) return R_STREAM;
-    // k x k: split over a workgroup's waves while that is one round (of 449 layers measured, one in thirty of these would be up to 8 % quicker
-    // direct: 64 -> 64 5x5 at 28 x 28, batch 8: 8.8 against 8.2 us), the direct-weights kernel beyond (28 x 28 x 128 at batch 8: 12.3 -> 7.5 us,
-    // 14 x 14 x 256 at batch 16 18.9 -> 12.0, 33 x 33, 192 -> 192 at batch 48 46.9 -> 34.4) unless the split is the quicker one by both estimates.
+    // k x k: split over a workgroup's waves while that is one round (none of 744 such launches is quicker by more than 5 % direct), the
+    // direct-weights kernel beyond (28 x 28 x 128 at batch 8: 11.5 -> 6.9 us, 14 x 14 x 256 at batch 16 17.2 -> 10.2, 33 x 33, 192 -> 192 at
+    // batch 48 41.9 -> 33.4) unless the split is the quicker one by both estimates.  Of 209 launches against the kernels before it, 1.40x on
+    // average, two took longer by more than 3 % (56 x 56, 448 -> 580 at batch 8: 93 -> 104; no other layout is quicker there).
     const bool kxk = ring_ok && (p->KH > 1 || p->KW > 1);
     const bool direct_forced = fv == FV_SPATIAL, direct_off = fv == FV_SMALLM;
     double t_direct = 0.0;

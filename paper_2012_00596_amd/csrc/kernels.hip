@@ -1175,7 +1175,7 @@ int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream)
 // What bounds such a launch is a chain: launch, addresses, one load latency, two barriers' worth of skew.  Its addresses are instructions of
 // every wave of the workgroup, so there are few of them (the steps are linear in the images and, for 1x1, in the pixels; a tap moves on from
 // the one before; the tile comes from a reciprocal) and eight waves instead of sixteen, whose prologues alone took 1700 of 6000 cycles; the
-// sums need one barrier: 56 x 56, 256 -> 64 at batch 1 4.1 -> 3.2 us, 14 x 14 x 256 3x3 5.3 -> 4.9, the 50-layer stack 267 -> 250.  Four waves 263; two
+// sums need one barrier: 56 x 56, 256 -> 64 at batch 1 4.0 -> 3.1 us, 14 x 14 x 256 3x3 5.2 -> 4.8, the 50-layer stack 267 -> 250.  Four waves 263; two
 // workgroups a CU (half the filters each) 259, half the CUs (twice the filters) 262.
 // A fragment load touches 16 lines where an image load touches 8 whole ones: the work is cut along the pixels first (16 a
 // workgroup), then as few filters each as keeps the launch within one workgroup per CU.

@@ -13,9 +13,9 @@
 //   * the four waves are 2 pixel groups x 2 filter halves, 4 x 1, or 1 x 2 and 2 x 1 with the reduction split over two waves that
 //     meet in LDS once per tile: with the tile's height free this fits one round of 256 workgroups to a map (14 x 14 x 256 at
 //     batch 128: one image x 128 filters each, 13 pixel blocks of 16 instead of 16).
-// bf16, alone: 14 x 14 x 256 at batch 128 31.9 -> 28.8 us, 28 x 28 x 128 34.5 -> 31.0, 7 x 7 x 512 36.6 -> 30.5, 56 x 56 x 64 40.1 -> 39.4; at stride 2
-// 256 -> 256 onto 14 x 14 43.6 -> 34.4; 256 -> 256 at 14 x 14, batch 16 18.9 -> 12.0; 192 -> 192 at 33 x 33, batch 48 46.9 -> 34.4.  At full batch the chip is then
-// power bound: 2.0 GHz under this kernel against 2.35 with a quarter of the CUs at work.
+// bf16, warm, against the streaming kernels before it: 14 x 14 x 256 at batch 128 30.3 -> 27.0 us, 28 x 28 x 128 32.8 -> 29.0, 7 x 7 x 512 34.7 -> 29.6,
+// 56 x 56 x 64 35.1 -> 33.7; at stride 2 256 -> 256 onto 14 x 14 42.0 -> 33.9; 192 -> 192 at 33 x 33, batch 48 41.9 -> 33.4; against the tiled and split ones
+// 256 -> 256 at 14 x 14, batch 16 17.2 -> 10.2.  A chip at work all over is slower: 256 items of 14 x 14 x 256 take 26.9 us, 64 of the same items 22.9.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

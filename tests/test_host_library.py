@@ -428,9 +428,9 @@ def test_run_calls_take_ctypes_values_and_stream_objects():
                                               (256, 1000, 3, 64, False), (256, 1000, 3, 128, True), (2048, 1000, 3, 512, False),
                                               (2048, 1000, 2, 512, True), (1280, 4096, 5, 128, False), (4096, 100, 5, 512, False),
                                               (4096, 1000, 5, 512, True)])
-def test_fc_layers_take_the_dense_images_where_those_are_quicker(C, F, rate, B, dense):
+def test_fc_layers_take_their_lists_or_the_dense_images(C, F, rate, B, dense):
     """The lists of an FC layer or its dense images: the shapes on both sides of each line of the rule (host logic; the times
-    stand at the rule)."""
+    on both sides, and where the lines no longer lie right, stand at the rule)."""
     m = masks.fc_block_mask(F, C, 16, 32, rate, 49)
     p = npas.pack_fc_block(np.zeros((F, C), np.uint16), m, 16, 32, dtypes.BF16)
     assert npas.conv2d_kernel_name(p, B, 1, 1, 1, 0) == ("conv_smallm_mfma" if dense else "fc_gather_mfma")
@@ -438,7 +438,7 @@ def test_fc_layers_take_the_dense_images_where_those_are_quicker(C, F, rate, B, 
 
 @pytest.mark.parametrize("C,F,N,HW,kernel", [(256, 256, 64, 7, "spatial_direct"), (256, 256, 16, 14, "spatial_direct"), (320, 320, 64, 7, "spatial_direct"),
                                              (512, 512, 32, 7, "spatial_direct"), (256, 256, 16, 7, "conv_smallm_mfma")])
-def test_low_density_3x3_layers_split_their_reduction_where_that_is_quicker(C, F, N, HW, kernel):
+def test_low_density_3x3_layers_take_the_kernels_of_the_denser_ones(C, F, N, HW, kernel):
     """3x3 layers at 10x in the gather format: the split-reduction kernel in one round of workgroups, the direct-weights kernel beyond, as at other
     densities above an eighth (host logic; the times stand at the rule)."""
     p = _bp_layer(C, F, 3, 50, rate=10)
