@@ -396,8 +396,9 @@ static double t_tiled(const npas_packed *p, int N, long Ho, long Wo, long steps,
     return 2.0 + (small_maps ? 0.21 : 0.33) * steps;
 }
 
+// (x_dwords: the input lies at a multiple of 4 bytes, as direct loads to LDS have to be asked for)
 static Route choose_route(const npas_packed *p, int N, int H, int W, int stride, int pad, SpatialDirectArgs *sp,
-                          SmallCArgs *sc = nullptr)
+                          SmallCArgs *sc = nullptr, bool x_dwords = true)
 {
     if (p->fmt.variant == V_VALU_F32) {
         // few lanes in all (a small layer: the launch is a chain of load latencies): split every reduction over 8 lanes
@@ -452,7 +453,7 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
     // batch 48 41.9 -> 33.4) unless the split is the quicker one by both estimates.  Of 209 launches against the kernels before it, 1.40x on
     // average, two took longer by more than 3 % (56 x 56, 448 -> 580 at batch 8: 93 -> 104; no other layout is quicker there).
     const bool kxk = ring_ok && (p->KH > 1 || p->KW > 1);
-    const bool direct_forced = fv == FV_SPATIAL, direct_off = fv == FV_SMALLM;
+    const bool direct_forced = fv == FV_SPATIAL, direct_off = fv == FV_SMALLM || !x_dwords;
     double t_direct = 0.0;
     if (kxk && !direct_off && (direct_forced || !smallm_ok || rounds > 1) && plan_direct(p, N, H, W, pad, stride, sp, &t_direct) &&
         (direct_forced || !smallm_ok || t_direct <= t_smallm))
@@ -495,7 +496,7 @@ int run_conv(const npas_packed *p, const ConvPlan *plan, const void *x, void *y,
     }
     SpatialDirectArgs sp;
     SmallCArgs sc;
-    const Route route = choose_route(p, N, H, W, stride, pad, &sp, &sc);
+    const Route route = choose_route(p, N, H, W, stride, pad, &sp, &sc, words(x, nullptr, nullptr));
     if (route == R_SMALLC) { // fewer than 8 input channels: whole reduction in a few MFMA steps
         SmallCRowsArgs rows;
         if (words(x, y, residual) && plan_smallc_rows(p, N, H, W, stride, pad, false, &rows)) return run_smallc_rows(p, rows, x, y, bias, residual, act, stream);

@@ -705,6 +705,31 @@ def test_direct_weights_output_at_smaller_alignment(npas, torch, off):
     assert (y1[:off // 2] == 0x7FC1).all() and (y1[off // 2 + n:] == 0x7FC1).all()
 
 
+@pytest.mark.parametrize("C,F,N,HW,stride,off", [(64, 72, 20, 28, 1, 8), (64, 72, 20, 28, 1, 2), (128, 128, 32, 28, 2, 4), (128, 128, 32, 28, 2, 2),
+                                                   (64, 128, 2, 21, 1, 2)],
+                         ids=["direct_8_bytes", "direct_2_bytes", "direct_s2_4_bytes", "direct_s2_2_bytes", "split_2_bytes"])
+def test_inputs_at_smaller_alignment(npas, torch, C, F, N, HW, stride, off):
+    """An input that starts 8, 4 or 2 bytes past an aligned address; at 2 bytes a launch of the direct-weights kernel, whose loads go to LDS, goes to a
+    kernel that loads into registers."""
+    L = configs._bp_conv(32, 0, C, F, 3, stride, 1, 8, 8, 2, 0.1, dtypes.BF16, configs.ACT_NONE)
+    p = pack_layer(npas, L, dtypes.BF16)
+    assert npas.device_kernel(p, N, HW, HW, stride, 1) == ("conv_smallm_mfma_kernel" if N == 2 else "spatial_direct_kernel")
+    xs, xe = configs._tensor(32, 1, (N, HW, HW, C), 1.0, dtypes.BF16)
+    Ho = (HW - 1) // stride + 1
+    ref = oracle.round_to(oracle.conv2d_masked(xe[:2], L.w_exact, L.mask, stride, 1), dtypes.BF16)
+    flat = np.zeros(xs.size + 16, np.uint16)
+    flat[off // 2:off // 2 + xs.size] = xs.reshape(-1)
+    y0, y = (new_dev((N, Ho, Ho, F), dtypes.BF16, torch, fill=0x7FC1) for _ in range(2))
+    x = to_dev(flat, torch)
+    npas.conv2d_sparse(p, x.data_ptr() + off, y, N, HW, HW, stride, 1)
+    npas.conv2d_sparse(p, to_dev(xs, torch), y0, N, HW, HW, stride, 1)
+    torch.cuda.synchronize()
+    got = from_dev(y, dtypes.BF16).reshape(N, Ho, Ho, F)
+    assert rel_err(got[:2], ref) <= TOL[dtypes.BF16]
+    # against the aligned call: another order of additions moves a value that lies on a rounding boundary by a bf16 step
+    assert rel_err(got, from_dev(y0, dtypes.BF16).reshape(got.shape)) <= TOL[dtypes.BF16]
+
+
 @pytest.mark.parametrize("C,F,N,HW,k,off", [(144, 40, 3, 29, 1, 8), (64, 128, 2, 21, 3, 2), (144, 40, 3, 29, 1, 2), (24, 960, 3, 29, 1, 8),
                                               (24, 960, 3, 29, 1, 2)],
                          ids=["flat_8_bytes", "split_2_bytes", "flat_2_bytes", "flat_groups_8_bytes", "flat_groups_2_bytes"])
