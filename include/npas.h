@@ -209,7 +209,8 @@ typedef struct {
 } npas_layer_desc;
 
 enum {
-    NPAS_STACK_FUSE_POINTWISE = 1,         /* allow a 1x1 -> act -> 1x1 pair to run as one kernel */
+    NPAS_STACK_FUSE_POINTWISE = 1,         /* allow a 1x1 -> act -> 1x1 pair to run as one kernel; also, at batch sizes where that is quicker, a 1x1 layer with a
+                                              residual together with the 1x1 layer that reads it and with a 1x1 projection in front whose output is that residual */
     NPAS_STACK_FUSE_INVERTED_RESIDUAL = 2, /* allow 1x1 -> depthwise 3x3 (stride 1 or 2) -> 1x1, each with or without bias, (+ block input at stride 1) to run as one kernel */
     NPAS_STACK_FUSE_CONV_MAXPOOL = 4       /* allow a conv on fewer than 8 channels (an image stem) and the max pool after it to run as one kernel */
 };
@@ -235,7 +236,8 @@ int npas_run_stack(const npas_stack *s, const void *x_dev, void *y_dev, int N, v
  * (different streams, or threads) race; calls on one stream are safe.  Nothing in the array needs clearing. */
 #define NPAS_STATIC_WORKSPACE_BYTES (32u << 20)
 int npas_run_stack_static(const npas_stack *s, const void *x_dev, void *y_dev, int N, void *hip_stream);
-/* Number of kernels one npas_run_stack call launches (after fusion). */
+/* Number of kernels one npas_run_stack call launches (after fusion; a run of 1x1 layers that becomes one launch only at some batch
+ * sizes, see NPAS_STACK_FUSE_POINTWISE, is counted and described layer by layer: there the call launches fewer). */
 int npas_stack_num_launches(const npas_stack *s);
 /* For tests and reports: the launches one npas_run_stack call makes for batch N, in order, and where their
  * tensors live.  Row r of rows_host (int64 [max_rows][NPAS_DESCRIBE_COLS]) =

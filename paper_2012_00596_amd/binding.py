@@ -11,7 +11,7 @@ _CSRC = os.path.join(_HERE, "csrc")
 _LIB = os.path.join(_HERE, "libnpas.so")
 _CALLS = os.path.join(_HERE, "_pycalls.so")  # CPython entry points of the run calls, linked to libnpas.so
 SOURCES = ["pack.cpp", "api.cpp", "kernels.hip", "spatial_direct_kernel.hip", "small_channel_rows_kernel.hip", "small_kernels.hip", "block_kernels.hip",
-           "inverted_residual_kernel.hip", "pointwise_stream_kernel.hip", "noalloc.hip"]
+           "inverted_residual_kernel.hip", "pointwise_stream_kernel.hip", "bottleneck_tail_kernel.hip", "noalloc.hip"]
 HEADER = os.path.join(os.path.dirname(_HERE), "include", "npas.h")
 
 F32, BF16, F16 = 0, 1, 2

@@ -266,6 +266,10 @@ bool plan_direct(const npas_packed *p, int N, int H, int W, int pad, int stride,
     return it->second.ok;
 }
 
+// A gather-format layer (few surviving positions) leaves the kernels that multiply every position of the operand images only the launches they win
+// (measured on the 3x3 256 -> 256 rate sweep and the 16 x 32-block FC layer): those above 1/8 density.
+static bool ring_usable(const npas_packed *p) { return p->ring.present && (p->fmt.variant != V_MFMA_GATHER || p->fmt.density >= 0.125); }
+
 // Which kernel a run call launches for this layer and geometry.
 enum Route { R_VALU, R_WAVE_F32, R_FC_GATHER, R_POINTWISE_RING, R_DIRECT, R_SMALLC, R_SMALLM, R_STREAM, R_SLAB, R_GATHER };
 
@@ -406,11 +410,8 @@ static Route choose_route(const npas_packed *p, int N, int H, int W, int stride,
         const bool small = (double)N * Ho0 * Wo0 * p->fmt.nvg * 8.0 <= 4.0 * 1024 * 1024;
         return p->wavef.present && small && switches().force != FV_VALU ? R_WAVE_F32 : R_VALU;
     }
-    // A gather-format layer (few surviving positions) leaves the ring kernels, which multiply
-    // everything, only the launches they win (measured on the 3x3 256 -> 256 rate sweep and the
-    // 16 x 32-block FC layer): those above 1/8 density.
     const bool gather = p->fmt.variant == V_MFMA_GATHER;
-    const bool ring_ok = p->ring.present && (!gather || p->fmt.density >= 0.125);
+    const bool ring_ok = ring_usable(p);
     // Rounds of the kernel that splits the reduction over a workgroup's waves (one workgroup of 16 pixels x 16 .. 64
     // filters or of 32 x 64 per CU, see launch_conv_smallm), and what it takes, us: 0.95 .. 1.17 of the time of 72 k x k launches of two
     // rounds and more.  In one round it is high (1.0 .. 2.7 of 744, fitted as it is to sixteen waves), which decides nothing: the direct-weights
@@ -673,8 +674,16 @@ struct npas_stack {
         const uint32_t *ir_wdw = nullptr;
         int ir_nslots = 0, ir_residual = 0;
         int ir_TH[3] = {0, 0, 0}, ir_TW[3] = {0, 0, 0}; // tiles of at most 32, 64 and any number of output pixels
+        int run = -1;                     // first layer of a run of 1x1 layers (see Run)
+    };
+    // Neighbouring 1x1 layers that one launch can take at the batch sizes where that is quicker: a projection whose only reader, the next layer,
+    // adds it to its own product (sum), and the layer that reads the sum (tail).
+    struct Run {
+        int first, add, last; // layers: the projection, or the adding layer itself; the adding layer; the last one covered
+        bool sum, tail;
     };
     std::vector<Node> nodes;
+    std::vector<Run> runs;
     std::vector<void *> blobs; // device allocations owned by the stack (fused-pair weight images)
     int H = 0, W = 0, C = 0, dtype = 0;
     unsigned flags = 0;
@@ -684,6 +693,7 @@ struct npas_stack {
     mutable int place_N = -1;
     mutable size_t place_need = 0;
     mutable std::vector<size_t> place_off;
+    mutable std::vector<char> place_runs; // runs whose inputs that placement keeps until the run's last layer
 };
 
 namespace npas {
@@ -700,10 +710,10 @@ static int absorbed_after(const npas_stack::Node &n) { return n.ir_head ? 2 : (n
 
 // Greedy first-fit placement of the intermediate tensors (1 .. n-1) into the
 // workspace; a tensor's slot is free again after the last launch reading it has run.
-// `last_use[t]` is the last layer reading tensor t; a fused launch reads its inputs while it writes the
+// last_use[t] is the last layer reading tensor t; a fused launch reads its inputs while it writes the
 // output of the last layer it absorbs, which npas_stack_create has recorded by moving last_use of those
 // inputs to that layer.  Returns total bytes; offsets[t] for intermediates.
-static size_t place_tensors(const npas_stack *s, int N, std::vector<size_t> *offsets)
+static size_t place_tensors(const npas_stack *s, int N, const std::vector<int> &last_use, std::vector<size_t> *offsets)
 {
     const int nt = (int)s->nodes.size() + 1;
     std::vector<size_t> off(nt, 0), sz(nt, 0);
@@ -726,11 +736,35 @@ static size_t place_tensors(const npas_stack *s, int N, std::vector<size_t> *off
             pos = std::max(pos, l.off + l.sz);
         }
         off[t] = pos;
-        live.push_back({pos, sz[t], s->last_use[t]});
+        live.push_back({pos, sz[t], last_use[t]});
         total = std::max(total, pos + sz[t]);
     }
     if (offsets) *offsets = off;
     return total;
+}
+
+// The same with the inputs of the runs of 1x1 layers kept until a run's last layer, for as many runs as that is possible without a larger
+// workspace (*runs: which).  Every tensor keeps a place of its own: whether a run is one launch is decided at the call.
+static size_t place_runs(const npas_stack *s, int N, std::vector<size_t> *offsets, std::vector<char> *runs)
+{
+    const size_t need = place_tensors(s, N, s->last_use, offsets);
+    runs->assign(s->runs.size(), 0);
+    std::vector<int> use = s->last_use;
+    for (size_t g = 0; g < s->runs.size(); ++g) {
+        const npas_stack::Run &r = s->runs[g];
+        std::vector<int> trial = use;
+        for (int j = r.first; j <= r.add; ++j) {
+            const npas_layer_desc &d = s->nodes[j].d;
+            trial[d.src] = std::max(trial[d.src], r.last);
+            if (d.res >= 0) trial[d.res] = std::max(trial[d.res], r.last);
+        }
+        std::vector<size_t> off;
+        if (place_tensors(s, N, trial, &off) > need) continue;
+        (*runs)[g] = 1;
+        *offsets = off;
+        use = trial;
+    }
+    return need;
 }
 
 } // namespace npas
@@ -896,6 +930,11 @@ static void plan_ir_tile(int Ho, int Wo, int nslots, int stride, int act1, int a
             }
         }
 }
+
+// Pixels from which the end of a bottleneck block and the next layer are one launch when the shortcut is a tensor: below, the weights' way into
+// LDS outweighs the bytes saved (64 -> 256 -> 64 on 25088 pixels 14.3 us in two launches, 14.7 in one; 37632: 25 -> 16; 401408: 128 -> 93).  With
+// the projection in the same launch it is quicker wherever the layers run on the ring (12544 pixels, three launches 18.3 -> 13.8 us).
+constexpr double kTailMinPixels = 32768;
 
 // a 16-bit 1 x 1 layer at stride 1 without padding (the fused block takes a bias, the fused pair does not)
 static bool is_pointwise16(const npas_layer_desc &d)
@@ -1238,6 +1277,34 @@ int npas_stack_create(const npas_layer_desc *layers, int n_layers, int H, int W,
             b.fused_away = true;
         }
     }
+    if (flags & NPAS_STACK_FUSE_POINTWISE) {
+        auto image_layer = [](const npas_layer_desc &d) { // a 16-bit 1x1 layer with operand images that its density lets it run on
+            return d.kind == NPAS_LAYER_CONV && d.packed->KH == 1 && d.packed->KW == 1 && d.pad == 0 && d.packed->dtype != NPAS_F32 && ring_usable(d.packed);
+        };
+        for (int i = 0; i < n_layers; ++i) {
+            const npas_layer_desc &d = s->nodes[i].d;
+            if (busy(s->nodes[i]) || !image_layer(d) || d.stride != 1 || d.res < 0) continue;
+            npas_stack::Run r{i, i, i, false, false};
+            if (i > 0 && d.res == i && d.src < i && !busy(s->nodes[i - 1])) {
+                const npas_layer_desc &p = s->nodes[i - 1].d;
+                bool other_reader = false;
+                for (int j = i; j < n_layers; ++j)
+                    if (s->nodes[j].d.src == i || (j != i && s->nodes[j].d.res == i)) other_reader = true;
+                r.sum = image_layer(p) && p.res < 0 && p.act == NPAS_ACT_NONE && !other_reader;
+            }
+            if (r.sum) r.first = i - 1;
+            if (i + 1 < n_layers && !busy(s->nodes[i + 1])) {
+                const npas_layer_desc &n = s->nodes[i + 1].d, &p = s->nodes[r.first].d;
+                r.tail = image_layer(n) && n.stride == 1 && n.src == i + 1 && n.res < 0 && d.packed->C == 64 && d.packed->F == 256 &&
+                         (n.packed->F == 64 || n.packed->F == 128) && d.act != NPAS_ACT_HARDSWISH && n.act != NPAS_ACT_HARDSWISH &&
+                         (!r.sum || (p.packed->C == 64 && p.stride == 1));
+            }
+            if (!r.tail) continue;
+            r.last = i + 1;
+            s->nodes[r.first].run = (int)s->runs.size();
+            s->runs.push_back(r);
+        }
+    }
     // A fused launch reads its inputs while it writes the output of the last layer it absorbs: keep them
     // allocated until then (the workspace placement frees a tensor after the layer recorded here).
     for (int i = 0; i < n_layers; ++i) {
@@ -1257,7 +1324,7 @@ int npas_stack_create(const npas_layer_desc *layers, int n_layers, int H, int W,
 size_t npas_stack_workspace_bytes(const npas_stack *s, int N)
 {
     if (!s || N <= 0) return 0;
-    return place_tensors(s, N, nullptr);
+    return place_tensors(s, N, s->last_use, nullptr);
 }
 
 int npas_stack_num_launches(const npas_stack *s)
@@ -1279,7 +1346,8 @@ int npas_stack_describe(const npas_stack *s, int N, int64_t *rows_host, int max_
         return NPAS_E_SHAPE;
     }
     std::vector<size_t> off;
-    (void)place_tensors(s, N, &off);
+    std::vector<char> runs;
+    (void)place_runs(s, N, &off, &runs);
     const int nl = (int)s->nodes.size();
     const int64_t esz = dtype_size(s->dtype);
     auto where = [&](int t) -> int64_t { return t < 0 ? -3 : t == 0 ? -1 : t == nl ? -2 : (int64_t)off[t]; };
@@ -1304,6 +1372,37 @@ int npas_stack_describe(const npas_stack *s, int N, int64_t *rows_host, int max_
 
 namespace npas {
 
+// Launches the first layers of a run as one kernel where the rule says so; *covered: how many (0: none).
+template <typename Tensor>
+static int run_pointwise_run(const npas_stack *s, const npas_stack::Run &r, int N, Tensor &&tensor, void *stream, int *covered)
+{
+    const npas_stack::Node &add = s->nodes[r.add], &proj = s->nodes[r.first];
+    const npas_packed *p3 = add.d.packed;
+    const double pixels = (double)N * add.H * add.W;
+    SpatialDirectArgs sp;
+    auto on_ring = [&](const npas_stack::Node &n) { return choose_route(n.d.packed, N, n.H, n.W, n.d.stride, 0, &sp) == R_POINTWISE_RING; };
+    if (r.tail && (r.sum || pixels >= kTailMinPixels) && pixels <= kTailMaxPixels && switches().force == FV_NONE && on_ring(add) && on_ring(s->nodes[r.last])) {
+        const npas_stack::Node &next = s->nodes[r.last];
+        TailArgs a;
+        a.a = tensor(add.d.src); a.y = tensor(r.add + 1); a.z = tensor(r.last + 1);
+        a.r = r.sum ? nullptr : tensor(add.d.res); a.x2 = r.sum ? tensor(proj.d.src) : nullptr;
+        a.b3 = (const float *)add.d.bias_dev; a.bsc = r.sum ? (const float *)proj.d.bias_dev : nullptr; a.b1 = (const float *)next.d.bias_dev;
+        a.w3 = p3->dev.wimg; a.wsc = r.sum ? proj.d.packed->dev.wimg : nullptr; a.w1 = next.d.packed->dev.wimg;
+        a.M = (uint32_t)pixels; a.act3 = add.d.act; a.act1 = next.d.act;
+        const uintptr_t all = (uintptr_t)a.a | (uintptr_t)a.y | (uintptr_t)a.z | (uintptr_t)a.r | (uintptr_t)a.x2;
+        if ((all & 15u) == 0) {
+            for (int j = r.first; j <= r.last; ++j) {
+                const npas_stack::Node &n = s->nodes[j];
+                int rc = check_run(n.d.packed, tensor(n.d.src), tensor(j + 1), N, n.H, n.W, n.d.stride, n.d.pad);
+                if (rc) return rc;
+            }
+            *covered = r.last - r.first + 1;
+            return launch_bottleneck_tail(p3->dtype, a, next.F, r.sum, stream);
+        }
+    }
+    return NPAS_OK;
+}
+
 // The body of npas_run_stack; also behind the allocation-free entry point.
 int run_stack_impl(const npas_stack *s, const void *x_dev, void *y_dev, int N, void *workspace_dev, size_t workspace_bytes,
                    void *hip_stream)
@@ -1319,7 +1418,7 @@ int run_stack_impl(const npas_stack *s, const void *x_dev, void *y_dev, int N, v
     // placement depends on N only; the last one is kept (and read under the lock: no copy, no allocation per call)
     std::lock_guard<std::mutex> lock(s->place_mu);
     if (s->place_N != N) {
-        s->place_need = place_tensors(s, N, &s->place_off);
+        s->place_need = place_runs(s, N, &s->place_off, &s->place_runs);
         s->place_N = N;
     }
     const std::vector<size_t> &off = s->place_off;
@@ -1340,6 +1439,15 @@ int run_stack_impl(const npas_stack *s, const void *x_dev, void *y_dev, int N, v
         const void *x = tensor(n.d.src);
         void *y = tensor(i + 1);
         int rc = NPAS_OK;
+        if (n.run >= 0 && s->place_runs[n.run]) { // this layer and the next one or two as one kernel, where that is quicker
+            int covered = 0;
+            rc = run_pointwise_run(s, s->runs[n.run], N, tensor, hip_stream, &covered);
+            if (rc) return rc;
+            if (covered) {
+                i += covered - 1;
+                continue;
+            }
+        }
         if (n.ir_head) { // this layer and the next two as one kernel; the tensors between them are never stored
             const npas_packed *p1 = n.d.packed, *p3 = s->nodes[i + 2].d.packed;
             rc = check_run(p1, x, tensor(i + 3), N, n.H, n.W, 1, 0);

@@ -322,6 +322,17 @@ struct SpatialDirectArgs {
     uint32_t div_tw, div_pw, div_thtw, div_phpw, div_nfb, div_tx, div_ty; // magic reciprocals
 };
 
+// 64 -> 256 (+ residual, or + a projection from 64 channels) and 256 -> 64 or 128 as one launch: see bottleneck_tail_kernel
+struct TailArgs {
+    const void *a, *r, *x2;     // r: residual (256 channels), x2: projection input (64 channels); the other one null
+    void *y, *z;
+    const float *b3, *bsc, *b1;
+    const void *w3, *wsc, *w1;  // ring-format images
+    uint32_t M;                 // pixels
+    int act3, act1;             // no hard-swish
+};
+constexpr uint32_t kTailMaxPixels = 8000000; // byte offsets of y stay 32-bit, also those of the pixels past the end that a wave asks for
+
 // Sparse 1x1 / FC layer on few pixels through the exact per-tile lists: see fc_gather_mfma_kernel
 struct FcGatherArgs {
     const void *x;
@@ -390,6 +401,7 @@ size_t spatial_direct_lds_bytes(int npb, int G, int KS, int NB); // LDS of a lau
 int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream);
 int launch_conv_smallc_rows(int dtype, const SmallCRowsArgs &a, void *stream);
 int launch_conv_smallm(int dtype, SmallMArgs a, void *stream);
+int launch_bottleneck_tail(int dtype, const TailArgs &a, int G, bool join, void *stream);
 int launch_fc_gather(int dtype, const FcGatherArgs &a, void *stream);
 bool pw_stream_supported(int C, int F);
 int launch_pointwise_stream(int dtype, PwStreamArgs a, void *stream);

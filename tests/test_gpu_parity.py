@@ -1197,6 +1197,55 @@ def test_config5_full_size_run_stack_batch2_logits(npas, torch, flags):
     assert (got.argmax(1) == ref.argmax(1)).all()
 
 
+def _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, proj_act, G, dtype, bias, act, flags):
+    """Stack x -> a (1x1, C), x -> s (1x1, 4C), y = act(W a + s), z = act(W y): (y, z) on the device, and from the oracle with the
+    projection rounded to storage only where it is a tensor of its own (proj_act is not none)."""
+    A = configs
+
+    def pw(idx, Ci, F, act, src, res=-1, st=1):
+        L = configs._bp_conv(7, idx, Ci, F, 1, st, 0, 8, 4, 2, (1.0 / Ci) ** 0.5, dtype, act, src, res, name=f"pw{idx}")
+        if bias:
+            L.bias = prng.normal(8, 300 + idx, F, 0.5).astype(np.float32)
+        return L
+
+    layers = [pw(0, C0, C, A.ACT_RELU, 0, st=stride), pw(1, C0, 4 * C, proj_act, 0, st=stride), pw(2, C, 4 * C, act, 1, 2)]
+    if G:
+        layers.append(pw(3, 4 * C, G, act, 3))
+    xs, xe = configs._tensor(9, 1, (N, HW, HW, C0), 1.0, dtype)
+    packed = [pack_layer(npas, L, dtype) for L in layers]
+    biases = helpers.bias_tensors(layers, torch)
+    st = npas.Stack(helpers.stack_descs(npas, layers, packed, biases), HW, HW, flags)
+    wsb, Ho = st.workspace_bytes(N), (HW - 1) // stride + 1
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
+    out = new_dev((N, Ho, Ho, G or 4 * C), dtype, torch, fill=0x7FC1)
+    st.run(to_dev(xs, torch), out, N, ws, wsb)
+    torch.cuda.synchronize()
+    got = [from_dev(out, dtype).reshape(N, Ho, Ho, -1)]
+    if G:
+        row = st.describe(N)[2]
+        got.insert(0, from_dev(ws[row["off_out"]:row["off_out"] + row["bytes_out"]].view(torch.int16), dtype).reshape(N, Ho, Ho, -1))
+    t = [xe]
+    for i, L in enumerate(layers):
+        v = oracle.run_layer(L, t, dtype)
+        t.append(v if flags and i == 1 and proj_act == A.ACT_NONE else oracle.round_to(v, dtype))
+    return got, t[3:]
+
+
+# 16 pixels a wave and block: a last block of 1, 15 and 16 pixels; fewer blocks than waves, more than one round of them; both widths of the
+# second layer; the projection and the residual (from 32768 pixels on).
+@pytest.mark.parametrize("N,HW,proj,G,dtype,bias,act", [
+    (1, 111, True, 64, dtypes.BF16, True, configs.ACT_RELU), (3, 47, True, 128, dtypes.F16, False, configs.ACT_RELU6),
+    (2, 192, True, 64, dtypes.BF16, False, configs.ACT_RELU), (1, 181, False, 64, dtypes.BF16, True, configs.ACT_RELU6),
+    (1, 184, False, 128, dtypes.F16, False, configs.ACT_NONE), (3, 161, False, 128, dtypes.BF16, False, configs.ACT_RELU)])
+def test_end_of_a_bottleneck_block_with_the_next_layer(npas, torch, N, HW, proj, G, dtype, bias, act):
+    print(f"bottleneck tail {N}x{HW}x{HW} projection={proj} G={G}", flush=True)
+    got, ref = _run_of_pointwise_layers(npas, torch, N, HW, 64, 64, 1, configs.ACT_NONE if proj else configs.ACT_RELU, G, dtype, bias, act,
+                                        npas.STACK_FUSE_POINTWISE)
+    for name, g, r in zip(("sum", "next layer"), got, ref):
+        norm, worst = helpers.check_stack_output(g, r, STACK_NORM_TOL if dtype == dtypes.BF16 else STACK_NORM_TOL / 8)
+        print(f"  {name}: norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
+
+
 def test_chained_fused_launches_against_the_oracle(npas, torch):
     """Fused launches whose inputs and outputs are workspace tensors (the placement must keep a fused launch's input
     alive while it writes the output of the last layer it absorbs): three fused 1x1 pairs of unequal widths in a row,

@@ -288,6 +288,25 @@ def test_fused_launches_never_write_over_their_own_inputs():
         assert rows[-1]["off_out"] == -2 and rows[0]["off_src"] == -1
 
 
+@pytest.mark.parametrize("N,HW", [(1, 64), (3, 96), (8, 224)])
+def test_runs_of_pointwise_layers_never_write_over_their_inputs(N, HW):
+    """A projection, the layer that adds it and the next layer may run as one launch: what the first two read is still there when the last one
+    writes, and the workspace is no larger than without."""
+    w = configs.config5(batch=1, HW=32, width=64, blocks=(2, 1, 1, 1))
+    plain, st = _stack(w.layers, HW, 0), _stack(w.layers, HW, npas.STACK_FUSE_POINTWISE)
+    assert st.workspace_bytes(N) <= plain.workspace_bytes(N)
+    rows = _assert_placement_is_safe(st, N)
+    at = {w.layers[r["first"]].name: r for r in rows}
+    for names in (("s0b0_sc", "s0b0_c3", "s0b1_c1"), ("s0b1_c3", "s1b0_c1")):
+        run = [at[n] for n in names]
+        reads = [(r["off_" + k], r["bytes_" + k]) for r in run[:-1] for k in ("src", "res") if r[k] >= 0 and r[k] not in [q["out"] for q in run]]
+        writes = [(r["off_out"], r["bytes_out"]) for r in run]
+        assert len(reads) == 2
+        for ro, rs in reads:
+            for wo, ws in writes:
+                assert ro + rs <= wo or wo + ws <= ro, names
+
+
 def test_a_layer_joins_one_fused_launch_only():
     """A 1x1 layer in front of a fused inverted-residual block must not swallow the block's first layer as the
     second half of a fused pair (the block would then never run)."""
