@@ -488,6 +488,67 @@ RouteNames route_names(const npas_packed *p, int N, int H, int W, int stride, in
     }
 }
 
+// Launches of the two 1x1 kernels (the second for any kernel size): everything but the tensors, the bias and the activation.
+static void plan_ring(const npas_packed *p, int N, int H, int W, int stride, RingArgs *a)
+{
+    a->rg_ptr = p->dev.rg_ptr; a->rg_chunk = p->dev.rg_chunk; a->wimg = p->dev.wimg;
+    a->C = p->C; a->F = p->F;
+    a->H = H; a->W = W; a->stride = stride;
+    a->Ho = (H - 1) / stride + 1; a->Wo = (W - 1) / stride + 1;
+    a->M = N * a->Ho * a->Wo;
+    a->xbytes = (uint32_t)((size_t)N * H * W * p->C * 2);
+    a->nptiles = (a->M + 255) / 256;
+    a->nfb = p->ring.nfb;
+    a->small = 0;
+    const long items_small = (long)((a->M + 63) / 64) * ((p->F + 63) / 64), items_med = (long)((a->M + 127) / 128) * a->nfb;
+    if ((long)a->nptiles * a->nfb < 96 && items_small > 256 && items_med <= 256) {
+        // ... unless those take two rounds where 128 x 128 tiles (four multiplying waves instead of one) take
+        // one: a stage costs about the same in both (1024 -> 256 at 14 x 14, batch 32: 19.9 -> 11.2 us)
+        a->small = 2;
+        a->nptiles = (a->M + 127) / 128;
+    } else if ((long)a->nptiles * a->nfb < 96) { // most CUs would get no tile: smaller tiles, deeper ring
+        a->small = 1;
+        a->nptiles = (a->M + 63) / 64;
+        a->nfb = (p->F + 63) / 64;
+    } else {
+        // 128 x 128 items (a little more than half the time of a 256 x 128 one: the weights are fetched
+        // per 128 pixels) when they divide over the 256 workgroups with fewer idle slots
+        const long big = (long)a->nptiles * a->nfb, med = (long)((a->M + 127) / 128) * a->nfb;
+        const double t_big = (double)((big + 255) / 256), t_med = 0.56 * (double)((med + 255) / 256);
+        if (t_med < 0.75 * t_big) {
+            a->small = 2;
+            a->nptiles = (a->M + 127) / 128;
+        }
+    }
+    // Items of equal size in whole rounds: with the number of rounds the full tiles need, as many pixel
+    // tiles as fill those rounds, each of P <= tile height pixels (784 items of 256 pixels on 256
+    // workgroups are 4 rounds, the last all but empty; 1008 items of 200 pixels are 4 rounds of 200).
+    const int th = a->small == 1 ? 64 : a->small == 2 ? 128 : 256;
+    a->P = th;
+    if (a->small != 1 && !switches().no_balance) {
+        const long rounds = ((long)a->nptiles * a->nfb + 255) / 256;
+        const long want = rounds * 256 / a->nfb; // pixel tiles that fill the rounds
+        if (want > a->nptiles) {
+            const int pp = (int)((a->M + want - 1) / want);
+            a->P = std::max(th / 2, std::min(th, (pp + 7) / 8 * 8));
+            a->nptiles = (a->M + a->P - 1) / a->P;
+        }
+    }
+    a->flat = stride == 1;
+    a->div_howo = magic_div((uint32_t)(a->Ho * a->Wo));
+    a->div_wo = magic_div((uint32_t)a->Wo);
+}
+static void plan_smallm(const npas_packed *p, int N, int H, int W, int stride, int pad, SmallMArgs *a)
+{
+    a->wimg = p->dev.wimg;
+    a->N = N; a->H = H; a->W = W; a->C = p->C; a->F = p->F;
+    a->Ho = (H + 2 * pad - p->KH) / stride + 1; a->Wo = (W + 2 * pad - p->KW) / stride + 1;
+    a->KH = p->KH; a->KW = p->KW; a->stride = stride; a->pad = pad;
+    a->M = N * a->Ho * a->Wo;
+    a->div_howo = magic_div((uint32_t)(a->Ho * a->Wo)); a->div_wo = magic_div((uint32_t)a->Wo);
+    a->div_kw = magic_div((uint32_t)p->KW); a->div_T2 = magic_div((uint32_t)(2 * p->KH * p->KW));
+}
+
 int run_conv(const npas_packed *p, const ConvPlan *plan, const void *x, void *y, int N, int H, int W, int stride,
              int pad, const void *bias, const void *residual, int act, void *stream)
 {
@@ -508,13 +569,8 @@ int run_conv(const npas_packed *p, const ConvPlan *plan, const void *x, void *y,
     }
     if (route == R_SMALLM) {
         SmallMArgs a;
-        a.x = x; a.y = y; a.residual = residual; a.bias = (const float *)bias; a.wimg = p->dev.wimg;
-        a.N = N; a.H = H; a.W = W; a.C = p->C; a.F = p->F;
-        a.Ho = (H + 2 * pad - p->KH) / stride + 1; a.Wo = (W + 2 * pad - p->KW) / stride + 1;
-        a.KH = p->KH; a.KW = p->KW; a.stride = stride; a.pad = pad; a.act = act;
-        a.M = N * a.Ho * a.Wo;
-        a.div_howo = magic_div((uint32_t)(a.Ho * a.Wo)); a.div_wo = magic_div((uint32_t)a.Wo);
-        a.div_kw = magic_div((uint32_t)p->KW); a.div_T2 = magic_div((uint32_t)(2 * p->KH * p->KW));
+        plan_smallm(p, N, H, W, stride, pad, &a);
+        a.x = x; a.y = y; a.residual = residual; a.bias = (const float *)bias; a.act = act;
         return launch_conv_smallm(p->dtype, a, stream);
     }
     if (route == R_FC_GATHER) {
@@ -569,54 +625,9 @@ int run_conv(const npas_packed *p, const ConvPlan *plan, const void *x, void *y,
     }
     if (route == R_POINTWISE_RING) { // streaming 1x1 path
         RingArgs a;
+        plan_ring(p, N, H, W, stride, &a);
         a.x = x; a.y = y; a.residual = residual; a.bias = (const float *)bias;
-        a.rg_ptr = p->dev.rg_ptr; a.rg_chunk = p->dev.rg_chunk; a.wimg = p->dev.wimg;
-        a.C = p->C; a.F = p->F;
-        a.H = H; a.W = W; a.stride = stride;
-        a.Ho = (H - 1) / stride + 1; a.Wo = (W - 1) / stride + 1;
-        a.M = N * a.Ho * a.Wo;
-        a.xbytes = (uint32_t)((size_t)N * H * W * p->C * 2);
-        a.nptiles = (a.M + 255) / 256;
-        a.nfb = p->ring.nfb;
-        a.small = 0;
-        const long items_small = (long)((a.M + 63) / 64) * ((p->F + 63) / 64), items_med = (long)((a.M + 127) / 128) * a.nfb;
-        if ((long)a.nptiles * a.nfb < 96 && items_small > 256 && items_med <= 256) {
-            // ... unless those take two rounds where 128 x 128 tiles (four multiplying waves instead of one) take
-            // one: a stage costs about the same in both (1024 -> 256 at 14 x 14, batch 32: 19.9 -> 11.2 us)
-            a.small = 2;
-            a.nptiles = (a.M + 127) / 128;
-        } else if ((long)a.nptiles * a.nfb < 96) { // most CUs would get no tile: smaller tiles, deeper ring
-            a.small = 1;
-            a.nptiles = (a.M + 63) / 64;
-            a.nfb = (p->F + 63) / 64;
-        } else {
-            // 128 x 128 items (a little more than half the time of a 256 x 128 one: the weights are fetched
-            // per 128 pixels) when they divide over the 256 workgroups with fewer idle slots
-            const long big = (long)a.nptiles * a.nfb, med = (long)((a.M + 127) / 128) * a.nfb;
-            const double t_big = (double)((big + 255) / 256), t_med = 0.56 * (double)((med + 255) / 256);
-            if (t_med < 0.75 * t_big) {
-                a.small = 2;
-                a.nptiles = (a.M + 127) / 128;
-            }
-        }
-        // Items of equal size in whole rounds: with the number of rounds the full tiles need, as many pixel
-        // tiles as fill those rounds, each of P <= tile height pixels (784 items of 256 pixels on 256
-        // workgroups are 4 rounds, the last all but empty; 1008 items of 200 pixels are 4 rounds of 200).
-        const int th = a.small == 1 ? 64 : a.small == 2 ? 128 : 256;
-        a.P = th;
-        if (a.small != 1 && !switches().no_balance) {
-            const long rounds = ((long)a.nptiles * a.nfb + 255) / 256;
-            const long want = rounds * 256 / a.nfb; // pixel tiles that fill the rounds
-            if (want > a.nptiles) {
-                const int pp = (int)((a.M + want - 1) / want);
-                a.P = std::max(th / 2, std::min(th, (pp + 7) / 8 * 8));
-                a.nptiles = (a.M + a.P - 1) / a.P;
-            }
-        }
         a.act = act;
-        a.flat = stride == 1;
-        a.div_howo = magic_div((uint32_t)(a.Ho * a.Wo));
-        a.div_wo = magic_div((uint32_t)a.Wo);
         return launch_pointwise_ring(p->dtype, a, stream);
     }
     if (route == R_DIRECT) { // k x k on whole 64-channel chunks
@@ -931,10 +942,11 @@ static void plan_ir_tile(int Ho, int Wo, int nslots, int stride, int act1, int a
         }
 }
 
-// Pixels from which the end of a bottleneck block and the next layer are one launch when the shortcut is a tensor: below, the weights' way into
-// LDS outweighs the bytes saved (64 -> 256 -> 64 on 25088 pixels 14.3 us in two launches, 14.7 in one; 37632: 25 -> 16; 401408: 128 -> 93).  With
-// the projection in the same launch it is quicker wherever the layers run on the ring (12544 pixels, three launches 18.3 -> 13.8 us).
-constexpr double kTailMinPixels = 32768;
+// Pixels from which the end of a bottleneck block and the next layer are one launch: below, the weights' way into LDS outweighs the bytes saved.  With
+// a shortcut that is a tensor (64 -> 256 -> 64 on 25088 pixels 14.3 us in two launches, 14.7 in one; 37632: 25 -> 16; 401408: 128 -> 93), and with the
+// projection, against the adding layer with the projection inside and the next layer (-> 64 / 128 on 32768 pixels 16.4 / 16.6 us in two, 16.6 / 18.7 in
+// one; 37632: 29.6 / 30.1 -> 17.3 / 19.7).
+constexpr double kTailMinPixels = 32768, kTailMinPixelsProjection = 36864;
 
 // a 16-bit 1 x 1 layer at stride 1 without padding (the fused block takes a bias, the fused pair does not)
 static bool is_pointwise16(const npas_layer_desc &d)
@@ -1299,8 +1311,8 @@ int npas_stack_create(const npas_layer_desc *layers, int n_layers, int H, int W,
                          (n.packed->F == 64 || n.packed->F == 128) && d.act != NPAS_ACT_HARDSWISH && n.act != NPAS_ACT_HARDSWISH &&
                          (!r.sum || (p.packed->C == 64 && p.stride == 1));
             }
-            if (!r.tail) continue;
-            r.last = i + 1;
+            if (!r.tail && !r.sum) continue;
+            r.last = r.tail ? i + 1 : i;
             s->nodes[r.first].run = (int)s->runs.size();
             s->runs.push_back(r);
         }
@@ -1379,9 +1391,19 @@ static int run_pointwise_run(const npas_stack *s, const npas_stack::Run &r, int 
     const npas_stack::Node &add = s->nodes[r.add], &proj = s->nodes[r.first];
     const npas_packed *p3 = add.d.packed;
     const double pixels = (double)N * add.H * add.W;
+    if (switches().force != FV_NONE) return NPAS_OK;
     SpatialDirectArgs sp;
-    auto on_ring = [&](const npas_stack::Node &n) { return choose_route(n.d.packed, N, n.H, n.W, n.d.stride, 0, &sp) == R_POINTWISE_RING; };
-    if (r.tail && (r.sum || pixels >= kTailMinPixels) && pixels <= kTailMaxPixels && switches().force == FV_NONE && on_ring(add) && on_ring(s->nodes[r.last])) {
+    auto route = [&](const npas_stack::Node &n) { return choose_route(n.d.packed, N, n.H, n.W, n.d.stride, 0, &sp); };
+    auto on_ring = [&](const npas_stack::Node &n) { return route(n) == R_POINTWISE_RING; };
+    auto check = [&](int last) {
+        int rc = NPAS_OK;
+        for (int j = r.first; j <= last && !rc; ++j) {
+            const npas_stack::Node &n = s->nodes[j];
+            rc = check_run(n.d.packed, tensor(n.d.src), tensor(j + 1), N, n.H, n.W, n.d.stride, n.d.pad);
+        }
+        return rc;
+    };
+    if (r.tail && pixels >= (r.sum ? kTailMinPixelsProjection : kTailMinPixels) && pixels <= kTailMaxPixels && on_ring(add) && on_ring(s->nodes[r.last])) {
         const npas_stack::Node &next = s->nodes[r.last];
         TailArgs a;
         a.a = tensor(add.d.src); a.y = tensor(r.add + 1); a.z = tensor(r.last + 1);
@@ -1391,14 +1413,40 @@ static int run_pointwise_run(const npas_stack *s, const npas_stack::Run &r, int 
         a.M = (uint32_t)pixels; a.act3 = add.d.act; a.act1 = next.d.act;
         const uintptr_t all = (uintptr_t)a.a | (uintptr_t)a.y | (uintptr_t)a.z | (uintptr_t)a.r | (uintptr_t)a.x2;
         if ((all & 15u) == 0) {
-            for (int j = r.first; j <= r.last; ++j) {
-                const npas_stack::Node &n = s->nodes[j];
-                int rc = check_run(n.d.packed, tensor(n.d.src), tensor(j + 1), N, n.H, n.W, n.d.stride, n.d.pad);
-                if (rc) return rc;
-            }
+            if (int rc = check(r.last)) return rc;
             *covered = r.last - r.first + 1;
             return launch_bottleneck_tail(p3->dtype, a, next.F, r.sum, stream);
         }
+    }
+    if (!r.sum) return NPAS_OK;
+    // The projection as further stages of the adding layer's sum, wherever both take the same kernel: its output exists nowhere.  Quicker at every one of
+    // 120 shapes (64 .. 512 channels, maps of 2 x 2 .. 56 x 56, batch 1 .. 128, rates 2 and 5): by 1 to 30 % on the split reduction, 1.2-1.9x on the ring.
+    const void *x = tensor(add.d.src), *x2 = tensor(proj.d.src);
+    void *y = tensor(r.add + 1);
+    const npas_packed *p2 = proj.d.packed;
+    if (((uintptr_t)x | (uintptr_t)x2 | (uintptr_t)y) & 15u) return NPAS_OK;
+    const Route ra = route(add), rp = route(proj);
+    const auto split = [](Route v) { return v == R_SMALLM || v == R_FC_GATHER; };
+    if (ra == R_POINTWISE_RING && rp == R_POINTWISE_RING) {
+        if (int rc = check(r.add)) return rc;
+        RingJoinArgs a;
+        plan_ring(p3, N, add.H, add.W, 1, &a);
+        a.x = x; a.y = y; a.residual = nullptr; a.bias = (const float *)add.d.bias_dev; a.act = add.d.act;
+        a.x2 = x2; a.bias2 = (const float *)proj.d.bias_dev; a.wimg2 = p2->dev.wimg;
+        a.C2 = p2->C; a.H2 = proj.H; a.W2 = proj.W; a.stride2 = proj.d.stride;
+        a.x2bytes = (uint32_t)((size_t)N * proj.H * proj.W * p2->C * 2);
+        *covered = 2;
+        return launch_pointwise_ring_join(p3->dtype, a, stream);
+    }
+    if (split(ra) && split(rp) && std::ceil(std::ceil(pixels / 16) / 2) * ((p3->F + 63) / 64) <= 256) {
+        if (int rc = check(r.add)) return rc;
+        SmallMJoinArgs a;
+        plan_smallm(p3, N, add.H, add.W, 1, 0, &a);
+        a.x = x; a.y = y; a.residual = nullptr; a.bias = (const float *)add.d.bias_dev; a.act = add.d.act;
+        plan_smallm(p2, N, proj.H, proj.W, proj.d.stride, 0, &a.b);
+        a.b.x = x2; a.b.y = nullptr; a.b.residual = nullptr; a.b.bias = (const float *)proj.d.bias_dev; a.b.act = NPAS_ACT_NONE;
+        *covered = 2;
+        return launch_conv_smallm_join(p3->dtype, a, stream);
     }
     return NPAS_OK;
 }

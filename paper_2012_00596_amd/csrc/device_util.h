@@ -197,9 +197,10 @@ __device__ __forceinline__ void wait_vmcnt(uint32_t n)
 // loop: it needs few registers beside the next item's weights), and an end as soon as all sums are NaN, because a map that has overflowed comes here
 // with all its outputs: 14 x 14 x 256 3x3 at batch 128, all inputs NaN 45 ms -> 0.11, one infinite channel 45 -> 4.4, one infinite value 8 -> 1.1.
 // (The kernel's arguments, a struct with the geometry fields, are read again: kept for this they would take registers from the loop.)
-template <int DT, typename Args, int NF> __device__ __forceinline__ void kept_sums(uint32_t m, uint32_t f, float (&v)[NF])
+// (AT: bytes of the arguments in front of the struct.)
+template <int DT, typename Args, int NF, int AT = 0> __device__ __forceinline__ void kept_sums(uint32_t m, uint32_t f, float (&v)[NF])
 {
-    auto ka = (const __attribute__((address_space(4))) Args *)__builtin_amdgcn_kernarg_segment_ptr();
+    auto ka = (const __attribute__((address_space(4))) Args *)((const __attribute__((address_space(4))) uint8_t *)__builtin_amdgcn_kernarg_segment_ptr() + AT);
     asm volatile("" : "+s"(ka));
     const auto &a = *ka;
     const uint32_t n = m / (uint32_t)(a.Ho * a.Wo), p = m - n * (uint32_t)(a.Ho * a.Wo), oy = p / (uint32_t)a.Wo, ox = p - oy * (uint32_t)a.Wo;

@@ -615,15 +615,20 @@ __device__ __forceinline__ void pointwise_epilogue(uint8_t *yb0, uint32_t pitch,
     }
 }
 
-template <int DT, typename Cfg>
-__global__ __launch_bounds__(Cfg::kThreads) void pointwise_ring_kernel(RingArgs a)
+// JOIN: a second input and weights for it follow the first's stages in the same sum (a projection shortcut inside the layer that adds it), for 4 F
+// bytes a pixel less (the shortcut written and read) than two launches: batch 128, inside the 50-layer stack, 128 + 256 / 2 -> 512 at 28 x 28 94 -> 53 us,
+// 256 + 512 / 2 -> 1024 at 14 x 14 65 -> 50, 512 + 1024 / 2 -> 2048 at 7 x 7 52 -> 45.
+template <int DT, typename Cfg, bool JOIN>
+__global__ __launch_bounds__(Cfg::kThreads) void pointwise_ring_kernel(std::conditional_t<JOIN, RingJoinArgs, RingArgs> a)
 {
     constexpr int PW = Cfg::PW, FW = Cfg::FW, XW = Cfg::XW, WW = Cfg::WW, D = Cfg::D, NC = Cfg::kComputeWaves, S = Cfg::S;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const uint32_t lbase = (uint32_t)(uintptr_t)lds;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n16 = lane & 15, q = lane >> 4;
     const uint32_t nwg = gridDim.x, nitems = (uint32_t)(a.nptiles * a.nfb);
-    const int nst = a.C >> 6; // stages (64-channel chunks) per item
+    const int nst1 = a.C >> 6; // stages (64-channel chunks) per item, of the first input and in all
+    int nst = nst1;
+    if constexpr (JOIN) nst += a.C2 >> 6;
     const uint32_t nfb = (uint32_t)a.nfb;
     const uint32_t lbias = (uint32_t)D * Cfg::kStageBytes; // two 1 KB bias buffers (item parity)
     uint32_t c_item = xcd_remap(blockIdx.x, nwg);
@@ -634,7 +639,7 @@ __global__ __launch_bounds__(Cfg::kThreads) void pointwise_ring_kernel(RingArgs 
         const int wl = wave - NC - WW;
         const int nblocks = (a.P + 7) >> 3;                 // 8-pixel blocks of a tile that hold pixels of it
         const int nld = max(0, (nblocks - wl + XW - 1) / XW); // this wave's loads per stage
-        const u32x4 xr = buffer_of(a.x, a.xbytes);
+        u32x4 xr = buffer_of(a.x, a.xbytes);
         const uint32_t pcv = (uint32_t)((lane & 7) ^ (lane >> 3)) * 16u; // which 16-byte vector of its pixel this lane fetches
         auto in_byte = [&](uint32_t m) __attribute__((always_inline)) -> uint32_t { // byte offset in x of output pixel m's input pixel
             m = min(m, (uint32_t)a.M - 1u);
@@ -643,27 +648,45 @@ __global__ __launch_bounds__(Cfg::kThreads) void pointwise_ring_kernel(RingArgs 
             const uint32_t oy = fastdiv(r, a.div_wo), ox = r - oy * (uint32_t)a.Wo;
             return ((n * a.H + oy * a.stride) * a.W + ox * a.stride) * (uint32_t)a.C * 2u;
         };
-        uint32_t p_item = c_item, p_slot = 0, ppix[Cfg::kXLoads];
-        int p_t = 0;
-        bool p_done = false;
-        auto producer_item = [&]() __attribute__((always_inline)) {
-            const PointwiseItem pi = pointwise_item(nfb, p_item);
-            p_t = 0;
-#pragma unroll
-            for (int i = 0; i < Cfg::kXLoads; ++i) ppix[i] = in_byte(pi.ptile * (uint32_t)a.P + (uint32_t)((wl + XW * i) * 8 + (lane >> 3))) + pcv;
+        auto in_byte2 = [&](uint32_t m) __attribute__((always_inline)) -> uint32_t { // the same in the second input
+            if constexpr (JOIN) {
+                m = min(m, (uint32_t)a.M - 1u);
+                if (a.stride2 == 1) return m * (uint32_t)a.C2 * 2u;
+                const uint32_t n = fastdiv(m, a.div_howo), r = m - n * (uint32_t)(a.Ho * a.Wo);
+                const uint32_t oy = fastdiv(r, a.div_wo), ox = r - oy * (uint32_t)a.Wo;
+                return ((n * a.H2 + oy * a.stride2) * a.W2 + ox * a.stride2) * (uint32_t)a.C2 * 2u;
+            } else return 0u;
         };
-        producer_item();
+        uint32_t p_item = c_item, p_slot = 0, ppix[Cfg::kXLoads];
+        int p_t = 0, p_t0 = 0; // stage, first stage of its input
+        bool p_done = false;
+        auto producer_item = [&](bool second) __attribute__((always_inline)) {
+            const PointwiseItem pi = pointwise_item(nfb, p_item);
+#pragma unroll
+            for (int i = 0; i < Cfg::kXLoads; ++i) {
+                const uint32_t m = pi.ptile * (uint32_t)a.P + (uint32_t)((wl + XW * i) * 8 + (lane >> 3));
+                ppix[i] = (JOIN && second ? in_byte2(m) : in_byte(m)) + pcv;
+            }
+            if constexpr (JOIN) {
+                p_t0 = second ? nst1 : 0;
+                xr = second ? buffer_of(a.x2, a.x2bytes) : buffer_of(a.x, a.xbytes);
+            }
+        };
+        producer_item(false);
         auto produce = [&]() __attribute__((always_inline)) { // always issues its nld loads; past the end it repeats the last stage
             const uint32_t dst = lbase + p_slot * Cfg::kStageBytes + (uint32_t)wl * 1024u;
 #pragma unroll
             for (int i = 0; i < Cfg::kXLoads; ++i)
-                if (i < nld) lds_buffer16(xr, ppix[i], (uint32_t)p_t * 128u, dst + (uint32_t)(XW * i) * 1024u);
+                if (i < nld) lds_buffer16(xr, ppix[i], (uint32_t)(p_t - p_t0) * 128u, dst + (uint32_t)(XW * i) * 1024u);
             if (++p_slot == (uint32_t)D) p_slot = 0;
             if (!p_done) {
-                if (p_t + 1 < nst) ++p_t;
-                else if (p_item + nwg < nitems) {
+                if (p_t + 1 < nst) {
+                    ++p_t;
+                    if (JOIN && p_t == nst1) producer_item(true);
+                } else if (p_item + nwg < nitems) {
                     p_item += nwg;
-                    producer_item();
+                    p_t = 0;
+                    producer_item(false);
                 } else p_done = true;
             }
         };
@@ -695,14 +718,20 @@ __global__ __launch_bounds__(Cfg::kThreads) void pointwise_ring_kernel(RingArgs 
         bool p_done = false;
         auto produce = [&]() __attribute__((always_inline)) { // always issues its loads; past the end it repeats the last stage
             const uint32_t fb128 = FW == 2 ? pi.fb : pi.fb >> 1, half = FW == 2 ? 0u : pi.fb & 1u;
-            const uint32_t wsrc = (fb128 * (uint32_t)nst + (uint32_t)p_t) * 16384u;
+            u32x4 ws = wr;
+            uint32_t wsrc = (fb128 * (uint32_t)nst1 + (uint32_t)p_t) * 16384u;
+            if constexpr (JOIN)
+                if (p_t >= nst1) {
+                    ws = buffer_of(a.wimg2, 0xffffffffu);
+                    wsrc = (fb128 * (uint32_t)(nst - nst1) + (uint32_t)(p_t - nst1)) * 16384u;
+                }
             const uint32_t dst = lbase + p_slot * Cfg::kStageBytes + Cfg::kXBytes;
 #pragma unroll
             for (int i = 0; i < Cfg::kWLoads; ++i) {
                 const int img = wl + WW * i; // local image: step * (FW * 4) + (filter group) * 4 + row tile
                 if (i < nld) {
                     const uint32_t src_img = FW == 2 ? (uint32_t)img : (uint32_t)((img >> 2) * 8 + (img & 3)) + half * 4u;
-                    lds_buffer16(wr, (uint32_t)lane * 16u, wsrc + src_img * 1024u, dst + (uint32_t)img * 1024u);
+                    lds_buffer16(ws, (uint32_t)lane * 16u, wsrc + src_img * 1024u, dst + (uint32_t)img * 1024u);
                 }
             }
             if (++p_slot == (uint32_t)D) p_slot = 0;
@@ -717,9 +746,15 @@ __global__ __launch_bounds__(Cfg::kThreads) void pointwise_ring_kernel(RingArgs 
         };
         // bias of an item's filters (lanes past the tile fetch a copy that nobody reads)
         auto bias_block = [&](uint32_t fb, uint32_t buf) __attribute__((always_inline)) {
-            if (!a.bias || wl != 0) return;
+            const float *b = a.bias;
+            if constexpr (JOIN) { // the second input's behind them (whichever is there in both places, where one is not)
+                const float *b1 = b ? b : a.bias2, *b2 = a.bias2 ? a.bias2 : b;
+                if (!b1) return;
+                b = lane & (FW * 16) ? b2 : b1;
+            } else if (!b) return;
+            if (wl != 0) return;
             const int f = (int)fb * (FW * 64) + (lane & (FW * 16 - 1)) * 4;
-            lds_dma16(a.bias + (f < a.F ? f : 0), lbase + lbias + buf * 1024u);
+            lds_dma16(b + (f < a.F ? f : 0), lbase + lbias + buf * 1024u);
         };
         uint32_t bbuf = 0;
         bias_block(pi.fb, 0);
@@ -803,6 +838,11 @@ __global__ __launch_bounds__(Cfg::kThreads) void pointwise_ring_kernel(RingArgs 
         {
             float4 bv = float4{0.f, 0.f, 0.f, 0.f};
             if (a.bias) bv = *reinterpret_cast<const float4 *>(lds + lbias + bbuf * 1024u + (uint32_t)(wf * 64 + 4 * n16) * 4u);
+            if constexpr (JOIN)
+                if (a.bias2) {
+                    const float4 b2 = *reinterpret_cast<const float4 *>(lds + lbias + bbuf * 1024u + (uint32_t)(FW * 64 + wf * 64 + 4 * n16) * 4u);
+                    bv = float4{bv.x + b2.x, bv.y + b2.y, bv.z + b2.z, bv.w + b2.w};
+                }
             pointwise_epilogue<DT, S>(yb + obase, (uint32_t)a.F * 2u, rows_left, rb != nullptr, acc, res, bv, cl);
         }
         if (c_item + nwg >= nitems) break;
@@ -811,31 +851,31 @@ __global__ __launch_bounds__(Cfg::kThreads) void pointwise_ring_kernel(RingArgs 
     }
 }
 
-template <int DT, typename Cfg> static void launch_pointwise_cfg(const RingArgs &a, hipStream_t st)
+template <int DT, typename Cfg, typename Args> static void launch_pointwise_cfg(const Args &a, hipStream_t st)
 {
     static std::once_flag once; // one per instantiation
-    auto kern = pointwise_ring_kernel<DT, Cfg>;
+    auto kern = pointwise_ring_kernel<DT, Cfg, std::is_same_v<Args, RingJoinArgs>>;
     allow_lds_once(once, kern, (int)Cfg::kLdsBytes);
     const unsigned grid = (unsigned)std::min<long>((long)a.nptiles * a.nfb, 256);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(Cfg::kThreads), Cfg::kLdsBytes, st, a);
 }
 
 // a.small: 0 = 256 x 128 tiles, 1 = 64 x 64, 2 = 128 x 128; a.nptiles / a.nfb count that configuration's tiles.
-int launch_pointwise_ring(int dtype, const RingArgs &a, void *stream)
+template <typename Args> static int launch_ring(int dtype, const Args &a, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    if (dtype == NPAS_BF16) {
-        if (a.small == 1) launch_pointwise_cfg<NPAS_BF16, PointwiseSmall>(a, st);
-        else if (a.small == 2) launch_pointwise_cfg<NPAS_BF16, PointwiseMedium>(a, st);
-        else launch_pointwise_cfg<NPAS_BF16, PointwiseBig>(a, st);
-    } else if (dtype == NPAS_F16) {
-        if (a.small == 1) launch_pointwise_cfg<NPAS_F16, PointwiseSmall>(a, st);
-        else if (a.small == 2) launch_pointwise_cfg<NPAS_F16, PointwiseMedium>(a, st);
-        else launch_pointwise_cfg<NPAS_F16, PointwiseBig>(a, st);
-    } else {
+    if (dtype != NPAS_BF16 && dtype != NPAS_F16) {
         set_error("pointwise_ring needs a 16-bit storage type");
         return NPAS_E_DTYPE;
     }
+    auto pick = [&](auto dtc) {
+        constexpr int DT = decltype(dtc)::value;
+        if (a.small == 1) launch_pointwise_cfg<DT, PointwiseSmall>(a, st);
+        else if (a.small == 2) launch_pointwise_cfg<DT, PointwiseMedium>(a, st);
+        else launch_pointwise_cfg<DT, PointwiseBig>(a, st);
+    };
+    if (dtype == NPAS_BF16) pick(std::integral_constant<int, NPAS_BF16>{});
+    else pick(std::integral_constant<int, NPAS_F16>{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         set_error("pointwise_ring launch failed: %s", hipGetErrorString(e));
@@ -843,6 +883,8 @@ int launch_pointwise_ring(int dtype, const RingArgs &a, void *stream)
     }
     return NPAS_OK;
 }
+int launch_pointwise_ring(int dtype, const RingArgs &a, void *stream) { return launch_ring(dtype, a, stream); }
+int launch_pointwise_ring_join(int dtype, const RingJoinArgs &a, void *stream) { return launch_ring(dtype, a, stream); }
 
 template <int DT, int S>
 static int launch_mfma_inst(const ConvMfmaArgs &a, unsigned grid, size_t lds_bytes, hipStream_t st)
@@ -1185,9 +1227,12 @@ int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream)
 
 // ONE: 1x1 without padding (steps are linear in both operands and no tap lies outside).
 constexpr int kSmallMWaves = 8;
-template <int DT, int FI, int PB, bool ONE>
-__global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(SmallMArgs a)
+// JOIN (with ONE): a second input and its weights follow the first's steps in the same sum: one chain instead of two (128 + 256 / 2 -> 512 onto 28 x 28 at
+// batch 1 9.2 -> 5.5 us inside the 50-layer stack, 512 + 1024 / 2 -> 2048 onto 7 x 7 8.4 -> 5.7; the stack 243 -> 233).
+template <int DT, int FI, int PB, bool ONE, bool JOIN>
+__global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(std::conditional_t<JOIN, SmallMJoinArgs, SmallMArgs> a)
 {
+    static_assert(ONE || !JOIN, "two inputs: 1x1 without padding");
     constexpr int NW = kSmallMWaves;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n16 = lane & 15, q = lane >> 4;
@@ -1195,14 +1240,23 @@ __global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(Sma
     const uint32_t id = xcd_remap(blockIdx.x, gridDim.x);
     const uint32_t ft = a.div_np ? fastdiv(id, a.div_np) : id / (uint32_t)a.nptiles, ptile = id - ft * (uint32_t)a.nptiles;
     const uint32_t img = ft * FI, fb = img >> 3, tile8 = img & 7u; // first image: 128-filter block, image in it
-    const uint32_t S = (uint32_t)a.S;                              // 32-deep steps: (chunk * KH * KW + tap) * 2 + half
+    const uint32_t S1 = (uint32_t)a.S;                             // 32-deep steps: (chunk * KH * KW + tap) * 2 + half
+    uint32_t S = S1;
+    if constexpr (JOIN) S += (uint32_t)a.b.S;
     const uint32_t st0 = (uint32_t)wave * S / NW, st1 = (uint32_t)(wave + 1) * S / NW; // this wave's
-    const uint8_t *wb = reinterpret_cast<const uint8_t *>(a.wimg) + ((size_t)fb * S + st0) * 8192u + tile8 * 1024u;
+    const uint8_t *wb = reinterpret_cast<const uint8_t *>(a.wimg) + ((size_t)fb * S1 + st0) * 8192u + tile8 * 1024u;
     const uint32_t lane16 = (uint32_t)lane * 16u;
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, (int)a.xbytes, 0x00020000);
 
     uint32_t pix0[PB];    // byte of the lane's 8 channels in step 0, at tap (0, 0) (modulo 2^32 where it lies outside)
+    [[maybe_unused]] uint32_t pix2[PB]; // the same in the second input
     int iy0[PB], ix0[PB]; // input coordinates of that tap
+    __amdgpu_buffer_rsrc_t xr2 = xr;
+    const uint8_t *wb2 = wb;
+    if constexpr (JOIN) {
+        xr2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.b.x), 0, (int)a.b.xbytes, 0x00020000);
+        wb2 = reinterpret_cast<const uint8_t *>(a.b.wimg) + ((ptrdiff_t)fb * a.b.S + st0 - S1) * 8192 + tile8 * 1024u;
+    }
 #pragma unroll
     for (int s = 0; s < PB; ++s) {
         const uint32_t mc = min((ptile * PB + s) * 16u + (uint32_t)n16, (uint32_t)a.M - 1u); // (past the last pixel: that one again, not stored)
@@ -1215,6 +1269,15 @@ __global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(Sma
             in = (pn * (uint32_t)a.H + (uint32_t)iy0[s]) * (uint32_t)a.W + (uint32_t)ix0[s];
         }
         pix0[s] = in * (uint32_t)a.C * 2u + 16u * (uint32_t)q;
+        if constexpr (JOIN) {
+            uint32_t in2 = mc;
+            if (a.b.stride != 1) {
+                const uint32_t pn = fastdiv(mc, a.div_howo), pr = mc - pn * (uint32_t)(a.Ho * a.Wo);
+                const uint32_t oy = fastdiv(pr, a.div_wo), ox = pr - oy * (uint32_t)a.Wo;
+                in2 = (pn * (uint32_t)a.b.H + oy * (uint32_t)a.b.stride) * (uint32_t)a.b.W + ox * (uint32_t)a.b.stride;
+            }
+            pix2[s] = in2 * (uint32_t)a.b.C * 2u + 16u * (uint32_t)q - S1 * 64u; // (of step 0 of all, modulo 2^32)
+        }
     }
     f32x4 acc[PB][FI];
 #pragma unroll
@@ -1232,17 +1295,19 @@ __global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(Sma
     }
     constexpr int NB = PB == 2 ? 6 : FI == 4 ? 8 : 9; // steps in flight
     uint32_t off[PB];
-    for (uint32_t sb = st0; sb < st1; sb += NB, wb += NB * 8192u) {
+    for (uint32_t sb = st0; sb < st1; sb += NB, wb += NB * 8192u, wb2 += NB * 8192u) {
         uint4 wf[NB][FI], xf[NB][PB];
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
             const uint32_t st = sb + (uint32_t)u;
             if (st < st1) { // wave-uniform
                 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+                const bool second = JOIN && st >= S1;
 #pragma unroll
                 for (int s = 0; s < PB; ++s) {
                     uint32_t o;
-                    if (ONE) o = pix0[s] + st * 64u;
+                    if (JOIN) o = (second ? pix2[s] : pix0[s]) + st * 64u;
+                    else if (ONE) o = pix0[s] + st * 64u;
                     else {
                         if (u == 0 || !(st & 1u)) { // a tap begins: outside the map nothing is loaded (past the descriptor's range: zeros)
                             const bool ok = (uint32_t)(iy0[s] + (int)kh) < (uint32_t)a.H && (uint32_t)(ix0[s] + (int)kw) < (uint32_t)a.W;
@@ -1250,10 +1315,11 @@ __global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(Sma
                         }
                         o = off[s] | (st & 1u) * 64u; // (chunks are 128 bytes)
                     }
-                    xf[u][s] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(xr, (int)o, 0, 0));
+                    xf[u][s] = __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(second ? xr2 : xr, (int)o, 0, 0));
                 }
+                const uint8_t *wu = second ? wb2 : wb;
 #pragma unroll
-                for (int j = 0; j < FI; ++j) wf[u][j] = *reinterpret_cast<const uint4 *>(wb + (size_t)u * 8192u + (lane16 + (uint32_t)j * 1024u));
+                for (int j = 0; j < FI; ++j) wf[u][j] = *reinterpret_cast<const uint4 *>(wu + (size_t)u * 8192u + (lane16 + (uint32_t)j * 1024u));
                 if (!ONE && (st & 1u)) {
                     ++kw;
                     toff += (uint32_t)a.C * 2u;
@@ -1291,6 +1357,7 @@ __global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(Sma
 #pragma unroll
     for (int j = 0; j < FI; ++j) {
         add[j] = out && a.bias ? a.bias[f + j] : 0.f;
+        if constexpr (JOIN) add[j] += out && a.b.bias ? a.b.bias[f + j] : 0.f;
         rs[j] = out && a.residual ? reinterpret_cast<const uint16_t *>(a.residual)[o + j] : (uint16_t)0;
     }
     // ---- the partial sums meet in LDS: [wave][pixel block, image][row of the quarter][lane], added in wave order -----------
@@ -1337,6 +1404,12 @@ __global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(Sma
     if (__builtin_expect(!nan, 1)) return;
     float kept[FI];
     kept_sums<DT, SmallMArgs>(m, (uint32_t)f, kept);
+    if constexpr (JOIN) {
+        float k2[FI];
+        kept_sums<DT, SmallMArgs, FI, sizeof(SmallMArgs)>(m, (uint32_t)f, k2);
+#pragma unroll
+        for (int j = 0; j < FI; ++j) kept[j] += k2[j];
+    }
 #pragma unroll
     for (int j = 0; j < FI; ++j) {
         if (vs[j] == vs[j]) continue;
@@ -1346,8 +1419,9 @@ __global__ __launch_bounds__(kSmallMWaves * 64) void conv_smallm_mfma_kernel(Sma
     }
 }
 
-int launch_conv_smallm(int dtype, SmallMArgs a, void *stream)
+template <typename Args> static int launch_smallm(int dtype, Args a, void *stream)
 {
+    constexpr bool JOIN = std::is_same_v<Args, SmallMJoinArgs>;
     hipStream_t st = (hipStream_t)stream;
     const long halves = (a.F + 63) / 64, blocks = ((long)a.M + 15) / 16; // 64-filter halves (four images each), 16-pixel blocks
     const bool narrow = ((uintptr_t)a.y & 7u) != 0; // an output at less than 8-byte alignment: one image, 2-byte stores
@@ -1366,19 +1440,28 @@ int launch_conv_smallm(int dtype, SmallMArgs a, void *stream)
     }
     a.S = a.C / 32 * a.KH * a.KW;
     a.xbytes = (uint32_t)((size_t)a.N * a.H * a.W * a.C * 2);
+    if constexpr (JOIN) {
+        if (a.b.C % 64 != 0 || a.KH != 1 || a.KW != 1 || a.pad != 0 || (double)a.N * a.b.H * a.b.W * a.b.C >= 2147483648.0) {
+            set_error("conv_smallm_mfma: unsupported second input");
+            return NPAS_E_SHAPE;
+        }
+        a.b.S = a.b.C / 32;
+        a.b.xbytes = (uint32_t)((size_t)a.N * a.b.H * a.b.W * a.b.C * 2);
+    }
     a.div_np = a.nptiles > 1 && grid * a.nptiles <= 0xffffffffL ? (uint32_t)(((1ull << 32) + a.nptiles - 1) / a.nptiles) : 0u; // (0: by division)
     static std::once_flag once[2][4][2];
     auto go = [&](auto dtc, auto fic, auto pbc, auto onec) {
         constexpr int DT = decltype(dtc)::value, FI = decltype(fic)::value, PB = decltype(pbc)::value;
         constexpr bool ONE = decltype(onec)::value;
         const int lds_bytes = kSmallMWaves * FI * PB * 1024;
-        auto kern = conv_smallm_mfma_kernel<DT, FI, PB, ONE>;
+        auto kern = conv_smallm_mfma_kernel<DT, FI, PB, ONE, JOIN>;
         allow_lds_once(once[DT == NPAS_F16][PB == 2 ? 3 : FI >> 1][ONE], kern, lds_bytes);
         hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kSmallMWaves * 64), lds_bytes, st, a);
     };
     using std::integral_constant;
     auto shape = [&](auto dtc, auto fic, auto pbc) {
-        if (a.KH == 1 && a.KW == 1 && a.pad == 0) go(dtc, fic, pbc, std::true_type{});
+        if constexpr (JOIN) go(dtc, fic, pbc, std::true_type{});
+        else if (a.KH == 1 && a.KW == 1 && a.pad == 0) go(dtc, fic, pbc, std::true_type{});
         else go(dtc, fic, pbc, std::false_type{});
     };
     auto pick = [&](auto dtc) {
@@ -1397,6 +1480,8 @@ int launch_conv_smallm(int dtype, SmallMArgs a, void *stream)
     }
     return NPAS_OK;
 }
+int launch_conv_smallm(int dtype, const SmallMArgs &a, void *stream) { return launch_smallm(dtype, a, stream); }
+int launch_conv_smallm_join(int dtype, const SmallMJoinArgs &a, void *stream) { return launch_smallm(dtype, a, stream); }
 
 // ------------------------------------------------------------------------------
 template <int VB>

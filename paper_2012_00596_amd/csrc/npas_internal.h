@@ -282,6 +282,10 @@ struct SmallMArgs {
     int nptiles, S;
     uint32_t div_np, xbytes;
 };
+struct SmallMJoinArgs : SmallMArgs { // 1x1: b's product of its own input is added to the sum (its y, residual, act and tiles are not read)
+    SmallMArgs b;
+};
+static_assert(sizeof(SmallMJoinArgs) == 2 * sizeof(SmallMArgs), "the kernel finds b behind a struct of the same size");
 
 struct RingArgs {
     const void *x;
@@ -301,6 +305,13 @@ struct RingArgs {
     int flat;                   // 1: stride 1, input pixel index == output pixel index
     uint32_t div_howo, div_wo;  // magic reciprocals of Ho*Wo and Wo
     uint32_t xbytes;                // of x
+};
+struct RingJoinArgs : RingArgs { // the product of a second input is added to the sum
+    const void *x2;
+    const float *bias2;
+    const void *wimg2;
+    int C2, H2, W2, stride2;
+    uint32_t x2bytes;
 };
 
 // k x k layer, weights from the L2 to registers: see spatial_direct_kernel
@@ -400,7 +411,9 @@ int launch_spatial_direct(int dtype, const SpatialDirectArgs &a, void *stream);
 size_t spatial_direct_lds_bytes(int npb, int G, int KS, int NB); // LDS of a launch with npb patch blocks a buffer
 int launch_conv_smallc(int dtype, const SmallCArgs &a, void *stream);
 int launch_conv_smallc_rows(int dtype, const SmallCRowsArgs &a, void *stream);
-int launch_conv_smallm(int dtype, SmallMArgs a, void *stream);
+int launch_conv_smallm(int dtype, const SmallMArgs &a, void *stream);
+int launch_pointwise_ring_join(int dtype, const RingJoinArgs &a, void *stream);
+int launch_conv_smallm_join(int dtype, const SmallMJoinArgs &a, void *stream);
 int launch_bottleneck_tail(int dtype, const TailArgs &a, int G, bool join, void *stream);
 int launch_fc_gather(int dtype, const FcGatherArgs &a, void *stream);
 bool pw_stream_supported(int C, int F);

@@ -1232,11 +1232,12 @@ def _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, proj_act, G, dty
 
 
 # 16 pixels a wave and block: a last block of 1, 15 and 16 pixels; fewer blocks than waves, more than one round of them; both widths of the
-# second layer; the projection and the residual (from 32768 pixels on).
+# second layer; the residual (from 32768 pixels on) and the projection (from 36864 on; below, the two launches that take its place).
 @pytest.mark.parametrize("N,HW,proj,G,dtype,bias,act", [
     (1, 111, True, 64, dtypes.BF16, True, configs.ACT_RELU), (3, 47, True, 128, dtypes.F16, False, configs.ACT_RELU6),
     (2, 192, True, 64, dtypes.BF16, False, configs.ACT_RELU), (1, 181, False, 64, dtypes.BF16, True, configs.ACT_RELU6),
-    (1, 184, False, 128, dtypes.F16, False, configs.ACT_NONE), (3, 161, False, 128, dtypes.BF16, False, configs.ACT_RELU)])
+    (1, 184, False, 128, dtypes.F16, False, configs.ACT_NONE), (3, 161, False, 128, dtypes.BF16, False, configs.ACT_RELU),
+    (1, 193, True, 128, dtypes.F16, True, configs.ACT_RELU6), (3, 113, True, 64, dtypes.BF16, True, configs.ACT_NONE)])
 def test_end_of_a_bottleneck_block_with_the_next_layer(npas, torch, N, HW, proj, G, dtype, bias, act):
     print(f"bottleneck tail {N}x{HW}x{HW} projection={proj} G={G}", flush=True)
     got, ref = _run_of_pointwise_layers(npas, torch, N, HW, 64, 64, 1, configs.ACT_NONE if proj else configs.ACT_RELU, G, dtype, bias, act,
@@ -1244,6 +1245,21 @@ def test_end_of_a_bottleneck_block_with_the_next_layer(npas, torch, N, HW, proj,
     for name, g, r in zip(("sum", "next layer"), got, ref):
         norm, worst = helpers.check_stack_output(g, r, STACK_NORM_TOL if dtype == dtypes.BF16 else STACK_NORM_TOL / 8)
         print(f"  {name}: norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
+
+
+# The projection as further stages of the layer that adds it: the three tile sizes of the ring, one and two pixel blocks of the split reduction (1, 2 and
+# 4 images), layers that have exact lists too, a last tile of few pixels, strides 1 and 2 on odd maps, biases on both, hard-swish.
+@pytest.mark.parametrize("N,HW,C0,C,stride,dtype,bias,act", [
+    (1, 3, 64, 64, 1, dtypes.BF16, True, configs.ACT_RELU), (1, 14, 512, 256, 2, dtypes.BF16, True, configs.ACT_RELU),
+    (3, 15, 128, 128, 2, dtypes.F16, True, configs.ACT_HARDSWISH), (1, 28, 256, 128, 1, dtypes.BF16, False, configs.ACT_NONE),
+    (1, 57, 64, 64, 2, dtypes.BF16, True, configs.ACT_RELU6), (2, 41, 64, 64, 1, dtypes.F16, True, configs.ACT_RELU),
+    (9, 27, 128, 128, 2, dtypes.BF16, True, configs.ACT_HARDSWISH), (5, 61, 256, 128, 2, dtypes.F16, False, configs.ACT_RELU),
+    (3, 113, 192, 64, 2, dtypes.BF16, True, configs.ACT_RELU6), (7, 63, 64, 192, 1, dtypes.BF16, True, configs.ACT_NONE)])
+def test_projection_shortcut_inside_the_layer_that_adds_it(npas, torch, N, HW, C0, C, stride, dtype, bias, act):
+    print(f"projection joined {N}x{HW}x{HW} {C0} / {stride} + {C} -> {4 * C}", flush=True)
+    got, ref = _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, configs.ACT_NONE, 0, dtype, bias, act, npas.STACK_FUSE_POINTWISE)
+    norm, worst = helpers.check_stack_output(got[0], ref[0], STACK_NORM_TOL if dtype == dtypes.BF16 else STACK_NORM_TOL / 8)
+    print(f"  norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
 
 
 def test_chained_fused_launches_against_the_oracle(npas, torch):
