@@ -942,11 +942,11 @@ static void plan_ir_tile(int Ho, int Wo, int nslots, int stride, int act1, int a
         }
 }
 
-// Pixels from which the end of a bottleneck block and the next layer are one launch: below, the weights' way into LDS outweighs the bytes saved.  With
-// a shortcut that is a tensor (64 -> 256 -> 64 on 25088 pixels 14.3 us in two launches, 14.7 in one; 37632: 25 -> 16; 401408: 128 -> 93), and with the
-// projection, against the adding layer with the projection inside and the next layer (-> 64 / 128 on 32768 pixels 16.4 / 16.6 us in two, 16.6 / 18.7 in
-// one; 37632: 29.6 / 30.1 -> 17.3 / 19.7).
-constexpr double kTailMinPixels = 32768, kTailMinPixelsProjection = 36864;
+// Pixels from which the end of a bottleneck block with a shortcut that is a tensor and a next layer of 128 filters are one launch: below, the weights' way
+// into LDS outweighs the bytes saved (64 -> 256 -> 128 on 20480 pixels 15.6 us in two launches, 15.7 in one; 25088: 18.5 -> 16.3; 401408: 137 -> 105).
+// With 64 filters, or with the projection (against the adding layer with the projection inside, and the next layer), it is quicker wherever the layers run
+// on the ring, from 4097 pixels on (8192: 12.1 -> 9.9 us; projection: 5120, 128 filters 12.7 -> 11.3; 12288, 64 filters 14.2 -> 11.0).
+constexpr double kTailMinPixels = 24576;
 
 // a 16-bit 1 x 1 layer at stride 1 without padding (the fused block takes a bias, the fused pair does not)
 static bool is_pointwise16(const npas_layer_desc &d)
@@ -1403,7 +1403,7 @@ static int run_pointwise_run(const npas_stack *s, const npas_stack::Run &r, int 
         }
         return rc;
     };
-    if (r.tail && pixels >= (r.sum ? kTailMinPixelsProjection : kTailMinPixels) && pixels <= kTailMaxPixels && on_ring(add) && on_ring(s->nodes[r.last])) {
+    if (r.tail && (r.sum || s->nodes[r.last].F == 64 || pixels >= kTailMinPixels) && pixels <= kTailMaxPixels && on_ring(add) && on_ring(s->nodes[r.last])) {
         const npas_stack::Node &next = s->nodes[r.last];
         TailArgs a;
         a.a = tensor(add.d.src); a.y = tensor(r.add + 1); a.z = tensor(r.last + 1);

@@ -7,13 +7,15 @@
 // (2 (2 x 64 + 4 x 256 + G) in three).  All weights (64 .. 128 KB) lie in LDS for the life of the workgroup, so there is no ring and no barrier: a
 // wave is a stream of its own, 16 pixels at a time, and keeps the next 16 pixels' inputs (10 KB) on their way in registers.  Sixteen waves a
 // CU are 160 KB in flight.  Every weight image is read from LDS for one MFMA only: a quarter of the LDS rate at the speed of HBM.
-// 401408 pixels, bf16, inside the 50-layer stack: with the projection, G = 64, 165 us in three launches -> 63 (5.7 TB/s); with a residual, G = 64, 128 in
-// two -> 93 (5.5 TB/s), G = 128 137 -> 105.
+// 401408 pixels, bf16, inside the 50-layer stack: with the projection, G = 64, 165 us in three launches -> 58 (6.2 TB/s); with a residual, G = 64, 128 in
+// two -> 92 (5.6 TB/s), G = 128 137 -> 105.
 //
-// The weights are the row operand, the pixels the column operand.  Row r of tile t of a 32-filter chunk u is filter 32 u + 8 (r / 4) + 4 t + r % 4, so
-// that a lane's eight results of a chunk are eight consecutive channels of its pixel and, rounded, exactly the column operand of step u of the
-// next layer's reduction.  A lane's vectors of two chunks are one 128-byte line of its pixel together with three other lanes; accesses
-// of half a line each took 150 us where whole ones (swap_lines) take 105.
+// The weights are the row operand, the pixels the column operand.  Row r of image j of 64 filters is filter 4 r + j, so that a lane's results of four
+// images are sixteen consecutive channels of its pixel and, rounded, two column operands of the next layer's reduction (whose order of channels is
+// free: its images are read from LDS in the same one).  So the images lie in LDS as they lie in memory, 1 KB a load; put together from 16-byte
+// pieces in another order they took 7 us of every launch (25088 pixels with the projection, G = 64, 16.2 -> 12.8 us, with a residual 15.8 -> 14.0).
+// A lane's two vectors are one 128-byte line of its pixel together with three other lanes; accesses of half a line each took 150 us where whole
+// ones (swap_lines) take 105.
 // Blocks are dealt to the workgroups one by one, so that a last round of few blocks is spread over all CUs: in runs of 16, 105 -> 93.
 #include <hip/hip_runtime.h>
 
@@ -28,13 +30,6 @@
 namespace npas {
 
 constexpr int kTailWaves = 16;
-
-// 16 bytes of W[f][8 channels from c8] in ring-format images of nch 64-channel chunks
-__device__ __forceinline__ const uint8_t *ring_vector(const void *wimg, uint32_t nch, uint32_t f, uint32_t c8)
-{
-    const uint32_t img = ((f >> 7) * nch + (c8 >> 6)) * 16u + (c8 >> 5 & 1u) * 8u + (f >> 6 & 1u) * 4u + (f & 3u);
-    return reinterpret_cast<const uint8_t *>(wimg) + (size_t)img * 1024u + (((c8 >> 3 & 3u) * 16u + (f >> 2 & 15u)) * 16u);
-}
 
 template <int DT, int NG, bool JOIN>
 __global__ __launch_bounds__(kTailWaves * 64) void bottleneck_tail_kernel(TailArgs a)
@@ -58,12 +53,12 @@ __global__ __launch_bounds__(kTailWaves * 64) void bottleneck_tail_kernel(TailAr
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)off, 0, kStream);
     };
     const Clamp c3 = clamp_of(a.act3), c1 = clamp_of(a.act1);
-    // results of a tile pair, clamped and rounded: eight consecutive channels of a pixel
-    const auto rounded = [](const f32x4 (&d)[2], Clamp c) __attribute__((always_inline)) {
+    // half h of the results of a 64-filter chunk, clamped and rounded: eight consecutive channels of a pixel
+    const auto rounded = [](const f32x4 *d, int h, Clamp c) __attribute__((always_inline)) {
         uint32_t o[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            o[i] = pack2<DT>(__builtin_amdgcn_fmed3f(d[i >> 1][2 * (i & 1)], c.lo, c.hi), __builtin_amdgcn_fmed3f(d[i >> 1][2 * (i & 1) + 1], c.lo, c.hi));
+            o[i] = pack2<DT>(__builtin_amdgcn_fmed3f(d[2 * (i & 1)][2 * h + (i >> 1)], c.lo, c.hi), __builtin_amdgcn_fmed3f(d[2 * (i & 1) + 1][2 * h + (i >> 1)], c.lo, c.hi));
         return uint4{o[0], o[1], o[2], o[3]};
     };
 
@@ -83,7 +78,8 @@ __global__ __launch_bounds__(kTailWaves * 64) void bottleneck_tail_kernel(TailAr
     };
     const uint32_t nblk = (a.M + 15u) >> 4, stride = gridDim.x * (uint32_t)kTailWaves;
     uint32_t blk = (uint32_t)wave * gridDim.x + blockIdx.x;
-    const uint32_t lane_line = ((uint32_t)n16 & 7u), lane_vec = 16u * (uint32_t)q + (upper ? 64u : 0u); // pixel and byte of a line access
+    // pixel and byte of a line access: of a lane's operand (8 channels of each half line), of its results (16 consecutive channels)
+    const uint32_t lane_line = ((uint32_t)n16 & 7u), lane_vec = 16u * (uint32_t)q + (upper ? 64u : 0u), lane_res = 32u * (uint32_t)q + (upper ? 16u : 0u);
     uint4 av[NS], rv[JOIN ? 1 : 8];
     const auto fetch_a = [&](uint32_t b, uint4 (&v)[NS]) __attribute__((always_inline)) {
         const uint32_t o = (b * 16u + lane_line) * 128u + lane_vec;
@@ -93,20 +89,20 @@ __global__ __launch_bounds__(kTailWaves * 64) void bottleneck_tail_kernel(TailAr
     fetch_a(blk, av);
     if (!JOIN) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) rv[k] = load(rr, (blk * 16u + lane_line + 8u * (k & 1)) * 512u + lane_vec + 128u * (k >> 1));
+        for (int k = 0; k < 8; ++k) rv[k] = load(rr, (blk * 16u + lane_line + 8u * (k & 1)) * 512u + lane_res + 128u * (k >> 1));
     }
-    {   // images in LDS: [chunk u][tile][step] of the first layer, then [step u][tile] of the second; then the biases
-        const uint32_t lbase = (uint32_t)(uintptr_t)lds, row = 8u * (uint32_t)(n16 >> 2) + (uint32_t)(n16 & 3);
+    {   // images in LDS as they lie in memory: [64-filter chunk][step][image] of the first layer, [step][64-filter chunk][image] of the second; then the biases
+        const uint32_t lbase = (uint32_t)(uintptr_t)lds;
         for (uint32_t i = (uint32_t)wave; i < kY + kZ; i += kTailWaves) {
-            const uint8_t *src;
+            const void *src = a.w1;
+            uint32_t img;
             if (i < kY) {
-                const uint32_t s = i % NS, t = i / NS & 1u, u = i / (2 * NS), f = 32u * u + 4u * t + row, c8 = 32u * (s & 1u) + 8u * (uint32_t)q;
-                src = ring_vector(s < 2 ? a.w3 : a.wsc, 1u, f, c8);
-            } else {
-                const uint32_t v = (i - kY) % (2 * NG), u = (i - kY) / (2 * NG), f = 32u * (v >> 1) + 4u * (v & 1u) + row;
-                src = ring_vector(a.w1, 4u, f, 32u * u + 8u * (uint32_t)q);
-            }
-            lds_dma16(src, lbase + i * 1024u);
+                const uint32_t s = i / 4 % NS;
+                if (s < 2) src = a.w3;
+                else src = a.wsc;
+                img = ring_image(1u, i / (4 * NS), s & 1u, i & 3u);
+            } else img = ring_image(4u, (i - kY) / 4 % (NG / 2), (i - kY) / (2 * NG), i & 3u);
+            lds_dma16(reinterpret_cast<const uint8_t *>(src) + (size_t)img * 1024u + (uint32_t)lane * 16u, lbase + i * 1024u);
         }
         float *lb = reinterpret_cast<float *>(lds + (kY + kZ) * 1024u);
         if (tid < 32 * NU + 32 * NG) {
@@ -115,46 +111,46 @@ __global__ __launch_bounds__(kTailWaves * 64) void bottleneck_tail_kernel(TailAr
                 if (a.b3) b += a.b3[tid];
                 if (JOIN && a.bsc) b += a.bsc[tid];
             } else if (a.b1) b = a.b1[tid - 32 * NU];
-            lb[tid] = b;
+            lb[result_slot((uint32_t)tid)] = b;
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     }
     while (blk < nblk) {
-        const uint32_t next = blk + stride, yo = (blk * 16u + lane_line) * 512u + lane_vec, ro = yo + stride * 16u * 512u;
+        const uint32_t next = blk + stride, yo = (blk * 16u + lane_line) * 512u + lane_res, ro = yo + stride * 16u * 512u;
         uint4 an[NS];
         fetch_a(next, an);
 #pragma unroll
         for (int s = 0; s < NS; s += 2) swap_lines(av[s], av[s + 1]);
-        uint32_t wo = (uint32_t)lane * 16u, bo = (kY + kZ) * 1024u + 32u * (uint32_t)q;
-        asm volatile("" : "+v"(wo), "+v"(bo)); // keeps the weights from being read (and held) outside the loop
-        const uint8_t *wl = lds + wo, *bl = lds + bo;
-        f32x4 z[NG][2];
+        // (of 64 channels of y a lane holds 16 q .. 16 q + 15 as two operands, so its weights for operand h are the vector 2 q + h of the chunk's eight)
+        uint32_t wo = (uint32_t)lane * 16u, zo2 = (uint32_t)(n16 + 32 * (q & 1)) * 16u + (uint32_t)(q >> 1) * (2u * NG * 1024u), bo = (kY + kZ) * 1024u + 64u * (uint32_t)q;
+        asm volatile("" : "+v"(wo), "+v"(zo2), "+v"(bo)); // keeps the weights from being read (and held) outside the loop
+        const uint8_t *wl = lds + wo, *zl = lds + zo2, *bl = lds + bo;
+        f32x4 z[2 * NG]; // [64-filter chunk, image j][i]: filter 16 q + 4 i + j of the chunk
+        const auto biases = [&](int f, f32x4 *d) __attribute__((always_inline)) {
 #pragma unroll
-        for (int w = 0; w < NG; ++w)
+            for (int j = 0; j < 4; ++j) d[j] = *reinterpret_cast<const f32x4 *>(bl + f * 4 + 16 * j);
+        };
 #pragma unroll
-            for (int t = 0; t < 2; ++t) z[w][t] = *reinterpret_cast<const f32x4 *>(bl + (32 * NU + 32 * w + 4 * t) * 4);
+        for (int w = 0; w < NG / 2; ++w) biases(32 * NU + 64 * w, z + 4 * w);
 #pragma unroll
         for (int c = 0; c < NU / 2; ++c) { // 64 channels of y
             if (!JOIN) swap_lines(rv[2 * c], rv[2 * c + 1]);
-            uint4 o[2];
+            f32x4 d[4];
+            biases(64 * c, d);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int u = 2 * c + h;
-                f32x4 d[2];
+            for (int s = 0; s < NS; ++s)
 #pragma unroll
-                for (int t = 0; t < 2; ++t) d[t] = *reinterpret_cast<const f32x4 *>(bl + (32 * u + 4 * t) * 4);
+                for (int j = 0; j < 4; ++j) d[j] = mfma16<DT>(*reinterpret_cast<const uint4 *>(wl + ((c * NS + s) * 4 + j) * 1024), av[s], d[j]);
+            if (!JOIN) {
 #pragma unroll
-                for (int s = 0; s < NS; ++s)
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t r[4] = {rv[2 * c + h].x, rv[2 * c + h].y, rv[2 * c + h].z, rv[2 * c + h].w};
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) d[t] = mfma16<DT>(*reinterpret_cast<const uint4 *>(wl + ((u * 2 + t) * NS + s) * 1024), av[s], d[t]);
-                if (!JOIN) {
-                    const uint32_t r[4] = {rv[u].x, rv[u].y, rv[u].z, rv[u].w};
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) d[i >> 2][i & 3] += from_storage<DT>((uint16_t)(r[i >> 1] >> 16 * (i & 1)));
+                    for (int i = 0; i < 8; ++i) d[i & 3][2 * h + (i >> 2)] += from_storage<DT>((uint16_t)(r[i >> 1] >> 16 * (i & 1)));
                 }
-                o[h] = rounded(d, c3);
             }
+            uint4 o[2] = {rounded(d, 0, c3), rounded(d, 1, c3)};
             if (!JOIN) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) rv[2 * c + h] = load(rr, ro + 4096u * h + 128u * c);
@@ -162,16 +158,16 @@ __global__ __launch_bounds__(kTailWaves * 64) void bottleneck_tail_kernel(TailAr
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int v = 0; v < 2 * NG; ++v)
-                    z[v >> 1][v & 1] = mfma16<DT>(*reinterpret_cast<const uint4 *>(wl + (kY + (2 * c + h) * 2 * NG + v) * 1024), o[h], z[v >> 1][v & 1]);
+                for (int v = 0; v < 2 * NG; ++v) z[v] = mfma16<DT>(*reinterpret_cast<const uint4 *>(zl + (kY + 4 * c * NG + v) * 1024 + 256 * h), o[h], z[v]);
             swap_lines(o[0], o[1]);
 #pragma unroll
             for (int h = 0; h < 2; ++h) store(yr, yo + 4096u * h + 128u * c, o[h]);
+            if (JOIN || NG == 2) __builtin_amdgcn_sched_barrier(0); // (the next chunk's images read here cost spills, 63 -> 80 us; with a rolled loop the waits count stores)
         }
-        const uint32_t zo = (blk * 16u + lane_line) * (uint32_t)(NG * 64) + lane_vec;
+        const uint32_t zo = (blk * 16u + lane_line) * (uint32_t)(NG * 64) + lane_res;
 #pragma unroll
         for (int w = 0; w < NG; w += 2) {
-            uint4 o[2] = {rounded(z[w], c1), rounded(z[w + 1], c1)};
+            uint4 o[2] = {rounded(z + 2 * w, 0, c1), rounded(z + 2 * w, 1, c1)};
             swap_lines(o[0], o[1]);
 #pragma unroll
             for (int h = 0; h < 2; ++h) store(zr, zo + (uint32_t)(NG * 64) * 8u * h + 64u * w, o[h]);

@@ -174,6 +174,15 @@ __device__ __forceinline__ void lds_buffer16(u32x4 rsrc, uint32_t voff, uint32_t
                  : "memory");
 }
 
+// Index of a 1 KB image of ring-format weights on nch 64-channel chunks: filters 64 f64 .. + 63, 32-channel step, image 0 .. 3 (row r is filter 4 r + image)
+__device__ __forceinline__ uint32_t ring_image(uint32_t nch, uint32_t f64, uint32_t step, uint32_t image)
+{
+    return ((f64 >> 1) * nch + (step >> 1)) * 16u + (step & 1u) * 8u + (f64 & 1u) * 4u + image;
+}
+
+// Where the bias of filter f lies so that a lane reads its results' in their order: [64-filter chunk][quarter q][image j][i] for f = 16 q + 4 i + j
+__device__ __forceinline__ uint32_t result_slot(uint32_t f) { return (f & ~15u) | (f & 3u) * 4u | (f >> 2 & 3u); }
+
 // "At most n vector-memory operations of this wave outstanding" for a wave-uniform n < 64
 // (the instruction takes an immediate).
 __device__ __forceinline__ void wait_vmcnt(uint32_t n)

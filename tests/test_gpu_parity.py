@@ -1232,12 +1232,13 @@ def _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, proj_act, G, dty
 
 
 # 16 pixels a wave and block: a last block of 1, 15 and 16 pixels; fewer blocks than waves, more than one round of them; both widths of the
-# second layer; the residual (from 32768 pixels on) and the projection (from 36864 on; below, the two launches that take its place).
+# second layer; the projection (from 4097 or 8193 pixels on, as its layers run on the ring) and the residual (the same, with 128 filters from 24576 on).
 @pytest.mark.parametrize("N,HW,proj,G,dtype,bias,act", [
     (1, 111, True, 64, dtypes.BF16, True, configs.ACT_RELU), (3, 47, True, 128, dtypes.F16, False, configs.ACT_RELU6),
     (2, 192, True, 64, dtypes.BF16, False, configs.ACT_RELU), (1, 181, False, 64, dtypes.BF16, True, configs.ACT_RELU6),
     (1, 184, False, 128, dtypes.F16, False, configs.ACT_NONE), (3, 161, False, 128, dtypes.BF16, False, configs.ACT_RELU),
-    (1, 193, True, 128, dtypes.F16, True, configs.ACT_RELU6), (3, 113, True, 64, dtypes.BF16, True, configs.ACT_NONE)])
+    (1, 193, True, 128, dtypes.F16, True, configs.ACT_RELU6), (3, 113, True, 64, dtypes.BF16, True, configs.ACT_NONE),
+    (1, 97, False, 64, dtypes.F16, True, configs.ACT_RELU), (1, 91, True, 64, dtypes.BF16, False, configs.ACT_RELU)])
 def test_end_of_a_bottleneck_block_with_the_next_layer(npas, torch, N, HW, proj, G, dtype, bias, act):
     print(f"bottleneck tail {N}x{HW}x{HW} projection={proj} G={G}", flush=True)
     got, ref = _run_of_pointwise_layers(npas, torch, N, HW, 64, 64, 1, configs.ACT_NONE if proj else configs.ACT_RELU, G, dtype, bias, act,
