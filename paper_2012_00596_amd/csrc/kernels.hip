@@ -1643,25 +1643,37 @@ __global__ __launch_bounds__(256) void global_avgpool_kernel(const void *x, void
     st_act<DT>(y, (size_t)i, (float)(s / (double)HW));
 }
 
-// 16-bit storage, C a multiple of 4: a thread averages 4 channels (8-byte loads, a wave reads 512
-// contiguous bytes of a pixel), seven loads in flight, fp32 sum (exact to ~1e-6 for a map of a few
-// thousand 16-bit values, far inside the storage type's rounding).
+// 16-bit storage, C a multiple of 4: a lane sums 4 channels (8-byte loads, a wave reads 512 contiguous bytes of a pixel) over every eighth pixel, seven
+// loads in flight; the eight waves' sums meet in LDS and are added in wave order, all in fp32 (exact to ~1e-6 for a map of a few thousand 16-bit
+// values, far inside the storage type's rounding).  One thread over all pixels was seven load latencies long.
+constexpr int kPoolWaves = 8;
 template <int DT>
-__global__ __launch_bounds__(256) void global_avgpool_vec4_kernel(const void *x, void *y, int N, int HW, int C)
+__global__ __launch_bounds__(kPoolWaves * 64) void global_avgpool_vec4_kernel(const void *x, void *y, int N, int HW, int C)
 {
-    const int C4 = C >> 2;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= N * C4) return;
-    const int n = i / C4, c4 = i - n * C4;
+    __shared__ float4 part[kPoolWaves][64];
+    const int C4 = C >> 2, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int i = blockIdx.x * 64 + lane, ic = min(i, N * C4 - 1);
+    const int n = ic / C4, c4 = ic - n * C4;
     const uint2 *xp = reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(x) + (size_t)n * HW * C) + c4;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
 #pragma unroll 7
-    for (int p = 0; p < HW; ++p) {
+    for (int p = wave; p < HW; p += kPoolWaves) {
         const uint2 v = xp[(size_t)p * C4];
         s0 += from_storage<DT>((uint16_t)(v.x & 0xffffu));
         s1 += from_storage<DT>((uint16_t)(v.x >> 16));
         s2 += from_storage<DT>((uint16_t)(v.y & 0xffffu));
         s3 += from_storage<DT>((uint16_t)(v.y >> 16));
+    }
+    part[wave][lane] = float4{s0, s1, s2, s3};
+    __syncthreads();
+    if (wave != 0 || i >= N * C4) return;
+#pragma unroll
+    for (int w = 1; w < kPoolWaves; ++w) {
+        const float4 o = part[w][lane];
+        s0 += o.x;
+        s1 += o.y;
+        s2 += o.z;
+        s3 += o.w;
     }
     const float r = 1.0f / (float)HW;
     uint2 out;
@@ -1712,9 +1724,9 @@ int launch_avgpool(const void *x, void *y, int N, int H, int W, int C, int dt, v
     hipStream_t st = (hipStream_t)stream;
     unsigned grid = (unsigned)((N * C + 255) / 256);
     if (dt != NPAS_F32 && C % 4 == 0) {
-        grid = (unsigned)((N * (C / 4) + 255) / 256);
-        if (dt == NPAS_BF16) hipLaunchKernelGGL(global_avgpool_vec4_kernel<NPAS_BF16>, dim3(grid), dim3(256), 0, st, x, y, N, H * W, C);
-        else hipLaunchKernelGGL(global_avgpool_vec4_kernel<NPAS_F16>, dim3(grid), dim3(256), 0, st, x, y, N, H * W, C);
+        grid = (unsigned)((N * (C / 4) + 63) / 64);
+        if (dt == NPAS_BF16) hipLaunchKernelGGL(global_avgpool_vec4_kernel<NPAS_BF16>, dim3(grid), dim3(kPoolWaves * 64), 0, st, x, y, N, H * W, C);
+        else hipLaunchKernelGGL(global_avgpool_vec4_kernel<NPAS_F16>, dim3(grid), dim3(kPoolWaves * 64), 0, st, x, y, N, H * W, C);
     } else if (dt == NPAS_F32) hipLaunchKernelGGL(global_avgpool_kernel<NPAS_F32>, dim3(grid), dim3(256), 0, st, x, y, N, H * W, C);
     else if (dt == NPAS_BF16) hipLaunchKernelGGL(global_avgpool_kernel<NPAS_BF16>, dim3(grid), dim3(256), 0, st, x, y, N, H * W, C);
     else hipLaunchKernelGGL(global_avgpool_kernel<NPAS_F16>, dim3(grid), dim3(256), 0, st, x, y, N, H * W, C);
