@@ -253,18 +253,19 @@ __global__ __launch_bounds__(256) void depthwise3x3_kernel(const void *x, void *
     }
 }
 
-// 16-bit storage, C a multiple of 8, stride 1 or 2: one thread owns 8 channels of R consecutive output rows of one
-// output column.  What bounded the layer was a chain of memory latencies (an input row asked for, multiplied, the next
+// 16-bit storage, C a multiple of 8, stride 1 or 2: one thread owns 8 channels of R consecutive output rows of CX
+// output columns.  What bounded the layer was a chain of memory latencies (an input row asked for, multiplied, the next
 // one asked for), so every input vector a thread needs is asked for before the first multiply; the zero padding comes
 // from the buffer descriptor's range check (an offset past the end reads zeros), which leaves no branch between the
-// loads.  The multiplies go column by column (kw): a tap's weights and an input vector are unpacked to fp32 once each
-// and feed up to three output rows; fp32 multiply-adds issue in half the time of a dot2 with one half zeroed.
+// loads.  The multiplies go input column by input column: a tap's weights and an input vector are unpacked to fp32 once each
+// and feed up to three output rows (an input vector those of two columns); fp32 multiply-adds issue in half the time of a dot2 with one half zeroed.
 // Consecutive lanes are consecutive 16-byte channel vectors of a pixel, then consecutive pixels of a row; an XCD gets runs of
 // 16 workgroups (a few row blocks) so that most rows two row blocks share come from its own L2, while the chip as a whole
 // works on one stretch of the tensors: with inputs beyond the Infinity Cache 64 x 56 x 56 x 144 36.4 us against 38.1 with one run per
 // XCD and 36.3 with none, 60 x 60 x 60 x 480 119.5 / 125.3 / 122.1, inside it 32 x 57 x 57 x 144 17.8 / 17.8 / 19.2.
 // 64 x 56 x 56 x 144, bf16, launches over three sets of tensors in turn: stride 1 31 -> 28 us (a copy of the same bytes: 23), stride 2
-// 57 -> 13 us (the thread of four rows had spilled); 32 x 57 x 57 x 144 with a bias 23 -> 17.2 us (22.6 -> 16.8 on one set, warm);
+// 57 -> 13 us (the thread of four rows had spilled); 32 x 57 x 57 x 144 with a bias 23 -> 17.2 us (22.6 -> 16.8 on one set, warm),
+// with two columns a thread 16.0: vector instructions are half of it, two waves per SIMD whose loads and multiplies overlap only in part the rest;
 // 1 x 46 x 28 x 272 at stride 2 16.5 -> 2.9 us.
 struct DwArgs {
     const void *x;
@@ -275,8 +276,8 @@ struct DwArgs {
     const void *zeros;                  // >= 16 bytes of zeros on the device
     int N, H, W, C, Ho, Wo, act;
     uint32_t xbytes;                    // size of x (read where it is below 2 GiB: see launch_depthwise3x3)
-    uint32_t CV, nyb, total;            // channel vectors, row blocks per image, threads
-    uint32_t div_cv, div_wo, div_nyb;   // fastdiv magics
+    uint32_t CV, nxb, nyb, total;       // channel vectors, column and row blocks per image, threads
+    uint32_t div_cv, div_nxb, div_nyb;  // fastdiv magics
 };
 
 template <int DT> __device__ __forceinline__ void unpack8(uint4 v, float *f)
@@ -292,7 +293,7 @@ template <int DT> __device__ __forceinline__ void unpack8(uint4 v, float *f)
 // BIG: the input does not fit a buffer descriptor's range check, or the reciprocals do not divide the thread index: 64-bit
 // addresses, a block of zeros for the padding, plain divisions.  Such launches took the one-output kernel: 65 x 256 x 256 x 256
 // 3380 -> 1216 us (3.6 TB/s), stride 2 924 -> 527; 32 x 512 x 512 x 64 at stride 2 (1 GiB, 2^32 as index times divisor) 404 -> 250.
-template <int DT, int STRIDE, int R, bool HSW, bool BIG>
+template <int DT, int STRIDE, int R, int CX, bool HSW, bool BIG>
 __global__ __launch_bounds__(256, R == 4 ? 2 : 3) void depthwise3x3_rows_kernel(DwArgs a)
 {
     // runs of 16 workgroups per XCD (see above); the last, partial window of eight runs stays as it is
@@ -302,11 +303,11 @@ __global__ __launch_bounds__(256, R == 4 ? 2 : 3) void depthwise3x3_rows_kernel(
     if (idx >= a.total) return;
     const uint32_t t = BIG ? idx / a.CV : fastdiv(idx, a.div_cv);
     const uint32_t cv = idx - t * a.CV;
-    const uint32_t t2 = BIG ? t / (uint32_t)a.Wo : fastdiv(t, a.div_wo);
-    const int ox = (int)(t - t2 * (uint32_t)a.Wo);
+    const uint32_t t2 = BIG ? t / a.nxb : fastdiv(t, a.div_nxb);
+    const int ox = (int)(t - t2 * a.nxb) * CX;
     const uint32_t n = BIG ? t2 / a.nyb : fastdiv(t2, a.div_nyb);
     const int oy0 = (int)(t2 - n * a.nyb) * R;
-    constexpr int NR = (R - 1) * STRIDE + 3; // input rows this thread reads
+    constexpr int NR = (R - 1) * STRIDE + 3, NC = (CX - 1) * STRIDE + 3; // input rows and columns this thread reads
     const int ix0 = ox * STRIDE - 1, iy0 = oy0 * STRIDE - 1;
 
     typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
@@ -317,12 +318,12 @@ __global__ __launch_bounds__(256, R == 4 ? 2 : 3) void depthwise3x3_rows_kernel(
     uint32_t rowo[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) rowo[r] = (uint32_t)(iy0 + r) < (uint32_t)a.H ? org + (uint32_t)r * rowb : 0x80000000u;
-    uint4 xv[3][NR], wv[3][3];
+    uint4 xv[NC][NR], wv[3][3];
 #pragma unroll
-    for (int kw = 0; kw < 3; ++kw) {
+    for (int kw = 0; kw < NC; ++kw) {
         const bool ok = (uint32_t)(ix0 + kw) < (uint32_t)a.W;
 #pragma unroll
-        for (int kh = 0; kh < 3; ++kh)
+        for (int kh = 0; kh < 3 && kw < 3; ++kh)
             wv[kw][kh] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(a.w) + (size_t)(kh * 3 + kw) * a.C + cv * 8u);
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
@@ -342,47 +343,58 @@ __global__ __launch_bounds__(256, R == 4 ? 2 : 3) void depthwise3x3_rows_kernel(
         b1 = *reinterpret_cast<const f32x4u *>(a.bias + cv * 8u + 4u);
     }
     __builtin_amdgcn_sched_barrier(0); // every load above the first use
-    float acc[R][8];
+    float acc[CX][R][8];
 #pragma unroll
     for (int k = 0; k < 8; ++k)
 #pragma unroll
-        for (int j = 0; j < R; ++j) acc[j][k] = k < 4 ? b0[k] : b1[k - 4];
+        for (int j = 0; j < R; ++j)
 #pragma unroll
-    for (int kw = 0; kw < 3; ++kw) {
-        float wf[3][8];
+            for (int o = 0; o < CX; ++o) acc[o][j][k] = k < 4 ? b0[k] : b1[k - 4];
 #pragma unroll
-        for (int kh = 0; kh < 3; ++kh) unpack8<DT>(wv[kw][kh], wf[kh]);
+    for (int ic = 0; ic < NC; ++ic) {
+        float wf[CX][3][8]; // of the tap column that input column ic is for output column o
+#pragma unroll
+        for (int o = 0; o < CX; ++o) {
+            const int kw = ic - o * STRIDE; // compile-time after unrolling, as kh
+            if (kw < 0 || kw > 2) continue;
+#pragma unroll
+            for (int kh = 0; kh < 3; ++kh) unpack8<DT>(wv[kw][kh], wf[o][kh]);
+        }
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             float xf[8];
-            unpack8<DT>(xv[kw][r], xf);
+            unpack8<DT>(xv[ic][r], xf);
 #pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const int kh = r - j * STRIDE; // compile-time after unrolling
-                if (kh < 0 || kh > 2) continue;
+            for (int o = 0; o < CX; ++o) {
+                if (ic - o * STRIDE < 0 || ic - o * STRIDE > 2) continue;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) acc[j][k] = fmaf(xf[k], wf[kh][k], acc[j][k]);
+                for (int j = 0; j < R; ++j) {
+                    const int kh = r - j * STRIDE;
+                    if (kh < 0 || kh > 2) continue;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) acc[o][j][k] = fmaf(xf[k], wf[o][kh][k], acc[o][j][k]);
+                }
             }
         }
         __builtin_amdgcn_sched_barrier(0); // one column's unpacked weights live at a time
     }
     const Clamp cl = clamp_of(a.act);
 #pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const int oy = oy0 + j;
-        if (oy >= a.Ho) continue;
-        const size_t yo = (((size_t)n * a.Ho + (size_t)oy) * a.Wo + (size_t)ox) * a.C + (size_t)cv * 8;
+    for (int jo = 0; jo < R * CX; ++jo) {
+        const int j = jo / CX, o = jo % CX, oy = oy0 + j;
+        if (oy >= a.Ho || (CX > 1 && ox + o >= a.Wo)) continue;
+        const size_t yo = (((size_t)n * a.Ho + (size_t)oy) * a.Wo + (size_t)(ox + o)) * a.C + (size_t)cv * 8;
         if (a.residual) {
             float rf[8];
             unpack8<DT>(*reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(a.residual) + yo), rf);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) acc[j][k] += rf[k];
+            for (int k = 0; k < 8; ++k) acc[o][j][k] += rf[k];
         }
         uint4 out;
-        out.x = pack2<DT>(clampf<HSW>(acc[j][0], cl), clampf<HSW>(acc[j][1], cl));
-        out.y = pack2<DT>(clampf<HSW>(acc[j][2], cl), clampf<HSW>(acc[j][3], cl));
-        out.z = pack2<DT>(clampf<HSW>(acc[j][4], cl), clampf<HSW>(acc[j][5], cl));
-        out.w = pack2<DT>(clampf<HSW>(acc[j][6], cl), clampf<HSW>(acc[j][7], cl));
+        out.x = pack2<DT>(clampf<HSW>(acc[o][j][0], cl), clampf<HSW>(acc[o][j][1], cl));
+        out.y = pack2<DT>(clampf<HSW>(acc[o][j][2], cl), clampf<HSW>(acc[o][j][3], cl));
+        out.z = pack2<DT>(clampf<HSW>(acc[o][j][4], cl), clampf<HSW>(acc[o][j][5], cl));
+        out.w = pack2<DT>(clampf<HSW>(acc[o][j][6], cl), clampf<HSW>(acc[o][j][7], cl));
         store_stream16(reinterpret_cast<uint16_t *>(a.y) + yo, out);
     }
 }
@@ -405,26 +417,33 @@ int launch_depthwise3x3(int dt, const void *x, void *y, const void *w, const flo
         // share one input row in five: one row is never slower by more than a tenth and mostly faster (12.9 us against 15.3 with two).
         const int R = stride == 1 && (double)N * Ho * Wo * CV > 256.0 * 12 * 64 ? 4 : 1;
         const uint32_t nyb = (uint32_t)((Ho + R - 1) / R);
-        const double threads = (double)N * nyb * Wo * CV;
+        // Two columns a thread share two of their four input columns (3 loads an output, a tenth fewer vector instructions) and halve the number of
+        // threads, which wants launches of several rounds (2 x 256 workgroups are resident): from 2.75 rounds of one-column threads on, 32 x 57 x 57 x 144
+        // 17.4 -> 16.1 us, 64 x 56 x 56 x 144 28.8 -> 27.0, 64 x 60 x 60 x 240 65.0 -> 58.3; with 2.3 rounds 64 x 28 x 28 x 192 11.9 against 12.2, with
+        // 0.7 16 x 28 x 28 x 240 5.6 against 6.5 (some launches between one and two rounds would gain, 8 x 60 x 60 x 240 10.0 -> 9.2, others not).
+        const int CX = R == 4 && (double)N * nyb * Wo * CV >= 2.75 * 512 * 256 ? 2 : 1;
+        const uint32_t nxb = (uint32_t)((Wo + CX - 1) / CX);
+        const double threads = (double)N * nyb * nxb * CV;
         // Offset 2 GiB is past the end for the descriptor's range check; the index decode divides by CV, Wo and nyb with 32-bit
         // reciprocals, exact while index * divisor < 2^32.
-        const bool big = xbytes >= 0x80000000u || threads * std::max({CV, (uint32_t)Wo, nyb}) >= 4294967296.0;
-        DwArgs a{x, y, w, bias, residual, zeros, N, H, W, C, Ho, Wo, act, (uint32_t)xbytes, CV, nyb, (uint32_t)threads,
-                 magic32(CV), magic32((uint32_t)Wo), magic32(nyb)};
+        const bool big = xbytes >= 0x80000000u || threads * std::max({CV, nxb, nyb}) >= 4294967296.0;
+        DwArgs a{x, y, w, bias, residual, zeros, N, H, W, C, Ho, Wo, act, (uint32_t)xbytes, CV, nxb, nyb, (uint32_t)threads,
+                 magic32(CV), magic32(nxb), magic32(nyb)};
         const unsigned grid = (a.total + 255u) / 256u;
-        auto go = [&](auto dtc, auto sc, auto rc) {
-            constexpr int DT = decltype(dtc)::value, S = decltype(sc)::value, RR = decltype(rc)::value;
+        auto go = [&](auto dtc, auto sc, auto rc, auto cc) {
+            constexpr int DT = decltype(dtc)::value, S = decltype(sc)::value, RR = decltype(rc)::value, CC = decltype(cc)::value;
             auto run = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, a); };
             const bool hsw = act == NPAS_ACT_HARDSWISH;
-            if (big) run(hsw ? depthwise3x3_rows_kernel<DT, S, RR, true, true> : depthwise3x3_rows_kernel<DT, S, RR, false, true>);
-            else run(hsw ? depthwise3x3_rows_kernel<DT, S, RR, true, false> : depthwise3x3_rows_kernel<DT, S, RR, false, false>);
+            if (big) run(hsw ? depthwise3x3_rows_kernel<DT, S, RR, CC, true, true> : depthwise3x3_rows_kernel<DT, S, RR, CC, false, true>);
+            else run(hsw ? depthwise3x3_rows_kernel<DT, S, RR, CC, true, false> : depthwise3x3_rows_kernel<DT, S, RR, CC, false, false>);
         };
         auto rows = [&](auto dtc) {
             using std::integral_constant;
             integral_constant<int, 1> one;
-            if (stride == 2) go(dtc, integral_constant<int, 2>{}, one);
-            else if (R == 4) go(dtc, one, integral_constant<int, 4>{});
-            else go(dtc, one, one);
+            if (stride == 2) go(dtc, integral_constant<int, 2>{}, one, one);
+            else if (R == 4 && CX == 2) go(dtc, one, integral_constant<int, 4>{}, integral_constant<int, 2>{});
+            else if (R == 4) go(dtc, one, integral_constant<int, 4>{}, one);
+            else go(dtc, one, one, one);
         };
         if (dt == NPAS_BF16) rows(std::integral_constant<int, NPAS_BF16>{});
         else rows(std::integral_constant<int, NPAS_F16>{});
