@@ -1198,7 +1198,7 @@ def test_config5_full_size_run_stack_batch2_logits(npas, torch, flags):
     assert (got.argmax(1) == ref.argmax(1)).all()
 
 
-def _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, proj_act, G, dtype, bias, act, flags):
+def _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, proj_act, G, dtype, bias, act, flags, infinite=()):
     """Stack x -> a (1x1, C), x -> s (1x1, 4C), y = act(W a + s), z = act(W y): (y, z) on the device, and from the oracle with the
     projection rounded to storage only where it is a tensor of its own (proj_act is not none)."""
     A = configs
@@ -1209,10 +1209,13 @@ def _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, proj_act, G, dty
             L.bias = prng.normal(8, 300 + idx, F, 0.5).astype(np.float32)
         return L
 
-    layers = [pw(0, C0, C, A.ACT_RELU, 0, st=stride), pw(1, C0, 4 * C, proj_act, 0, st=stride), pw(2, C, 4 * C, act, 1, 2)]
+    first = A.ACT_RELU6 if infinite else A.ACT_RELU # (finite)
+    layers = [pw(0, C0, C, first, 0, st=stride), pw(1, C0, 4 * C, proj_act, 0, st=stride), pw(2, C, 4 * C, act, 1, 2)]
     if G:
         layers.append(pw(3, 4 * C, G, act, 3))
     xs, xe = configs._tensor(9, 1, (N, HW, HW, C0), 1.0, dtype)
+    for at in infinite:
+        xs.reshape(N, HW, HW, C0)[at] = 0x7F80 if dtype == dtypes.BF16 else 0x7C00
     packed = [pack_layer(npas, L, dtype) for L in layers]
     biases = helpers.bias_tensors(layers, torch)
     st = npas.Stack(helpers.stack_descs(npas, layers, packed, biases), HW, HW, flags)
@@ -1262,6 +1265,19 @@ def test_projection_shortcut_inside_the_layer_that_adds_it(npas, torch, N, HW, C
     got, ref = _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, configs.ACT_NONE, 0, dtype, bias, act, npas.STACK_FUSE_POINTWISE)
     norm, worst = helpers.check_stack_output(got[0], ref[0], STACK_NORM_TOL if dtype == dtypes.BF16 else STACK_NORM_TOL / 8)
     print(f"  norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
+
+
+@pytest.mark.parametrize("N,HW,C0,C,stride,dtype", [(1, 14, 512, 256, 2, dtypes.BF16), (1, 28, 256, 128, 1, dtypes.F16), (1, 3, 64, 64, 1, dtypes.BF16)])
+def test_projection_inside_the_adding_layer_with_an_infinite_input(npas, torch, N, HW, C0, C, stride, dtype):
+    """Split reduction: an infinite value in the projection's input reaches the filters that keep its channel and no others."""
+    print(f"projection joined, infinite input {N}x{HW}x{HW} {C0} / {stride} + {C} -> {4 * C}", flush=True)
+    args = (npas, torch, N, HW, C0, C, stride, configs.ACT_NONE, 0, dtype, False, configs.ACT_RELU)
+    got = [_run_of_pointwise_layers(*args, flags, [(0, 0, 0, 1), (0, 2, 2, C0 - 3)])[0][0] for flags in (0, npas.STACK_FUSE_POINTWISE)]
+    assert np.isinf(got[0]).any() and np.isfinite(got[0]).any()
+    for kind in (np.isnan, np.isposinf):
+        np.testing.assert_array_equal(kind(got[1]), kind(got[0]))
+    finite = np.isfinite(got[0])
+    assert np.abs(got[1][finite] - got[0][finite]).max() <= 2e-2 * np.abs(got[0][finite]).max()
 
 
 def test_chained_fused_launches_against_the_oracle(npas, torch):
