@@ -24,7 +24,13 @@ typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 
 __device__ __forceinline__ uint32_t fastdiv(uint32_t n, uint32_t magic)
 {
-    return magic ? __umulhi(n, magic) : n; // magic = ceil(2^32 / d), 0 for d == 1
+    return magic ? __umulhi(n, magic) : n; // magic = ceil(2^32 / d), 0 for d == 1; exact while n * d < 2^32
+}
+// The same exact for every n below 2^32 - d: the reciprocal is at most one too high (n * (d * magic - 2^32) < n * d), which the product shows.
+__device__ __forceinline__ uint32_t fastdiv_any(uint32_t n, uint32_t magic, uint32_t d)
+{
+    const uint32_t q = fastdiv(n, magic);
+    return q * d > n ? q - 1u : q;
 }
 
 // Streaming (non-temporal) 8-byte accesses for tensors that are written or read once per launch and

@@ -644,16 +644,16 @@ __global__ __launch_bounds__(Cfg::kThreads) void pointwise_ring_kernel(std::cond
         auto in_byte = [&](uint32_t m) __attribute__((always_inline)) -> uint32_t { // byte offset in x of output pixel m's input pixel
             m = min(m, (uint32_t)a.M - 1u);
             if (a.flat) return m * (uint32_t)a.C * 2u;
-            const uint32_t n = fastdiv(m, a.div_howo), r = m - n * (uint32_t)(a.Ho * a.Wo);
-            const uint32_t oy = fastdiv(r, a.div_wo), ox = r - oy * (uint32_t)a.Wo;
+            const uint32_t howo = (uint32_t)(a.Ho * a.Wo), n = fastdiv_any(m, a.div_howo, howo), r = m - n * howo;
+            const uint32_t oy = fastdiv_any(r, a.div_wo, (uint32_t)a.Wo), ox = r - oy * (uint32_t)a.Wo;
             return ((n * a.H + oy * a.stride) * a.W + ox * a.stride) * (uint32_t)a.C * 2u;
         };
         auto in_byte2 = [&](uint32_t m) __attribute__((always_inline)) -> uint32_t { // the same in the second input
             if constexpr (JOIN) {
                 m = min(m, (uint32_t)a.M - 1u);
                 if (a.stride2 == 1) return m * (uint32_t)a.C2 * 2u;
-                const uint32_t n = fastdiv(m, a.div_howo), r = m - n * (uint32_t)(a.Ho * a.Wo);
-                const uint32_t oy = fastdiv(r, a.div_wo), ox = r - oy * (uint32_t)a.Wo;
+                const uint32_t howo = (uint32_t)(a.Ho * a.Wo), n = fastdiv_any(m, a.div_howo, howo), r = m - n * howo;
+                const uint32_t oy = fastdiv_any(r, a.div_wo, (uint32_t)a.Wo), ox = r - oy * (uint32_t)a.Wo;
                 return ((n * a.H2 + oy * a.stride2) * a.W2 + ox * a.stride2) * (uint32_t)a.C2 * 2u;
             } else return 0u;
         };

@@ -1267,6 +1267,19 @@ def test_projection_shortcut_inside_the_layer_that_adds_it(npas, torch, N, HW, C
     print(f"  norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
 
 
+# Pixels times pixels of an image beyond 2^32, where the reciprocal of Ho * Wo is one too high for an image's last pixel: strided layers on their own
+# (flags 0), and the strided projection inside the layer that adds it.
+@pytest.mark.parametrize("flags", [0, 1], ids=["per_layer", "joined"])
+@pytest.mark.parametrize("N,HW", [(2, 448), (4, 400)])
+def test_strided_pointwise_layers_on_many_pixels(npas, torch, N, HW, flags):
+    print(f"strided 1x1 {N}x{HW}x{HW} flags={flags}", flush=True)
+    got, ref = _run_of_pointwise_layers(npas, torch, N, HW, 64, 64, 2, configs.ACT_NONE, 0, dtypes.BF16, True, configs.ACT_NONE, flags)
+    g, r = got[0].reshape(N, -1, 256), ref[0].reshape(N, -1, 256)
+    err = np.sqrt(((g - r) ** 2).sum(-1) / (r ** 2).sum(-1))
+    print(f"  a pixel's error {err.max():.3e}, last pixels' {err[:, -1].max():.3e}", flush=True)
+    assert err.max() <= 5 * 2.0 ** -8      # bf16: two rounded inputs of the sum and its own rounding, half a step (2^-9) each at most; another pixel's sum gives about 1
+
+
 @pytest.mark.parametrize("N,HW,C0,C,stride,dtype", [(1, 14, 512, 256, 2, dtypes.BF16), (1, 28, 256, 128, 1, dtypes.F16), (1, 3, 64, 64, 1, dtypes.BF16)])
 def test_projection_inside_the_adding_layer_with_an_infinite_input(npas, torch, N, HW, C0, C, stride, dtype):
     """Split reduction: an infinite value in the projection's input reaches the filters that keep its channel and no others."""
