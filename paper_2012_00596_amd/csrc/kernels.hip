@@ -985,8 +985,8 @@ __device__ __forceinline__ void conv_smallc_mfma_kernel_body(SmallCArgs a)
     PV pv[NPV];
     const uint32_t row2 = (uint32_t)a.row2, patch_words = (uint32_t)a.PH * row2;
     auto fetch_patch = [&](uint32_t item) __attribute__((always_inline)) {
-        const uint32_t n = fastdiv(item, a.div_tiles), trem = item - n * tiles_img;
-        const uint32_t tyi = fastdiv(trem, a.div_tx), txi = trem - tyi * (uint32_t)a.tilesX;
+        const uint32_t n = fastdiv_any(item, a.div_tiles, tiles_img), trem = item - n * tiles_img;
+        const uint32_t tyi = fastdiv_any(trem, a.div_tx, (uint32_t)a.tilesX), txi = trem - tyi * (uint32_t)a.tilesX;
         const int fy0 = POOL ? 2 * (int)tyi * a.PTH - 1 : (int)tyi * a.TH, fx0 = POOL ? 2 * (int)txi * a.PTW - 1 : (int)txi * a.TW; // the tile's first conv pixel
         const int iy0 = fy0 * a.stride - a.pad, ixe0 = (fx0 * a.stride - a.pad) * a.C; // first row, first value of a row
         const uint16_t *xn = x16 + (size_t)n * a.H * (size_t)(a.W * a.C);
@@ -1009,8 +1009,8 @@ __device__ __forceinline__ void conv_smallc_mfma_kernel_body(SmallCArgs a)
     uint32_t item = blockIdx.x;
     if (item < a.nitems) fetch_patch(item);
     while (item < a.nitems) {
-        const uint32_t n = fastdiv(item, a.div_tiles), trem = item - n * tiles_img;
-        const uint32_t tyi = fastdiv(trem, a.div_tx), txi = trem - tyi * (uint32_t)a.tilesX;
+        const uint32_t n = fastdiv_any(item, a.div_tiles, tiles_img), trem = item - n * tiles_img;
+        const uint32_t tyi = fastdiv_any(trem, a.div_tx, (uint32_t)a.tilesX), txi = trem - tyi * (uint32_t)a.tilesX;
         const int ty0 = POOL ? 2 * (int)tyi * a.PTH - 1 : (int)tyi * a.TH, tx0 = POOL ? 2 * (int)txi * a.PTW - 1 : (int)txi * a.TW;
         __syncthreads(); // the tile before has been read
 #pragma unroll

@@ -907,6 +907,23 @@ def test_small_channel_kernel(npas, torch, case):
     _run_edge_case(npas, torch, case, expect_kernel="conv_smallc_mfma")
 
 
+def test_small_channel_kernel_on_more_than_65536_tiles_an_image(npas, torch):
+    """Tiles times tiles of an image beyond 2^32, where the reciprocal of the tiles of an image is one too high for an image's last tiles."""
+    N, HW, F, rows = 2, 5000, 8, 40
+    print(f"small channels {N}x{HW}x{HW}x3", flush=True)
+    L = configs._bp_conv(63, 0, 3, F, 3, 1, 1, 8, 3, 2, 0.2, dtypes.BF16, configs.ACT_NONE)
+    p = pack_layer(npas, L, dtypes.BF16)
+    assert npas.device_kernel(p, N, HW, HW, 1, 1) == "conv_smallc_mfma_kernel"
+    g = torch.Generator(device="cuda").manual_seed(63)
+    x = torch.randn(N, HW, HW, 3, generator=g, device="cuda").to(torch.bfloat16)
+    y = torch.full((N, HW, HW, F), float("nan"), dtype=torch.bfloat16, device="cuda")
+    npas.conv2d_sparse(p, x, y, N, HW, HW, 1, 1)
+    torch.cuda.synchronize()
+    assert torch.isfinite(y).all()
+    ref = oracle.round_to(oracle.conv2d_masked(x[:, -rows - 1:].double().cpu().numpy(), L.w_exact, L.mask, 1, 1), dtypes.BF16)[:, 1:]
+    assert rel_err(y[:, -rows:].double().cpu().numpy(), ref) <= TOL[dtypes.BF16]
+
+
 # Stride 2 on at most 3 channels and whole 4-byte rows: the kernel by kernel rows.  Partial column blocks and filter quads, one or an odd
 # number of conv rows, images smaller than the kernel's reach, both parities of the padding, bands of one pair and of many.
 SMALLC_ROWS = [
