@@ -236,14 +236,18 @@ int npas_run_stack(const npas_stack *s, const void *x_dev, void *y_dev, int N, v
  * (different streams, or threads) race; calls on one stream are safe.  Nothing in the array needs clearing. */
 #define NPAS_STATIC_WORKSPACE_BYTES (32u << 20)
 int npas_run_stack_static(const npas_stack *s, const void *x_dev, void *y_dev, int N, void *hip_stream);
-/* Number of kernels one npas_run_stack call launches (after fusion; a run of 1x1 layers that becomes one launch only at some batch
- * sizes, see NPAS_STACK_FUSE_POINTWISE, is counted and described layer by layer: there the call launches fewer). */
+/* Number of kernels one npas_run_stack call launches after the fusions that hold for every batch size: the most it launches.
+ * With NPAS_STACK_FUSE_POINTWISE a run of 1x1 layers around a shortcut is one launch at some batch sizes only;
+ * npas_stack_describe(s, N, NULL, 0) is the number at batch N. */
 int npas_stack_num_launches(const npas_stack *s);
-/* For tests and reports: the launches one npas_run_stack call makes for batch N, in order, and where their
- * tensors live.  Row r of rows_host (int64 [max_rows][NPAS_DESCRIBE_COLS]) =
+/* For tests and reports: the launches one npas_run_stack call makes for batch N (x_dev and y_dev at multiples of 16 bytes), in
+ * order, and where their tensors live.  Row r of rows_host (int64 [max_rows][NPAS_DESCRIBE_COLS]) =
  *   { first layer of the launch, last layer it absorbs, input tensor, residual tensor (-1: none), output tensor,
  *     workspace offset of the input, of the residual, of the output (-1: the tensor is x_dev, -2: y_dev, -3: none),
  *     bytes of the input, of the residual, of the output }.
+ * Where a projection shortcut runs inside the layer that adds it, the launch is that layer's, from the projection on: its input is
+ * the adding layer's, its residual the projection's input.  Tensors between two layers of a launch are not written, but for
+ * the sum of a shortcut that the launch hands to the next 1x1 layer: it lies where the later rows that read it say.
  * Returns the number of launches (rows beyond max_rows are not written), or a negative npas_status. */
 #define NPAS_DESCRIBE_COLS 11
 int npas_stack_describe(const npas_stack *s, int N, int64_t *rows_host, int max_rows);

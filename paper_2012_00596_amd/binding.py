@@ -336,8 +336,14 @@ class Stack:
     def workspace_bytes(self, N):
         return int(lib().npas_stack_workspace_bytes(self.handle, N))
 
-    def num_launches(self):
-        return int(lib().npas_stack_num_launches(self.handle))
+    def num_launches(self, N=None):
+        """Launches of one run at batch N (None: the most over all batch sizes)."""
+        if N is None:
+            return int(lib().npas_stack_num_launches(self.handle))
+        got = lib().npas_stack_describe(self.handle, N, None, 0)
+        if got < 0:
+            _check(got)
+        return got
 
     def run_static(self, x, y, N, stream=None):
         """npas_run_stack_static: the library's own static workspace, no allocation."""

@@ -948,6 +948,32 @@ static void plan_ir_tile(int Ho, int Wo, int nslots, int stride, int act1, int a
 // on the ring, from 4097 pixels on (8192: 12.1 -> 9.9 us; projection: 5120, 128 filters 12.7 -> 11.3; 12288, 64 filters 14.2 -> 11.0).
 constexpr double kTailMinPixels = 24576;
 
+// How a run of 1x1 layers goes at one batch size: its layers one by one, with the next layer (bottleneck_tail_kernel), or the projection inside the
+// layer that adds it, on the streaming kernel or the split reduction.  aligned(t): tensor t lies at a multiple of 16 bytes.
+enum RunForm { RUN_LAYERS, RUN_TAIL, RUN_RING_JOIN, RUN_SPLIT_JOIN };
+template <typename Aligned> static RunForm run_form(const npas_stack *s, const npas_stack::Run &r, int N, Aligned &&aligned)
+{
+    if (switches().force != FV_NONE) return RUN_LAYERS;
+    const npas_stack::Node &add = s->nodes[r.add], &proj = s->nodes[r.first];
+    const double pixels = (double)N * add.H * add.W;
+    SpatialDirectArgs sp;
+    auto route = [&](const npas_stack::Node &n) { return choose_route(n.d.packed, N, n.H, n.W, n.d.stride, 0, &sp); };
+    const Route ra = route(add);
+    const bool sum_aligned = aligned(add.d.src) && aligned(r.add + 1) && aligned(r.sum ? proj.d.src : add.d.res);
+    if (r.tail && (r.sum || s->nodes[r.last].F == 64 || pixels >= kTailMinPixels) && pixels <= kTailMaxPixels && ra == R_POINTWISE_RING &&
+        route(s->nodes[r.last]) == R_POINTWISE_RING && sum_aligned && aligned(r.last + 1))
+        return RUN_TAIL;
+    if (!r.sum || !sum_aligned) return RUN_LAYERS;
+    // The projection as further stages of the adding layer's sum, wherever both take the same kernel: its output exists nowhere.  Quicker at every one of
+    // 120 shapes (64 .. 512 channels, maps of 2 x 2 .. 56 x 56, batch 1 .. 128, rates 2 and 5): by 1 to 30 % on the split reduction, 1.2-1.9x on the ring.
+    const Route rp = route(proj);
+    const auto split = [](Route v) { return v == R_SMALLM || v == R_FC_GATHER; };
+    if (ra == R_POINTWISE_RING && rp == R_POINTWISE_RING) return RUN_RING_JOIN;
+    if (split(ra) && split(rp) && std::ceil(std::ceil(pixels / 16) / 2) * ((add.d.packed->F + 63) / 64) <= 256) return RUN_SPLIT_JOIN;
+    return RUN_LAYERS;
+}
+static int run_last(const npas_stack::Run &r, RunForm form) { return form == RUN_TAIL ? r.last : r.add; } // last layer of that launch
+
 // a 16-bit 1 x 1 layer at stride 1 without padding (the fused block takes a bias, the fused pair does not)
 static bool is_pointwise16(const npas_layer_desc &d)
 {
@@ -1365,14 +1391,22 @@ int npas_stack_describe(const npas_stack *s, int N, int64_t *rows_host, int max_
     auto where = [&](int t) -> int64_t { return t < 0 ? -3 : t == 0 ? -1 : t == nl ? -2 : (int64_t)off[t]; };
     auto bytes = [&](int t) -> int64_t { return t < 0 ? 0 : (int64_t)tensor_elems_per_image(s, t) * N * esz; };
     int r = 0;
-    for (int i = 0; i < nl; ++i) {
+    for (int i = 0, last; i < nl; i = last + 1) {
         const npas_stack::Node &n = s->nodes[i];
-        if (n.fused_away) continue;
-        const int last = i + absorbed_after(n);
-        const int res = n.ir_head ? s->nodes[last].d.res : n.d.res; // a fused block adds its input at its last layer
+        last = i + absorbed_after(n);
+        int src = n.d.src, res = n.ir_head ? s->nodes[last].d.res : n.d.res; // a fused block adds its input at its last layer
+        if (n.run >= 0 && runs[n.run]) {
+            const npas_stack::Run &run = s->runs[n.run];
+            const RunForm form = run_form(s, run, N, [](int) { return true; });
+            if (form != RUN_LAYERS) {
+                last = run_last(run, form);
+                src = s->nodes[run.add].d.src;
+                if (run.sum) res = n.d.src; // the projection's input
+            }
+        }
         if (r < max_rows) {
-            const int64_t row[NPAS_DESCRIBE_COLS] = {i, last, n.d.src, res, last + 1, where(n.d.src), where(res), where(last + 1),
-                                                     bytes(n.d.src), bytes(res), bytes(last + 1)};
+            const int64_t row[NPAS_DESCRIBE_COLS] = {i, last, src, res, last + 1, where(src), where(res), where(last + 1),
+                                                     bytes(src), bytes(res), bytes(last + 1)};
             std::memcpy(rows_host + (size_t)r * NPAS_DESCRIBE_COLS, row, sizeof row);
         }
         ++r;
@@ -1384,71 +1418,47 @@ int npas_stack_describe(const npas_stack *s, int N, int64_t *rows_host, int max_
 
 namespace npas {
 
-// Launches the first layers of a run as one kernel where the rule says so; *covered: how many (0: none).
+// The first layers of a run as one kernel; *covered: how many (0: none, they run one by one).
 template <typename Tensor>
 static int run_pointwise_run(const npas_stack *s, const npas_stack::Run &r, int N, Tensor &&tensor, void *stream, int *covered)
 {
+    const RunForm form = run_form(s, r, N, [&](int t) { return ((uintptr_t)tensor(t) & 15u) == 0; });
+    if (form == RUN_LAYERS) return NPAS_OK;
     const npas_stack::Node &add = s->nodes[r.add], &proj = s->nodes[r.first];
-    const npas_packed *p3 = add.d.packed;
-    const double pixels = (double)N * add.H * add.W;
-    if (switches().force != FV_NONE) return NPAS_OK;
-    SpatialDirectArgs sp;
-    auto route = [&](const npas_stack::Node &n) { return choose_route(n.d.packed, N, n.H, n.W, n.d.stride, 0, &sp); };
-    auto on_ring = [&](const npas_stack::Node &n) { return route(n) == R_POINTWISE_RING; };
-    auto check = [&](int last) {
-        int rc = NPAS_OK;
-        for (int j = r.first; j <= last && !rc; ++j) {
-            const npas_stack::Node &n = s->nodes[j];
-            rc = check_run(n.d.packed, tensor(n.d.src), tensor(j + 1), N, n.H, n.W, n.d.stride, n.d.pad);
-        }
-        return rc;
-    };
-    if (r.tail && (r.sum || s->nodes[r.last].F == 64 || pixels >= kTailMinPixels) && pixels <= kTailMaxPixels && on_ring(add) && on_ring(s->nodes[r.last])) {
+    const npas_packed *p3 = add.d.packed, *p2 = proj.d.packed;
+    const int last = run_last(r, form);
+    *covered = last - r.first + 1;
+    for (int j = r.first; j <= last; ++j) {
+        const npas_stack::Node &n = s->nodes[j];
+        if (int rc = check_run(n.d.packed, tensor(n.d.src), tensor(j + 1), N, n.H, n.W, n.d.stride, n.d.pad)) return rc;
+    }
+    const void *x = tensor(add.d.src), *x2 = r.sum ? tensor(proj.d.src) : nullptr;
+    void *y = tensor(r.add + 1);
+    if (form == RUN_TAIL) {
         const npas_stack::Node &next = s->nodes[r.last];
         TailArgs a;
-        a.a = tensor(add.d.src); a.y = tensor(r.add + 1); a.z = tensor(r.last + 1);
-        a.r = r.sum ? nullptr : tensor(add.d.res); a.x2 = r.sum ? tensor(proj.d.src) : nullptr;
+        a.a = x; a.y = y; a.z = tensor(r.last + 1);
+        a.r = r.sum ? nullptr : tensor(add.d.res); a.x2 = x2;
         a.b3 = (const float *)add.d.bias_dev; a.bsc = r.sum ? (const float *)proj.d.bias_dev : nullptr; a.b1 = (const float *)next.d.bias_dev;
-        a.w3 = p3->dev.wimg; a.wsc = r.sum ? proj.d.packed->dev.wimg : nullptr; a.w1 = next.d.packed->dev.wimg;
-        a.M = (uint32_t)pixels; a.act3 = add.d.act; a.act1 = next.d.act;
-        const uintptr_t all = (uintptr_t)a.a | (uintptr_t)a.y | (uintptr_t)a.z | (uintptr_t)a.r | (uintptr_t)a.x2;
-        if ((all & 15u) == 0) {
-            if (int rc = check(r.last)) return rc;
-            *covered = r.last - r.first + 1;
-            return launch_bottleneck_tail(p3->dtype, a, next.F, r.sum, stream);
-        }
+        a.w3 = p3->dev.wimg; a.wsc = r.sum ? p2->dev.wimg : nullptr; a.w1 = next.d.packed->dev.wimg;
+        a.M = (uint32_t)((size_t)N * add.H * add.W); a.act3 = add.d.act; a.act1 = next.d.act;
+        return launch_bottleneck_tail(p3->dtype, a, next.F, r.sum, stream);
     }
-    if (!r.sum) return NPAS_OK;
-    // The projection as further stages of the adding layer's sum, wherever both take the same kernel: its output exists nowhere.  Quicker at every one of
-    // 120 shapes (64 .. 512 channels, maps of 2 x 2 .. 56 x 56, batch 1 .. 128, rates 2 and 5): by 1 to 30 % on the split reduction, 1.2-1.9x on the ring.
-    const void *x = tensor(add.d.src), *x2 = tensor(proj.d.src);
-    void *y = tensor(r.add + 1);
-    const npas_packed *p2 = proj.d.packed;
-    if (((uintptr_t)x | (uintptr_t)x2 | (uintptr_t)y) & 15u) return NPAS_OK;
-    const Route ra = route(add), rp = route(proj);
-    const auto split = [](Route v) { return v == R_SMALLM || v == R_FC_GATHER; };
-    if (ra == R_POINTWISE_RING && rp == R_POINTWISE_RING) {
-        if (int rc = check(r.add)) return rc;
+    if (form == RUN_RING_JOIN) {
         RingJoinArgs a;
         plan_ring(p3, N, add.H, add.W, 1, &a);
         a.x = x; a.y = y; a.residual = nullptr; a.bias = (const float *)add.d.bias_dev; a.act = add.d.act;
         a.x2 = x2; a.bias2 = (const float *)proj.d.bias_dev; a.wimg2 = p2->dev.wimg;
         a.C2 = p2->C; a.H2 = proj.H; a.W2 = proj.W; a.stride2 = proj.d.stride;
         a.x2bytes = (uint32_t)((size_t)N * proj.H * proj.W * p2->C * 2);
-        *covered = 2;
         return launch_pointwise_ring_join(p3->dtype, a, stream);
     }
-    if (split(ra) && split(rp) && std::ceil(std::ceil(pixels / 16) / 2) * ((p3->F + 63) / 64) <= 256) {
-        if (int rc = check(r.add)) return rc;
-        SmallMJoinArgs a;
-        plan_smallm(p3, N, add.H, add.W, 1, 0, &a);
-        a.x = x; a.y = y; a.residual = nullptr; a.bias = (const float *)add.d.bias_dev; a.act = add.d.act;
-        plan_smallm(p2, N, proj.H, proj.W, proj.d.stride, 0, &a.b);
-        a.b.x = x2; a.b.y = nullptr; a.b.residual = nullptr; a.b.bias = (const float *)proj.d.bias_dev; a.b.act = NPAS_ACT_NONE;
-        *covered = 2;
-        return launch_conv_smallm_join(p3->dtype, a, stream);
-    }
-    return NPAS_OK;
+    SmallMJoinArgs a;
+    plan_smallm(p3, N, add.H, add.W, 1, 0, &a);
+    a.x = x; a.y = y; a.residual = nullptr; a.bias = (const float *)add.d.bias_dev; a.act = add.d.act;
+    plan_smallm(p2, N, proj.H, proj.W, proj.d.stride, 0, &a.b);
+    a.b.x = x2; a.b.y = nullptr; a.b.residual = nullptr; a.b.bias = (const float *)proj.d.bias_dev; a.b.act = NPAS_ACT_NONE;
+    return launch_conv_smallm_join(p3->dtype, a, stream);
 }
 
 // The body of npas_run_stack; also behind the allocation-free entry point.

@@ -1215,41 +1215,48 @@ def test_config5_full_size_run_stack_batch2_logits(npas, torch, flags):
     assert (got.argmax(1) == ref.argmax(1)).all()
 
 
-def _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, proj_act, G, dtype, bias, act, flags, infinite=()):
-    """Stack x -> a (1x1, C), x -> s (1x1, 4C), y = act(W a + s), z = act(W y): (y, z) on the device, and from the oracle with the
-    projection rounded to storage only where it is a tensor of its own (proj_act is not none)."""
-    A = configs
+def _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, proj_act, G, dtype, bias, act, flags, infinite=(), kernel=None):
+    """Stack x -> a (1x1, C), x -> s (1x1, 4C), y = act(W a + s), and with G z = act(W y), between a layer that nothing reads (it takes more workspace than
+    the run may ask for) and one that adds y to its product of z (and shows where both lie): y and z on the device, the same from the oracle with the
+    projection rounded to storage only where it is a tensor of its own (proj_act is not none), and the first and last layer of each launch of a .. z, counted
+    from a.  bias: on all layers, none, or those of these numbers.  kernel: the device function of the layer that adds."""
+    A, at = configs, 1 if G else 0      # at: number of layer a
 
     def pw(idx, Ci, F, act, src, res=-1, st=1):
         L = configs._bp_conv(7, idx, Ci, F, 1, st, 0, 8, 4, 2, (1.0 / Ci) ** 0.5, dtype, act, src, res, name=f"pw{idx}")
-        if bias:
+        if bias is True or (bias and idx in bias):
             L.bias = prng.normal(8, 300 + idx, F, 0.5).astype(np.float32)
         return L
 
     first = A.ACT_RELU6 if infinite else A.ACT_RELU # (finite)
-    layers = [pw(0, C0, C, first, 0, st=stride), pw(1, C0, 4 * C, proj_act, 0, st=stride), pw(2, C, 4 * C, act, 1, 2)]
+    layers = [pw(0, C0, C, first, 0, st=stride), pw(1, C0, 4 * C, proj_act, 0, st=stride), pw(2, C, 4 * C, act, at + 1, at + 2)]
     if G:
-        layers.append(pw(3, 4 * C, G, act, 3))
+        layers = [pw(9, C0, 12 * C, A.ACT_NONE, 0)] + layers + [pw(3, 4 * C, G, act, at + 3), pw(4, G, 4 * C, A.ACT_NONE, at + 4, at + 3)]
     xs, xe = configs._tensor(9, 1, (N, HW, HW, C0), 1.0, dtype)
-    for at in infinite:
-        xs.reshape(N, HW, HW, C0)[at] = 0x7F80 if dtype == dtypes.BF16 else 0x7C00
+    for i in infinite:
+        xs.reshape(N, HW, HW, C0)[i] = 0x7F80 if dtype == dtypes.BF16 else 0x7C00
     packed = [pack_layer(npas, L, dtype) for L in layers]
     biases = helpers.bias_tensors(layers, torch)
     st = npas.Stack(helpers.stack_descs(npas, layers, packed, biases), HW, HW, flags)
     wsb, Ho = st.workspace_bytes(N), (HW - 1) // stride + 1
+    if kernel:
+        assert npas.device_kernel(packed[at + 2], N, Ho, Ho, 1, 0) == kernel
     ws = torch.empty(wsb, dtype=torch.uint8, device="cuda")
-    out = new_dev((N, Ho, Ho, G or 4 * C), dtype, torch, fill=0x7FC1)
+    ws.view(torch.int16).fill_(0x7FC1)
+    out = new_dev((N, Ho, Ho, 4 * C), dtype, torch, fill=0x7FC1)
     st.run(to_dev(xs, torch), out, N, ws, wsb)
     torch.cuda.synchronize()
+    rows = st.describe(N)
     got = [from_dev(out, dtype).reshape(N, Ho, Ho, -1)]
     if G:
-        row = st.describe(N)[2]
-        got.insert(0, from_dev(ws[row["off_out"]:row["off_out"] + row["bytes_out"]].view(torch.int16), dtype).reshape(N, Ho, Ho, -1))
-    t = [xe]
-    for i, L in enumerate(layers):
+        row = rows[-1]
+        assert (row["src"], row["res"]) == (at + 4, at + 3)
+        got = [from_dev(ws[row["off_" + k]:row["off_" + k] + row["bytes_" + k]].view(torch.int16), dtype).reshape(N, Ho, Ho, -1) for k in ("res", "src")]
+    t = [xe] + [None] * at
+    for i, L in enumerate(layers[at:at + (4 if G else 3)]):
         v = oracle.run_layer(L, t, dtype)
         t.append(v if flags and i == 1 and proj_act == A.ACT_NONE else oracle.round_to(v, dtype))
-    return got, t[3:]
+    return got, t[at + 3:], [(r["first"] - at, r["last"] - at) for r in rows if at <= r["first"] < at + 4]
 
 
 # 16 pixels a wave and block: a last block of 1, 15 and 16 pixels; fewer blocks than waves, more than one round of them; both widths of the
@@ -1259,27 +1266,39 @@ def _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, proj_act, G, dty
     (2, 192, True, 64, dtypes.BF16, False, configs.ACT_RELU), (1, 181, False, 64, dtypes.BF16, True, configs.ACT_RELU6),
     (1, 184, False, 128, dtypes.F16, False, configs.ACT_NONE), (3, 161, False, 128, dtypes.BF16, False, configs.ACT_RELU),
     (1, 193, True, 128, dtypes.F16, True, configs.ACT_RELU6), (3, 113, True, 64, dtypes.BF16, True, configs.ACT_NONE),
-    (1, 97, False, 64, dtypes.F16, True, configs.ACT_RELU), (1, 91, True, 64, dtypes.BF16, False, configs.ACT_RELU)])
+    (1, 97, False, 64, dtypes.F16, True, configs.ACT_RELU), (1, 91, True, 64, dtypes.BF16, False, configs.ACT_RELU),
+    (1, 111, True, 64, dtypes.BF16, (1,), configs.ACT_RELU), (1, 93, True, 64, dtypes.BF16, (2,), configs.ACT_RELU),
+    (1, 93, True, 128, dtypes.F16, (3,), configs.ACT_RELU), (1, 97, False, 64, dtypes.F16, (3,), configs.ACT_RELU)])
 def test_end_of_a_bottleneck_block_with_the_next_layer(npas, torch, N, HW, proj, G, dtype, bias, act):
     print(f"bottleneck tail {N}x{HW}x{HW} projection={proj} G={G}", flush=True)
-    got, ref = _run_of_pointwise_layers(npas, torch, N, HW, 64, 64, 1, configs.ACT_NONE if proj else configs.ACT_RELU, G, dtype, bias, act,
-                                        npas.STACK_FUSE_POINTWISE)
+    got, ref, launches = _run_of_pointwise_layers(npas, torch, N, HW, 64, 64, 1, configs.ACT_NONE if proj else configs.ACT_RELU, G, dtype, bias, act,
+                                                  npas.STACK_FUSE_POINTWISE)
+    assert launches == ([(0, 0), (1, 3)] if proj else [(0, 0), (1, 1), (2, 3)])
     for name, g, r in zip(("sum", "next layer"), got, ref):
         norm, worst = helpers.check_stack_output(g, r, STACK_NORM_TOL if dtype == dtypes.BF16 else STACK_NORM_TOL / 8)
         print(f"  {name}: norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
 
 
 # The projection as further stages of the layer that adds it: the three tile sizes of the ring, one and two pixel blocks of the split reduction (1, 2 and
-# 4 images), layers that have exact lists too, a last tile of few pixels, strides 1 and 2 on odd maps, biases on both, hard-swish.
-@pytest.mark.parametrize("N,HW,C0,C,stride,dtype,bias,act", [
-    (1, 3, 64, 64, 1, dtypes.BF16, True, configs.ACT_RELU), (1, 14, 512, 256, 2, dtypes.BF16, True, configs.ACT_RELU),
-    (3, 15, 128, 128, 2, dtypes.F16, True, configs.ACT_HARDSWISH), (1, 28, 256, 128, 1, dtypes.BF16, False, configs.ACT_NONE),
-    (1, 57, 64, 64, 2, dtypes.BF16, True, configs.ACT_RELU6), (2, 41, 64, 64, 1, dtypes.F16, True, configs.ACT_RELU),
-    (9, 27, 128, 128, 2, dtypes.BF16, True, configs.ACT_HARDSWISH), (5, 61, 256, 128, 2, dtypes.F16, False, configs.ACT_RELU),
-    (3, 113, 192, 64, 2, dtypes.BF16, True, configs.ACT_RELU6), (7, 63, 64, 192, 1, dtypes.BF16, True, configs.ACT_NONE)])
-def test_projection_shortcut_inside_the_layer_that_adds_it(npas, torch, N, HW, C0, C, stride, dtype, bias, act):
+# 4 images), layers that have exact lists too, a last tile of few pixels, strides 1 and 2 on odd maps, biases on both, one or none (of both widths of the
+# ring's tiles), hard-swish.
+RING, SPLIT = "pointwise_ring_kernel", "conv_smallm_mfma_kernel"
+
+
+@pytest.mark.parametrize("N,HW,C0,C,stride,dtype,bias,act,kernel", [
+    (1, 3, 64, 64, 1, dtypes.BF16, True, configs.ACT_RELU, None), (1, 14, 512, 256, 2, dtypes.BF16, True, configs.ACT_RELU, None),
+    (3, 15, 128, 128, 2, dtypes.F16, True, configs.ACT_HARDSWISH, None), (1, 28, 256, 128, 1, dtypes.BF16, False, configs.ACT_NONE, None),
+    (1, 57, 64, 64, 2, dtypes.BF16, True, configs.ACT_RELU6, SPLIT), (2, 41, 64, 64, 1, dtypes.F16, True, configs.ACT_RELU, RING),
+    (9, 27, 128, 128, 2, dtypes.BF16, True, configs.ACT_HARDSWISH, RING), (5, 61, 256, 128, 2, dtypes.F16, False, configs.ACT_RELU, RING),
+    (3, 113, 192, 64, 2, dtypes.BF16, True, configs.ACT_RELU6, RING), (7, 63, 64, 192, 1, dtypes.BF16, True, configs.ACT_NONE, RING),
+    (1, 14, 512, 256, 2, dtypes.BF16, (1,), configs.ACT_RELU, None), (1, 57, 64, 64, 2, dtypes.BF16, (2,), configs.ACT_RELU6, SPLIT),
+    (2, 41, 64, 64, 1, dtypes.F16, (1,), configs.ACT_RELU, RING), (2, 41, 64, 64, 1, dtypes.F16, (2,), configs.ACT_RELU, RING),
+    (7, 63, 64, 192, 1, dtypes.BF16, (1,), configs.ACT_NONE, RING), (7, 63, 64, 192, 1, dtypes.BF16, (2,), configs.ACT_NONE, RING)])
+def test_projection_shortcut_inside_the_layer_that_adds_it(npas, torch, N, HW, C0, C, stride, dtype, bias, act, kernel):
     print(f"projection joined {N}x{HW}x{HW} {C0} / {stride} + {C} -> {4 * C}", flush=True)
-    got, ref = _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, configs.ACT_NONE, 0, dtype, bias, act, npas.STACK_FUSE_POINTWISE)
+    got, ref, launches = _run_of_pointwise_layers(npas, torch, N, HW, C0, C, stride, configs.ACT_NONE, 0, dtype, bias, act, npas.STACK_FUSE_POINTWISE,
+                                                  kernel=kernel)
+    assert launches == [(0, 0), (1, 2)]
     norm, worst = helpers.check_stack_output(got[0], ref[0], STACK_NORM_TOL if dtype == dtypes.BF16 else STACK_NORM_TOL / 8)
     print(f"  norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
 
@@ -1290,7 +1309,8 @@ def test_projection_shortcut_inside_the_layer_that_adds_it(npas, torch, N, HW, C
 @pytest.mark.parametrize("N,HW", [(2, 448), (4, 400)])
 def test_strided_pointwise_layers_on_many_pixels(npas, torch, N, HW, flags):
     print(f"strided 1x1 {N}x{HW}x{HW} flags={flags}", flush=True)
-    got, ref = _run_of_pointwise_layers(npas, torch, N, HW, 64, 64, 2, configs.ACT_NONE, 0, dtypes.BF16, True, configs.ACT_NONE, flags)
+    got, ref, launches = _run_of_pointwise_layers(npas, torch, N, HW, 64, 64, 2, configs.ACT_NONE, 0, dtypes.BF16, True, configs.ACT_NONE, flags, kernel=RING)
+    assert launches == ([(0, 0), (1, 2)] if flags else [(0, 0), (1, 1), (2, 2)])
     g, r = got[0].reshape(N, -1, 256), ref[0].reshape(N, -1, 256)
     err = np.sqrt(((g - r) ** 2).sum(-1) / (r ** 2).sum(-1))
     print(f"  a pixel's error {err.max():.3e}, last pixels' {err[:, -1].max():.3e}", flush=True)
@@ -1302,7 +1322,10 @@ def test_projection_inside_the_adding_layer_with_an_infinite_input(npas, torch, 
     """Split reduction: an infinite value in the projection's input reaches the filters that keep its channel and no others."""
     print(f"projection joined, infinite input {N}x{HW}x{HW} {C0} / {stride} + {C} -> {4 * C}", flush=True)
     args = (npas, torch, N, HW, C0, C, stride, configs.ACT_NONE, 0, dtype, False, configs.ACT_RELU)
-    got = [_run_of_pointwise_layers(*args, flags, [(0, 0, 0, 1), (0, 2, 2, C0 - 3)])[0][0] for flags in (0, npas.STACK_FUSE_POINTWISE)]
+    (apart,), _, one_by_one = _run_of_pointwise_layers(*args, 0, [(0, 0, 0, 1), (0, 2, 2, C0 - 3)])
+    (joined,), _, launches = _run_of_pointwise_layers(*args, npas.STACK_FUSE_POINTWISE, [(0, 0, 0, 1), (0, 2, 2, C0 - 3)])
+    assert one_by_one == [(0, 0), (1, 1), (2, 2)] and launches == [(0, 0), (1, 2)]
+    got = [apart, joined]
     assert np.isinf(got[0]).any() and np.isfinite(got[0]).any()
     for kind in (np.isnan, np.isposinf):
         np.testing.assert_array_equal(kind(got[1]), kind(got[0]))

@@ -231,9 +231,12 @@ def _assert_placement_is_safe(st, N):
     """No launch may write over bytes that it, or a later launch, still has to read: tensors whose lifetimes
     (launch that writes them .. last launch that reads them) intersect must not share workspace bytes."""
     rows = st.describe(N)
-    assert len(rows) == st.num_launches()
+    assert len(rows) == st.num_launches(N) <= st.num_launches()
+    assert [r["first"] for r in rows] == [0] + [r["last"] + 1 for r in rows[:-1]]     # every layer in one launch
     born, last_read, where = {}, {}, {}
     for r, row in enumerate(rows):
+        for t in range(row["first"] + 1, row["last"] + 2):      # also the sum that a launch stores in front of its last layer
+            born[t] = r
         for key in ("src", "res"):
             t = row[key]
             if t >= 0:
@@ -241,10 +244,11 @@ def _assert_placement_is_safe(st, N):
                 if row["off_" + key] >= 0:
                     assert where.setdefault(t, (row["off_" + key], row["bytes_" + key])) == (row["off_" + key], row["bytes_" + key])
         t = row["out"]
-        born[t] = r
+        assert t == row["last"] + 1
         if row["off_out"] >= 0:
             where[t] = (row["off_out"], row["bytes_out"])
-            assert row["off_out"] % 256 == 0 and row["off_out"] + row["bytes_out"] <= st.workspace_bytes(N)
+    for off, size in where.values():
+        assert off % 256 == 0 and off + size <= st.workspace_bytes(N)
     ts = sorted(where)
     for i, a in enumerate(ts):
         for b in ts[i + 1:]:
@@ -288,23 +292,26 @@ def test_fused_launches_never_write_over_their_own_inputs():
         assert rows[-1]["off_out"] == -2 and rows[0]["off_src"] == -1
 
 
-@pytest.mark.parametrize("N,HW", [(1, 64), (3, 96), (8, 224)])
-def test_runs_of_pointwise_layers_never_write_over_their_inputs(N, HW):
+@pytest.mark.parametrize("N,HW,tails,joined", [(1, 64, 0, 4), (3, 96, 0, 4), (8, 224, 2, 3), (7, 224, 1, 3)])
+def test_runs_of_pointwise_layers_never_write_over_their_inputs(N, HW, tails, joined):
     """A projection, the layer that adds it and the next layer may run as one launch: what the first two read is still there when the last one
-    writes, and the workspace is no larger than without."""
+    writes, the workspace is no larger than without, and the launches listed are those that are made."""
     w = configs.config5(batch=1, HW=32, width=64, blocks=(2, 1, 1, 1))
     plain, st = _stack(w.layers, HW, 0), _stack(w.layers, HW, npas.STACK_FUSE_POINTWISE)
     assert st.workspace_bytes(N) <= plain.workspace_bytes(N)
-    rows = _assert_placement_is_safe(st, N)
-    at = {w.layers[r["first"]].name: r for r in rows}
-    for names in (("s0b0_sc", "s0b0_c3", "s0b1_c1"), ("s0b1_c3", "s1b0_c1")):
-        run = [at[n] for n in names]
-        reads = [(r["off_" + k], r["bytes_" + k]) for r in run[:-1] for k in ("src", "res") if r[k] >= 0 and r[k] not in [q["out"] for q in run]]
-        writes = [(r["off_out"], r["bytes_out"]) for r in run]
-        assert len(reads) == 2
-        for ro, rs in reads:
-            for wo, ws in writes:
-                assert ro + rs <= wo or wo + ws <= ro, names
+    rows, names = _assert_placement_is_safe(st, N), [L.name for L in w.layers]
+    assert [(r["first"], r["last"]) for r in _assert_placement_is_safe(plain, N)] == [(i, i) for i in range(len(names))]
+    runs = [[names[i] for i in range(r["first"], r["last"] + 1)] for r in rows if r["last"] > r["first"]]
+    joins = [[f"s{s}b0_sc", f"s{s}b0_c3"] for s in range(joined)]    # (of 7 and 8 images the last stage's two layers take different kernels)
+    if tails:
+        joins[0].append("s0b1_c1")
+    if tails == 2:                          # 128 filters: from 24576 pixels on
+        joins.insert(1, ["s0b1_c3", "s1b0_c1"])
+    assert runs == joins
+    for r in rows:
+        if r["first"] in [names.index(j[0]) for j in joins if j[0].endswith("_sc")]:
+            add, proj = w.layers[r["first"] + 1], w.layers[r["first"]]
+            assert (r["src"], r["res"]) == (add.src, proj.src)
 
 
 def test_a_layer_joins_one_fused_launch_only():
