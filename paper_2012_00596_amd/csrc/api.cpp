@@ -700,11 +700,13 @@ struct npas_stack {
     unsigned flags = 0;
     // per-tensor placement for a given N is computed on the fly (sizes scale with N)
     std::vector<int> last_use; // last layer reading tensor t
+    struct Place {
+        size_t need = 0;
+        std::vector<size_t> off;
+        std::vector<char> runs; // runs whose inputs this placement keeps until the run's last layer
+    };
     mutable std::mutex place_mu;
-    mutable int place_N = -1;
-    mutable size_t place_need = 0;
-    mutable std::vector<size_t> place_off;
-    mutable std::vector<char> place_runs; // runs whose inputs that placement keeps until the run's last layer
+    mutable std::map<int, Place> places; // by N, of at most kMaxPlaces batch sizes
 };
 
 namespace npas {
@@ -727,55 +729,60 @@ static int absorbed_after(const npas_stack::Node &n) { return n.ir_head ? 2 : (n
 static size_t place_tensors(const npas_stack *s, int N, const std::vector<int> &last_use, std::vector<size_t> *offsets)
 {
     const int nt = (int)s->nodes.size() + 1;
-    std::vector<size_t> off(nt, 0), sz(nt, 0);
-    struct Live { size_t off, sz; int until; };
-    std::vector<Live> live;
+    if (offsets) offsets->assign(nt, 0);
+    struct Live { size_t off, end; int until; };
+    std::vector<Live> live; // by offset
+    live.reserve(16);
     size_t total = 0;
     const int esz = dtype_size(s->dtype);
     for (int t = 1; t < nt - 1; ++t) { // tensor t is written by layer t-1
         const npas_stack::Node &w = s->nodes[t - 1];
         if (w.pair_head || w.ir_head || w.pool_fused) continue;          // intermediate of a fused pair / block never reaches memory
         if (t >= 2 && s->nodes[t - 2].ir_head) continue;                 // nor does the second one of a fused block
-        sz[t] = (tensor_elems_per_image(s, t) * N * esz + 255) / 256 * 256;
+        const size_t sz = (tensor_elems_per_image(s, t) * N * esz + 255) / 256 * 256;
         // drop tensors whose last reader ran before layer t-1
         live.erase(std::remove_if(live.begin(), live.end(), [&](const Live &l) { return l.until < t - 1; }),
                    live.end());
-        std::sort(live.begin(), live.end(), [](const Live &a, const Live &b) { return a.off < b.off; });
         size_t pos = 0;
-        for (const Live &l : live) {
-            if (pos + sz[t] <= l.off) break;
-            pos = std::max(pos, l.off + l.sz);
-        }
-        off[t] = pos;
-        live.push_back({pos, sz[t], last_use[t]});
-        total = std::max(total, pos + sz[t]);
+        auto at = live.begin();
+        for (; at != live.end() && pos + sz > at->off; ++at) pos = std::max(pos, at->end);
+        if (offsets) (*offsets)[t] = pos;
+        live.insert(at, Live{pos, pos + sz, last_use[t]});
+        total = std::max(total, pos + sz);
     }
-    if (offsets) *offsets = off;
     return total;
 }
 
-// The same with the inputs of the runs of 1x1 layers kept until a run's last layer, for as many runs as that is possible without a larger
-// workspace (*runs: which).  Every tensor keeps a place of its own: whether a run is one launch is decided at the call.
-static size_t place_runs(const npas_stack *s, int N, std::vector<size_t> *offsets, std::vector<char> *runs)
+// The same with the inputs of the runs of 1x1 layers kept until a run's last layer, for all of them or, where that would take a larger workspace, for
+// as many as one after the other still fit (runs: which).  Every tensor keeps a place of its own: whether a run is one launch is decided at the call.
+static void place_runs(const npas_stack *s, int N, npas_stack::Place *p)
 {
-    const size_t need = place_tensors(s, N, s->last_use, offsets);
-    runs->assign(s->runs.size(), 0);
     std::vector<int> use = s->last_use;
-    for (size_t g = 0; g < s->runs.size(); ++g) {
-        const npas_stack::Run &r = s->runs[g];
-        std::vector<int> trial = use;
+    auto keep = [&](const npas_stack::Run &r, std::vector<int> *u) {
         for (int j = r.first; j <= r.add; ++j) {
             const npas_layer_desc &d = s->nodes[j].d;
-            trial[d.src] = std::max(trial[d.src], r.last);
-            if (d.res >= 0) trial[d.res] = std::max(trial[d.res], r.last);
+            (*u)[d.src] = std::max((*u)[d.src], r.last);
+            if (d.res >= 0) (*u)[d.res] = std::max((*u)[d.res], r.last);
         }
-        std::vector<size_t> off;
-        if (place_tensors(s, N, trial, &off) > need) continue;
-        (*runs)[g] = 1;
-        *offsets = off;
+    };
+    p->need = place_tensors(s, N, s->last_use, &p->off);
+    for (const npas_stack::Run &r : s->runs) keep(r, &use);
+    std::vector<size_t> off;
+    const bool all = s->runs.empty() || place_tensors(s, N, use, &off) <= p->need;
+    p->runs.assign(s->runs.size(), all);
+    if (all) {
+        if (!off.empty()) p->off = off;
+        return;
+    }
+    use = s->last_use;
+    for (size_t g = 0; g < s->runs.size(); ++g) {
+        std::vector<int> trial = use;
+        keep(s->runs[g], &trial);
+        if (place_tensors(s, N, trial, &off) > p->need) continue;
+        p->runs[g] = 1;
+        p->off = off;
         use = trial;
     }
-    return need;
 }
 
 } // namespace npas
@@ -1383,19 +1390,18 @@ int npas_stack_describe(const npas_stack *s, int N, int64_t *rows_host, int max_
         set_error("bad batch %d or row count %d", N, max_rows);
         return NPAS_E_SHAPE;
     }
-    std::vector<size_t> off;
-    std::vector<char> runs;
-    (void)place_runs(s, N, &off, &runs);
+    npas_stack::Place place;
+    place_runs(s, N, &place);
     const int nl = (int)s->nodes.size();
     const int64_t esz = dtype_size(s->dtype);
-    auto where = [&](int t) -> int64_t { return t < 0 ? -3 : t == 0 ? -1 : t == nl ? -2 : (int64_t)off[t]; };
+    auto where = [&](int t) -> int64_t { return t < 0 ? -3 : t == 0 ? -1 : t == nl ? -2 : (int64_t)place.off[t]; };
     auto bytes = [&](int t) -> int64_t { return t < 0 ? 0 : (int64_t)tensor_elems_per_image(s, t) * N * esz; };
     int r = 0;
     for (int i = 0, last; i < nl; i = last + 1) {
         const npas_stack::Node &n = s->nodes[i];
         last = i + absorbed_after(n);
         int src = n.d.src, res = n.ir_head ? s->nodes[last].d.res : n.d.res; // a fused block adds its input at its last layer
-        if (n.run >= 0 && runs[n.run]) {
+        if (n.run >= 0 && place.runs[n.run]) {
             const npas_stack::Run &run = s->runs[n.run];
             const RunForm form = run_form(s, run, N, [](int) { return true; });
             if (form != RUN_LAYERS) {
@@ -1461,6 +1467,9 @@ static int run_pointwise_run(const npas_stack *s, const npas_stack::Run &r, int 
     return launch_conv_smallm_join(p3->dtype, a, stream);
 }
 
+// Batch sizes whose placements a stack keeps (half a KB each for 50 layers; one takes 2 us to work out, on the host path of a call)
+constexpr size_t kMaxPlaces = 64;
+
 // The body of npas_run_stack; also behind the allocation-free entry point.
 int run_stack_impl(const npas_stack *s, const void *x_dev, void *y_dev, int N, void *workspace_dev, size_t workspace_bytes,
                    void *hip_stream)
@@ -1473,14 +1482,17 @@ int run_stack_impl(const npas_stack *s, const void *x_dev, void *y_dev, int N, v
         set_error("bad batch %d", N);
         return NPAS_E_SHAPE;
     }
-    // placement depends on N only; the last one is kept (and read under the lock: no copy, no allocation per call)
+    // placement depends on N only and is kept (and read under the lock: no copy, no allocation per call)
     std::lock_guard<std::mutex> lock(s->place_mu);
-    if (s->place_N != N) {
-        s->place_need = place_runs(s, N, &s->place_off, &s->place_runs);
-        s->place_N = N;
+    auto place = s->places.find(N);
+    if (place == s->places.end()) {
+        npas_stack::Place p;
+        place_runs(s, N, &p);
+        if (s->places.size() >= kMaxPlaces) s->places.clear();
+        place = s->places.emplace(N, std::move(p)).first;
     }
-    const std::vector<size_t> &off = s->place_off;
-    const size_t need = s->place_need;
+    const std::vector<size_t> &off = place->second.off;
+    const size_t need = place->second.need;
     if (need > 0 && (!workspace_dev || workspace_bytes < need || ((uintptr_t)workspace_dev & 255))) {
         set_error("workspace: need %zu bytes, 256-byte aligned; got %zu at %p", need, workspace_bytes, workspace_dev);
         return NPAS_E_WORKSPACE;
@@ -1497,7 +1509,7 @@ int run_stack_impl(const npas_stack *s, const void *x_dev, void *y_dev, int N, v
         const void *x = tensor(n.d.src);
         void *y = tensor(i + 1);
         int rc = NPAS_OK;
-        if (n.run >= 0 && s->place_runs[n.run]) { // this layer and the next one or two as one kernel, where that is quicker
+        if (n.run >= 0 && place->second.runs[n.run]) { // this layer and the next one or two as one kernel, where that is quicker
             int covered = 0;
             rc = run_pointwise_run(s, s->runs[n.run], N, tensor, hip_stream, &covered);
             if (rc) return rc;

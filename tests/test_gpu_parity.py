@@ -1333,6 +1333,22 @@ def test_projection_inside_the_adding_layer_with_an_infinite_input(npas, torch, 
     assert np.abs(got[1][finite] - got[0][finite]).max() <= 2e-2 * np.abs(got[0][finite]).max()
 
 
+def test_run_stack_at_changing_batch_sizes(npas, torch):
+    """One stack called at more batch sizes than it keeps placements of, some of them again later: each call gives what a stack of its own gives."""
+    w = configs.config5(batch=1, HW=32, width=64, blocks=(1, 2, 1, 1))
+    packed = [pack_layer(npas, L, w.dtype) if L.kind in ("conv", "fc") else None for L in w.layers]
+    new = lambda: npas.Stack(helpers.stack_descs(npas, w.layers, packed), 32, 32, 7)  # noqa: E731
+    one, x = new(), torch.randn(72, 32, 32, 3, generator=torch.Generator(device="cuda").manual_seed(5), device="cuda").to(torch.bfloat16)
+    ws = torch.empty(one.workspace_bytes(72), dtype=torch.uint8, device="cuda")
+    for N in [3, 1, 3] + list(range(1, 73)) + [2, 72, 1]:
+        ys = [torch.full((N, w.layers[-1].F), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+        for st, y in zip((one, new()), ys):
+            ws.view(torch.int16).fill_(0x7FC1)
+            st.run(x[:N], y, N, ws, ws.numel())
+        torch.cuda.synchronize()
+        assert torch.isfinite(ys[0]).all() and torch.equal(ys[0], ys[1]), N
+
+
 def test_chained_fused_launches_against_the_oracle(npas, torch):
     """Fused launches whose inputs and outputs are workspace tensors (the placement must keep a fused launch's input
     alive while it writes the output of the last layer it absorbs): three fused 1x1 pairs of unequal widths in a row,
