@@ -1643,32 +1643,36 @@ __global__ __launch_bounds__(256) void global_avgpool_kernel(const void *x, void
     st_act<DT>(y, (size_t)i, (float)(s / (double)HW));
 }
 
-// 16-bit storage, C a multiple of 4: a lane sums 4 channels (8-byte loads, a wave reads 512 contiguous bytes of a pixel) over every eighth pixel, seven
-// loads in flight; the eight waves' sums meet in LDS and are added in wave order, all in fp32 (exact to ~1e-6 for a map of a few thousand 16-bit
-// values, far inside the storage type's rounding).  One thread over all pixels was seven load latencies long.
-constexpr int kPoolWaves = 8;
-template <int DT>
-__global__ __launch_bounds__(kPoolWaves * 64) void global_avgpool_vec4_kernel(const void *x, void *y, int N, int HW, int C)
+// 16-bit storage, C a multiple of 4: a lane sums 4 channels (8-byte loads, a wave reads 512 contiguous bytes of a pixel) over every PW-th pixel,
+// in groups of seven loads and the rest one by one; the sums of PW waves meet in LDS and are added in wave order, all in fp32 (exact to ~1e-6 for a
+// map of a few thousand 16-bit values, far inside the storage type's rounding).  Bound by the chain of load latencies of a wave (PW = 8) or, with many
+// waves, by memory (PW = 1): see launch_avgpool.
+template <int DT, int PW>
+__global__ __launch_bounds__(PW == 8 ? 512 : 256) void global_avgpool_vec4_kernel(const void *x, void *y, int N, int HW, int C)
 {
-    __shared__ float4 part[kPoolWaves][64];
-    const int C4 = C >> 2, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int i = blockIdx.x * 64 + lane, ic = min(i, N * C4 - 1);
+    static_assert(PW == 1 || PW == 8, "waves that share 64 channel vectors");
+    __shared__ float4 part[PW][64];
+    const int C4 = C >> 2, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, pw = PW > 1 ? wave : 0;
+    const int i = PW > 1 ? blockIdx.x * 64 + lane : blockIdx.x * 256 + threadIdx.x, ic = min(i, N * C4 - 1);
+    if (PW == 1 && i >= N * C4) return;
     const int n = ic / C4, c4 = ic - n * C4;
     const uint2 *xp = reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(x) + (size_t)n * HW * C) + c4;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
 #pragma unroll 7
-    for (int p = wave; p < HW; p += kPoolWaves) {
+    for (int p = pw; p < HW; p += PW) {
         const uint2 v = xp[(size_t)p * C4];
         s0 += from_storage<DT>((uint16_t)(v.x & 0xffffu));
         s1 += from_storage<DT>((uint16_t)(v.x >> 16));
         s2 += from_storage<DT>((uint16_t)(v.y & 0xffffu));
         s3 += from_storage<DT>((uint16_t)(v.y >> 16));
     }
-    part[wave][lane] = float4{s0, s1, s2, s3};
-    __syncthreads();
-    if (wave != 0 || i >= N * C4) return;
+    if (PW > 1) {
+        part[wave][lane] = float4{s0, s1, s2, s3};
+        __syncthreads();
+        if (wave != 0 || i >= N * C4) return;
+    }
 #pragma unroll
-    for (int w = 1; w < kPoolWaves; ++w) {
+    for (int w = 1; w < PW; ++w) {
         const float4 o = part[w][lane];
         s0 += o.x;
         s1 += o.y;
@@ -1724,9 +1728,20 @@ int launch_avgpool(const void *x, void *y, int N, int H, int W, int C, int dt, v
     hipStream_t st = (hipStream_t)stream;
     unsigned grid = (unsigned)((N * C + 255) / 256);
     if (dt != NPAS_F32 && C % 4 == 0) {
-        grid = (unsigned)((N * (C / 4) + 63) / 64);
-        if (dt == NPAS_BF16) hipLaunchKernelGGL(global_avgpool_vec4_kernel<NPAS_BF16>, dim3(grid), dim3(kPoolWaves * 64), 0, st, x, y, N, H * W, C);
-        else hipLaunchKernelGGL(global_avgpool_vec4_kernel<NPAS_F16>, dim3(grid), dim3(kPoolWaves * 64), 0, st, x, y, N, H * W, C);
+        // Eight waves over the pixels of 64 channel vectors shorten a wave's chain of loads; with few pixels, or waves enough to fill the chip, they only
+        // cost: bf16, inputs in the Infinity Cache, us with one wave / with eight: 2 x 2, 512 waves of vectors 2.8 / 2.4, 2048 3.4 / 4.1; 3 x 3, 512
+        // 2.9 / 2.95, 1024 3.3 / 3.5; 4 x 4, 1024 4.1 / 3.8, 2048 5.0 / 5.5; 7 x 7, 64 4.7 / 4.0, 1024 5.9 / 6.0 (from HBM 7.7 / 7.25, from the L2
+        // 3.7 / 4.05), 2048 9.0 / 9.8; 10 x 10, 512 8.8 / 6.35, 2048 16.5 / 16.4; 14 x 14, 4096 72 / 65; 56 x 56, 32 178 / 28; 1 x 1, 4096 2.5 / 4.6.
+        const long waves = ((long)N * (C / 4) + 63) / 64;
+        const int HW = H * W;
+        const bool split = HW >= 64 || (HW >= 16 && waves <= 1024) || (HW >= 4 && waves <= 512);
+        auto pick = [&](auto dtc) {
+            constexpr int DT = decltype(dtc)::value;
+            if (split) hipLaunchKernelGGL((global_avgpool_vec4_kernel<DT, 8>), dim3((unsigned)waves), dim3(512), 0, st, x, y, N, HW, C);
+            else hipLaunchKernelGGL((global_avgpool_vec4_kernel<DT, 1>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, x, y, N, HW, C);
+        };
+        if (dt == NPAS_BF16) pick(std::integral_constant<int, NPAS_BF16>{});
+        else pick(std::integral_constant<int, NPAS_F16>{});
     } else if (dt == NPAS_F32) hipLaunchKernelGGL(global_avgpool_kernel<NPAS_F32>, dim3(grid), dim3(256), 0, st, x, y, N, H * W, C);
     else if (dt == NPAS_BF16) hipLaunchKernelGGL(global_avgpool_kernel<NPAS_BF16>, dim3(grid), dim3(256), 0, st, x, y, N, H * W, C);
     else hipLaunchKernelGGL(global_avgpool_kernel<NPAS_F16>, dim3(grid), dim3(256), 0, st, x, y, N, H * W, C);

@@ -1477,3 +1477,17 @@ def test_pools(npas, torch):
         z = new_dev((2, C), dtype, torch)
         npas.global_avgpool(x, z, 2, 9, 11, C, dtype)
         assert rel_err(from_dev(z, dtype).reshape(2, C), oracle.round_to(oracle.global_avgpool(xe), dtype)) <= TOL[dtype]
+
+
+# Both forms of the vector kernel: fewer pixels than waves, one more than the waves' groups of loads, 64 vectors of four channels and one more, and above
+# the numbers of waves (64 vectors each) from which one wave walks all pixels.
+@pytest.mark.parametrize("N,H,W,C,dtype", [(3, 1, 1, 24, dtypes.BF16), (1, 1, 3, 260, dtypes.F16), (2, 1, 7, 256, dtypes.BF16), (1, 7, 7, 260, dtypes.F16),
+                                           (3, 8, 8, 1028, dtypes.BF16), (513, 2, 2, 256, dtypes.BF16), (512, 2, 2, 256, dtypes.F16),
+                                           (1025, 5, 5, 256, dtypes.BF16), (1024, 5, 5, 256, dtypes.BF16), (1030, 1, 1, 260, dtypes.F16)])
+def test_global_average_pool_forms(npas, torch, N, H, W, C, dtype):
+    print(f"average pool {N}x{H}x{W}x{C}", flush=True)
+    xs, xe = dtypes.quantize(prng.normal(9, 2, N * H * W * C).reshape(N, H, W, C) + 1.0, dtype)
+    y = new_dev((N, C), dtype, torch, fill=0x7FC1)
+    npas.global_avgpool(to_dev(xs, torch), y, N, H, W, C, dtype)
+    torch.cuda.synchronize()
+    assert rel_err(from_dev(y, dtype).reshape(N, C), oracle.round_to(oracle.global_avgpool(xe), dtype)) <= TOL[dtype]
