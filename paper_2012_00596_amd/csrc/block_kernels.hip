@@ -421,10 +421,13 @@ int launch_depthwise3x3(int dt, const void *x, void *y, const void *w, const flo
         // threads, which wants launches of several rounds (2 x 256 workgroups are resident): from 2.75 rounds of one-column threads on, 32 x 57 x 57 x 144
         // 17.4 -> 16.1 us, 64 x 56 x 56 x 144 28.8 -> 27.0, 64 x 60 x 60 x 240 65.0 -> 58.3; with 2.3 rounds 64 x 28 x 28 x 192 11.9 against 12.2, with
         // 0.7 16 x 28 x 28 x 240 5.6 against 6.5 (some launches between one and two rounds would gain, 8 x 60 x 60 x 240 10.0 -> 9.2, others not).
-        const int CX = R == 4 && (double)N * nyb * Wo * CV >= 2.75 * 512 * 256 ? 2 : 1;
+        // The last pair of an odd row computes a column for nothing: up to a ninth more columns.  64 images of 64 channels, 400 000 / 700 000 one-column
+        // threads, us with one column / with two: 9 columns 14.7 / 13.9 and 22.0 / 20.9, 7 14.7 / 13.8 and 21.7 / 22.7, 5 14.6 / 13.9 and 21.7 / 22.7,
+        // 3 14.6 / 16.4 and 21.9 / 24.5, one 14.4 / 15.4 and 21.5 / 22.8; 2 columns 14.4 / 13.8 and 21.6 / 20.6.
+        const int CX = R == 4 && (double)N * nyb * Wo * CV >= 2.75 * 512 * 256 && (Wo % 2 == 0 || Wo >= 9) ? 2 : 1;
         const uint32_t nxb = (uint32_t)((Wo + CX - 1) / CX);
         const double threads = (double)N * nyb * nxb * CV;
-        // Offset 2 GiB is past the end for the descriptor's range check; the index decode divides by CV, Wo and nyb with 32-bit
+        // Offset 2 GiB is past the end for the descriptor's range check; the index decode divides by CV, nxb and nyb with 32-bit
         // reciprocals, exact while index * divisor < 2^32.
         const bool big = xbytes >= 0x80000000u || threads * std::max({CV, nxb, nyb}) >= 4294967296.0;
         DwArgs a{x, y, w, bias, residual, zeros, N, H, W, C, Ho, Wo, act, (uint32_t)xbytes, CV, nxb, nyb, (uint32_t)threads,

@@ -445,10 +445,11 @@ def test_depthwise3x3(npas, torch, case):
 
 
 # Edges of the row-block kernel: four rows a thread (launches of more than 196608 output vectors) with one row left over and
-# with whole blocks, two columns too (from 360448 one-column threads on: odd, even, one), one row a thread, stride 2 on odd and even maps, maps narrower than the window, a bias at 4-byte alignment.
+# with whole blocks, two columns too (from 360448 one-column threads on: odd, even, two and nine; one, seven stay), one row a thread, stride 2 on odd and even maps, maps narrower than the window, a bias at 4-byte alignment.
 @pytest.mark.parametrize("N,H,W,C,stride,dtype", [(5, 201, 199, 8, 1, dtypes.BF16), (13, 64, 60, 32, 1, dtypes.F16), (1, 3, 1, 24, 1, dtypes.BF16),
                                                   (2, 9, 7, 40, 2, dtypes.F16), (3, 32, 2, 16, 2, dtypes.BF16), (9, 151, 149, 16, 2, dtypes.BF16),
-                                                  (25, 57, 57, 144, 1, dtypes.BF16), (41, 62, 76, 64, 1, dtypes.F16), (3, 30001, 1, 136, 1, dtypes.BF16)])
+                                                  (25, 57, 57, 144, 1, dtypes.BF16), (41, 62, 76, 64, 1, dtypes.F16), (3, 30001, 1, 136, 1, dtypes.BF16),
+                                                  (3, 15001, 2, 136, 1, dtypes.BF16), (9, 2225, 9, 64, 1, dtypes.F16), (9, 2861, 7, 64, 1, dtypes.BF16)])
 def test_depthwise3x3_row_blocks(npas, torch, N, H, W, C, stride, dtype):
     print(f"depthwise rows N={N} {H}x{W}x{C} stride {stride}", flush=True)
     xs, xe = dtypes.quantize(prng.normal(18, 1, N * H * W * C).reshape(N, H, W, C), dtype)
