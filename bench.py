@@ -179,29 +179,29 @@ def layer_costs(w, packed, harness):
         vec = w.dtype == 0 or L.kind == "dwconv"  # fp32 and depthwise layers run on the vector ALUs
         peak = VALU_PEAK_TFLOPS if vec else MFMA_PEAK_TFLOPS
         t_hbm, t_mm = abytes / (HBM_PEAK_GBS * 1e9) * 1e6, 2.0 * macs / (peak * 1e12) * 1e6
-        rows.append(dict(i=i, L=L, ishape=ishape, oshape=oshape, nin=nin, nout=nout, flop=2.0 * macs, kept_flop=2.0 * kept,
+        rows.append(dict(i=i, L=L, ishape=ishape, oshape=oshape, nin=nin, nout=nout, nin_alg=nin_alg, esz=esz, flop=2.0 * macs, kept_flop=2.0 * kept,
                          abytes=abytes, wbytes=wbytes, t_hbm=t_hbm, t_mm=t_mm, floor_us=max(t_hbm, t_mm),
                          bound="hbm" if t_hbm >= t_mm else ("alu" if vec else "mfma")))
     return rows
 
 
-def stack_floor_us(rows, fused_conv_pool=True):
-    """Sum of the per-launch floors.  A conv whose max pool runs in the same launch neither writes the conv output
-    nor reads it back: its floor is taken on input + pooled output."""
+def stack_floor_us(rows, launches):
+    """Sum of the floors of a call's launches (npas.Stack.describe): each tensor that a launch takes from outside read once, its last layer's output
+    and what other launches read of the tensors between its layers written once, its weights; a tensor that stays inside a launch moves no bytes."""
     total = 0.0
-    skip = set()
-    for k, r in enumerate(rows):
-        if k in skip:
-            continue
-        L = r["L"]
-        nxt = rows[k + 1] if k + 1 < len(rows) else None
-        if fused_conv_pool and L.kind == "conv" and L.C < 8 and nxt is not None and nxt["L"].kind == "maxpool" and nxt["L"].src == k + 1:
-            esz = 2
-            b = (r["nin"] + nxt["nout"]) * esz + r["wbytes"]
-            total += max(b / (HBM_PEAK_GBS * 1e9) * 1e6, r["t_mm"])
-            skip.add(k + 1)
-            continue
-        total += r["floor_us"]
+    for l in launches:
+        span = rows[l["first"]:l["last"] + 1]
+        inner = {r["i"] + 1 for r in span}
+        reads, written = {}, 0
+        for r in span:
+            L = r["L"]
+            for t, n in ((L.src, r["nin_alg"]), (L.res, r["nout"])):
+                if t >= 0 and t not in inner:
+                    reads[t] = max(reads.get(t, 0), n)
+            if r is span[-1] or any(r["i"] + 1 in (q["L"].src, q["L"].res) for q in rows[l["last"] + 1:]):
+                written += r["nout"]
+        b = (sum(reads.values()) + written) * span[0]["esz"] + sum(r["wbytes"] for r in span)
+        total += max(b / (HBM_PEAK_GBS * 1e9) * 1e6, sum(r["t_mm"] for r in span))
     return total
 
 
@@ -326,11 +326,11 @@ def headline(args, torch, npas, harness, configs):
     torch.cuda.empty_cache()
     run = StackRunner(w, torch, npas, harness, flags, nsets)
     wall, per = run.timed(args.steps, args.warmup)
-    launches = run.st.num_launches()
+    launches = run.st.num_launches(batch)
     dense_flop = 2.0 * w.dense_macs()
     rows = layer_costs(w, run.packed, harness)
     kept_flop = sum(r["kept_flop"] for r in rows)
-    floor_us = stack_floor_us(rows, fused_conv_pool=bool(flags & 4))
+    floor_us = stack_floor_us(rows, run.st.describe(batch))
     med_ms, min_ms = float(np.median(per)), float(per.min())
 
     name = ("configs[4]: 50-layer bottleneck residual stack, 224x224x3, batch %d, bf16 NHWC, every conv block-punched 8x4 at a "
@@ -346,9 +346,7 @@ def headline(args, torch, npas, harness, configs):
         "kept_TFLOPs": kept_flop / wall / 1e12,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16", "data": "synthetic",
-        "config": {"workload": name, "launches_per_step": launches,
-                   "launches_note": "counted layer by layer after the fusions of stack creation; runs of 1x1 layers around a shortcut "
-                                    "that become one launch at this batch size are not subtracted", "buffer_sets": nsets, "images_per_s": batch / wall,
+        "config": {"workload": name, "launches_per_step": launches, "buffer_sets": nsets, "images_per_s": batch / wall,
                    "workspace_MB": run.wsb / 2**20, "dense_equiv_gflop_per_step": dense_flop / 1e9,
                    "kept_gflop_per_step": kept_flop / 1e9,
                    "executed_gflop_per_step_note": "the MFMA kernels of this stack multiply every position of a 16-filter "
@@ -359,7 +357,7 @@ def headline(args, torch, npas, harness, configs):
     # most of the stack's time, from a per-layer timing pass of the same run
     roof = {"stack_floor_ms": floor_us / 1e3, "stack_frac": floor_us / 1e3 / med_ms,
             "stack_floor_note": "sum over launches of max(algorithmic bytes / 8 TB/s, dense-equivalent FLOP / 2.5 PFLOP/s); "
-                                "bytes = activations in + out (+ residual) once + compact weights + 4 B per list entry"}
+                                "bytes = activations in + out (+ residual) of a launch once + compact weights + 4 B per list entry"}
     if not args.no_extras:
         time_layers(w, run.packed, rows, torch, npas, max(5, min(20, args.steps // 5)))
         per_kernel = {}
@@ -410,8 +408,8 @@ def headline(args, torch, npas, harness, configs):
         r1 = StackRunner(w1, torch, npas, harness, flags, 4)
         _, p1 = r1.timed(200, 20, chunk=10)
         out["batch1"] = {"workload": "configs[4] at batch 1", "timing": "means over 10 consecutive steps", "median_us": float(np.median(p1)) * 1e3, "min_us": float(p1.min()) * 1e3,
-                         "launches": r1.st.num_launches(), "floor_us": stack_floor_us(layer_costs(w1, r1.packed, harness)),
-                         "launch_floor_us": out["launch_floor_us"]["empty_kernel"] * r1.st.num_launches()}
+                         "launches": r1.st.num_launches(1), "floor_us": stack_floor_us(layer_costs(w1, r1.packed, harness), r1.st.describe(1)),
+                         "launch_floor_us": out["launch_floor_us"]["empty_kernel"] * r1.st.num_launches(1)}
         del r1
         w2 = configs.config2(batch=64)
         x2 = int(np.prod(w2.x_shape)) * 2
@@ -423,7 +421,7 @@ def headline(args, torch, npas, harness, configs):
         out["config2_fused_pair"] = {"workload": "configs[1]: 24->144->24, batch 64, 56x56, one fused launch",
                                      "timing": "one pass over the rotating buffer sets captured in a HIP graph, 40 replays, mean per launch of a replay",
                                      "host_issued_median_us": float(np.median(p2h)) * 1e3, "median_us": med2,
-                                     "min_us": float(p2.min()) * 1e3, "launches": r2.st.num_launches(),
+                                     "min_us": float(p2.min()) * 1e3, "launches": r2.st.num_launches(64),
                                      "algorithmic_bytes": b2, "GBps": b2 / med2 / 1e3, "hbm_frac": b2 / med2 / 1e3 / HBM_PEAK_GBS,
                                      "TFLOPs_dense_equiv": 2.0 * w2.dense_macs() / med2 / 1e6}
         del r2
@@ -518,7 +516,7 @@ def time_stack(w, reps, torch, npas, harness, fuse=True, graph=False):
             run.step(0)
         e1.record()
     torch.cuda.synchronize()
-    return e0.elapsed_time(e1) * 1e3 / reps, run.st.num_launches(), run.wsb
+    return e0.elapsed_time(e1) * 1e3 / reps, run.st.num_launches(N), run.wsb
 
 
 def stack_mode(args, torch, npas, harness, configs):

@@ -314,6 +314,25 @@ def test_runs_of_pointwise_layers_never_write_over_their_inputs(N, HW, tails, jo
             assert (r["src"], r["res"]) == (add.src, proj.src)
 
 
+def test_benchmark_floor_counts_what_the_launches_move():
+    """bench.stack_floor_us: layer by layer without fusion; a projection inside the layer that adds it moves no bytes, a sum handed to the next layer is
+    written and not read again."""
+    import bench
+    w = configs.config5(batch=1, HW=32, width=64, blocks=(2, 1, 1, 1))
+    w.x_shape = (8, 224, 224, 3)
+    packed = [helpers.pack_layer(npas, L, dtypes.BF16) if L.kind in ("conv", "fc") else None for L in w.layers]
+    rows = bench.layer_costs(w, packed, helpers)
+    descs, names, px = helpers.stack_descs(npas, w.layers, packed), [L.name for L in w.layers], 8 * 56 * 56
+    plain = npas.Stack(descs, 224, 224, 0).describe(8)
+    assert bench.stack_floor_us(rows, plain) == pytest.approx(sum(r["floor_us"] for r in rows))
+    launches = npas.Stack(descs, 224, 224, npas.STACK_FUSE_POINTWISE).describe(8)
+    for first, last, channels in (("s0b0_sc", "s0b1_c1", 64 + 64 + 256 + 64), ("s0b1_c3", "s1b0_c1", 64 + 256 + 256 + 128)):
+        span = range(names.index(first), names.index(last) + 1)
+        l = [l for l in launches if (l["first"], l["last"]) == (span[0], span[-1])]
+        us = 2 * px * channels + sum(rows[i]["wbytes"] for i in span)
+        assert bench.stack_floor_us(rows, l) == pytest.approx(us / (bench.HBM_PEAK_GBS * 1e3))
+
+
 def test_a_layer_joins_one_fused_launch_only():
     """A 1x1 layer in front of a fused inverted-residual block must not swallow the block's first layer as the
     second half of a fused pair (the block would then never run)."""
