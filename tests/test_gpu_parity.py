@@ -1280,6 +1280,40 @@ def test_end_of_a_bottleneck_block_with_the_next_layer(npas, torch, N, HW, proj,
         print(f"  {name}: norm-wise {norm:.3e} worst element {worst:.3e}", flush=True)
 
 
+@pytest.mark.parametrize("proj,G", [(True, 64), (False, 128)], ids=["projection", "residual"])
+def test_end_of_a_bottleneck_block_beyond_2_gib(npas, torch, proj, G):
+    """The most pixels one launch takes (sums of 3.8 GiB, byte offsets up to 2^32): 3200 times the same image, whose outputs all have to be the
+    first one's; that one is checked against the oracle."""
+    A, N, HW, C = configs, 3200, 50, 64
+    print(f"bottleneck tail {N}x{HW}x{HW} projection={proj} G={G}", flush=True)
+    pw = lambda i, Ci, F, act, src, res=-1: configs._bp_conv(7, i, Ci, F, 1, 1, 0, 8, 4, 2, 0.12, dtypes.BF16, act, src, res)  # noqa: E731
+    layers = [pw(0, C, C, A.ACT_RELU, 0), pw(1, C, 4 * C, A.ACT_NONE if proj else A.ACT_RELU, 0), pw(2, C, 4 * C, A.ACT_RELU, 1, 2),
+              pw(3, 4 * C, G, A.ACT_RELU, 3)]
+    packed = [pack_layer(npas, L, dtypes.BF16) for L in layers]
+    st = npas.Stack(helpers.stack_descs(npas, layers, packed), HW, HW, npas.STACK_FUSE_POINTWISE)
+    assert [(r["first"], r["last"]) for r in st.describe(N)] == ([(0, 0), (1, 3)] if proj else [(0, 0), (1, 1), (2, 3)])
+    assert [(r["first"], r["last"]) for r in st.describe(N + 1)][-1] == (3, 3)      # one image more is too many
+    xs, xe = configs._tensor(9, 1, (1, HW, HW, C), 1.0, dtypes.BF16)
+    x = to_dev(xs, torch).repeat(N, 1, 1, 1)
+    px, wsb = N * HW * HW, st.workspace_bytes(N)
+    assert wsb == 2 * px * 9 * C                                                    # a, the shortcut, the sum: all alive in that launch
+    ws, z = torch.full((wsb // 2,), 0x7FC1, dtype=torch.int16, device="cuda"), new_dev((N, HW * HW * G), dtypes.BF16, torch, fill=0x7FC1)
+    st.run(x, z, N, ws, wsb)
+    torch.cuda.synchronize()
+    y = ws[5 * C * px:].view(N, -1)
+    t = [xe]
+    for i, L in enumerate(layers):
+        v = oracle.run_layer(L, t, dtypes.BF16)
+        t.append(v if proj and i == 1 else oracle.round_to(v, dtypes.BF16))
+    for name, got, ref in (("sum", y, t[3]), ("next layer", z, t[4])):
+        norm, _ = helpers.check_stack_output(from_dev(got[0], dtypes.BF16).reshape(ref.shape), ref, STACK_NORM_TOL)
+        print(f"  {name}: norm-wise {norm:.3e}", flush=True)
+        for k in range(0, N, 200):
+            assert (got[k:k + 200] == got[0]).all(), (name, k)
+    del x, ws, y, z
+    torch.cuda.empty_cache()
+
+
 # The projection as further stages of the layer that adds it: the three tile sizes of the ring, one and two pixel blocks of the split reduction (1, 2 and
 # 4 images), layers that have exact lists too, a last tile of few pixels, strides 1 and 2 on odd maps, biases on both, one or none (of both widths of the
 # ring's tiles), hard-swish.
