@@ -950,9 +950,10 @@ static void plan_ir_tile(int Ho, int Wo, int nslots, int stride, int act1, int a
 }
 
 // Pixels from which the end of a bottleneck block with a shortcut that is a tensor and a next layer of 128 filters are one launch: below, the weights' way
-// into LDS outweighs the bytes saved (64 -> 256 -> 128 on 20480 pixels 15.6 us in two launches, 15.7 in one; 25088: 18.5 -> 16.3; 401408: 137 -> 105).
+// into LDS outweighs the bytes saved (64 -> 256 -> 128 and the layer in front: 15680 pixels 15.8 us in two launches, 15.4 in one; 16384 15.2 / 15.4 and
+// 15.1 / 15.8; 20480 16.4 / 15.6; 24576 17.7 / 16.5; 25088 19.4 / 16.5; 401408 183 / 148).
 // With 64 filters, or with the projection (against the adding layer with the projection inside, and the next layer), it is quicker wherever the layers run
-// on the ring, from 4097 pixels on (8192: 12.1 -> 9.9 us; projection: 5120, 128 filters 12.7 -> 11.3; 12288, 64 filters 14.2 -> 11.0).
+// on the ring, from 4097 or 8193 pixels on (9408: 13.9 -> 12.2 us; projection: 5120, 128 filters 12.5 -> 10.4; 9408, 64 filters 13.5 -> 10.9).
 constexpr double kTailMinPixels = 24576;
 
 // How a run of 1x1 layers goes at one batch size: its layers one by one, with the next layer (bottleneck_tail_kernel), or the projection inside the
@@ -971,8 +972,8 @@ template <typename Aligned> static RunForm run_form(const npas_stack *s, const n
         route(s->nodes[r.last]) == R_POINTWISE_RING && sum_aligned && aligned(r.last + 1))
         return RUN_TAIL;
     if (!r.sum || !sum_aligned) return RUN_LAYERS;
-    // The projection as further stages of the adding layer's sum, wherever both take the same kernel: its output exists nowhere.  Quicker at every one of
-    // 120 shapes (64 .. 512 channels, maps of 2 x 2 .. 56 x 56, batch 1 .. 128, rates 2 and 5): by 1 to 30 % on the split reduction, 1.2-1.9x on the ring.
+    // The projection as further stages of the adding layer's sum, wherever both take the same kernel: its output exists nowhere.  Of 240 launches (64 .. 512
+    // channels, maps of 2 x 2 .. 56 x 56, batch 1 .. 128, rates 2 and 5) 11 stay apart; the call with the others and the layer in front is 1.11 .. 1.93x as fast.
     const Route rp = route(proj);
     const auto split = [](Route v) { return v == R_SMALLM || v == R_FC_GATHER; };
     if (ra == R_POINTWISE_RING && rp == R_POINTWISE_RING) return RUN_RING_JOIN;
