@@ -16,6 +16,12 @@
 namespace npas {
 
 static uint32_t magic_div(uint32_t d) { return d <= 1 ? 0u : (uint32_t)(((1ull << 32) + d - 1) / d); }
+static WideDiv magic_div_wide(uint32_t d)
+{
+    uint32_t shift = 0;
+    while (shift < 30 && d > 2u << shift) ++shift;
+    return WideDiv{d <= 1 ? 0u : (uint32_t)(((1ull << (32 + shift)) + d - 1) / d), shift};
+}
 
 // Best output tile of at most `max_pix` pixels for one launch: candidates are scored by
 // how much of the MFMA columns and of the tile grid does useful work, then by halo
@@ -535,8 +541,8 @@ static void plan_ring(const npas_packed *p, int N, int H, int W, int stride, Rin
         }
     }
     a->flat = stride == 1;
-    a->div_howo = magic_div((uint32_t)(a->Ho * a->Wo));
-    a->div_wo = magic_div((uint32_t)a->Wo);
+    a->div_howo = magic_div_wide((uint32_t)(a->Ho * a->Wo));
+    a->div_wo = magic_div_wide((uint32_t)a->Wo);
 }
 static void plan_smallm(const npas_packed *p, int N, int H, int W, int stride, int pad, SmallMArgs *a)
 {

@@ -32,6 +32,8 @@ __device__ __forceinline__ uint32_t fastdiv_any(uint32_t n, uint32_t magic, uint
     const uint32_t q = fastdiv(n, magic);
     return q * d > n ? q - 1u : q;
 }
+// The same for every n below 2^31 from a reciprocal of 32 significant bits (magic_div_wide), without a second product: for vectors of pixels.
+__device__ __forceinline__ uint32_t fastdiv_wide(uint32_t n, WideDiv d) { return d.magic ? __umulhi(n, d.magic) >> d.shift : n; }
 
 // Streaming (non-temporal) 8-byte accesses for tensors that are written or read once per launch and
 // are far larger than the L2: they leave the cache to the operands that are reused.

@@ -641,31 +641,29 @@ __global__ __launch_bounds__(Cfg::kThreads) void pointwise_ring_kernel(std::cond
         const int nld = max(0, (nblocks - wl + XW - 1) / XW); // this wave's loads per stage
         u32x4 xr = buffer_of(a.x, a.xbytes);
         const uint32_t pcv = (uint32_t)((lane & 7) ^ (lane >> 3)) * 16u; // which 16-byte vector of its pixel this lane fetches
-        auto in_byte = [&](uint32_t m) __attribute__((always_inline)) -> uint32_t { // byte offset in x of output pixel m's input pixel
-            m = min(m, (uint32_t)a.M - 1u);
-            if (a.flat) return m * (uint32_t)a.C * 2u;
-            const uint32_t howo = (uint32_t)(a.Ho * a.Wo), n = fastdiv_any(m, a.div_howo, howo), r = m - n * howo;
-            const uint32_t oy = fastdiv_any(r, a.div_wo, (uint32_t)a.Wo), ox = r - oy * (uint32_t)a.Wo;
-            return ((n * a.H + oy * a.stride) * a.W + ox * a.stride) * (uint32_t)a.C * 2u;
-        };
-        auto in_byte2 = [&](uint32_t m) __attribute__((always_inline)) -> uint32_t { // the same in the second input
-            if constexpr (JOIN) {
-                m = min(m, (uint32_t)a.M - 1u);
-                if (a.stride2 == 1) return m * (uint32_t)a.C2 * 2u;
-                const uint32_t howo = (uint32_t)(a.Ho * a.Wo), n = fastdiv_any(m, a.div_howo, howo), r = m - n * howo;
-                const uint32_t oy = fastdiv_any(r, a.div_wo, (uint32_t)a.Wo), ox = r - oy * (uint32_t)a.Wo;
-                return ((n * a.H2 + oy * a.stride2) * a.W2 + ox * a.stride2) * (uint32_t)a.C2 * 2u;
-            } else return 0u;
-        };
         uint32_t p_item = c_item, p_slot = 0, ppix[Cfg::kXLoads];
         int p_t = 0, p_t0 = 0; // stage, first stage of its input
         bool p_done = false;
-        auto producer_item = [&](bool second) __attribute__((always_inline)) {
-            const PointwiseItem pi = pointwise_item(nfb, p_item);
+        auto producer_item = [&](bool second) __attribute__((always_inline)) { // byte offsets of the input pixels of an item's output pixels
+            const uint32_t m0 = pointwise_item(nfb, p_item).ptile * (uint32_t)a.P + (uint32_t)(wl * 8 + (lane >> 3)), mlast = (uint32_t)a.M - 1u;
+            bool flat = a.flat;
+            uint32_t H = (uint32_t)a.H, W = (uint32_t)a.W, stride = (uint32_t)a.stride, pitch = (uint32_t)a.C * 2u;
+            if constexpr (JOIN)
+                if (second) {
+                    flat = a.stride2 == 1;
+                    H = (uint32_t)a.H2; W = (uint32_t)a.W2; stride = (uint32_t)a.stride2; pitch = (uint32_t)a.C2 * 2u;
+                }
+            if (flat) {
 #pragma unroll
-            for (int i = 0; i < Cfg::kXLoads; ++i) {
-                const uint32_t m = pi.ptile * (uint32_t)a.P + (uint32_t)((wl + XW * i) * 8 + (lane >> 3));
-                ppix[i] = (JOIN && second ? in_byte2(m) : in_byte(m)) + pcv;
+                for (int i = 0; i < Cfg::kXLoads; ++i) ppix[i] = min(m0 + (uint32_t)(XW * 8 * i), mlast) * pitch + pcv;
+            } else { // (a reciprocal put right by a second product for each pixel cost 2 to 4 % of such launches: 512 -> 256 / 2 onto 14 x 14, 64 images 7.9 -> 8.15 us)
+                const uint32_t howo = (uint32_t)(a.Ho * a.Wo);
+#pragma unroll
+                for (int i = 0; i < Cfg::kXLoads; ++i) {
+                    const uint32_t m = min(m0 + (uint32_t)(XW * 8 * i), mlast), n = fastdiv_wide(m, a.div_howo), r = m - n * howo;
+                    const uint32_t oy = fastdiv_wide(r, a.div_wo), ox = r - oy * (uint32_t)a.Wo;
+                    ppix[i] = ((n * H + oy * stride) * W + ox * stride) * pitch + pcv;
+                }
             }
             if constexpr (JOIN) {
                 p_t0 = second ? nst1 : 0;

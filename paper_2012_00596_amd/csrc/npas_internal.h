@@ -287,6 +287,11 @@ struct SmallMJoinArgs : SmallMArgs { // 1x1: b's product of its own input is add
 };
 static_assert(sizeof(SmallMJoinArgs) == 2 * sizeof(SmallMArgs), "the kernel finds b behind a struct of the same size");
 
+// A divisor's reciprocal of 32 significant bits, ceil(2^(32 + shift) / d) with 2^shift < d <= 2^(shift + 1); magic 0 for d = 1 (see fastdiv_wide)
+struct WideDiv {
+    uint32_t magic, shift;
+};
+
 struct RingArgs {
     const void *x;
     void *y;
@@ -303,7 +308,7 @@ struct RingArgs {
     int small;                  // 0: 256 x 128 tiles, 3-stage ring; 1: 64 x 64 tiles, 8-stage ring
     int act;
     int flat;                   // 1: stride 1, input pixel index == output pixel index
-    uint32_t div_howo, div_wo;  // magic reciprocals of Ho*Wo and Wo
+    WideDiv div_howo, div_wo;       // reciprocals of Ho*Wo and Wo
     uint32_t xbytes;                // of x
 };
 struct RingJoinArgs : RingArgs { // the product of a second input is added to the sum
