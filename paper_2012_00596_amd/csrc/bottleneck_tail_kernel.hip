@@ -8,7 +8,7 @@
 // wave is a stream of its own, 16 pixels at a time, and keeps the next 16 pixels' inputs (10 KB) on their way in registers.  Sixteen waves a
 // CU are 160 KB in flight.  Every weight image is read from LDS for one MFMA only: a quarter of the LDS rate at the speed of HBM.
 // 401408 pixels, bf16, inside the 50-layer stack: with the projection, G = 64, 165 us in three launches -> 62 (5.8 TB/s); with a residual, G = 64, 128 in
-// two -> 91 (5.6 TB/s), G = 128 137 -> 103.
+// two -> 91 (5.6 TB/s), G = 128 137 -> 105.
 //
 // The weights are the row operand, the pixels the column operand.  Row r of image j of 64 filters is filter 4 r + j, so that a lane's results of four
 // images are sixteen consecutive channels of its pixel and, rounded, two column operands of the next layer's reduction (whose order of channels is
